@@ -51,23 +51,24 @@ def traffic_source_hash():
     return h.hexdigest()
 
 
-def s_rows_run(N, M):
-    """Rows of the b and W blocks (R = M + N M useful ones) that the S contraction runs on the matrix cores,
-    padding included: tiles of 8 extended sites x 16 units over the full site blocks; in the last block, when
-    it holds r < 7 of the N + 1 extended sites, 2-site fragments of 16 units, with the lone site N of two
-    hidden blocks sharing one fragment when r is odd."""
+def s_entries_run(N, M):
+    """Complex entries that the S contraction forms on the matrix cores for the b and W rows: pairs of 128-row
+    tiles (8 extended sites x 16 units) with site blocks sA <= sB and hidden blocks hA <= hB (the others follow
+    by exchanging the sites), and the 2-site fragments of the last, partly filled site block against them, the
+    lone site N of two hidden blocks sharing one fragment when that block holds an odd count of sites."""
     full, last = divmod(N + 1, 8)
     n_hb = (M + 15) // 16
-    rows = 8 * full * 16 * n_hb
-    if last == 0:
-        return rows
-    if last >= 7:
-        return rows + 8 * 16 * n_hb
-    rf = (last + 1) // 2
-    if last % 2:
-        pairs, odd = divmod(n_hb, 2)
-        return rows + 32 * (pairs * (2 * rf - 1) + odd * rf)
-    return rows + 32 * n_hb * rf
+    if last == 7:
+        full, last = full + 1, 0
+    pairs = full * (full + 1) // 2 * (n_hb * (n_hb + 1) // 2)
+    entries = 128 * 128 * pairs
+    if last:
+        rf = (last + 1) // 2
+        for n_h in range(1, n_hb + 1):
+            two, odd = divmod(n_h, 2)
+            frags = two * (2 * rf - 1) + odd * rf if last % 2 else n_h * rf
+            entries += 32 * 128 * (full * frags + n_h * rf)
+    return entries
 
 
 def measured_traffic():
@@ -216,10 +217,12 @@ def main():
         c, t = prof["sbuild"]
         avg_s = t / c / 1e3
         # the contraction builds the rows and columns of b and W (R = M + N M of the P parameters):
-        # R(R+1)/2 complex entries x N_s samples x 8 real flops; the N rows of a are the border kernel's.
+        # its raw sums <s_i s_i' T_j^* T_j'> are symmetric in the sites and Hermitian in the units, so the distinct
+        # ones are (N+1)(N+2)/2 x M(M+1)/2, x N_s samples x 8 real flops; the N rows of a are the border kernel's.
         # One launch takes the tile pairs of the full 8-site blocks and the ragged pairs of the last.
         R_rows = P - N
-        flops = 4.0 * R_rows * (R_rows + 1) * ns
+        distinct = (N + 1) * (N + 2) // 2 * (M * (M + 1) // 2)
+        flops = 8.0 * distinct * ns
         peak = BF16_PEAK_TFLOPS if prec == crbm.BF16 else FP32_MATRIX_PEAK_TFLOPS
         achieved = flops / avg_s / 1e12
         traffic = measured_traffic() if (prec == crbm.BF16 and C == wl.chains and sweeps == wl.sweeps) else None
@@ -230,7 +233,7 @@ def main():
                 # each operand read once (T re and im of M units, the sign rows of the N + 1 extended sites)
                 # and both triangles of the block written
                 "algorithmic_bytes": (2 * M + N + 1) * ns * esz + 8 * R_rows * R_rows,
-                "rows_run_per_useful_row": s_rows_run(N, M) / R_rows,
+                "entries_run_per_distinct_entry": s_entries_run(N, M) / distinct,
                 "note": ("the b and W rows (R = P - N = %d) in one launch: the tile pairs of the full 8-site blocks "
                          "and the ragged pairs of the last block; the N rows of a in k_sbuild_border (phase "
                          "'sborder')" % R_rows)}
@@ -472,17 +475,16 @@ def bench_chain40(crbm, args):
 
     el, phases = _timed(plan, step, args.steps, args.warmup)
     st = stats.cpu().numpy()
-    # the FP32 S contraction of the b and W rows (R = P - N): 4 R (R + 1) N_s FLOP on the FP32 matrix cores;
+    # the FP32 S contraction of the b and W rows: 8 FLOP per distinct raw sum and sample on the FP32 matrix cores;
     # its row tiles are 8 sites x 16 units; the last site block (site 40 alone) runs as one fragment per
     # two hidden blocks (ragged pairs)
     t_sb = phases["sbuild"]["avg_ms"] / 1e3
-    R_rows = P - N
-    flops = 4.0 * R_rows * (R_rows + 1) * ns
-    rows_run = s_rows_run(N, M)
+    distinct = (N + 1) * (N + 2) // 2 * (M * (M + 1) // 2)   # symmetric in the sites, Hermitian in the units
+    flops = 8.0 * distinct * ns
     roof = {"kernel": "k_sbuild_mfma<false> (FP32 operands, one launch)", "bound": "mfma",
             "achieved": flops / t_sb / 1e12,
             "peak": FP32_MATRIX_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": flops / t_sb / 1e12 / FP32_MATRIX_PEAK_TFLOPS,
-            "traffic": None, "algorithmic_flops": flops, "rows_run_per_useful_row": rows_run / R_rows}
+            "traffic": None, "algorithmic_flops": flops, "entries_run_per_distinct_entry": s_entries_run(N, M) / distinct}
     print(json.dumps({"metric": "MC samples/s + SR steps/s", "value": ns / el, "unit": "samples/s", "n_gpus": 1,
                       "steps": args.steps, "warmup": args.warmup, "ms_per_step": el * 1e3, "higher_is_better": True,
                       "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",

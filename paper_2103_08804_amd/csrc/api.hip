@@ -27,8 +27,8 @@ hipError_t launch_moment_accum(const double2* f, const double2* B, int b_is_f, c
                                int nn, int entry0, int total, double2* partial, int n_blocks, hipStream_t stream);
 hipError_t launch_moment_final(const double2* partial, int n_blocks, int total, double2* mu, hipStream_t stream);
 size_t sbuild_pack_bytes(int N, int M, long max_samples);
-std::vector<int2> sbuild_order(int N, int M, int n_xcd, int g);
-std::vector<int2> sbuild_order_ragged(int N, int M);
+std::vector<int2> sbuild_order(int N, int M, int n_xcd, bool fold);
+std::vector<int2> sbuild_order_ragged(int N, int M, bool fold);
 hipError_t launch_basis_pack(long n, const double2* B, const float2* loc, int mul, float2* Bcol, float2* HBcol,
                              hipStream_t stream);
 long gram_partial_len(int K);
@@ -71,10 +71,6 @@ constexpr long kMaxSplits = 12;
 constexpr long kBorderSplitBytes = 256L << 20;   // bound of the border kernel's split slices
 constexpr long kMaxBorderSplits = 16;
 constexpr int kXcds = 8;                   // accelerator complex dies of the MI355X (round-robin dispatch)
-#ifndef CRBM_SUPERTILE
-#define CRBM_SUPERTILE 8
-#endif
-constexpr int kSuperTile = CRBM_SUPERTILE; // tile pairs per super-tile side in the S contraction order
 
 thread_local char g_err[512] = "";
 
@@ -286,6 +282,9 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
         return fail(CRBM_EUNSUPPORTED, "CRBM_PLAN_CHOLESKY needs P <= %ld (P = %ld)", kCholMaxP, N + n_hidden + N * n_hidden);
     }
 
+    if (hipDeviceGetAttribute(&p->n_cu, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess || p->n_cu < 1)
+        p->n_cu = 256;
+
     // bonds of the periodic lattice (Sec. VI)
     std::vector<int2> bonds;
     if (lat->kind == CRBM_LATTICE_CHAIN) {
@@ -346,14 +345,6 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     if (!rc && (flags & (CRBM_PLAN_DENSE_S | CRBM_PLAN_CHOLESKY))) {
         p->w.pack_bytes = sbuild_pack_bytes((int)N, (int)M, S);
         rc = p->alloc(reinterpret_cast<unsigned char**>(&p->w.pack), p->w.pack_bytes);
-        // the pairs of full tiles, then the ragged pairs of the last site block (one launch takes both)
-        order = sbuild_order((int)N, (int)M, kXcds, kSuperTile);
-        const std::vector<int2> rag = sbuild_order_ragged((int)N, (int)M);
-        order.insert(order.end(), rag.begin(), rag.end());
-        int2* d_order = nullptr;
-        rc = rc ? rc : p->alloc(&d_order, order.size());
-        p->w.sb_order = d_order;
-        p->w.sb_order_len = (long)order.size();
         // buffer of a contraction split over samples when the tile pairs alone cannot fill the device
         const long slice = P * P * (long)sizeof(float2);
         const long nsm = std::min<long>(kMaxSplits, kSplitBytes / slice);
@@ -361,6 +352,15 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
             rc = p->alloc(&p->w.spart, (size_t)(nsm * P * P));
             p->w.nsplit_max = (int)nsm;
         }
+        // the pairs of full tiles, then the ragged pairs of the last site block (one launch takes both)
+        p->w.sb_fold = sbuild_fold((int)N, (int)M, p->n_cu, p->w.nsplit_max);
+        order = sbuild_order((int)N, (int)M, kXcds, p->w.sb_fold);
+        const std::vector<int2> rag = sbuild_order_ragged((int)N, (int)M, p->w.sb_fold);
+        order.insert(order.end(), rag.begin(), rag.end());
+        int2* d_order = nullptr;
+        rc = rc ? rc : p->alloc(&d_order, order.size());
+        p->w.sb_order = d_order;
+        p->w.sb_order_len = (long)order.size();
         // slices of the border kernel split over samples (at least as many as the tile pairs use)
         const long nsb = std::min<long>(kMaxBorderSplits, kBorderSplitBytes / (N * P * (long)sizeof(float2)));
         p->w.nsb_max = 1;
@@ -392,8 +392,6 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     p->w.prof = &p->prof;
     if (rc) { delete p; return rc; }
     p->w.red_len = red_len;
-    if (hipDeviceGetAttribute(&p->n_cu, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess || p->n_cu < 1)
-        p->n_cu = 256;
     p->b_waves = 4;
     p->b_blocks = 4 * p->n_cu;
     p->w.n_cu = p->n_cu;
@@ -1237,7 +1235,8 @@ int crbm_sbuild_autotune(crbm_plan p, const int8_t* samples, const void* tanh_th
     if (int rc = set_device(p)) return rc;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return fail(CRBM_EHIP, "hipEventCreate");
-    const int nsplit = p->w.spart ? sbuild_splits((int)p->N, (int)p->M, n, p->w.n_cu, p->w.nsplit_max) : 1;
+    const int nsplit = p->w.spart ? sbuild_splits((int)p->N, (int)p->M, n, p->w.n_cu, p->w.nsplit_max,
+                                                   p->w.sb_fold) : 1;
     const int nsb = sbuild_border_splits((int)p->N, (int)p->M, n, p->w.n_cu, p->w.nsb_max);
     Profiler off;
     double best = 1e300;
@@ -1250,7 +1249,7 @@ int crbm_sbuild_autotune(crbm_plan p, const int8_t* samples, const void* tanh_th
             r = launch_sbuild_mfma((int)p->N, (int)p->M, p->P, samples, static_cast<const float2*>(tanh_theta), n,
                                    p->w.Om, p->w.Om, p->w.S, CRBM_PREC_BF16, tiles[ti], p->w.pack, p->w.pack_bytes,
                                    p->w.sb_order, p->w.sb_order_len,
-                                   p->w.spart, nsplit, p->w.bx, p->w.bx_part, nsb, &off, stream);
+                                   p->w.spart, nsplit, p->w.bx, p->w.bx_part, nsb, p->w.sb_fold, &off, stream);
         if (r == hipSuccess) r = hipEventRecord(e1, stream);
         if (r == hipSuccess) r = hipEventSynchronize(e1);
         if (r == hipSuccess) r = hipEventElapsedTime(&ms, e0, e1);

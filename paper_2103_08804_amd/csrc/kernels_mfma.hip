@@ -18,6 +18,10 @@
 // contraction sees (T' rounded as packed, plus c) are supplied by the caller,
 // so that S stays the centred Gram matrix of one set of vectors.
 //
+// The raw sums are symmetric in the sites and Hermitian in the units, so of the pairs of tiles (site block,
+// hidden block) only those with sA <= sB and hA <= hB are formed, and each also gives the entries of (sB, hA)
+// against (sA, hB) (sbuild_fold).
+//
 // Main kernel (W and b rows).  A row tile is 8 extended sites x 16 hidden
 // units = 128 rows, made of four 32-row matrix-core fragments of 2 sites x 16
 // hidden units each; N + 1 sites and M hidden units are padded only to
@@ -76,6 +80,7 @@ struct SbGeom {
     long P;
     int nSB, nHB;       // site blocks of 8 (over N + 1 extended sites), hidden blocks of 16
     int Np, Mp;         // padded plane heights: 8 nSB mask rows, 16 nHB T rows
+    int fold;           // the tile pairs hold hidden blocks hA <= hB only (sbuild_fold)
 };
 static SbGeom sb_geom(int N, int M) {
     SbGeom g;
@@ -84,6 +89,7 @@ static SbGeom sb_geom(int N, int M) {
     g.nHB = (M + MK_TH - 1) / MK_TH;
     g.Np = g.nSB * MK_TS;
     g.Mp = g.nHB * MK_TH;
+    g.fold = 0;
     return g;
 }
 
@@ -193,10 +199,9 @@ __device__ __forceinline__ double centre_y(const Centre& c, int i, int ip) {
     if (lo < c.N) return c.Om[lo].x;
     return 1.0;
 }
-// S entry of the W/b rows (i, j) = parameter k and (i', j') = parameter kp from
-// raw = <s_i s_i' T'^*_j T'_j'>
-__device__ __forceinline__ double2 centre_wb(const Centre& c, double2 raw, int i, int j, int ip, int jp, long k,
-                                              long kp) {
+// <O^*_(i,j) O_(i',j')> of the W/b rows (i, j) and (i', j') from raw = <s_i s_i' T'^*_j T'_j'>; symmetric in
+// (i, i') to the bit
+__device__ __forceinline__ double2 centre_oo(const Centre& c, double2 raw, int i, int j, int ip, int jp) {
     const double2 cj = centre_c(c, j), cjp = centre_c(c, jp);
     const double2 x1 = centre_x(c, i, ip, jp), x2 = centre_x(c, i, ip, j);
     const double y = centre_y(c, i, ip);
@@ -204,8 +209,12 @@ __device__ __forceinline__ double2 centre_wb(const Centre& c, double2 raw, int i
     v = zadd(v, zconjmul(cj, x1));                       // c_j^* X(i,i',j')
     v = zadd(v, zconjmul(x2, cjp));                      // X(i,i',j)^* c_j'
     const double2 cc = zconjmul(cj, cjp);
-    v = make_double2(v.x + cc.x * y, v.y + cc.y * y);    // c_j^* c_j' Y(i,i')
-    return zsub(v, zconjmul(c.Om[k], c.Om[kp]));
+    return make_double2(v.x + cc.x * y, v.y + cc.y * y); // c_j^* c_j' Y(i,i')
+}
+// S entry of parameters k = (i, j) and kp = (i', j')
+__device__ __forceinline__ double2 centre_wb(const Centre& c, double2 raw, int i, int j, int ip, int jp, long k,
+                                              long kp) {
+    return zsub(centre_oo(c, raw, i, j, ip, jp), zconjmul(c.Om[k], c.Om[kp]));
 }
 // extended site and unit of the W/b parameter kp >= N
 __device__ __forceinline__ void wb_of_p(long kp, int N, int M, int& i, int& j) {
@@ -538,16 +547,29 @@ __device__ __forceinline__ void sb_tile_pair(const SbGeom& gm, int sbA, int hbA,
                     const float2 prev = out[k * P + kp];
                     sum = make_float2(prev.x + sum.x, prev.y + sum.y);
                 }
-                float2 val;
+                // the same raw sum is that of (iB, jA) and (iA, jB) (the sites exchanged), which no tile pair
+                // holds when both blocks differ
+                const bool mirror = gm.fold && sbA != sbB && jA / MK_TH != hbB;
+                const long km = wb_to_p(iB, jA, N, M), kpm = wb_to_p(iA, jB, N, M);
+                float2 val, vmir;
                 if (raw) {
-                    val = sum;
+                    val = vmir = sum;
                 } else {
                     const double2 r = make_double2((double)sum.x * cen.inv_n, (double)sum.y * cen.inv_n);
-                    const double2 d = centre_wb(cen, r, iA, jA, iB, jB, k, kp);
+                    const double2 oo = centre_oo(cen, r, iA, jA, iB, jB);
+                    const double2 d = zsub(oo, zconjmul(cen.Om[k], cen.Om[kp]));
                     val = make_float2((float)d.x, k == kp ? 0.f : (float)d.y);   // Hermitian: real diagonal
+                    if (mirror) {
+                        const double2 dm = zsub(oo, zconjmul(cen.Om[km], cen.Om[kpm]));
+                        vmir = make_float2((float)dm.x, (float)dm.y);
+                    }
                 }
                 out[k * P + kp] = val;
                 if (!diag) out[kp * P + k] = cconj(val);
+                if (mirror) {
+                    out[km * P + kpm] = vmir;
+                    out[kpm * P + km] = cconj(vmir);
+                }
             }
         }
     }
@@ -883,7 +905,7 @@ struct RagGroup {
     std::vector<int2> pairs;
     double work;
 };
-static std::vector<RagGroup> ragged_groups(int N, int M) {
+static std::vector<RagGroup> ragged_groups(int N, int M, bool fold) {
     std::vector<RagGroup> groups;
     const int rf = sbuild_ragged_frags(N);
     if (!rf) return groups;
@@ -894,9 +916,11 @@ static std::vector<RagGroup> ragged_groups(int N, int M) {
     for (int up = 0; up < nt_main; ++up) {
         RagGroup g{{}, 0.0};
         std::vector<int> rest_hb;
+        // folded: hidden blocks h <= that of the B tile (the others are mirrored)
+        const int n_h = fold ? up % gm.nHB + 1 : gm.nHB;
         int h = 0;
         if (mix) {
-            for (; h + 1 < gm.nHB; h += 2) rest_hb.push_back(h + 1);
+            for (; h + 1 < n_h; h += 2) rest_hb.push_back(h + 1);
             if (rf > 1) {
                 size_t k = 0;
                 for (; k + 1 < rest_hb.size(); k += 2) {
@@ -913,7 +937,7 @@ static std::vector<RagGroup> ragged_groups(int N, int M) {
                 g.work += 1.0;
             }
         }
-        for (; h < gm.nHB; ++h) {
+        for (; h < n_h; ++h) {
             g.pairs.push_back(make_int2(rag_entry(RAG_PLAIN, h, 0), up));
             g.work += 1.0;
         }
@@ -928,30 +952,56 @@ static std::vector<RagGroup> ragged_groups(int N, int M) {
     return groups;
 }
 
-// Number of sample splits for a contraction of n samples when the tile pairs alone cannot fill the
-// device: the split count s (at most max_splits, which the plan's slice buffer holds, and at least 4
-// K tiles per split) that minimises the modelled time of the launch,
-// ceil(work s / resident workgroups) / s (rounds per unit of one pair's full-sample work; a ragged pair
-// of f live fragments counts f / 4), so that the last round of the launch is not left nearly empty.
-int sbuild_splits(int N, int M, long n, int n_cu, int max_splits) {
+// Time of a contraction of s sample splits on `slots` resident workgroups, in units of one full pair over
+// all samples: the full pairs run in rounds, the shorter ragged pairs (f live fragments: f / 4 of a full
+// pair each) fill the slots that the last round leaves free and then run in rounds of their own.
+static double ragged_work(int N, int M, bool fold) {
+    double w = 0.0;
+    for (const RagGroup& g : ragged_groups(N, M, fold)) w += g.work;
+    return w;
+}
+static double sbuild_rounds(int N, int M, bool fold, double w_rag, long s, long slots) {
     const SbGeom gm = sb_geom(N, M);
     const int rf = sbuild_ragged_frags(N);
-    const long nt = (long)(rf ? gm.nSB - 1 : gm.nSB) * gm.nHB;
-    const long n_main = nt * (nt + 1) / 2;
-    double w_rag = 0.0;
-    for (const RagGroup& g : ragged_groups(N, M)) w_rag += g.work;
+    const long sb = rf ? gm.nSB - 1 : gm.nSB, nt = sb * gm.nHB;
+    const long n_main = fold ? sb * (sb + 1) / 2 * ((long)gm.nHB * (gm.nHB + 1) / 2) : nt * (nt + 1) / 2;
+    const long full = n_main * s, over = full % slots;
+    const double d = 0.25 * rf;                                    // duration of a ragged pair
+    double t = (double)(full / slots), rag = w_rag * (double)s;
+    if (over) {
+        t += 1.0;
+        if (rf) rag -= (double)(slots - over) * std::floor(1.0 / d);
+    }
+    if (rf && rag > 0.0) t += std::ceil(rag / (double)slots - 1e-9) * d;
+    return t / (double)s;
+}
+
+// Number of sample splits for a contraction of n samples when the tile pairs alone cannot fill the
+// device: the split count s (at most max_splits, which the plan's slice buffer holds, and at least 4
+// K tiles per split) of the shortest modelled launch (sbuild_rounds).
+int sbuild_splits(int N, int M, long n, int n_cu, int max_splits, bool fold) {
     const long n_kt = ((n + MK_KT - 1) / MK_KT * MK_KT) / 64;    // the finest K tile of any variant is 64
     long smax = max_splits < n_kt / 4 ? max_splits : n_kt / 4;
     if (smax < 1) smax = 1;
     const long slots = 2L * n_cu;                                  // two resident workgroups per CU
+    const double w_rag = ragged_work(N, M, fold);
     double best = 1e300;
     long bs = 1;
     for (long sp = 1; sp <= smax; ++sp) {
-        const double w = (double)n_main + 0.25 * rf * w_rag;
-        const double t = std::ceil(w * (double)sp / (double)slots - 1e-9) / (double)sp;
+        const double t = sbuild_rounds(N, M, fold, w_rag, sp, slots);
         if (t < best * (1.0 - 1e-9)) { best = t; bs = sp; }
     }
     return (int)bs;
+}
+
+// Whether the contraction leaves out the tile pairs that exchanging the sites gives back.  The raw sums
+// <s_i s_i' T'^*_j T'_j'> are symmetric in (i, i') and Hermitian in (j, j'), so the pair of tiles (sA, hB),
+// (sB, hA) holds the conjugates of (sA, hA), (sB, hB): for 10 x 10, M = 400 the launch runs 25,350 pairs
+// of full tiles instead of 45,150 (65,536 samples, BF16: 148 ms against 263 ms).  Not where all pairs, split
+// max_splits ways, already fit on the device at once: there fewer pairs are no faster.
+bool sbuild_fold(int N, int M, int n_cu, int max_splits) {
+    const long s = max_splits > 1 ? max_splits : 1;
+    return sbuild_rounds(N, M, false, ragged_work(N, M, false), s, 2L * n_cu) * (double)s > 1.0;
 }
 
 // Sample splits of the border kernel.  Its nA x (W/b tiles + nA) workgroups each run the whole sample
@@ -983,9 +1033,10 @@ int sbuild_border_splits(int N, int M, long n, int n_cu, int max_splits) {
 hipError_t launch_sbuild_mfma(int N, int M, long P, const int8_t* sig, const float2* T, long n,
                               const double2* shift, const double2* Om, float2* S, int prec, int kt_bf16, void* pack,
                               size_t pack_bytes, const int2* order, long n_order, float2* split_buf, int nsplit,
-                              float2* bx, float2* bx_part, int nsb, Profiler* prof,
+                              float2* bx, float2* bx_part, int nsb, bool fold, Profiler* prof,
                               hipStream_t stream) {
-    const SbGeom gm = sb_geom(N, M);
+    SbGeom gm = sb_geom(N, M);
+    gm.fold = fold;
     if (nsplit > 1 && !split_buf) return hipErrorInvalidValue;
     if (nsb < 1 || (nsb > 1 && !bx_part)) return hipErrorInvalidValue;
     if (kt_bf16 != 64 && kt_bf16 != 128) return hipErrorInvalidValue;
@@ -1061,40 +1112,33 @@ hipError_t launch_sbuild_mfma(int N, int M, long P, const int8_t* sig, const flo
     return hipGetLastError();
 }
 
-// Dispatch order of the W/b tile pairs (u <= u').  Workgroup b runs on XCD b % n_xcd (round-robin
-// dispatch), so the pairs are grouped into g x g super-tiles, super-tiles are dealt to the XCDs in
-// turn, and each XCD's list is interleaved into the grid: the workgroups one XCD runs together
-// then share few operand slabs, which stay in that XCD's L2.  Padding entries are (-1, -1).
-std::vector<int2> sbuild_order(int N, int M, int n_xcd, int g) {
+// Dispatch order of the pairs of full tiles (u <= u'; folded: site blocks sA <= sB and hidden blocks hA <= hB).
+// Workgroup b runs on XCD b % n_xcd (round-robin dispatch).  The pairs are listed by (hA, hB), all site-block
+// pairs of one hidden pair in a row, and each XCD takes a contiguous run of the list: the workgroups that an
+// XCD runs together then read the same T rows (64 of the 80 rows a workgroup stages) and the masks of all
+// sites, which its L2 serves after the first of them.  Padding entries are (-1, -1).
+std::vector<int2> sbuild_order(int N, int M, int n_xcd, bool fold) {
     const SbGeom gm = sb_geom(N, M);
     // with ragged pairs the main kernel takes the tiles of the full site blocks only
-    const int nt = (sbuild_ragged_frags(N) ? gm.nSB - 1 : gm.nSB) * gm.nHB;
-    const int ns = (nt + g - 1) / g;
-    std::vector<std::vector<int2>> per(n_xcd);
-    int st = 0;
-    for (int U = 0; U < ns; ++U)
-        for (int V = U; V < ns; ++V, ++st) {
-            std::vector<int2>& L = per[st % n_xcd];
-            for (int a = 0; a < g; ++a)
-                for (int b = 0; b < g; ++b) {
-                    const int u = U * g + a, v = V * g + b;
-                    if (u < nt && v < nt && u <= v) L.push_back(make_int2(u, v));
-                }
-        }
-    size_t longest = 0;
-    for (auto& L : per) longest = L.size() > longest ? L.size() : longest;
-    std::vector<int2> out(longest * n_xcd, make_int2(-1, -1));
-    for (int x = 0; x < n_xcd; ++x)
-        for (size_t k = 0; k < per[x].size(); ++k) out[k * n_xcd + x] = per[x][k];
+    const int nsb = sbuild_ragged_frags(N) ? gm.nSB - 1 : gm.nSB;
+    std::vector<int2> list;
+    for (int hA = 0; hA < gm.nHB; ++hA)
+        for (int hB = fold ? hA : 0; hB < gm.nHB; ++hB)
+            for (int sA = 0; sA < nsb; ++sA)
+                for (int sB = hA <= hB ? sA : sA + 1; sB < nsb; ++sB)
+                    list.push_back(make_int2(sA * gm.nHB + hA, sB * gm.nHB + hB));
+    const size_t per = (list.size() + n_xcd - 1) / n_xcd;
+    std::vector<int2> out(per * n_xcd, make_int2(-1, -1));
+    for (size_t k = 0; k < list.size(); ++k) out[(k % per) * n_xcd + k / per] = list[k];
     return out;
 }
 
 // Ragged pairs in dispatch order, after the pairs of full tiles: kind by kind, the longest first
 // (RAG_DUAL, then RAG_MIX and RAG_PLAIN, then RAG_REST), each kind by B tile.  Workgroups of one kind then
 // run side by side and the shortest fill the last round.
-std::vector<int2> sbuild_order_ragged(int N, int M) {
+std::vector<int2> sbuild_order_ragged(int N, int M, bool fold) {
     std::vector<int2> out;
-    const std::vector<RagGroup> groups = ragged_groups(N, M);
+    const std::vector<RagGroup> groups = ragged_groups(N, M, fold);
     const int kinds[] = {RAG_DUAL, RAG_MIX, RAG_PLAIN, RAG_REST};
     for (int kind : kinds)
         for (const RagGroup& g : groups)
