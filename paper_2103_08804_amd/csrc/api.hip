@@ -70,6 +70,8 @@ constexpr long kSplitBytes = 1L << 30;     // bound of the split-contraction buf
 constexpr long kMaxSplits = 12;
 constexpr long kBorderSplitBytes = 256L << 20;   // bound of the border kernel's split slices
 constexpr long kMaxBorderSplits = 16;
+constexpr long kWeightedBytes = 64L << 20;       // bound of the weighted S's sample-run slices
+constexpr long kMaxWeightedRuns = 32;
 constexpr int kXcds = 8;                   // accelerator complex dies of the MI355X (round-robin dispatch)
 
 thread_local char g_err[512] = "";
@@ -305,7 +307,8 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
 
     const long P = p->P, M = n_hidden, S = max_samples;
     const long plane = (N + 1) * (M + 1);
-    const long red_len = ot_chunks_bound(S) * 2 * plane + 2048;
+    // chunk planes of the O^H c contraction; at least 64 sample runs of the weighted sums for small P
+    const long red_len = std::max<long>(ot_chunks_bound(S) * 2 * plane, 128 * std::min<long>(P, 4096)) + 2048;
     int rc = CRBM_OK;
     rc = rc ? rc : p->alloc(&p->bonds, bonds.size());
     rc = rc ? rc : p->alloc(&p->bond_tab, bonds.size() * (size_t)n_hidden);
@@ -321,6 +324,7 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     rc = rc ? rc : p->alloc(&p->w.Ap, P);
     rc = rc ? rc : p->alloc(&p->w.vstage, P);
     rc = rc ? rc : p->alloc(&p->w.u, S);
+    rc = rc ? rc : p->alloc(&p->w.dots, sr_dots_len(P));
     rc = rc ? rc : p->alloc(&p->w.red, red_len);
     // G: the matrix-free product's O v partials, ceil(M / 64) double2 (2 ceil(M / 64) float2) per sample
     rc = rc ? rc : p->alloc(&p->w.G, S * 2 * ((M + 63) / 64));
@@ -341,6 +345,12 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
         rc = rc ? rc : p->alloc(&p->w.hv_part, nT * nT * kHemvTile);
     }
     if (!rc && (flags & CRBM_PLAN_CHOLESKY)) rc = p->alloc(&p->w.S64, P * P);
+    // sample-run slices of the weighted S of small systems
+    const long n_sw = std::min<long>(kMaxWeightedRuns, kWeightedBytes / (P * P * (long)sizeof(double2)));
+    if (!rc && (flags & (CRBM_PLAN_DENSE_S | CRBM_PLAN_CHOLESKY)) && n_sw >= 2) {
+        rc = p->alloc(&p->w.swpart, (size_t)(n_sw * P * P));
+        p->w.n_sw = (int)n_sw;
+    }
     std::vector<int2> order;
     if (!rc && (flags & (CRBM_PLAN_DENSE_S | CRBM_PLAN_CHOLESKY))) {
         p->w.pack_bytes = sbuild_pack_bytes((int)N, (int)M, S);
@@ -398,6 +408,8 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     p->w.sb_kt = 128;
     e = hipMemcpy(p->bonds, bonds.data(), bonds.size() * sizeof(int2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(p->w.scal, 0, 32 * sizeof(double));
+    // the padding of the split-W planes stays zero: every writer fills the places of real sites and units, or all
+    if (e == hipSuccess) e = hipMemset(p->wplanes, 0, lc_plane_elems(N, M) * sizeof(uint16_t));
     if (e == hipSuccess && !order.empty())
         e = hipMemcpy(const_cast<int2*>(p->w.sb_order), order.data(), order.size() * sizeof(int2),
                       hipMemcpyHostToDevice);

@@ -233,6 +233,25 @@ __device__ __forceinline__ float2 ctanhf(float2 z) {
     return make_float2(s * q.x, s * q.y);
 }
 
+// ---------------------------------------------------------------- exact split of a binary32 weight
+// The three BF16 parts (hi + mid + lo, by truncation) of the real and imaginary part of W_ik at their places in the
+// planes of the theta product: [part][ct 128 + cb 32 + c][Np], 64-unit tile ct = k / 64, column block cb = 2 ((k % 64) / 32)
+// for the real part and the next one for the imaginary part, c = k % 32.
+__device__ __forceinline__ void split_store(uint16_t* __restrict__ planes, long plane, long idx, float w) {
+    const uint32_t hi = __float_as_uint(w) & 0xFFFF0000u;
+    const float r1 = w - __uint_as_float(hi);
+    const uint32_t mid = __float_as_uint(r1) & 0xFFFF0000u;
+    const float r2 = r1 - __uint_as_float(mid);
+    planes[idx] = (uint16_t)(hi >> 16);
+    planes[plane + idx] = (uint16_t)(mid >> 16);
+    planes[2 * plane + idx] = (uint16_t)(__float_as_uint(r2) >> 16);
+}
+__device__ __forceinline__ void split_plane_store(uint16_t* __restrict__ planes, long rows, int Np, int i, int k, float2 w) {
+    const long r = (long)(k >> 6) * 128 + ((k & 32) << 1) + (k & 31);
+    split_store(planes, rows * Np, r * Np + i, w.x);
+    split_store(planes, rows * Np, (r + 32) * Np + i, w.y);
+}
+
 // ---------------------------------------------------------------- wave64 reductions
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

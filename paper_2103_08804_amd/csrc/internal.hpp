@@ -20,10 +20,14 @@ struct RbmView {            // device pointers, complex64 interleaved
 hipError_t launch_theta(const int8_t* sig, long n, int N, int M, const float2* b, const float2* W, float2* theta,
                         uint16_t* planes, hipStream_t stream, const double* skip = nullptr);
 // O v of the matrix-free S product, u[s] = sum_k T_sk (sigma_s V_W + v_b)_k + sigma_s . v_a, without
-// writing the n x M product; partial: n * ceil(M / 64) double2 scratch
-hipError_t launch_theta_ov(const int8_t* sig, long n, int N, int M, const float2* vb, const float2* vW,
-                           const double2* va, const float2* T, uint16_t* planes, double2* partial, double2* u,
-                           hipStream_t stream, const double* skip);
+// writing the n x M product; planes: V_W split as the theta product's W; partial: n * ceil(M / 64) double2
+// scratch; mean_out <- the sum of the n_omv partials omv (a double pair)
+hipError_t launch_theta_ov(const int8_t* sig, long n, int N, int M, const float2* vb, const double2* va,
+                           const float2* T, const uint16_t* planes, double2* partial, double2* u, const double2* omv,
+                           int n_omv, double* mean_out, hipStream_t stream, const double* skip);
+// padded row length (sites) and row count of one BF16 plane of the split W
+inline int theta_np(int N) { return (N + 31) / 32 * 32; }
+inline long theta_rows(int M) { return (long)((M + 63) / 64) * 128; }
 
 // elements of the three BF16 planes of W used by the theta product and the fused log-cosh sums: 3 x (tiles of 64 units x 128
 // real columns) x (sites rounded up to 32)
@@ -117,6 +121,9 @@ struct SrWork {
     double2* p;               // [P]
     double2* Ap;              // [P]
     double2* u;               // [n]  per-sample scratch for the matrix-free product
+    double* dots;             // [sr_dots_len(P)] per-block dot products of the solve
+    double2* swpart;          // [n_sw][P][P] sample-run slices of the weighted S (or null)
+    int n_sw;
     double2* red;             // reduction scratch [red_len]
     long red_len;
     float2* S;                // [P][P] dense (may be null)
@@ -167,6 +174,7 @@ inline int hemv_tiles(long P) { return (int)((P + kHemvTile - 1) / kHemvTile); }
 // the dense FP64 solve is meant for P of a few thousand (its factor is P^2 complex128 values)
 constexpr long kCholMaxP = 4000;
 
+long sr_dots_len(long P);
 hipError_t launch_sr_step(const SrArgs& args, const SrWork& w, hipStream_t stream);
 
 // ---------------------------------------------------------------- batched moments

@@ -89,14 +89,7 @@ __global__ __launch_bounds__(256) void k_wsplit(const float2* __restrict__ W, in
         const float2 v = W[(long)i * M + k];
         w = (cb & 1) ? v.y : v.x;
     }
-    const uint32_t u = __float_as_uint(w);
-    const uint32_t hi = u & 0xFFFF0000u;
-    const float r1 = w - __uint_as_float(hi);
-    const uint32_t mid = __float_as_uint(r1) & 0xFFFF0000u;
-    const float r2 = r1 - __uint_as_float(mid);
-    planes[idx] = (uint16_t)(hi >> 16);
-    planes[rows * Np + idx] = (uint16_t)(mid >> 16);
-    planes[2 * rows * Np + idx] = (uint16_t)(__float_as_uint(r2) >> 16);
+    split_store(planes, rows * Np, idx, w);
 }
 
 // combine two partial sums of log cosh: the linear parts add, the bounded factors multiply
@@ -256,9 +249,16 @@ __global__ __launch_bounds__(256, 4) void k_theta_ov(const int8_t* __restrict__ 
 constexpr int kOvFinalBlocks = 4096;
 __global__ __launch_bounds__(256) void k_ov_final(int N, long n, int Mt, const int8_t* __restrict__ sig,
                                                   const double2* __restrict__ va, const double2* __restrict__ partial,
-                                                  double2* __restrict__ u, const double* __restrict__ skip) {
+                                                  double2* __restrict__ u, const double2* __restrict__ omv, int n_omv,
+                                                  double* __restrict__ mean_out, const double* __restrict__ skip) {
     if (skip && *skip != 0.0) return;
     const int lane = threadIdx.x & 63;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) {   // <O>.v, in one fixed order
+        double2 m = make_double2(0.0, 0.0);
+        for (int b = lane; b < n_omv; b += kWave) m = zadd(m, omv[b]);
+        m = wave_sum(m);
+        if (lane == 0) { mean_out[0] = m.x; mean_out[1] = m.y; }
+    }
     for (long s = (long)blockIdx.x * 4 + (threadIdx.x >> 6); s < n; s += (long)gridDim.x * 4) {
         double ax = 0.0, ay = 0.0;
         for (int i = lane; i < N; i += kWave) {
@@ -277,20 +277,17 @@ __global__ __launch_bounds__(256) void k_ov_final(int N, long n, int Mt, const i
     }
 }
 
-hipError_t launch_theta_ov(const int8_t* sig, long n, int N, int M, const float2* vb, const float2* vW,
-                           const double2* va, const float2* T, uint16_t* planes, double2* partial, double2* u,
-                           hipStream_t stream, const double* skip) {
+hipError_t launch_theta_ov(const int8_t* sig, long n, int N, int M, const float2* vb, const double2* va,
+                           const float2* T, const uint16_t* planes, double2* partial, double2* u, const double2* omv,
+                           int n_omv, double* mean_out, hipStream_t stream, const double* skip) {
     if (n <= 0) return hipSuccess;
-    const int Np = (N + TH_K - 1) / TH_K * TH_K;
+    const int Np = theta_np(N);
     const int Mt = (M + 63) / 64;
-    const long cnt = (long)Mt * TH_C * Np;
-    hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, stream, vW, N, M, Np, Mt, planes,
-                       skip);
     hipLaunchKernelGGL(k_theta_ov, dim3((unsigned)((n + TH_S - 1) / TH_S), (unsigned)Mt), dim3(256), 0, stream, sig,
                        n, N, Np, M, vb, planes, Mt, T, partial, skip);
     const long fb = (n + 3) / 4;
     hipLaunchKernelGGL(k_ov_final, dim3((unsigned)(fb < kOvFinalBlocks ? fb : kOvFinalBlocks)), dim3(256), 0, stream,
-                       N, n, Mt, sig, va, partial, u, skip);
+                       N, n, Mt, sig, va, partial, u, omv, n_omv, mean_out, skip);
     return hipGetLastError();
 }
 

@@ -20,11 +20,11 @@
 namespace crbm {
 
 
-// device scalar slots (SC_RR and SC_RR1 hold r^H r of the even and odd CG iterations; SC_WSUM the sum of the
-// sample weights)
+// device scalar slots (SC_DONE0 and SC_DONE1: whether the solve had ended before an even and an odd CG
+// iteration; SC_WSUM the sum of the sample weights; SC_OMV <O>.p of the matrix-free product, two slots)
 enum {
     SC_RM_RE = 0, SC_RM_IM, SC_R2, SC_GAMMA, SC_GCOT, SC_COEF,
-    SC_RR = 8, SC_PAP, SC_RR1, SC_WSUM, SC_FF, SC_DONE, SC_ITERS, SC_FLAGS, SC_RESID, SC_XX,
+    SC_DONE0 = 8, SC_DONE1, SC_WSUM = 11, SC_FF, SC_ITERS = 14, SC_FLAGS, SC_OMV = 18,
     SC_COUNT = 32
 };
 
@@ -67,15 +67,24 @@ __global__ __launch_bounds__(256) void k_r_moments(const float2* __restrict__ R,
 // Fit mode (0): gamma = arccos sqrt(|<R>|^2/<|R|^2>) and the force scale dgamma gamma cot gamma.
 // Energy mode (1): R holds E_loc; the SC_GAMMA slot takes the variance <|E|^2> - |<E>|^2 and the
 // force scale is -lr (passed as dgamma).
-__global__ void k_r_final(const double2* __restrict__ red, int n_blocks, double dgamma, int mode,
-                          double* __restrict__ sc) {
-    if (threadIdx.x != 0) return;
-    double a = 0, b = 0, c = 0, d = 0;
-    for (int k = 0; k < n_blocks; ++k) {
+// One wave: each lane adds its share of the partials (one thread adding all 256 in turn took 37-47 us).
+__device__ __forceinline__ void sum_r_partials(const double2* __restrict__ red, int n_blocks, double& a, double& b,
+                                               double& c, double& d) {
+    a = b = c = d = 0.0;
+#pragma unroll 4
+    for (int k = threadIdx.x; k < n_blocks; k += kWave) {
         a += red[2 * k].x; b += red[2 * k].y; c += red[2 * k + 1].x; d += red[2 * k + 1].y;
     }
+    a = wave_sum(a); b = wave_sum(b); c = wave_sum(c); d = wave_sum(d);
+}
+
+__global__ __launch_bounds__(64) void k_r_final(const double2* __restrict__ red, int n_blocks, double dgamma, int mode,
+                                                double* __restrict__ sc) {
+    double a, b, c, d;
+    sum_r_partials(red, n_blocks, a, b, c, d);
+    if (threadIdx.x != 0) return;
     sc[SC_RM_RE] = a; sc[SC_RM_IM] = b; sc[SC_R2] = c;
-    for (int k = SC_RR; k < SC_COUNT; ++k) sc[k] = 0.0;
+    for (int k = SC_DONE0; k < SC_COUNT; ++k) sc[k] = 0.0;
     sc[SC_WSUM] = d;
     if (mode == 1) {
         sc[SC_GAMMA] = c - (a * a + b * b);
@@ -93,10 +102,11 @@ __global__ void k_r_final(const double2* __restrict__ red, int n_blocks, double 
 
 // gamma and beta = <R> of the fit as it stands (Sec. III: beta is taken once the steps are done):
 // out = {gamma, Re <R>, Im <R>, <|R|^2>, flags}
-__global__ void k_fit_stats(const double2* __restrict__ red, int n_blocks, double* __restrict__ out) {
+__global__ __launch_bounds__(64) void k_fit_stats(const double2* __restrict__ red, int n_blocks,
+                                                  double* __restrict__ out) {
+    double a, b, c, d;
+    sum_r_partials(red, n_blocks, a, b, c, d);
     if (threadIdx.x != 0) return;
-    double a = 0, b = 0, c = 0;
-    for (int k = 0; k < n_blocks; ++k) { a += red[2 * k].x; b += red[2 * k].y; c += red[2 * k + 1].x; }
     const double gamma = acos(fmin(1.0, sqrt((a * a + b * b) / c)));
     out[0] = gamma;
     out[1] = a;
@@ -132,32 +142,31 @@ __global__ __launch_bounds__(256) void k_lse_partial(const float2* __restrict__ 
 __global__ __launch_bounds__(256) void k_lse_weights(const float2* __restrict__ lp, long n,
                                                      const double2* __restrict__ part, int n_part,
                                                      double* __restrict__ w) {
-    __shared__ double lse;
-    if (threadIdx.x == 0) {
-        double mx = -INFINITY;
-        for (int k = 0; k < n_part; ++k) mx = fmax(mx, part[k].x);
-        double z = 0.0;
-        for (int k = 0; k < n_part; ++k)
-            if (part[k].x > -INFINITY) z += part[k].y * exp(part[k].x - mx);
-        lse = mx + log(z);   // NaN or infinite when no amplitude is finite and non-zero
-    }
-    __syncthreads();
-    const double L = lse;
+    // every wave merges the partials, its lanes in parallel (one thread in turn took 35 us)
+    double mx = -INFINITY;
+    for (int k = threadIdx.x & 63; k < n_part; k += kWave) mx = fmax(mx, part[k].x);
+    for (int o = 32; o >= 1; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, kWave));
+    double z = 0.0;
+    for (int k = threadIdx.x & 63; k < n_part; k += kWave)
+        if (part[k].x > -INFINITY) z += part[k].y * exp(part[k].x - mx);
+    z = wave_sum(z);
+    const double L = mx + log(z);   // NaN or infinite when no amplitude is finite and non-zero
     for (long s = (long)blockIdx.x * 256 + threadIdx.x; s < n; s += (long)gridDim.x * 256)
         w[s] = exp(2.0 * (double)lp[s].x - L);
 }
 
 hipError_t launch_fit_stats(const float2* R, const double* w, long n, double2* red, double* out, hipStream_t stream) {
-    const int nb = 256;
+    const int nb = (int)std::min<long>((n + 255) / 256, 256);
     hipLaunchKernelGGL(k_r_moments, dim3(nb), dim3(256), 0, stream, R, w, n, red);
     hipLaunchKernelGGL(k_fit_stats, dim3(1), dim3(64), 0, stream, red, nb, out);
     return hipGetLastError();
 }
 
 hipError_t launch_enum_weights(const float2* lp, long n, double2* part, double* w, hipStream_t stream) {
-    hipLaunchKernelGGL(k_lse_partial, dim3(kLseBlocks), dim3(256), 0, stream, lp, n, part);
+    const int np = (int)std::min<long>((n + 255) / 256, kLseBlocks);
+    hipLaunchKernelGGL(k_lse_partial, dim3(np), dim3(256), 0, stream, lp, n, part);
     const unsigned nb = (unsigned)std::min<long>((n + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_lse_weights, dim3(nb), dim3(256), 0, stream, lp, n, part, kLseBlocks, w);
+    hipLaunchKernelGGL(k_lse_weights, dim3(nb), dim3(256), 0, stream, lp, n, part, np, w);
     return hipGetLastError();
 }
 
@@ -172,7 +181,7 @@ hipError_t launch_enum_weights(const float2* lp, long n, double2* part, double* 
 // and both parts (64 accumulator registers for two coefficients), so that three workgroups share a
 // CU and one's staging overlaps another's products.  The tile after the current one is loaded into
 // registers while the products run.  Chunk sums are written in FP32 and added across chunks in FP64.
-// coef kinds: 0 -> c = w; 1 -> c = w R; 2 -> c = w u (u double2 [n]);
+// coef kinds: 0 -> c = w; 1 -> c = w R; 2 -> c = w (u - mean) (u double2 [n], mean a double pair);
 //             3 -> c = 2 (1 - R) conj(R) / n; 4 -> c = w (R - u[0]) (u pointing at <R>: the centred
 //             ratio, whose contraction <O^* (R - <R>)> = <O^* R> - <O^*><R> carries no cancellation of
 //             the mean of O)
@@ -188,12 +197,12 @@ __device__ __forceinline__ float round_to_bf16(float x) {
 }
 
 __device__ __forceinline__ float2 coef_of(int kind, long s, const double* w, double wdef, const float2* R,
-                                          const double2* u, double two_over_n) {
+                                          const double2* u, const double* mean, double two_over_n) {
     const float ws = w ? (float)w[s] : (float)wdef;
     switch (kind) {
         case 0: return make_float2(ws, 0.f);
         case 1: return cscale(R[s], ws);
-        case 2: return make_float2((float)(u[s].x) * ws, (float)(u[s].y) * ws);
+        case 2: return make_float2((float)(u[s].x - mean[0]) * ws, (float)(u[s].y - mean[1]) * ws);
         case 4: return cscale(csub(R[s], make_float2((float)u[0].x, (float)u[0].y)), ws);
         default: {
             const float2 r = R[s];
@@ -227,7 +236,7 @@ template <int NK>
 __device__ __forceinline__ void ot_load(OtRaw<NK>& r, int tid, int row, int M, int i0, int j0, long sb, long s_end,
                                         const int8_t* __restrict__ sig16, const float2* __restrict__ T, int kind0,
                                         int kind1, const double* __restrict__ w, double wdef,
-                                        const float2* __restrict__ R, const double2* __restrict__ u,
+                                        const float2* __restrict__ R, const double2* __restrict__ u, const double* __restrict__ mean,
                                         double two_over_n, int round_bf16, const double2* __restrict__ shift_b) {
     const long s = sb + (tid >> 3);
     const int g = tid & 7;
@@ -254,7 +263,7 @@ __device__ __forceinline__ void ot_load(OtRaw<NK>& r, int tid, int row, int M, i
     r.cf = make_float2(0.f, 0.f);
     if (tid < NK * OM_S) {
         const long sc = sb + tid % OM_S;
-        if (sc < s_end) r.cf = coef_of(tid / OM_S == 0 ? kind0 : kind1, sc, w, wdef, R, u, two_over_n);
+        if (sc < s_end) r.cf = coef_of(tid / OM_S == 0 ? kind0 : kind1, sc, w, wdef, R, u, mean, two_over_n);
     }
 }
 
@@ -265,7 +274,8 @@ __device__ __forceinline__ void ot_stage(OtRaw<NK>& raw, float (&sA)[OM_S][OM_R 
                                          int M, int i0, int j0, long sb, long s_end, const int8_t* __restrict__ sig16,
                                          const float2* __restrict__ T, int kind0, int kind1,
                                          const double* __restrict__ w, double wdef, const float2* __restrict__ R,
-                                         const double2* __restrict__ u, double two_over_n, int round_bf16,
+                                         const double2* __restrict__ u, const double* __restrict__ mean,
+                                         double two_over_n, int round_bf16,
                                          const double2* __restrict__ shift_b) {
     const int ss = tid >> 3, g = tid & 7;
     if (tid < NK * OM_S) sC[tid / OM_S][tid % OM_S] = raw.cf;
@@ -285,7 +295,7 @@ __device__ __forceinline__ void ot_stage(OtRaw<NK>& raw, float (&sA)[OM_S][OM_R 
     __syncthreads();
     // the next tile's loads, in flight during the products
     if (sb + OM_S < s_end)
-        ot_load<NK>(raw, tid, row, M, i0, j0, sb + OM_S, s_end, sig16, T, kind0, kind1, w, wdef, R, u, two_over_n,
+        ot_load<NK>(raw, tid, row, M, i0, j0, sb + OM_S, s_end, sig16, T, kind0, kind1, w, wdef, R, u, mean, two_over_n,
                     round_bf16, shift_b);
 }
 
@@ -296,8 +306,8 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_ot(int N, int M, int r
                                             const float2* __restrict__ T,
                                             long n, long chunk, int n_chunks, int kind0, int kind1,
                                             const double* __restrict__ w, const float2* __restrict__ R,
-                                            const double2* __restrict__ u, float* __restrict__ partial,
-                                            const double* __restrict__ skip, int round_bf16,
+                                            const double2* __restrict__ u, const double* __restrict__ mean,
+                                            float* __restrict__ partial, const double* __restrict__ skip, int round_bf16,
                                             const double2* __restrict__ shift_b) {
     if (skip && *skip != 0.0) return;
     __shared__ __align__(16) float sA[OM_S][OM_R + 4];      // sigma~ [sample][site]
@@ -314,13 +324,13 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_ot(int N, int M, int r
         const long s_begin = (long)ck * chunk;
         const long s_end = min(n, s_begin + chunk);
         OtRaw<NK> raw;
-        ot_load<NK>(raw, tid, row, M, i0, j0, s_begin, s_end, sig16, T, kind0, kind1, w, wdef, R, u, two_over_n,
+        ot_load<NK>(raw, tid, row, M, i0, j0, s_begin, s_end, sig16, T, kind0, kind1, w, wdef, R, u, mean, two_over_n,
                     round_bf16, shift_b);
         if (i0 + 32 * wv > N) {
             // no extended site in this wave's rows: it only helps to stage the tiles
             for (long sb = s_begin; sb < s_end; sb += OM_S) {
                 ot_stage<NK>(raw, sA, sY, sC, tid, row, M, i0, j0, sb, s_end, sig16, T, kind0, kind1, w, wdef, R, u,
-                             two_over_n, round_bf16, shift_b);
+                             mean, two_over_n, round_bf16, shift_b);
                 __syncthreads();
             }
             continue;
@@ -334,7 +344,7 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_ot(int N, int M, int r
                 for (int v = 0; v < 16; ++v) acc[c][ri][v] = 0.f;
         for (long sb = s_begin; sb < s_end; sb += OM_S) {
             ot_stage<NK>(raw, sA, sY, sC, tid, row, M, i0, j0, sb, s_end, sig16, T, kind0, kind1, w, wdef, R, u,
-                         two_over_n, round_bf16, shift_b);
+                         mean, two_over_n, round_bf16, shift_b);
             // lane l supplies row l % 32 (A) and column l % 32 (B) at sample 2 ks + l / 32; rows past N are zeros
 #pragma unroll 4
             for (int ks = 0; ks < OM_S / 2; ++ks) {
@@ -371,39 +381,87 @@ __global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_ot(int N, int M, int r
 // shift_b: the chunks summed conj(T - c_j) for the units j < M, and conj(c_j) times the same coefficient
 // vector's sum over sigma~_i (its column j = M) is added back here; for coefficient vector 0 (the weights)
 // that sum is exactly 1 on the b row.
-__global__ void k_ot_reduce(int N, int M, const float* __restrict__ partial, int n_chunks, int nk, int conj0,
-                            double2* __restrict__ out0, double2* __restrict__ out1, const double* __restrict__ skip,
-                            const double2* __restrict__ shift_b) {
-    if (skip && *skip != 0.0) return;
-    const long plane = (long)(N + 1) * (M + 1);
-    const long o = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= plane) return;
-    const int i = (int)(o / (M + 1)), j = (int)(o % (M + 1));
-    if (i == N && j == M) return;
-    const long k = ij_to_p(i, j, N, M);
-    for (int c = 0; c < nk; ++c) {
-        double2 acc = make_double2(0.0, 0.0);
-        for (int b = 0; b < n_chunks; ++b) {
-            const float* pc = partial + ((long)b * nk + c) * 2 * plane;
-            acc.x += (double)pc[o];
-            acc.y += (double)pc[plane + o];
+// A block adds 64 entries: wave v the chunks v, v + 4, .., the four waves' sums in order (a thread per entry walking
+// all chunks left most of the device idle: 250 us at 10 x 10 with 256 chunks, now 52 us).
+// tail (one coefficient vector, the matrix-free S v): out = sum + eps v, and the block's dot products.
+struct OpTail {
+    int on;
+    double eps;
+    const double2* v;    // the vector S acts on
+    const double2* r;    // residual of the CG (null with F)
+    const double2* F;    // right-hand side: the dots are |F - y|^2 and |v|^2 instead (null within the CG)
+    double* dots;        // [blocks][4]: r^H r, v^H y, r^H y, y^H y (real parts)
+};
+// dot products of one wave's 64 entries (k < P valid) of y = (S + eps) v
+__device__ __forceinline__ void tail_dots(const OpTail& t, long k, bool valid, double2 v, double2 y, int lane, long blk) {
+    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
+    if (valid) {
+        if (t.F) {
+            const double2 f = zsub(t.F[k], y);
+            d0 = f.x * f.x + f.y * f.y;
+            d1 = v.x * v.x + v.y * v.y;
+        } else {
+            const double2 r = t.r[k];
+            d0 = r.x * r.x + r.y * r.y;
+            d1 = v.x * y.x + v.y * y.y;
+            d2 = r.x * y.x + r.y * y.y;
+            d3 = y.x * y.x + y.y * y.y;
         }
-        if (shift_b && j < M) {
-            double2 y = make_double2(1.0, 0.0);
-            if (i < N || c > 0) {
-                const long oy = (long)i * (M + 1) + M;
-                y = make_double2(0.0, 0.0);
-                for (int b = 0; b < n_chunks; ++b) {
-                    const float* pc = partial + ((long)b * nk + c) * 2 * plane;
+    }
+    d0 = wave_sum(d0); d1 = wave_sum(d1); d2 = wave_sum(d2); d3 = wave_sum(d3);
+    if (lane == 0) {
+        double* o = t.dots + 4 * blk;
+        o[0] = d0; o[1] = d1; o[2] = d2; o[3] = d3;
+    }
+}
+__global__ __launch_bounds__(256) void k_ot_reduce(int N, int M, const float* __restrict__ partial, int n_chunks, int nk,
+                                                   int conj0, double2* __restrict__ out0, double2* __restrict__ out1,
+                                                   const double* __restrict__ skip, const double2* __restrict__ shift_b,
+                                                   OpTail tail) {
+    if (skip && *skip != 0.0) return;
+    __shared__ double2 sa[4][64], sy[4][64];
+    const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
+    const long plane = (long)(N + 1) * (M + 1);
+    const long o = (long)blockIdx.x * 64 + lane;
+    const bool in = o < plane - 1;               // the last entry (i = N, j = M) is no parameter
+    const int i = in ? (int)(o / (M + 1)) : 0, j = in ? (int)(o % (M + 1)) : M;
+    const long k = in ? ij_to_p(i, j, N, M) : 0;
+    for (int c = 0; c < nk; ++c) {
+        const bool shifted = shift_b && j < M, summed = shifted && (i < N || c > 0);
+        const long oy = (long)i * (M + 1) + M;
+        double2 acc = make_double2(0.0, 0.0), y = make_double2(0.0, 0.0);
+        if (in)
+#pragma unroll 8
+            for (int b = v; b < n_chunks; b += 4) {
+                const float* pc = partial + ((long)b * nk + c) * 2 * plane;
+                acc.x += (double)pc[o];
+                acc.y += (double)pc[plane + o];
+                if (summed) {
                     y.x += (double)pc[oy];
                     y.y += (double)pc[plane + oy];
                 }
             }
+        if (c > 0) __syncthreads();
+        sa[v][lane] = acc;
+        sy[v][lane] = y;
+        __syncthreads();
+        if (v != 0) continue;
+        for (int b = 1; b < 4; ++b) { acc = zadd(acc, sa[b][lane]); y = zadd(y, sy[b][lane]); }
+        if (shifted) {
+            if (!summed) y = make_double2(1.0, 0.0);
             const double2 cj = make_double2((double)(float)shift_b[j].x, (double)(float)shift_b[j].y);
             acc = zadd(acc, zconjmul(cj, y));
         }
         if (c == 0 && conj0) acc.y = -acc.y;
-        (c == 0 ? out0 : out1)[k] = acc;
+        if (tail.on) {
+            double2 vk = make_double2(0.0, 0.0);
+            if (in) {
+                vk = tail.v[k];
+                acc = make_double2(acc.x + tail.eps * vk.x, acc.y + tail.eps * vk.y);
+            }
+            tail_dots(tail, k, in, vk, acc, lane, blockIdx.x);
+        }
+        if (in) (c == 0 ? out0 : out1)[k] = acc;
     }
 }
 
@@ -448,7 +506,8 @@ static OtPlan ot_plan(int N, int M, long n, int nk, int n_cu) {
 static hipError_t run_ot(int N, int M, const int8_t* sig16, const float2* T, long n, int kind0, int kind1, int nk,
                          const double* w, const float2* R, const double2* u, void* partial_buf, int conj0,
                          double2* out0, double2* out1, hipStream_t stream, const double* skip, Profiler* prof,
-                         int n_cu, int round_bf16 = 0, const double2* shift_b = nullptr) {
+                         int n_cu, int round_bf16 = 0, const double2* shift_b = nullptr,
+                         const double* mean = nullptr, const OpTail& tail = OpTail{}) {
     const OtPlan op = ot_plan(N, M, n, nk, n_cu);
     const int row = sig16_row(N);
     float* partial = static_cast<float*>(partial_buf);
@@ -456,14 +515,14 @@ static hipError_t run_ot(int N, int M, const int8_t* sig16, const float2* T, lon
     if (prof) prof->begin(PROF_OT, stream);
     if (nk == 2)
         hipLaunchKernelGGL(k_ot<2>, grid, dim3(256), 0, stream, N, M, row, sig16, T, n, op.chunk, op.n_chunks, kind0,
-                           kind1, w, R, u, partial, skip, round_bf16, shift_b);
+                           kind1, w, R, u, mean, partial, skip, round_bf16, shift_b);
     else
         hipLaunchKernelGGL(k_ot<1>, grid, dim3(256), 0, stream, N, M, row, sig16, T, n, op.chunk, op.n_chunks, kind0,
-                           kind1, w, R, u, partial, skip, round_bf16, shift_b);
+                           kind1, w, R, u, mean, partial, skip, round_bf16, shift_b);
     if (prof) prof->end(stream);
     const long plane = (long)(N + 1) * (M + 1);
-    hipLaunchKernelGGL(k_ot_reduce, dim3((unsigned)((plane + 255) / 256)), dim3(256), 0, stream, N, M, partial,
-                       op.n_chunks, nk, conj0, out0, out1, skip, shift_b);
+    hipLaunchKernelGGL(k_ot_reduce, dim3((unsigned)((plane + 63) / 64)), dim3(256), 0, stream, N, M, partial,
+                       op.n_chunks, nk, conj0, out0, out1, skip, shift_b, tail);
     return hipGetLastError();
 }
 
@@ -473,50 +532,61 @@ static void pack_sig16(const int8_t* sig, long n, int N, int8_t* out, hipStream_
                        sig16_row(N), out);
 }
 
+// sum of v over the workgroup (256 threads, four waves); thread 0 has the result
+__device__ __forceinline__ double block_total(double v, double (&sh)[4]) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return sh[0] + sh[1] + sh[2] + sh[3];
+}
+
 // ORc = <O^* (R - <R>)> = <O^* R> - <O^*><R>  (R = E_loc in energy mode):
 // fit mode (0):    F_k = coef [<O_k^* R>/<R> - <O_k^*>] = coef ORc_k / <R>;
 // energy mode (1): F_k = coef [<O_k^* E> - <O_k^*><E>] = coef ORc_k   (coef = -lr).
-// Om holds conj(<O>) on entry and <O> on exit.
-__global__ void k_make_f(long P, int mode, double2* __restrict__ Om, const double2* __restrict__ ORm,
-                         const double* __restrict__ sc, double2* __restrict__ F) {
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= P) return;
+// means: Om holds conj(<O>) on entry and <O> on exit (else it is left as it is); ff[block] = |F|^2 of the block.
+__device__ __forceinline__ double2 force_of(double2 orc, int mode, const double* __restrict__ sc) {
     const double2 rm = make_double2(sc[SC_RM_RE], sc[SC_RM_IM]);
     const double coef = sc[SC_COEF];
-    const double2 omc = Om[k];
-    const double2 d = mode == 1 ? ORm[k] : zdiv(ORm[k], rm);
-    F[k] = make_double2(coef * d.x, coef * d.y);
-    Om[k] = make_double2(omc.x, -omc.y);
+    const double2 d = mode == 1 ? orc : zdiv(orc, rm);
+    return make_double2(coef * d.x, coef * d.y);
 }
-
-// F alone from ORc (as k_make_f, the means left as they are)
-__global__ void k_f_of(long P, int mode, const double2* __restrict__ ORm, const double* __restrict__ sc,
-                       double2* __restrict__ F) {
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= P) return;
-    const double2 rm = make_double2(sc[SC_RM_RE], sc[SC_RM_IM]);
-    const double coef = sc[SC_COEF];
-    const double2 d = mode == 1 ? ORm[k] : zdiv(ORm[k], rm);
-    F[k] = make_double2(coef * d.x, coef * d.y);
+__global__ __launch_bounds__(256) void k_make_f(long P, int mode, int means, double2* __restrict__ Om,
+                                                const double2* __restrict__ ORm, const double* __restrict__ sc,
+                                                double2* __restrict__ F, double* __restrict__ ff) {
+    __shared__ double sh[4];
+    const long k = (long)blockIdx.x * 256 + threadIdx.x;
+    double2 f = make_double2(0.0, 0.0);
+    if (k < P) {
+        f = force_of(ORm[k], mode, sc);
+        F[k] = f;
+        if (means) Om[k].y = -Om[k].y;
+    }
+    const double t = block_total(f.x * f.x + f.y * f.y, sh);
+    if (threadIdx.x == 0) ff[blockIdx.x] = t;
 }
 
 // ------------------------------------------------------------------ weighted P-vector contractions in double
 // With sample weights (exact enumeration: every configuration once, weighted by |psi|^2 / Z) the weights span
 // many orders of magnitude and the configurations next to nodes of the state carry O_k of the same size
 // inverted, so the sums over samples run in double here: Om_k = sum_s w_s conj(O_sk) and
-// ORc_k = sum_s w_s conj(O_sk) (R_s - <R>).  One thread per parameter; threads of one site row read
-// consecutive hidden units of T.
-__global__ __launch_bounds__(256) void k_ot64(int N, int M, long P, const int8_t* __restrict__ sig,
-                                              const float2* __restrict__ T, const double* __restrict__ w,
-                                              const float2* __restrict__ R, long n, const double* __restrict__ sc,
-                                              double2* __restrict__ Om, double2* __restrict__ ORc) {
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
+// ORc_k = sum_s w_s conj(O_sk) (R_s - <R>).  One thread per parameter and run of samples (threads of one site
+// row read consecutive hidden units of T), the runs added in order by a second pass, which also forms F: P is a
+// few hundred, so without the split two workgroups walked all samples, each step waiting on its loads (P = 120,
+// 1024 samples: 350 us, now 9 us and 4 us for the second pass).
+constexpr int OT64_T = 128;
+__global__ __launch_bounds__(OT64_T) void k_ot64(int N, int M, long P, const int8_t* __restrict__ sig,
+                                                 const float2* __restrict__ T, const double* __restrict__ w,
+                                                 const float2* __restrict__ R, long n, long run,
+                                                 const double* __restrict__ sc, double2* __restrict__ part) {
+    const long k = (long)blockIdx.x * OT64_T + threadIdx.x;
     if (k >= P) return;
     int i, j;
     p_to_ij(k, N, M, i, j);
     const double rx = sc[SC_RM_RE], ry = sc[SC_RM_IM];
     double ox = 0, oy = 0, qx = 0, qy = 0;
-    for (long s = 0; s < n; ++s) {
+    const long s0 = (long)blockIdx.y * run, s1 = min(n, s0 + run);
+#pragma unroll 8
+    for (long s = s0; s < s1; ++s) {
         const double ws = w[s];
         const double sv = (i == N) ? 1.0 : (double)sig[s * N + i];
         double tx = 1.0, ty = 0.0;
@@ -526,8 +596,38 @@ __global__ __launch_bounds__(256) void k_ot64(int N, int M, long P, const int8_t
         ox += cx; oy += cy;
         qx += cx * dx - cy * dy; qy += cx * dy + cy * dx;
     }
-    Om[k] = make_double2(ox, oy);
-    ORc[k] = make_double2(qx, qy);
+    part[(2L * blockIdx.y) * P + k] = make_double2(ox, oy);
+    part[(2L * blockIdx.y + 1) * P + k] = make_double2(qx, qy);
+}
+// the runs added in order; Om = <O>, ORc, F and the block's |F|^2: 64 parameters a block, wave v the runs v, v + 4, ..
+__global__ __launch_bounds__(256) void k_ot64_final(long P, int n_run, int mode, const double2* __restrict__ part,
+                                                    const double* __restrict__ sc, double2* __restrict__ Om,
+                                                    double2* __restrict__ ORc, double2* __restrict__ F,
+                                                    double* __restrict__ ff) {
+    __shared__ double2 so[4][64], sq[4][64];
+    const int lane = threadIdx.x & 63, v = threadIdx.x >> 6;
+    const long k = (long)blockIdx.x * 64 + lane;
+    double2 o = make_double2(0.0, 0.0), q = make_double2(0.0, 0.0);
+    if (k < P)
+#pragma unroll 4
+        for (int b = v; b < n_run; b += 4) {
+            o = zadd(o, part[(2L * b) * P + k]);
+            q = zadd(q, part[(2L * b + 1) * P + k]);
+        }
+    so[v][lane] = o;
+    sq[v][lane] = q;
+    __syncthreads();
+    if (v != 0) return;
+    double2 f = make_double2(0.0, 0.0);
+    if (k < P) {
+        for (int b = 1; b < 4; ++b) { o = zadd(o, so[b][lane]); q = zadd(q, sq[b][lane]); }
+        f = force_of(q, mode, sc);
+        Om[k] = make_double2(o.x, -o.y);
+        ORc[k] = q;
+        F[k] = f;
+    }
+    const double t = wave_sum(f.x * f.x + f.y * f.y);
+    if (lane == 0) ff[blockIdx.x] = t;
 }
 
 // ------------------------------------------------------------------ dense S (FP32, VALU)
@@ -538,12 +638,31 @@ __global__ __launch_bounds__(256) void k_ot64(int N, int M, long P, const int8_t
 // ratio's digits.  Binary32 operands, products and sums in double (the weighted sums serve exact enumeration
 // with a dense solve, where a few configurations next to nodes of the state can make |S| large against the
 // diagonal shift); S is written in binary32 and, for the Cholesky solve, also in double (S64).
+// The samples run in gridDim.y runs, each into its own slice of `part` (added by k_sbuild_runs), where the few
+// tiles of a small P would leave the device idle (P = 120, 1024 samples: 374 us on 3 workgroups, now 20 us on 96, and 4 us for the sum).
+// The double matrix S64 is that of the solve: it takes the diagonal shift eps as well.
 constexpr int SB_T = 64, SB_K = 16;
+
+__device__ __forceinline__ void sbuild_store(long P, long k, long kp, bool mirror, double2 sum,
+                                             const double2* __restrict__ Om, const double* __restrict__ sc,
+                                             float2* __restrict__ S, double2* __restrict__ S64, double eps) {
+    const double2 mm = zconjmul(Om[k], Om[kp]);
+    const double rest = 1.0 - sc[SC_WSUM];
+    const double2 d = make_double2(sum.x + rest * mm.x, sum.y + rest * mm.y);
+    const float2 v = make_float2((float)d.x, (float)d.y);
+    S[k * P + kp] = v;
+    if (mirror) S[kp * P + k] = cconj(v);
+    if (S64) {
+        S64[k * P + kp] = k == kp ? make_double2(d.x + eps, d.y) : d;
+        if (mirror) S64[kp * P + k] = make_double2(d.x, -d.y);
+    }
+}
 
 __global__ __launch_bounds__(256) void k_sbuild(int N, int M, long P, const int8_t* __restrict__ sig,
                                                 const float2* __restrict__ T, const double* __restrict__ w, long n,
                                                 const double2* __restrict__ Om, float2* __restrict__ S, int ntile,
-                                                const double* __restrict__ sc, double2* __restrict__ S64) {
+                                                const double* __restrict__ sc, double2* __restrict__ S64, double eps,
+                                                long run, double2* __restrict__ part) {
     __shared__ float2 sa[SB_K][SB_T];
     __shared__ float2 sb[SB_K][SB_T];
     // map blockIdx.x -> (I, J), I <= J
@@ -568,13 +687,14 @@ __global__ __launch_bounds__(256) void k_sbuild(int N, int M, long P, const int8
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[r][c] = make_double2(0.0, 0.0);
 
-    for (long s0 = 0; s0 < n; s0 += SB_K) {
+    const long s_end = min(n, (long)(blockIdx.y + 1) * run);
+    for (long s0 = (long)blockIdx.y * run; s0 < s_end; s0 += SB_K) {
 #pragma unroll
         for (int st = 0; st < SB_K / 4; ++st) {
             const int ss = (tid >> 6) + 4 * st;
             const long s = s0 + ss;
             float2 oa = make_float2(0.f, 0.f), ob = make_float2(0.f, 0.f);
-            if (s < n) {
+            if (s < s_end) {
                 const float ws = w ? (float)w[s] : (float)wdef;
                 if (va) {
                     const float sv = (ia == N) ? 1.f : (float)sig[s * N + ia];
@@ -613,24 +733,28 @@ __global__ __launch_bounds__(256) void k_sbuild(int N, int M, long P, const int8
     for (int r = 0; r < 4; ++r) {
         const long k = kA0 + ty + 16 * r;
         if (k >= P) continue;
-        const double2 omk = Om[k];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const long kp = kB0 + tx + 16 * c;
             if (kp >= P) continue;
-            const double2 omkp = Om[kp];
-            const double2 mm = zconjmul(omk, omkp);
-            const double rest = 1.0 - sc[SC_WSUM];
-            const double2 d = make_double2(acc[r][c].x + rest * mm.x, acc[r][c].y + rest * mm.y);
-            const float2 v = make_float2((float)d.x, (float)d.y);
-            S[k * P + kp] = v;
-            if (I != J) S[kp * P + k] = cconj(v);
-            if (S64) {
-                S64[k * P + kp] = d;
-                if (I != J) S64[kp * P + k] = make_double2(d.x, -d.y);
-            }
+            if (part) part[((long)blockIdx.y * P + k) * P + kp] = acc[r][c];
+            else sbuild_store(P, k, kp, I != J, acc[r][c], Om, sc, S, S64, eps);
         }
     }
+}
+
+// S of the sample runs' slices, added in order (upper tiles; the others are written from them)
+__global__ __launch_bounds__(256) void k_sbuild_runs(long P, int n_run, const double2* __restrict__ part,
+                                                     const double2* __restrict__ Om, const double* __restrict__ sc,
+                                                     float2* __restrict__ S, double2* __restrict__ S64, double eps) {
+    const long e = (long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= P * P) return;
+    const long k = e / P, kp = e % P;
+    if (k / SB_T > kp / SB_T) return;
+    double2 a = make_double2(0.0, 0.0);
+#pragma unroll 8
+    for (int z = 0; z < n_run; ++z) a = zadd(a, part[(long)z * P * P + e]);
+    sbuild_store(P, k, kp, k / SB_T != kp / SB_T, a, Om, sc, S, S64, eps);
 }
 
 // ------------------------------------------------------------------ dense Hermitian product
@@ -646,8 +770,8 @@ constexpr int HV_T = kHemvTile;
 template <bool PAIR>
 __global__ __launch_bounds__(256) void k_hemv_tiles(long P, int nT, const float2* __restrict__ S,
                                                     const double2* __restrict__ x, double2* __restrict__ part,
-                                                    const double* __restrict__ sc) {
-    if (sc[SC_DONE] != 0.0) return;
+                                                    const double* __restrict__ skip) {
+    if (skip && *skip != 0.0) return;
     // lower-triangle tile (I, J) of this workgroup: t = I (I + 1) / 2 + J
     const long t = blockIdx.x;
     int I = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
@@ -723,11 +847,11 @@ __global__ __launch_bounds__(256) void k_hemv_tiles(long P, int nT, const float2
 }
 
 // y_k = sum_B part[k / HV_T][B][k % HV_T] + eps x_k; 64 rows per workgroup, its 4 waves add a quarter
-// of the slots each, combined in wave order
+// of the slots each, combined in wave order; the first wave also forms the rows' dot products
 __global__ __launch_bounds__(256) void k_hemv_reduce(long P, int nT, const double2* __restrict__ part,
-                                                     const double2* __restrict__ x, double eps,
-                                                     double2* __restrict__ y, const double* __restrict__ sc) {
-    if (sc[SC_DONE] != 0.0) return;
+                                                     double2* __restrict__ y, const double* __restrict__ skip,
+                                                     OpTail tail) {
+    if (skip && *skip != 0.0) return;
     __shared__ double2 q[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const long k = (long)blockIdx.x * 64 + lane;
@@ -746,277 +870,244 @@ __global__ __launch_bounds__(256) void k_hemv_reduce(long P, int nT, const doubl
     }
     q[w][lane] = make_double2(sx, sy);
     __syncthreads();
-    if (w == 0 && k < P) {
+    if (w != 0) return;
+    double2 yk = make_double2(0.0, 0.0), xk = make_double2(0.0, 0.0);
+    if (k < P) {
         const double2 a = q[0][lane], b = q[1][lane], c = q[2][lane], d = q[3][lane];
-        y[k] = make_double2((((a.x + b.x) + c.x) + d.x) + eps * x[k].x, (((a.y + b.y) + c.y) + d.y) + eps * x[k].y);
+        xk = tail.v[k];
+        yk = make_double2((((a.x + b.x) + c.x) + d.x) + tail.eps * xk.x, (((a.y + b.y) + c.y) + d.y) + tail.eps * xk.y);
+        y[k] = yk;
     }
+    tail_dots(tail, k, k < P, xk, yk, lane, blockIdx.x);
 }
 
 // ------------------------------------------------------------------ matrix-free S v
-// u_s = sum_j T~_sj G_sj + sum_i sigma_si v_a_i with G = theta-GEMM(b = v_b, W = v_W)
-__global__ __launch_bounds__(256) void k_pack_v(int N, int M, const double2* __restrict__ v, float2* __restrict__ vb,
-                                                float2* __restrict__ vW, const double* __restrict__ sc) {
-    if (sc[SC_DONE] != 0.0) return;
-    const long P = (long)N + M + (long)N * M;
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < N || k >= P) return;
-    const float2 f = make_float2((float)v[k].x, (float)v[k].y);
-    if (k < N + M) vb[k - N] = f; else vW[k - N - M] = f;
-}
-
-
-// u <- u - <O>.v (scalar), so that the contraction gives <O^*(O v)> - <O>^* <O>.v with <O^*> folded.
-__global__ __launch_bounds__(256) void k_dot_ov(long P, const double2* __restrict__ Om, const double2* __restrict__ v,
-                                                double2* __restrict__ red, const double* __restrict__ sc) {
-    if (sc[SC_DONE] != 0.0) return;
-    __shared__ double sh[2][4];
-    double ax = 0, ay = 0;
-    for (long k = (long)blockIdx.x * 256 + threadIdx.x; k < P; k += (long)gridDim.x * 256) {
-        const double2 t = zmul(Om[k], v[k]);
-        ax += t.x; ay += t.y;
-    }
-    ax = wave_sum(ax); ay = wave_sum(ay);
-    if ((threadIdx.x & 63) == 0) { sh[0][threadIdx.x >> 6] = ax; sh[1][threadIdx.x >> 6] = ay; }
-    __syncthreads();
-    if (threadIdx.x == 0) red[blockIdx.x] = make_double2(sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3],
-                                                         sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3]);
-}
-
-__global__ __launch_bounds__(256) void k_sub_mean(long n, double2* __restrict__ u, const double2* __restrict__ red,
-                                                  int n_red, const double* __restrict__ sc) {
-    if (sc[SC_DONE] != 0.0) return;
-    double2 m = make_double2(0.0, 0.0);
-    for (int b = 0; b < n_red; ++b) m = zadd(m, red[b]);
-    const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < n) u[s] = make_double2(u[s].x - m.x, u[s].y - m.y);
-}
-
-__global__ void k_add_shift(long P, const double2* __restrict__ x, double eps, double2* __restrict__ y,
-                            const double* __restrict__ sc) {
-    if (sc[SC_DONE] != 0.0) return;
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < P) y[k] = make_double2(y[k].x + eps * x[k].x, y[k].y + eps * x[k].y);
-}
-
-// ------------------------------------------------------------------ CG helpers (double)
-// red[blk] = sum conj(a) b over the block's range
-__global__ __launch_bounds__(256) void k_zdot(long P, const double2* __restrict__ a, const double2* __restrict__ b,
-                                              double2* __restrict__ red, const double* __restrict__ sc, int check) {
-    if (check && sc[SC_DONE] != 0.0) return;
-    __shared__ double sh[2][4];
-    double ax = 0, ay = 0;
-    for (long k = (long)blockIdx.x * 256 + threadIdx.x; k < P; k += (long)gridDim.x * 256) {
-        const double2 t = zconjmul(a[k], b[k]);
-        ax += t.x; ay += t.y;
-    }
-    ax = wave_sum(ax); ay = wave_sum(ay);
-    if ((threadIdx.x & 63) == 0) { sh[0][threadIdx.x >> 6] = ax; sh[1][threadIdx.x >> 6] = ay; }
-    __syncthreads();
-    if (threadIdx.x == 0) red[blockIdx.x] = make_double2(sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3],
-                                                         sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3]);
-}
-
-// slot <- Re sum(red)
-__global__ void k_sum_to(const double2* __restrict__ red, int n_red, double* __restrict__ sc, int slot, int check) {
-    if (check && sc[SC_DONE] != 0.0) return;
-    if (threadIdx.x != 0) return;
-    double a = 0;
-    for (int b = 0; b < n_red; ++b) a += red[b].x;
-    sc[slot] = a;
-}
-
-// real part of red[0] + ... + red[n-1] in one fixed order, the same in every block (256 threads)
-__device__ __forceinline__ double block_sum_re(const double2* __restrict__ red, int n, double* sh) {
-    double a = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) a += red[i].x;
-    sh[threadIdx.x] = a;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    const double t = sh[0];
-    __syncthreads();
-    return t;
-}
-
-// x += alpha p, r -= alpha Ap with alpha = rr / pAp (pAp from the 64 partials of k_zdot, rr in slot
-// `slot`); each block leaves its part of the new r^H r in red_rr[block]
-__global__ __launch_bounds__(256) void k_cg_xr(long P, double2* __restrict__ x, double2* __restrict__ r,
-                                               const double2* __restrict__ p, const double2* __restrict__ Ap,
-                                               const double2* __restrict__ red_pap, double2* __restrict__ red_rr,
-                                               double* __restrict__ sc, int slot) {
-    __shared__ double sh[256];
-    if (sc[SC_DONE] != 0.0) return;              // set only by k_cg_check_p: fixed during this launch
-    const double pap = block_sum_re(red_pap, 64, sh);
-    const double alpha = sc[slot] / pap;
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    double rr = 0.0;
-    if (k < P) {
-        x[k] = make_double2(x[k].x + alpha * p[k].x, x[k].y + alpha * p[k].y);
-        const double2 rk = make_double2(r[k].x - alpha * Ap[k].x, r[k].y - alpha * Ap[k].y);
-        r[k] = rk;
-        rr = rk.x * rk.x + rk.y * rk.y;
-    }
-    sh[threadIdx.x] = rr;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        red_rr[blockIdx.x] = make_double2(sh[0], 0.0);
-        if (blockIdx.x == 0) sc[SC_PAP] = pap;
-    }
-}
-
-// Convergence test of iteration `it` and the direction update p = r + beta p.  Every block adds the
-// r^H r partials in the same order and takes the same decision; block 0 records it: the new r^H r goes
-// to the other slot than the one read, so no block reads a slot written in this launch.
-__global__ __launch_bounds__(256) void k_cg_check_p(long P, double2* __restrict__ p, const double2* __restrict__ r,
-                                                    const double2* __restrict__ red_rr, int n_red,
-                                                    double* __restrict__ sc, double tol, int maxit, int it, int slot) {
-    __shared__ double sh[256];
-    __shared__ int s_done;
-    if (threadIdx.x == 0) s_done = sc[SC_DONE] != 0.0;   // block 0 may set it during this launch
-    __syncthreads();
-    if (s_done) return;
-    const double rn = block_sum_re(red_rr, n_red, sh);
-    const bool bad = !isfinite(rn) || !(sc[SC_PAP] > 0.0);
-    const bool conv = !bad && sqrt(rn) <= tol * sqrt(sc[SC_FF]);
-    const bool last = it + 1 >= maxit;
-    const int next = slot == SC_RR ? SC_RR1 : SC_RR;
-    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-    if (bad || conv || last) {
-        if (lead) {
-            int fl = (int)sc[SC_FLAGS];
-            if (bad) fl |= CRBM_FLAG_NONFINITE;
-            else if (!conv) fl |= CRBM_FLAG_NOT_CONVERGED;
-            sc[SC_FLAGS] = (double)fl;
-            sc[SC_ITERS] = (double)(it + 1);
-            sc[next] = rn;
-            sc[SC_DONE] = 1.0;
+// u_s = sum_j T_sj G_sj + sum_i sigma_si v_a_i with G = theta-GEMM(b = v_b, W = v_W).  The product reads v as the
+// split planes of v_W and v_b in binary32, and subtracts <O>.v from every u_s; whoever forms v writes these along
+// with it (mf_publish), so that an iteration has no launch of its own for them.
+struct MfView {
+    int N, M, Np;            // M = 0: dense product, nothing to publish
+    long rows;
+    uint16_t* planes;
+    float2* vb;
+    const double2* Om;
+    double2* omv;            // [blocks] partial sums of <O>.v
+};
+__device__ __forceinline__ void mf_publish(const MfView& f, long k, bool valid, double2 v, double (&shx)[4],
+                                           double (&shy)[4]) {
+    double2 t = make_double2(0.0, 0.0);
+    if (valid) {
+        t = zmul(f.Om[k], v);
+        const float2 c = make_float2((float)v.x, (float)v.y);
+        if (k >= f.N + f.M) {
+            const long r = k - f.N - f.M;
+            split_plane_store(f.planes, f.rows, f.Np, (int)(r / f.M), (int)(r % f.M), c);
+        } else if (k >= f.N) {
+            f.vb[k - f.N] = c;
         }
+    }
+    const double tx = block_total(t.x, shx), ty = block_total(t.y, shy);
+    if (threadIdx.x == 0) f.omv[blockIdx.x] = make_double2(tx, ty);
+}
+__global__ __launch_bounds__(256) void k_mf_publish(long P, const double2* __restrict__ v, MfView f) {
+    __shared__ double shx[4], shy[4];
+    const long k = (long)blockIdx.x * 256 + threadIdx.x;
+    mf_publish(f, k, k < P, k < P ? v[k] : make_double2(0.0, 0.0), shx, shy);
+}
+
+// ------------------------------------------------------------------ CG (double)
+// x = 0, r = p = F; the first block adds the |F|^2 partials and opens the iteration
+__global__ __launch_bounds__(256) void k_cg_init(long P, const double2* __restrict__ F, const double* __restrict__ ff,
+                                                 int n_ff, double2* __restrict__ x, double2* __restrict__ r,
+                                                 double2* __restrict__ p, double* __restrict__ sc, MfView f) {
+    __shared__ double sh[4], shx[4], shy[4];
+    const long k = (long)blockIdx.x * 256 + threadIdx.x;
+    const double2 v = k < P ? F[k] : make_double2(0.0, 0.0);
+    if (k < P) {
+        x[k] = make_double2(0.0, 0.0);
+        r[k] = v;
+        p[k] = v;
+    }
+    if (f.M) mf_publish(f, k, k < P, v, shx, shy);
+    if (blockIdx.x != 0) return;
+    double a = 0.0;
+    for (int b = threadIdx.x; b < n_ff; b += 256) a += ff[b];
+    a = block_total(a, sh);
+    if (threadIdx.x == 0) {
+        sc[SC_FF] = a;
+        sc[SC_DONE0] = (a == 0.0 || (int)sc[SC_FLAGS] != 0) ? 1.0 : 0.0;
+        sc[SC_ITERS] = 0.0;
+    }
+}
+
+// One iteration after Ap: with the dot products that the product's last kernel left per block (r^H r, p^H Ap,
+// r^H Ap, |Ap|^2), alpha = r^H r / p^H Ap, x += alpha p, r -= alpha Ap, the new |r|^2 = r^H r - 2 alpha r^H Ap +
+// alpha^2 |Ap|^2 (r^H r is formed from r itself in every iteration, so nothing accumulates), the convergence test
+// and p = r + beta p.  Every block adds the partials in the same order and takes the same decision; block 0
+// records it in the other of the two done slots than the one this iteration reads.
+// Launches that a finished solve skips cost about 2 us each, so an iteration has 3 (dense) or 5 (matrix-free) of
+// them; with the vector updates, dot products and operand packing apart it had 5 and 12.
+__global__ __launch_bounds__(256) void k_cg_step(long P, double2* __restrict__ x, double2* __restrict__ r,
+                                                 double2* __restrict__ p, const double2* __restrict__ Ap,
+                                                 const double* __restrict__ dots, int n_dots, double* __restrict__ sc,
+                                                 double tol, int maxit, int it, MfView f) {
+    __shared__ double s0[4], s1[4], s2[4], s3[4];
+    const int now = SC_DONE0 + (it & 1), next = SC_DONE0 + ((it + 1) & 1);
+    const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+    if (sc[now] != 0.0) {
+        if (lead) sc[next] = 1.0;
         return;
     }
-    const double beta = rn / sc[slot];
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < P) p[k] = make_double2(r[k].x + beta * p[k].x, r[k].y + beta * p[k].y);
+    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
+    for (int b = threadIdx.x; b < n_dots; b += 256) {
+        const double2 u = *reinterpret_cast<const double2*>(dots + 4 * b), v = *reinterpret_cast<const double2*>(dots + 4 * b + 2);
+        d0 += u.x; d1 += u.y; d2 += v.x; d3 += v.y;
+    }
+    const double rr = block_total(d0, s0), pap = block_total(d1, s1), rap = block_total(d2, s2), aa = block_total(d3, s3);
+    const double alpha = rr / pap;
+    double rn = rr - 2.0 * alpha * rap + alpha * alpha * aa;
+    const bool bad = !isfinite(rn) || !(pap > 0.0);
+    rn = fmax(rn, 0.0);
+    const bool conv = !bad && sqrt(rn) <= tol * sqrt(sc[SC_FF]);
+    const bool stop = bad || conv || it + 1 >= maxit;
+    const long k = (long)blockIdx.x * 256 + threadIdx.x;
+    double2 pk = make_double2(0.0, 0.0);
+    if (k < P) {
+        pk = p[k];
+        const double2 ak = Ap[k];
+        x[k] = make_double2(x[k].x + alpha * pk.x, x[k].y + alpha * pk.y);
+        const double2 rk = make_double2(r[k].x - alpha * ak.x, r[k].y - alpha * ak.y);
+        r[k] = rk;
+        if (!stop) {
+            const double beta = rn / rr;
+            pk = make_double2(rk.x + beta * pk.x, rk.y + beta * pk.y);
+            p[k] = pk;
+        }
+    }
+    if (f.M && !stop) {
+        __shared__ double shx[4], shy[4];
+        mf_publish(f, k, k < P, pk, shx, shy);
+    }
     if (lead) {
-        sc[next] = rn;
+        if (bad || (stop && !conv))
+            sc[SC_FLAGS] = (double)((int)sc[SC_FLAGS] | (bad ? CRBM_FLAG_NONFINITE : CRBM_FLAG_NOT_CONVERGED));
         sc[SC_ITERS] = (double)(it + 1);
+        sc[next] = stop ? 1.0 : 0.0;
     }
 }
 
-__global__ __launch_bounds__(256) void k_cg_init(long P, const double2* __restrict__ F, double2* __restrict__ x,
-                                                 double2* __restrict__ r, double2* __restrict__ p) {
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= P) return;
-    x[k] = make_double2(0.0, 0.0);
-    r[k] = F[k];
-    p[k] = F[k];
-}
-
-__global__ void k_cg_start(double* __restrict__ sc) {
-    if (threadIdx.x != 0) return;
-    sc[SC_RR] = sc[SC_FF];
-    sc[SC_DONE] = (sc[SC_FF] == 0.0 || (int)sc[SC_FLAGS] != 0) ? 1.0 : 0.0;
-    sc[SC_ITERS] = 0.0;
-}
-
-// r = F - Ap (true residual), used once after the iterations
-__global__ __launch_bounds__(256) void k_resid(long P, const double2* __restrict__ F, const double2* __restrict__ Ax,
-                                               double2* __restrict__ r) {
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < P) r[k] = make_double2(F[k].x - Ax[k].x, F[k].y - Ax[k].y);
-}
-
-__global__ void k_undone(double* __restrict__ sc) { if (threadIdx.x == 0) sc[SC_DONE] = 0.0; }
-
-// a, b, W += dalpha  (skipped when the step was flagged non-finite)
-__global__ __launch_bounds__(256) void k_update(int N, int M, float2* __restrict__ a, float2* __restrict__ b,
+// a, b, W += dalpha  (skipped when the step was flagged non-finite); the first block adds the residual's, the
+// solution's and F's partials and writes the statistics
+__global__ __launch_bounds__(256) void k_finish(int N, int M, float2* __restrict__ a, float2* __restrict__ b,
                                                 float2* __restrict__ W, const double2* __restrict__ x,
-                                                const double* __restrict__ sc) {
+                                                const double* __restrict__ dots, int n_dots,
+                                                const double* __restrict__ ff, int n_ff,
+                                                const double* __restrict__ sc, double* __restrict__ out) {
+    __shared__ double s0[4], s1[4], s2[4];
+    if (out && blockIdx.x == 0) {
+        double d0 = 0.0, d1 = 0.0, d2 = 0.0;
+        for (int k = threadIdx.x; k < n_dots; k += 256) {
+            const double2 u = *reinterpret_cast<const double2*>(dots + 4 * k);
+            d0 += u.x; d1 += u.y;
+        }
+        for (int k = threadIdx.x; k < n_ff; k += 256) d2 += ff[k];
+        const double res = block_total(d0, s0), xx = block_total(d1, s1), f2 = block_total(d2, s2);
+        if (threadIdx.x == 0) {
+            out[0] = sc[SC_GAMMA];
+            out[1] = sc[SC_RM_RE];
+            out[2] = sc[SC_RM_IM];
+            out[3] = sqrt(f2);
+            out[4] = f2 > 0.0 ? sqrt(res / f2) : 0.0;
+            out[5] = sc[SC_ITERS];
+            out[6] = sc[SC_FLAGS];
+            out[7] = sqrt(xx);
+        }
+    }
     if (((int)sc[SC_FLAGS] & (CRBM_FLAG_NONFINITE | CRBM_FLAG_CHOLESKY_FAIL)) != 0) return;
     const long P = (long)N + M + (long)N * M;
-    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long k = (long)blockIdx.x * 256 + threadIdx.x;
     if (k >= P) return;
     float2* dst = (k < N) ? &a[k] : (k < N + M) ? &b[k - N] : &W[k - N - M];
     *dst = make_float2(dst->x + (float)x[k].x, dst->y + (float)x[k].y);
 }
 
-__global__ void k_stats(const double* __restrict__ sc, double* __restrict__ out) {
-    if (threadIdx.x != 0) return;
-    out[0] = sc[SC_GAMMA];
-    out[1] = sc[SC_RM_RE];
-    out[2] = sc[SC_RM_IM];
-    out[3] = sqrt(sc[SC_FF]);
-    out[4] = sc[SC_FF] > 0.0 ? sqrt(sc[SC_RESID] / sc[SC_FF]) : 0.0;
-    out[5] = sc[SC_ITERS];
-    out[6] = sc[SC_FLAGS];
-    out[7] = sqrt(sc[SC_XX]);
-}
-
 // ------------------------------------------------------------------ driver
 static inline unsigned nblk(long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
-hipError_t launch_cholesky_solve(long P, const float2* S, double eps, const double2* F, double2* A64, double2* x,
-                                 double* sc, bool a64_holds_s, hipStream_t stream);
+// slots of W.dots: [4 nb] dot products, [nb] |F|^2, [2 nb] <O>.v partials, nb >= blocks of 64 entries
+static long dots_blocks(long P) { return P / 64 + 8; }
+long sr_dots_len(long P) { return 8 * dots_blocks(P); }
 
-static hipError_t apply_op(const SrArgs& A, const SrWork& W, const double2* v, double2* y, hipStream_t stream) {
+// y = (S + eps I) v with the dot products of its tail; skip: device flag of a finished solve, or null.  The
+// matrix-free product expects v published (k_mf_publish).  n_dots: blocks that left dot products.
+static hipError_t apply_op(const SrArgs& A, const SrWork& W, const double2* v, double2* y, const double2* F,
+                           const double* skip, int* n_dots, const MfView& f, hipStream_t stream) {
     const long P = A.P;
+    OpTail t{};
+    t.on = 1;
+    t.eps = A.eps;
+    t.v = v;
+    t.r = W.r;
+    t.F = F;
+    t.dots = W.dots;
     if (A.solver == CRBM_SOLVER_CG_MATFREE) {
-        // V = (v_b, v_W) in float for the theta product (b = v_b, W = v_W)
-        float2* vb = W.vstage;
-        float2* vW = vb + A.M;
-        hipLaunchKernelGGL(k_pack_v, dim3(nblk(P)), dim3(256), 0, stream, A.N, A.M, v, vb, vW, W.scal);
         // u = O v per sample, the theta product of V fused with the sum over T (partials in the G scratch)
-        hipError_t e = launch_theta_ov(A.samples, A.n, A.N, A.M, vb, vW, v, A.T, W.wplanes,
-                                       reinterpret_cast<double2*>(W.G), W.u, stream, W.scal + SC_DONE);
+        hipError_t e = launch_theta_ov(A.samples, A.n, A.N, A.M, f.vb, v, A.T, W.wplanes,
+                                       reinterpret_cast<double2*>(W.G), W.u, f.omv, (int)nblk(P),
+                                       W.scal + SC_OMV, stream, skip);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_dot_ov, dim3(64), dim3(256), 0, stream, P, W.Om, v, W.red, W.scal);
-        hipLaunchKernelGGL(k_sub_mean, dim3(nblk(A.n)), dim3(256), 0, stream, A.n, W.u, W.red, 64, W.scal);
-        e = run_ot(A.N, A.M, W.sig16, A.T, A.n, 2, 0, 1, A.weights, A.R, W.u, W.red + 64, 0, y, nullptr, stream,
-                   W.scal + SC_DONE, nullptr, W.n_cu);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_add_shift, dim3(nblk(P)), dim3(256), 0, stream, P, v, A.eps, y, W.scal);
-    } else {
-        const int nT = hemv_tiles(P);
-        const dim3 grid((unsigned)((long)nT * (nT + 1) / 2));
-        if (P % 2 == 0)
-            hipLaunchKernelGGL(k_hemv_tiles<true>, grid, dim3(256), 0, stream, P, nT, W.S, v, W.hv_part, W.scal);
-        else
-            hipLaunchKernelGGL(k_hemv_tiles<false>, grid, dim3(256), 0, stream, P, nT, W.S, v, W.hv_part, W.scal);
-        hipLaunchKernelGGL(k_hemv_reduce, dim3(nblk(P, 64)), dim3(256), 0, stream, P, nT, W.hv_part, v, A.eps, y,
-                           W.scal);
+        *n_dots = (int)nblk((long)(A.N + 1) * (A.M + 1), 64);
+        return run_ot(A.N, A.M, W.sig16, A.T, A.n, 2, 0, 1, A.weights, A.R, W.u, W.red, 0, y, nullptr, stream, skip,
+                      nullptr, W.n_cu, 0, nullptr, W.scal + SC_OMV, t);
     }
+    const int nT = hemv_tiles(P);
+    const dim3 grid((unsigned)((long)nT * (nT + 1) / 2));
+    if (P % 2 == 0)
+        hipLaunchKernelGGL(k_hemv_tiles<true>, grid, dim3(256), 0, stream, P, nT, W.S, v, W.hv_part, skip);
+    else
+        hipLaunchKernelGGL(k_hemv_tiles<false>, grid, dim3(256), 0, stream, P, nT, W.S, v, W.hv_part, skip);
+    *n_dots = (int)nblk(P, 64);
+    hipLaunchKernelGGL(k_hemv_reduce, dim3(nblk(P, 64)), dim3(256), 0, stream, P, nT, W.hv_part, y, skip, t);
     return hipGetLastError();
 }
+
+hipError_t launch_cholesky_solve(long P, const float2* S, double eps, const double2* F, double2* A64, double2* x,
+                                 double* sc, bool a64_holds_s, hipStream_t stream);
 
 hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) {
     const long P = A.P;
     hipError_t e;
     // scalars gamma, beta, gamma cot gamma
-    const int nb_r = 256;
+    const int nb_r = (int)std::min<long>((A.n + 255) / 256, 256);
     hipLaunchKernelGGL(k_r_moments, dim3(nb_r), dim3(256), 0, stream, A.R, A.weights, A.n, W.red);
     hipLaunchKernelGGL(k_r_final, dim3(1), dim3(64), 0, stream, W.red, nb_r, A.dgamma, A.mode, W.scal);
+    double* ff = W.dots + 4 * dots_blocks(P);
+    int n_ff;
+    // the packed sigma~ rows serve the O^H c contraction only
+    if (!A.weights || A.solver == CRBM_SOLVER_CG_MATFREE) pack_sig16(A.samples, A.n, A.N, W.sig16, stream);
     // conj(<O>) and <O^* (R - <R>)>: FP32 chunk sums on the matrix cores, or in double with sample weights
-    pack_sig16(A.samples, A.n, A.N, W.sig16, stream);
     if (A.weights) {
+        // runs of at least 16 samples, as many as the reduction buffer holds up to 64
+        long z = std::min<long>(std::min<long>(64, (A.n + 15) / 16), W.red_len / (2 * P));
+        z = std::max<long>(z, 1);
+        const long run = (A.n + z - 1) / z;
+        z = (A.n + run - 1) / run;
         W.prof->begin(PROF_OT, stream);
-        hipLaunchKernelGGL(k_ot64, dim3(nblk(P)), dim3(256), 0, stream, A.N, A.M, P, A.samples, A.T, A.weights, A.R,
-                           A.n, W.scal, W.Om, W.ORm);
+        hipLaunchKernelGGL(k_ot64, dim3(nblk(P, OT64_T), (unsigned)z), dim3(OT64_T), 0, stream, A.N, A.M, P, A.samples,
+                           A.T, A.weights, A.R, A.n, run, W.scal, W.red);
         W.prof->end(stream);
+        n_ff = (int)nblk(P, 64);
+        hipLaunchKernelGGL(k_ot64_final, dim3(n_ff), dim3(256), 0, stream, P, (int)z, A.mode, W.red, W.scal, W.Om, W.ORm,
+                           W.F, ff);
         e = hipGetLastError();
     } else {
         e = run_ot(A.N, A.M, W.sig16, A.T, A.n, 0, 4, 2, A.weights, A.R,
                    reinterpret_cast<const double2*>(W.scal + SC_RM_RE), W.red, 0, W.Om, W.ORm, stream, nullptr, W.prof,
                    W.n_cu);
+        n_ff = (int)nblk(P);
+        hipLaunchKernelGGL(k_make_f, dim3(n_ff), dim3(256), 0, stream, P, A.mode, 1, W.Om, W.ORm, W.scal, W.F, ff);
     }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_make_f, dim3(nblk(P)), dim3(256), 0, stream, P, A.mode, W.Om, W.ORm, W.scal, W.F);
-    hipLaunchKernelGGL(k_zdot, dim3(64), dim3(256), 0, stream, P, W.F, W.F, W.red, W.scal, 0);
-    hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(64), 0, stream, W.red, 64, W.scal, (int)SC_FF, 0);
 
     if (A.solver != CRBM_SOLVER_CG_MATFREE) {
         if (A.weights == nullptr) {
@@ -1032,9 +1123,8 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
                            reinterpret_cast<const double2*>(W.scal + SC_RM_RE), W.red, 1, W.Om16, W.ORm, stream,
                            nullptr, nullptr, W.n_cu, 1, W.Om + A.N);
                 if (e != hipSuccess) return e;
-                hipLaunchKernelGGL(k_f_of, dim3(nblk(P)), dim3(256), 0, stream, P, A.mode, W.ORm, W.scal, W.F);
-                hipLaunchKernelGGL(k_zdot, dim3(64), dim3(256), 0, stream, P, W.F, W.F, W.red, W.scal, 0);
-                hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(64), 0, stream, W.red, 64, W.scal, (int)SC_FF, 0);
+                hipLaunchKernelGGL(k_make_f, dim3(n_ff), dim3(256), 0, stream, P, A.mode, 0, W.Om, W.ORm, W.scal, W.F,
+                                   ff);
             } else {
                 e = run_ot(A.N, A.M, W.sig16, A.T, A.n, 0, 0, 1, nullptr, A.R, nullptr, W.red, 1, W.Om16, nullptr,
                            stream, nullptr, nullptr, W.n_cu, 0, W.Om + A.N);
@@ -1046,61 +1136,67 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
                                    W.pack_bytes, W.sb_order, W.sb_order_len,
                                    W.spart, nsplit, W.bx, W.bx_part, nsb, W.sb_fold, W.prof, stream);
         } else {
-            // weighted (enumeration) sums: FP32 contraction on the vector units
+            // weighted (enumeration) sums: FP32 contraction on the vector units, the samples in as many runs (of at
+            // least 16) as four workgroups per compute unit and the slices allow
             const int nt = (int)((P + SB_T - 1) / SB_T);
             const long ntri = (long)nt * (nt + 1) / 2;
+            long z = std::min<long>(std::min<long>(W.n_sw, (A.n + SB_K - 1) / SB_K), 4L * W.n_cu / ntri);
+            z = std::max<long>(z, 1);
+            const long run = ((A.n + z - 1) / z + SB_K - 1) / SB_K * SB_K;
+            z = (A.n + run - 1) / run;
+            double2* S64 = A.solver == CRBM_SOLVER_CHOLESKY ? W.S64 : nullptr;
             W.prof->begin(PROF_SBUILD, stream);
-            hipLaunchKernelGGL(k_sbuild, dim3((unsigned)ntri), dim3(256), 0, stream, A.N, A.M, P, A.samples, A.T,
-                               A.weights, A.n, W.Om, W.S, nt, W.scal,
-                               A.solver == CRBM_SOLVER_CHOLESKY ? W.S64 : nullptr);
+            hipLaunchKernelGGL(k_sbuild, dim3((unsigned)ntri, (unsigned)z), dim3(256), 0, stream, A.N, A.M, P, A.samples,
+                               A.T, A.weights, A.n, W.Om, W.S, nt, W.scal, S64, A.eps, run, z > 1 ? W.swpart : nullptr);
+            if (z > 1)
+                hipLaunchKernelGGL(k_sbuild_runs, dim3(nblk(P * P)), dim3(256), 0, stream, P, (int)z, W.swpart, W.Om,
+                                   W.scal, W.S, S64, A.eps);
             W.prof->end(stream);
             e = hipGetLastError();
         }
         if (e != hipSuccess) return e;
     }
 
+    MfView f{};
+    if (A.solver == CRBM_SOLVER_CG_MATFREE) {
+        f.N = A.N;
+        f.M = A.M;
+        f.Np = theta_np(A.N);
+        f.rows = theta_rows(A.M);
+        f.planes = W.wplanes;
+        f.vb = W.vstage;
+        f.Om = W.Om;
+        f.omv = reinterpret_cast<double2*>(W.dots + 6 * dots_blocks(P));
+    }
+    int n_dots = 0;
     if (A.solver == CRBM_SOLVER_CHOLESKY) {
         W.prof->begin(PROF_CHOLESKY, stream);
         e = launch_cholesky_solve(P, W.S, A.eps, W.F, W.S64, W.x, W.scal, A.weights != nullptr, stream);
         W.prof->end(stream);
         if (e != hipSuccess) return e;
-        // residual of the double solve against the FP32-stored S
-        hipLaunchKernelGGL(k_undone, dim3(1), dim3(64), 0, stream, W.scal);
     } else {
-        hipLaunchKernelGGL(k_cg_init, dim3(nblk(P)), dim3(256), 0, stream, P, W.F, W.x, W.r, W.p);
-        hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(64), 0, stream, W.scal);
+        hipLaunchKernelGGL(k_cg_init, dim3(nblk(P)), dim3(256), 0, stream, P, W.F, ff, n_ff, W.x, W.r, W.p, W.scal, f);
         W.prof->begin(PROF_CG, stream);
-        // partials: W.red[0, 64) for p^H Ap, W.red[64, 64 + nblk(P)) for r^H r
-        const int n_rr = (int)nblk(P);
         for (int it = 0; it < A.cg_maxit; ++it) {
-            const int slot = (it & 1) ? (int)SC_RR1 : (int)SC_RR;
-            e = apply_op(A, W, W.p, W.Ap, stream);
+            e = apply_op(A, W, W.p, W.Ap, nullptr, W.scal + SC_DONE0 + (it & 1), &n_dots, f, stream);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(k_zdot, dim3(64), dim3(256), 0, stream, P, W.p, W.Ap, W.red, W.scal, 1);
-            hipLaunchKernelGGL(k_cg_xr, dim3(n_rr), dim3(256), 0, stream, P, W.x, W.r, W.p, W.Ap, W.red, W.red + 64,
-                               W.scal, slot);
-            hipLaunchKernelGGL(k_cg_check_p, dim3(n_rr), dim3(256), 0, stream, P, W.p, W.r, W.red + 64, n_rr, W.scal,
-                               A.cg_tol, A.cg_maxit, it, slot);
+            hipLaunchKernelGGL(k_cg_step, dim3(nblk(P)), dim3(256), 0, stream, P, W.x, W.r, W.p, W.Ap, W.dots, n_dots,
+                               W.scal, A.cg_tol, A.cg_maxit, it, f);
         }
         W.prof->end(stream);
-        hipLaunchKernelGGL(k_undone, dim3(1), dim3(64), 0, stream, W.scal);
     }
-    // true residual |F - (S + eps) x|^2 in double
-    e = apply_op(A, W, W.x, W.Ap, stream);
+    // true residual |F - (S + eps) x|^2 in double (of a Cholesky solve: against the FP32-stored S)
+    if (f.M) hipLaunchKernelGGL(k_mf_publish, dim3(nblk(P)), dim3(256), 0, stream, P, W.x, f);
+    e = apply_op(A, W, W.x, W.Ap, W.F, nullptr, &n_dots, f, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_resid, dim3(nblk(P)), dim3(256), 0, stream, P, W.F, W.Ap, W.r);
-    hipLaunchKernelGGL(k_zdot, dim3(64), dim3(256), 0, stream, P, W.r, W.r, W.red, W.scal, 0);
-    hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(64), 0, stream, W.red, 64, W.scal, (int)SC_RESID, 0);
-    hipLaunchKernelGGL(k_zdot, dim3(64), dim3(256), 0, stream, P, W.x, W.x, W.red, W.scal, 0);
-    hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(64), 0, stream, W.red, 64, W.scal, (int)SC_XX, 0);
-    hipLaunchKernelGGL(k_update, dim3(nblk(P)), dim3(256), 0, stream, A.N, A.M, A.a, A.b, A.W, W.x, W.scal);
-    if (A.stats) hipLaunchKernelGGL(k_stats, dim3(1), dim3(64), 0, stream, W.scal, A.stats);
+    hipLaunchKernelGGL(k_finish, dim3(nblk(P)), dim3(256), 0, stream, A.N, A.M, A.a, A.b, A.W, W.x, W.dots, n_dots, ff,
+                       n_ff, W.scal, A.stats);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ fidelity gradient
-__global__ void k_loss(const float2* __restrict__ R, long n, double* __restrict__ loss) {
-    __shared__ double sh[4];
+__global__ __launch_bounds__(1024) void k_loss(const float2* __restrict__ R, long n, double* __restrict__ loss) {
+    __shared__ double sh[16];
     double acc = 0;
     for (long s = threadIdx.x; s < n; s += blockDim.x) {
         const double x = 1.0 - (double)R[s].x, y = -(double)R[s].y;
@@ -1109,7 +1205,10 @@ __global__ void k_loss(const float2* __restrict__ R, long n, double* __restrict_
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) *loss = (sh[0] + sh[1] + sh[2] + sh[3]) / (double)n;
+    if (threadIdx.x != 0) return;
+    double t = 0.0;
+    for (int k = 0; k < 16; ++k) t += sh[k];
+    *loss = t / (double)n;
 }
 
 // the gradient from caller-chosen scratch: sig16 (n sig16_row(N) bytes) and the contraction's chunk planes
@@ -1121,7 +1220,7 @@ static hipError_t fidelity_grad_on(const GradArgs& A, int8_t* sig16, void* parti
                               stream, nullptr, prof, n_cu);
         if (e != hipSuccess) return e;
     }
-    if (A.loss) hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, stream, A.R, A.n, A.loss);
+    if (A.loss) hipLaunchKernelGGL(k_loss, dim3(1), dim3(1024), 0, stream, A.R, A.n, A.loss);
     return hipGetLastError();
 }
 
