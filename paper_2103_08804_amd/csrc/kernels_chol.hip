@@ -5,12 +5,11 @@
 //
 // Right-looking and blocked in panels of CH_NB = 64 columns, per panel k:
 //   1. the diagonal block A_kk is factored in LDS by one workgroup;
-//   2. the rows below solve L_ik L_kk^H = A_ik, one wave per row (the lanes hold
-//      the 64 unknowns of the row, the substitution runs along the columns);
+//   2. the rows below solve L_ik L_kk^H = A_ik, four rows per wave (the lanes hold
+//      the 64 unknowns of a row, the substitution runs along the columns);
 //   3. the trailing lower triangle is updated, A_ij -= L_ik L_jk^H (i >= j), in
 //      32 x 32 output tiles with both 32 x 64 panels staged in LDS.
-// The triangular solves run by blocks of 64 rows: one wave substitutes in the
-// diagonal block, a wide kernel applies the block to the rest of the vector.
+// The triangular solves run by blocks of 64 rows, one launch per block.
 // Everything is in double, in a fixed order.
 #include "../../include/chebrbm.h"
 #include "device.hpp"
@@ -29,6 +28,35 @@ __device__ __forceinline__ double lane_value(double v, int m) {
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
+// 1 / sqrt(d), d > 0 and finite: the hardware estimate and two Newton steps (the serial chain of a column waits
+// on it)
+__device__ __forceinline__ double inv_sqrt(double d) {
+    // scaled by a power of four into [1, 4) so that the steps neither overflow nor underflow
+    const int e = (ilogb(d) >> 1) << 1;
+    const double m = ldexp(d, -e);
+    double y = __builtin_amdgcn_rsq(m);
+    y = fma(y * fma(-m * y, y, 1.0), 0.5, y);
+    y = fma(y * fma(-m * y, y, 1.0), 0.5, y);
+    return ldexp(y, -(e / 2));
+}
+
+// the lower triangle of the diagonal block [b0, b0 + nb)^2 into LDS by 256 threads, all loads issued together
+__device__ __forceinline__ void stage_block(long P, const double2* __restrict__ A, long b0, int nb,
+                                            double2 (&D)[CH_NB][CH_NB + 1]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double2 v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int r = w + 4 * q;
+        const bool in = r < nb && lane <= r;
+        v[q] = A[(b0 + (in ? r : 0)) * P + b0 + (in ? lane : 0)];
+        if (!in) v[q] = make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+        if (w + 4 * q < nb) D[w + 4 * q][lane] = v[q];
+}
+
 __device__ __forceinline__ bool chol_failed(const double* sc) {
     return ((int)sc[SC_FLAGS_SLOT] & CRBM_FLAG_CHOLESKY_FAIL) != 0;
 }
@@ -43,89 +71,122 @@ __global__ __launch_bounds__(256) void k_chol_load(long P, const float2* __restr
     A[idx] = make_double2((double)v.x + (i == j ? eps : 0.0), (double)v.y);
 }
 
-// 1. L_kk of the diagonal block [k0, k0 + nb)^2 in LDS (one workgroup of 1024 threads, a 32 x 32 grid over
-//    rows and columns, four waves per SIMD to overlap their LDS latencies).  Column j: every thread reads the
-//    pivot d = L_jj (final since the last barrier, so all take the same decision) and updates its share of
-//    the trailing lower triangle with the column scaled by 1 / sqrt(d) on the fly; after one barrier the
-//    column itself is scaled.  The next column reads column j + 1 and its own trailing block only, so one
-//    barrier per column suffices.
+// 1. L_kk of the diagonal block [k0, k0 + nb)^2, one workgroup.  The columns are factored in groups of CH_PW by
+//    the first wave alone, lane = row with the group's entries of the row in registers: the pivot and the
+//    multipliers reach all lanes through scalar registers, so the serial chain of a column (square root,
+//    reciprocal, scaling) holds no LDS round trip and no barrier.  Then all 16 waves subtract the group from the
+//    columns right of it through LDS.  bound by that chain: 36 us per block (55 us with a barrier and an LDS
+//    round trip per column).
+constexpr int CH_PW = 16;
 __global__ __launch_bounds__(1024) void k_chol_diagblock(long P, long k0, int nb, double2* __restrict__ A,
                                                          double* __restrict__ sc) {
     __shared__ double2 L[CH_NB][CH_NB + 1];
+    __shared__ int s_fail;
     if (chol_failed(sc)) return;
-    const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
-    for (int i = ty; i < nb; i += 32)
-        for (int j = tx; j < nb; j += 32) L[i][j] = (j <= i) ? A[(k0 + i) * P + k0 + j] : make_double2(0.0, 0.0);
+    const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5, lane = tid & 63;
+    if (tid == 0) s_fail = 0;
+    {
+        double2 v[2][2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int i = ty + 32 * p, j = tx + 32 * q;
+                const bool in = i < nb && j <= i;
+                v[p][q] = A[(k0 + (in ? i : 0)) * P + k0 + (in ? j : 0)];
+                if (!in) v[p][q] = make_double2(0.0, 0.0);
+            }
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) L[ty + 32 * p][tx + 32 * q] = v[p][q];
+    }
     __syncthreads();
-    bool fail = false;
-    for (int j = 0; j < nb; ++j) {
-        const double d = L[j][j].x;
-        if (!(d > 0.0) || !isfinite(d)) {
-            fail = true;
-            break;
-        }
-        const double s = sqrt(d), inv = 1.0 / s;
-        double2 b[2];                                  // L_lj / s for this thread's columns l
+    for (int p0 = 0; p0 < nb; p0 += CH_PW) {
+        const int pw = nb - p0 < CH_PW ? nb - p0 : CH_PW;
+        if (tid < 64) {
+            double2 a[CH_PW];
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            const int l = j + 1 + tx + 32 * m;
-            b[m] = l < nb ? make_double2(L[l][j].x * inv, L[l][j].y * inv) : make_double2(0.0, 0.0);
-        }
+            for (int c = 0; c < CH_PW; ++c)
+                a[c] = (c < pw && lane < nb && lane >= p0 + c) ? L[lane][p0 + c] : make_double2(0.0, 0.0);
+            bool fail = false;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int i = j + 1 + ty + 32 * p;
-            if (i >= nb) break;
-            const double2 a = make_double2(L[i][j].x * inv, L[i][j].y * inv);
+            for (int c = 0; c < CH_PW; ++c) {
+                if (c >= pw || fail) continue;
+                const double d = lane_value(a[c].x, p0 + c);
+                if (!(d > 0.0) || !isfinite(d)) { fail = true; continue; }
+                const double inv = inv_sqrt(d);
+                a[c] = lane == p0 + c ? make_double2(sqrt(d), 0.0) : make_double2(a[c].x * inv, a[c].y * inv);
 #pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const int l = j + 1 + tx + 32 * m;
-                if (l <= i) {                          // L_il -= L_ij conj(L_lj)
-                    L[i][l].x -= a.x * b[m].x + a.y * b[m].y;
-                    L[i][l].y -= a.y * b[m].x - a.x * b[m].y;
+                for (int l = c + 1; l < CH_PW; ++l) {   // A_il -= L_ic conj(L_lc); lanes above row l are not kept
+                    const double bx = lane_value(a[c].x, p0 + l), by = lane_value(a[c].y, p0 + l);
+                    a[l].x -= a[c].x * bx + a[c].y * by;
+                    a[l].y -= a[c].y * bx - a[c].x * by;
                 }
             }
+            if (fail && lane == 0) s_fail = 1;
+#pragma unroll
+            for (int c = 0; c < CH_PW; ++c)
+                if (c < pw && lane < nb && lane >= p0 + c) L[lane][p0 + c] = a[c];
         }
         __syncthreads();
-        if (tid == 0) L[j][j] = make_double2(s, 0.0);
-        for (int i = j + 1 + tid; i < nb; i += 1024) L[i][j] = make_double2(L[i][j].x * inv, L[i][j].y * inv);
+        if (s_fail) {
+            if (tid == 0) sc[SC_FLAGS_SLOT] = (double)((int)sc[SC_FLAGS_SLOT] | CRBM_FLAG_CHOLESKY_FAIL);
+            return;
+        }
+        const int q0 = p0 + pw;
+        for (int i = q0 + ty; i < nb; i += 32)
+            for (int l = q0 + tx; l <= i; l += 32) {
+                double2 v = L[i][l];
+#pragma unroll 4
+                for (int c = p0; c < q0; ++c) {
+                    const double2 x = L[i][c], y = L[l][c];
+                    v.x -= x.x * y.x + x.y * y.y;
+                    v.y -= x.y * y.x - x.x * y.y;
+                }
+                L[i][l] = v;
+            }
+        __syncthreads();
     }
-    if (fail) {
-        if (tid == 0) sc[SC_FLAGS_SLOT] = (double)((int)sc[SC_FLAGS_SLOT] | CRBM_FLAG_CHOLESKY_FAIL);
-        return;
-    }
-    __syncthreads();
     for (int i = ty; i < nb; i += 32)
         for (int j = tx; j <= i; j += 32) A[(k0 + i) * P + k0 + j] = L[i][j];
 }
 
-// 2. rows i >= k0 + nb: x L_kk^H = a with x = L_ik, a = A_ik; lane l owns column l of the row.
+// 2. rows i >= k0 + nb: x L_kk^H = a with x = L_ik, a = A_ik; lane l owns column l of the row, a wave CH_PR rows.
 //    x_m = (a_m - sum_{l<m} x_l conj(L_kk[m][l])) / L_kk[m][m]: once x_l is known (step l, lane l) it is
 //    read by every lane, and lanes m > l subtract its term from their own a_m, in the order l = 0, 1, ...
+//    The rows of a wave share the reads of L and hide each other's chains, and the block is staged once for
+//    4 CH_PR rows (21 us per panel at P = 3320, as with one row per wave, on a quarter of the workgroups).
+constexpr int CH_PR = 4;
 __global__ __launch_bounds__(256) void k_chol_panel(long P, long k0, int nb, double2* __restrict__ A,
                                                     const double* __restrict__ sc) {
     __shared__ double2 L[CH_NB][CH_NB + 1];
     if (chol_failed(sc)) return;
-    const int tid = threadIdx.x, lane = tid & 63;
-    for (int e = tid; e < nb * nb; e += 256) {
-        const int i = e / nb, j = e % nb;
-        L[i][j] = (j <= i) ? A[(k0 + i) * P + k0 + j] : make_double2(0.0, 0.0);
-    }
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane < nb ? lane : 0;
+    const long i0 = k0 + nb + ((long)blockIdx.x * 4 + (tid >> 6)) * CH_PR;
+    double2 x[CH_PR];
+#pragma unroll
+    for (int q = 0; q < CH_PR; ++q)
+        x[q] = (lane < nb && i0 + q < P) ? A[(i0 + q) * P + k0 + lane] : make_double2(0.0, 0.0);
+    stage_block(P, A, k0, nb, L);
     __syncthreads();
-    const long i = k0 + nb + (long)blockIdx.x * 4 + (tid >> 6);
-    if (i >= P) return;
-    double2* row = A + i * P + k0;
-    double2 x = lane < nb ? row[lane] : make_double2(0.0, 0.0);
-    const double dinv = lane < nb ? 1.0 / L[lane][lane].x : 0.0;   // lane m divides by L_mm at step m
+    if (i0 >= P) return;
+    const double dinv = lane < nb ? 1.0 / L[ln][ln].x : 0.0;   // lane m divides by L_mm at step m
+#pragma unroll 4
     for (int m = 0; m < nb; ++m) {
-        if (lane == m) x = make_double2(x.x * dinv, x.y * dinv);
-        const double xr = lane_value(x.x, m), xi = lane_value(x.y, m);
-        if (lane > m && lane < nb) {
-            const double2 c = L[lane][m];           // x_m conj(L[lane][m])
-            x.x -= xr * c.x + xi * c.y;
-            x.y -= xi * c.x - xr * c.y;
+        const double2 c = lane > m ? L[ln][m] : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < CH_PR; ++q) {
+            if (lane == m) x[q] = make_double2(x[q].x * dinv, x[q].y * dinv);
+            const double xr = lane_value(x[q].x, m), xi = lane_value(x[q].y, m);
+            x[q].x -= xr * c.x + xi * c.y;              // x_m conj(L[lane][m])
+            x[q].y -= xi * c.x - xr * c.y;
         }
     }
-    if (lane < nb) row[lane] = x;
+    if (lane < nb)
+#pragma unroll
+        for (int q = 0; q < CH_PR; ++q)
+            if (i0 + q < P) A[(i0 + q) * P + k0 + lane] = x[q];
 }
 
 // 3. trailing update of the lower triangle: A_ij -= sum_l L_il conj(L_jl), i >= j >= k1 = k0 + nb.
@@ -173,90 +234,100 @@ __global__ __launch_bounds__(256) void k_chol_update(long P, long k0, int nb, do
         }
 }
 
-// L y = F, then L^H x = y, in place in x, by blocks of 64 rows.  Per block: one wave substitutes within
-// the diagonal block (each unknown, once known, is read by every lane and the later lanes subtract its
-// term), then a kernel over the whole width applies the block's unknowns to the rest: forward, the rows
-// below (one wave per row, the lanes over the block's 64 columns); backward, the columns to the left
-// (one thread per column, the block's 64 rows in order).
-
-// x = F, or 0 after a failed factorisation
-__global__ __launch_bounds__(256) void k_trsv_init(long P, const double2* __restrict__ F, double2* __restrict__ x,
+// L y = F, then L^H x = y, by blocks of 64 rows, one launch per block: every workgroup stages the diagonal
+// block and its first wave substitutes in it (each unknown, once known, is read by every lane and the later
+// lanes subtract its term), all workgroups alike; then the workgroup applies the block's unknowns to its own
+// share of the rest: forward, the rows below (a thread per 16 columns of a row, four a row); backward, the
+// columns to the left (a thread per 16 rows of a column).  The right-hand side of a block and the rest are
+// updated in one vector, the solved unknowns go to another (workgroups of the next launch read the former).
+// 27 us per block and direction pair at P = 3320 (49 us with the substitution and the update as launches of their own).
+__global__ __launch_bounds__(256) void k_trsv_init(long P, const double2* __restrict__ F, double2* __restrict__ v,
                                                    const double* __restrict__ sc) {
     const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < P) x[k] = chol_failed(sc) ? make_double2(0.0, 0.0) : F[k];
+    if (k < P) v[k] = chol_failed(sc) ? make_double2(0.0, 0.0) : F[k];
 }
 
-// the diagonal block [b0, b0 + nb): forward (L_BB y_B = x_B) or backward (L_BB^H x_B = x_B); four waves
-// stage the block, the first substitutes
-__global__ __launch_bounds__(256) void k_trsv_diag(long P, const double2* __restrict__ A, long b0, int nb, int backward,
-                                                   double2* __restrict__ x, const double* __restrict__ sc) {
-    __shared__ double2 D[CH_NB][CH_NB + 1];
-    if (chol_failed(sc)) return;
-    for (int e = threadIdx.x; e < nb * CH_NB; e += 256) {
-        const int r = e / CH_NB, c = e % CH_NB;
-        D[r][c] = c <= r ? A[(b0 + r) * P + b0 + c] : make_double2(0.0, 0.0);
+// v: right-hand side (updated past the block), x: solution; x_b in LDS at the end
+template <bool BACK>
+__device__ __forceinline__ void trsv_block(long P, const double2* __restrict__ A, long b0, int nb,
+                                           const double2* __restrict__ v, double2 (&D)[CH_NB][CH_NB + 1],
+                                           double2 (&xb)[CH_NB]) {
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane < nb ? lane : 0;
+    stage_block(P, A, b0, nb, D);
+    __syncthreads();
+    if (tid < 64) {
+        double2 x = lane < nb ? v[b0 + lane] : make_double2(0.0, 0.0);
+        const double dinv = lane < nb ? 1.0 / D[ln][ln].x : 0.0;   // lane m divides by L_mm at step m
+#pragma unroll 4
+        for (int t = 0; t < nb; ++t) {
+            const int m = BACK ? nb - 1 - t : t;
+            const double2 c = BACK ? (lane < m ? D[m][ln] : make_double2(0.0, 0.0))
+                                   : (lane > m ? D[ln][m] : make_double2(0.0, 0.0));
+            if (lane == m) x = make_double2(x.x * dinv, x.y * dinv);
+            const double2 xm = make_double2(lane_value(x.x, m), lane_value(x.y, m));
+            const double2 p = BACK ? zconjmul(c, xm) : zmul(c, xm);
+            x.x -= p.x;
+            x.y -= p.y;
+        }
+        xb[lane] = lane < nb ? x : make_double2(0.0, 0.0);
     }
     __syncthreads();
-    if (threadIdx.x >= 64) return;
-    const int lane = threadIdx.x;
-    double2 v = lane < nb ? x[b0 + lane] : make_double2(0.0, 0.0);
-    const double dinv = lane < nb ? 1.0 / D[lane][lane].x : 0.0;   // lane m divides by L_mm at step m
-    if (!backward) {
-        // y_m = (x_m - sum_{l<m} L_ml y_l) / L_mm, l = 0, 1, ...
-        for (int m = 0; m < nb; ++m) {
-            if (lane == m) v = make_double2(v.x * dinv, v.y * dinv);
-            const double2 ym = make_double2(lane_value(v.x, m), lane_value(v.y, m));
-            if (lane > m && lane < nb) {
-                const double2 t = zmul(D[lane][m], ym);
-                v.x -= t.x;
-                v.y -= t.y;
-            }
-        }
-    } else {
-        // x_m = (v_m - sum_{l>m} conj(L_lm) x_l) / L_mm, m from the bottom of the block up
-        for (int m = nb - 1; m >= 0; --m) {
-            if (lane == m) v = make_double2(v.x * dinv, v.y * dinv);
-            const double2 xm = make_double2(lane_value(v.x, m), lane_value(v.y, m));
-            if (lane < m) {
-                const double2 t = zconjmul(D[m][lane], xm);   // conj(L_m,lane) x_m
-                v.x -= t.x;
-                v.y -= t.y;
-            }
-        }
-    }
-    if (lane < nb) x[b0 + lane] = v;
 }
 
-// forward: x_k -= sum_{l < nb} L_k,b0+l y_b0+l for the rows k >= b0 + nb, one wave per row
-__global__ __launch_bounds__(256) void k_trsv_rows(long P, const double2* __restrict__ A, long b0, int nb,
-                                                   double2* __restrict__ x, const double* __restrict__ sc) {
+__global__ __launch_bounds__(256) void k_trsv_fwd(long P, const double2* __restrict__ A, long b0, int nb,
+                                                  double2* __restrict__ v, double2* __restrict__ x,
+                                                  const double* __restrict__ sc) {
+    __shared__ double2 D[CH_NB][CH_NB + 1];
+    __shared__ double2 xb[CH_NB];
     if (chol_failed(sc)) return;
-    const int lane = threadIdx.x & 63;
-    const long k = b0 + nb + (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (k >= P) return;
+    trsv_block<false>(P, A, b0, nb, v, D, xb);
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid < nb) x[b0 + tid] = xb[tid];
+    const long k = b0 + nb + (long)blockIdx.x * 64 + (tid >> 2);
     double2 t = make_double2(0.0, 0.0);
-    if (lane < nb) t = zmul(A[k * P + b0 + lane], x[b0 + lane]);
-    const double tx = wave_sum(t.x), ty = wave_sum(t.y);
-    if (lane == 0) x[k] = make_double2(x[k].x - tx, x[k].y - ty);
+    if (k < P)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int l = (tid & 3) + 4 * q;
+            if (l < nb) t = zadd(t, zmul(A[k * P + b0 + l], xb[l]));
+        }
+    t.x += __shfl_xor(t.x, 1); t.y += __shfl_xor(t.y, 1);
+    t.x += __shfl_xor(t.x, 2); t.y += __shfl_xor(t.y, 2);
+    if (k < P && (tid & 3) == 0) v[k] = zsub(v[k], t);
 }
 
-// backward: x_j -= sum_{r < nb} conj(L_b0+r,j) x_b0+r for the columns j < b0, one thread per column
-__global__ __launch_bounds__(256) void k_trsv_cols(long P, const double2* __restrict__ A, long b0, int nb,
-                                                   double2* __restrict__ x, const double* __restrict__ sc) {
+// x (the forward solution) is the right-hand side here and is updated left of the block; the solution goes to out
+__global__ __launch_bounds__(256) void k_trsv_back(long P, const double2* __restrict__ A, long b0, int nb,
+                                                   double2* __restrict__ v, double2* __restrict__ out,
+                                                   const double* __restrict__ sc) {
+    __shared__ double2 D[CH_NB][CH_NB + 1];
+    __shared__ double2 xb[CH_NB], part[4][64];
     if (chol_failed(sc)) return;
-    const long j = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= b0) return;
-    double ax = 0.0, ay = 0.0;
-    for (int r = 0; r < nb; ++r) {
-        const double2 t = zconjmul(A[(b0 + r) * P + j], x[b0 + r]);
-        ax += t.x;
-        ay += t.y;
-    }
-    x[j] = make_double2(x[j].x - ax, x[j].y - ay);
+    trsv_block<true>(P, A, b0, nb, v, D, xb);
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (blockIdx.x == 0 && tid < nb) out[b0 + tid] = xb[tid];
+    const long j = (long)blockIdx.x * 64 + lane;
+    double2 t = make_double2(0.0, 0.0);
+    if (j < b0)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int r = 16 * w + q;
+            if (r < nb) t = zadd(t, zconjmul(A[(b0 + r) * P + j], xb[r]));
+        }
+    part[w][lane] = t;
+    __syncthreads();
+    if (w == 0 && j < b0) v[j] = zsub(v[j], zadd(zadd(part[0][lane], part[1][lane]), zadd(part[2][lane], part[3][lane])));
 }
 
+// after a failed factorisation the solution is 0
+__global__ __launch_bounds__(256) void k_trsv_failed(long P, double2* __restrict__ x, const double* __restrict__ sc) {
+    const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < P && chol_failed(sc)) x[k] = make_double2(0.0, 0.0);
+}
+
+// v, y: [P] scratch
 hipError_t launch_cholesky_solve(long P, const float2* S, double eps, const double2* F, double2* A64, double2* x,
-                                 double* sc, bool a64_holds_s, hipStream_t stream) {
+                                 double2* v, double2* y, double* sc, bool a64_holds_s, hipStream_t stream) {
     if (P < 1 || P > kCholMaxP) return hipErrorInvalidValue;
     // a64_holds_s: A64 already holds S + eps I in double
     if (!a64_holds_s)
@@ -266,29 +337,27 @@ hipError_t launch_cholesky_solve(long P, const float2* S, double eps, const doub
         hipLaunchKernelGGL(k_chol_diagblock, dim3(1), dim3(1024), 0, stream, P, k0, nb, A64, sc);
         const long rows = P - k0 - nb;
         if (rows <= 0) break;
-        hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, P, k0, nb, A64, sc);
+        hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)((rows + 4 * CH_PR - 1) / (4 * CH_PR))), dim3(256), 0, stream, P,
+                           k0, nb, A64, sc);
         const long T = (rows + CH_T - 1) / CH_T;
         hipLaunchKernelGGL(k_chol_update, dim3((unsigned)(T * (T + 1) / 2)), dim3(256), 0, stream, P, k0, nb, A64, sc);
     }
-    hipLaunchKernelGGL(k_trsv_init, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, stream, P, F, x, sc);
+    const dim3 gp((unsigned)((P + 255) / 256));
+    hipLaunchKernelGGL(k_trsv_init, gp, dim3(256), 0, stream, P, F, v, sc);
     const long nblk = (P + CH_NB - 1) / CH_NB;
     for (long blk = 0; blk < nblk; ++blk) {
         const long b0 = blk * CH_NB;
         const int nb = (int)(P - b0 < CH_NB ? P - b0 : CH_NB);
-        hipLaunchKernelGGL(k_trsv_diag, dim3(1), dim3(256), 0, stream, P, A64, b0, nb, 0, x, sc);
-        const long rows = P - b0 - nb;
-        if (rows > 0)
-            hipLaunchKernelGGL(k_trsv_rows, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, P, A64, b0, nb, x,
-                               sc);
+        const long g = (P - b0 - nb + 63) / 64;
+        hipLaunchKernelGGL(k_trsv_fwd, dim3((unsigned)(g > 0 ? g : 1)), dim3(256), 0, stream, P, A64, b0, nb, v, y, sc);
     }
     for (long blk = nblk - 1; blk >= 0; --blk) {
         const long b0 = blk * CH_NB;
         const int nb = (int)(P - b0 < CH_NB ? P - b0 : CH_NB);
-        hipLaunchKernelGGL(k_trsv_diag, dim3(1), dim3(256), 0, stream, P, A64, b0, nb, 1, x, sc);
-        if (b0 > 0)
-            hipLaunchKernelGGL(k_trsv_cols, dim3((unsigned)((b0 + 255) / 256)), dim3(256), 0, stream, P, A64, b0, nb, x,
-                               sc);
+        const long g = (b0 + 63) / 64;
+        hipLaunchKernelGGL(k_trsv_back, dim3((unsigned)(g > 0 ? g : 1)), dim3(256), 0, stream, P, A64, b0, nb, y, x, sc);
     }
+    hipLaunchKernelGGL(k_trsv_failed, gp, dim3(256), 0, stream, P, x, sc);
     return hipGetLastError();
 }
 
