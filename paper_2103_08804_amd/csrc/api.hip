@@ -18,10 +18,10 @@
 namespace crbm {
 hipError_t launch_local_core(const LocalArgs& A, const float2* th1, const float2* thn, const float2* thm,
                              hipStream_t stream);
-hipError_t launch_lc_sums(const int8_t* sig, long n, int N, int M, const float2* a, const float2* b,
-                          const float2* W, uint16_t* planes, float2* partial, const double2* Lg,
-                          const double2* beta, double2* B, double2* Lg_out, hipStream_t stream);
-hipError_t launch_fq_chunk(const Geometry& g, const int8_t* sig, long n_s, const double* q_host, int n_q,
+hipError_t launch_lc_sums(const int8_t* sig, const uint32_t* bits, long n, int N, int M, const float2* a,
+                          const float2* b, const float2* W, uint16_t* planes, float2* partial, const double2* Lg,
+                          const double2* beta, double2* B, double2* Lg_out, int n_cu, hipStream_t stream);
+hipError_t launch_fq_chunk(const Geometry& g, const uint32_t* bits, long n_s, const double* q_host, int n_q,
                            double2* f, hipStream_t stream);
 hipError_t launch_moment_accum(const double2* f, const double2* B, int b_is_f, const double* w, long n_s, int n_q,
                                int nn, int entry0, int total, double2* partial, int n_blocks, hipStream_t stream);
@@ -333,7 +333,8 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     rc = rc ? rc : p->alloc(&p->momB, S);
     rc = rc ? rc : p->alloc(&p->momF, (long)kQChunk * S);
     rc = rc ? rc : p->alloc(&p->mom_partial, (long)kMomBlocks * kMaxMomentEntries);
-    rc = rc ? rc : p->alloc(&p->wplanes, lc_plane_elems(N, M));
+    rc = rc ? rc : p->alloc(&p->wplanes, 3 * lc_plane_elems(N, M));
+    rc = rc ? rc : p->alloc(&p->w.bits, S * spin_words((int)N));
     p->w.wplanes = p->wplanes;
     rc = rc ? rc : p->alloc(&p->lcLg, S);
     rc = rc ? rc : p->alloc(&p->bcounter, 1);
@@ -409,7 +410,7 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     e = hipMemcpy(p->bonds, bonds.data(), bonds.size() * sizeof(int2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(p->w.scal, 0, 32 * sizeof(double));
     // the padding of the split-W planes stays zero: every writer fills the places of real sites and units, or all
-    if (e == hipSuccess) e = hipMemset(p->wplanes, 0, lc_plane_elems(N, M) * sizeof(uint16_t));
+    if (e == hipSuccess) e = hipMemset(p->wplanes, 0, 3 * lc_plane_elems(N, M) * sizeof(uint16_t));
     if (e == hipSuccess && !order.empty())
         e = hipMemcpy(const_cast<int2*>(p->w.sb_order), order.data(), order.size() * sizeof(int2),
                       hipMemcpyHostToDevice);
@@ -571,15 +572,20 @@ int crbm_local_estimators(crbm_plan p, const crbm_rbm* fit, const crbm_rbm* psi_
     A.R_out = static_cast<float2*>(R_out);
     A.tanh_out = static_cast<float2*>(tanh_out);
     A.O_out = static_cast<float2*>(O_out);
-    auto theta = [&](const RbmView& v, float2* out) {
+    ThetaSet set{};
+    set.count = cheb_mode ? (cheb->order >= 1 ? 3 : 2) : 1;
+    const RbmView* views[3] = {&A.fit, &A.psn, &A.psm};
+    for (int k = 0; k < set.count; ++k) {
+        set.b[k] = views[k]->b;
+        set.W[k] = views[k]->W;
+        set.out[k] = p->theta[k];
+    }
+    hipError_t e = launch_spin_bits(samples, n, p->N, p->w.bits, stream);
+    if (e == hipSuccess) {
         p->prof.begin(PROF_THETA, stream);
-        hipError_t r = launch_theta(samples, n, p->N, p->M, v.b, v.W, out, p->wplanes, stream);
+        e = launch_theta(p->w.bits, n, p->N, p->M, set, p->wplanes, p->n_cu, stream);
         p->prof.end(stream);
-        return r;
-    };
-    hipError_t e = theta(A.fit, p->theta[0]);
-    if (e == hipSuccess && cheb_mode) e = theta(A.psn, p->theta[1]);
-    if (e == hipSuccess && cheb_mode && cheb->order >= 1) e = theta(A.psm, p->theta[2]);
+    }
     if (e == hipSuccess) {
         p->prof.begin(PROF_LOCAL, stream);
         e = launch_local_core(A, p->theta[0], p->theta[1], p->theta[2], stream);
@@ -686,14 +692,16 @@ int crbm_chebyshev_moment(crbm_plan p, const crbm_rbm* gs, const void* t_params,
     const int nn = n_max + 1;
     const long P = p->P;
     const float2* tp = static_cast<const float2*>(t_params);
+    hipError_t e = launch_spin_bits(samples, n, p->N, p->w.bits, stream);
+    if (e != hipSuccess) return hip_fail(e, "chebyshev_moment launch");
     // per-sample sum log cosh theta + a.sigma of psi_gs, once; the tile partials go to theta[2]
     p->prof.begin(PROF_MOMENT, stream);
-    hipError_t e = launch_lc_sums(samples, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2], nullptr,
-                                  nullptr, nullptr, p->lcLg, stream);
+    e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2], nullptr,
+                                  nullptr, nullptr, p->lcLg, p->n_cu, stream);
     p->prof.end(stream);
     for (int q0 = 0; q0 < n_q && e == hipSuccess; q0 += kQChunk) {
         const int nq = (n_q - q0) < kQChunk ? (n_q - q0) : kQChunk;
-        e = launch_fq_chunk(g, samples, n, q + 2 * q0, nq, p->momF, stream);
+        e = launch_fq_chunk(g, p->w.bits, n, q + 2 * q0, nq, p->momF, stream);
         if (e == hipSuccess)
             e = launch_moment_accum(p->momF, nullptr, 1, weights, n, nq, nn, q0 * nn, nn * n_q, p->mom_partial,
                                     kMomBlocks, stream);
@@ -701,8 +709,8 @@ int crbm_chebyshev_moment(crbm_plan p, const crbm_rbm* gs, const void* t_params,
             const float2* at = tp + (long)(t - 1) * P;
             // B_t = beta_t t~_t / psi_gs from the fused product and log-cosh sums
             p->prof.begin(PROF_MOMENT, stream);
-            e = launch_lc_sums(samples, n, p->N, p->M, at, at + p->N, at + p->N + p->M, p->wplanes, p->theta[2],
-                               p->lcLg, reinterpret_cast<const double2*>(betas) + (t - 1), p->momB, nullptr, stream);
+            e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, at, at + p->N, at + p->N + p->M, p->wplanes, p->theta[2],
+                               p->lcLg, reinterpret_cast<const double2*>(betas) + (t - 1), p->momB, nullptr, p->n_cu, stream);
             p->prof.end(stream);
             if (e == hipSuccess)
                 e = launch_moment_accum(p->momF, p->momB, 0, weights, n, nq, nn, q0 * nn + t, nn * n_q,
@@ -830,10 +838,20 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
     const float2* tp = static_cast<const float2*>(t_params);
 
     // order 0: B_0 = f_q, HB_0 = (H S^z_q psi_gs)/psi_gs
-    p->prof.begin(PROF_THETA, stream);
-    hipError_t e = launch_theta(samples, n, p->N, p->M, vg.b, vg.W, p->theta[0], p->wplanes, stream);
-    p->prof.end(stream);
-    if (e == hipSuccess) e = launch_fq_chunk(g, samples, n, q, 1, p->momF, stream);
+    auto theta = [&](const RbmView& v, float2* out) {
+        ThetaSet set{};
+        set.count = 1;
+        set.b[0] = v.b;
+        set.W[0] = v.W;
+        set.out[0] = out;
+        p->prof.begin(PROF_THETA, stream);
+        hipError_t r = launch_theta(p->w.bits, n, p->N, p->M, set, p->wplanes, p->n_cu, stream);
+        p->prof.end(stream);
+        return r;
+    };
+    hipError_t e = launch_spin_bits(samples, n, p->N, p->w.bits, stream);
+    if (e == hipSuccess) e = theta(vg, p->theta[0]);
+    if (e == hipSuccess) e = launch_fq_chunk(g, p->w.bits, n, q, 1, p->momF, stream);
     LocalArgs A{};
     A.g = g;
     A.samples = samples;
@@ -854,8 +872,8 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
     if (e == hipSuccess) e = launch_basis_pack(n, p->momF, loc, 0, Bm, HBm, stream);
     if (e == hipSuccess && n_max > 0) {
         p->prof.begin(PROF_MOMENT, stream);
-        e = launch_lc_sums(samples, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2], nullptr, nullptr,
-                           nullptr, p->lcLg, stream);
+        e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2], nullptr, nullptr,
+                           nullptr, p->lcLg, p->n_cu, stream);
         p->prof.end(stream);
     }
     // orders 1..n_max: B_t = beta_t t~_t/psi_gs, HB_t = B_t E_loc[t~_t]
@@ -865,9 +883,7 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
         vt.a = at;
         vt.b = at + p->N;
         vt.W = at + p->N + p->M;
-        p->prof.begin(PROF_THETA, stream);
-        e = launch_theta(samples, n, p->N, p->M, vt.b, vt.W, p->theta[1], p->wplanes, stream);
-        p->prof.end(stream);
+        e = theta(vt, p->theta[1]);
         LocalArgs At{};
         At.g = g;
         At.samples = samples;
@@ -881,8 +897,8 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
         }
         if (e == hipSuccess) {
             p->prof.begin(PROF_MOMENT, stream);
-            e = launch_lc_sums(samples, n, p->N, p->M, at, vt.b, vt.W, p->wplanes, p->theta[2], p->lcLg,
-                               reinterpret_cast<const double2*>(betas) + (t - 1), p->momB, nullptr, stream);
+            e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, at, vt.b, vt.W, p->wplanes, p->theta[2], p->lcLg,
+                               reinterpret_cast<const double2*>(betas) + (t - 1), p->momB, nullptr, p->n_cu, stream);
             p->prof.end(stream);
         }
         if (e == hipSuccess) e = launch_basis_pack(n, p->momB, loc, 1, Bm + (long)t * n, HBm + (long)t * n, stream);
@@ -947,9 +963,14 @@ int crbm_sym_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, con
     const float2* tp = static_cast<const float2*>(t_params);
     const int Ly = p->lat.kind == CRBM_LATTICE_CHAIN ? 1 : p->lat.Ly;
     hipError_t e = hipSuccess;
-    auto theta = [&](const int8_t* sig, long rows, const RbmView& v, float2* out) {
+    auto theta = [&](long rows, const RbmView& v, float2* out) {
+        ThetaSet set{};
+        set.count = 1;
+        set.b[0] = v.b;
+        set.W[0] = v.W;
+        set.out[0] = out;
         p->prof.begin(PROF_THETA, stream);
-        hipError_t r = launch_theta(sig, rows, N, M, v.b, v.W, out, p->wplanes, stream);
+        hipError_t r = launch_theta(p->w.bits, rows, N, M, set, p->wplanes, p->n_cu, stream);
         p->prof.end(stream);
         return r;
     };
@@ -964,14 +985,16 @@ int crbm_sym_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, con
         const long rows = c * ng;
         const int8_t* sig = samples + s0 * N;
         // log psi_gs of the chunk's samples
-        e = theta(sig, c, vg, p->theta[2]);
+        e = launch_spin_bits(sig, c, N, p->w.bits, stream);
+        if (e == hipSuccess) e = theta(c, vg, p->theta[2]);
         LocalArgs A0{};
         A0.g = geo; A0.fit = vg; A0.samples = sig; A0.n_samples = c; A0.logpsi_out = lg;
         if (e == hipSuccess) e = local(A0, p->theta[2]);
         // the images of every sample under the group
         if (e == hipSuccess) e = launch_sym_images(sig, c, N, p->lat.kind, p->lat.Lx, Ly, nrot, img, stream);
+        if (e == hipSuccess) e = launch_spin_bits(img, rows, N, p->w.bits, stream);
         // order 0: t_000 = S^z_0 psi_gs on the images
-        if (e == hipSuccess) e = theta(img, rows, vg, p->theta[0]);
+        if (e == hipSuccess) e = theta(rows, vg, p->theta[0]);
         LocalArgs A1{};
         A1.g = geo; A1.fit = vg; A1.psn = vg; A1.cheb_mode = 1; A1.local_op = 1; A1.order = 0; A1.W_scale = 1.0;
         A1.samples = img; A1.n_samples = rows; A1.logpsi_out = lt; A1.eloc_out = el;
@@ -981,7 +1004,7 @@ int crbm_sym_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, con
             const float2* at = tp + (long)(t - 1) * P;
             RbmView vt;
             vt.a = at; vt.b = at + N; vt.W = at + N + M;
-            e = theta(img, rows, vt, p->theta[1]);
+            e = theta(rows, vt, p->theta[1]);
             LocalArgs At{};
             At.g = geo; At.fit = vt; At.samples = img; At.n_samples = rows; At.logpsi_out = lt; At.eloc_out = el;
             if (e == hipSuccess) e = local(At, p->theta[1]);

@@ -15,16 +15,27 @@ struct RbmView {            // device pointers, complex64 interleaved
     const float2* W;
 };
 
-// theta = sigma W + b (complex64 [n][M]) on the matrix cores; planes: lc_plane_elems(N, M) scratch for
-// the split W; skip (device, may be null) != 0 makes both launches return at once
-hipError_t launch_theta(const int8_t* sig, long n, int N, int M, const float2* b, const float2* W, float2* theta,
-                        uint16_t* planes, hipStream_t stream, const double* skip = nullptr);
+// rows of sign bits: ceil(N / 32) words per sample, bit set where sigma = -1
+inline int spin_words(int N) { return (N + 31) / 32; }
+hipError_t launch_spin_bits(const int8_t* sig, long n, int N, uint32_t* bits, hipStream_t stream);
+
+// up to three RBMs whose theta is taken on the same samples
+struct ThetaSet {
+    const float2* b[3];
+    const float2* W[3];
+    float2* out[3];
+    int count;
+};
+// theta = sigma W + b (complex64 [n][M]) on the matrix cores; planes: count x lc_plane_elems(N, M) scratch for
+// the split W
+hipError_t launch_theta(const uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes, int n_cu,
+                        hipStream_t stream);
 // O v of the matrix-free S product, u[s] = sum_k T_sk (sigma_s V_W + v_b)_k + sigma_s . v_a, without
 // writing the n x M product; planes: V_W split as the theta product's W; partial: n * ceil(M / 64) double2
 // scratch; mean_out <- the sum of the n_omv partials omv (a double pair)
-hipError_t launch_theta_ov(const int8_t* sig, long n, int N, int M, const float2* vb, const double2* va,
+hipError_t launch_theta_ov(const uint32_t* bits, long n, int N, int M, const float2* vb, const double2* va,
                            const float2* T, const uint16_t* planes, double2* partial, double2* u, const double2* omv,
-                           int n_omv, double* mean_out, hipStream_t stream, const double* skip);
+                           int n_omv, double* mean_out, int n_cu, hipStream_t stream, const double* skip);
 // padded row length (sites) and row count of one BF16 plane of the split W
 inline int theta_np(int N) { return (N + 31) / 32 * 32; }
 inline long theta_rows(int M) { return (long)((M + 63) / 64) * 128; }
@@ -129,6 +140,7 @@ struct SrWork {
     float2* S;                // [P][P] dense (may be null)
     double2* S64;             // [P][P] dense double (Cholesky, may be null)
     float2* G;                // [n][2 ceil(M / 64)] scratch of the matrix-free product (its O v partials)
+    uint32_t* bits;           // [n][spin_words(N)] sign bits of the samples
     int8_t* sig16;            // [n][sig16_row(N)] sigma~ rows for the O^H c contraction
     float2* vstage;           // [P] float copy of a CG direction
     void* pack;               // packed operand planes of the matrix-core S contraction

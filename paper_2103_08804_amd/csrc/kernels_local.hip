@@ -11,6 +11,8 @@
 // lane multiplies its own factors and the wave adds their logarithms.
 // Log-amplitude differences between RBMs are summed element by element so
 // that the M log 2 constants cancel before any rounding of the total.
+#include <type_traits>
+
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -24,14 +26,58 @@ namespace crbm {
 // FP32 accumulation.  The B columns of a tile of 64 hidden units are the real and imaginary
 // parts of W ordered [Re 0..31 | Im 0..31 | Re 32..63 | Im 32..63], so that both parts of a
 // unit end in one lane; W is split into its parts in that order once per RBM (k_wsplit).
-// Tile: 128 samples x 128 real columns per workgroup (4 waves x 32 samples x 4 column blocks),
-// K chunks of 32 sites through LDS.
+//
+// sigma comes as one sign bit per site (k_spin_bits, once per sample set): a lane builds its A operand, the
+// eight sites of its sample that a matrix-core step reads, from one byte in registers, so the spins pass
+// through no LDS.  The W tile (three parts x 128 rows x up to 128 sites, 104 KB) is staged in LDS once per
+// workgroup, which then walks its samples in tiles of 16 waves x 32 with no barrier; beyond 128 sites the
+// tile is staged in pieces of 128 sites per sample tile.  65,536 samples, 10 x 10, M = 400: 64 us per product,
+// bound by the writes of theta (122 us with both operands staged per 128-sample tile, the spins a byte a load).
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 
-constexpr int TH_S = 128, TH_C = 128, TH_K = 32;
-constexpr int TH_ROW = TH_K * 2 + 16;          // bytes per LDS row (32 bf16 + padding)
+constexpr int TH_C = 128, TH_K = 32;           // plane rows of a unit tile; sites are padded to TH_K
+constexpr int TH_W = 8, TH_S = 32 * TH_W;      // waves and samples of a workgroup's tile
+constexpr int TH_KMAX = 128;                   // sites of W staged at a time
+
+// bits[s][w]: bit b of word w set where sigma of site 32 w + b is negative; nw = ceil(N / 32) words a row
+template <bool WORDS>
+__global__ __launch_bounds__(256) void k_spin_bits(const int8_t* __restrict__ sig, long n, int N, int nw,
+                                                   uint32_t* __restrict__ bits) {
+    const long e = (long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= n * nw) return;
+    const long s = e / nw;
+    const int i0 = 32 * (int)(e % nw), cnt = N - i0 < 32 ? N - i0 : 32;
+    const int8_t* row = sig + s * N + i0;
+    uint32_t m = 0;
+    if (WORDS) {   // rows start on 4 bytes and N is a multiple of 4: four sign bits per word
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+            if (4 * d < cnt) {
+                const uint32_t x = (reinterpret_cast<const uint32_t*>(row)[d] >> 7) & 0x01010101u;
+                m |= ((x * 0x10204080u) >> 28) << (4 * d);
+            }
+    } else {
+        for (int b = 0; b < cnt; ++b) m |= (row[b] < 0 ? 1u : 0u) << b;
+    }
+    bits[e] = m;
+}
+
+hipError_t launch_spin_bits(const int8_t* sig, long n, int N, uint32_t* bits, hipStream_t stream) {
+    if (n <= 0) return hipSuccess;
+    const int nw = spin_words(N);
+    const dim3 grid((unsigned)((n * nw + 255) / 256));
+    if (N % 4 == 0 && (reinterpret_cast<uintptr_t>(sig) & 3) == 0)
+        hipLaunchKernelGGL(k_spin_bits<true>, grid, dim3(256), 0, stream, sig, n, N, nw, bits);
+    else
+        hipLaunchKernelGGL(k_spin_bits<false>, grid, dim3(256), 0, stream, sig, n, N, nw, bits);
+    return hipGetLastError();
+}
+// sigma of site i from its row of sign bits
+__device__ __forceinline__ float spin_of(const uint32_t* __restrict__ row, int i) {
+    return (row[i >> 5] >> (i & 31)) & 1u ? -1.f : 1.f;
+}
 
 // ------------------------------------------------------------------ helpers
 // f_q(sigma) = N^{-1/2} sum_r exp(-i q.r) sigma_r / 2 over the wave's spins
@@ -75,9 +121,10 @@ __device__ __forceinline__ float2 a_dot_sigma(const float2* a, const WaveSpins& 
 //
 // The planes of W are [3][Mt 128][Np], Np = N rounded up to TH_K, zero padded; the product's
 // workgroups only copy tiles of them.
-__global__ __launch_bounds__(256) void k_wsplit(const float2* __restrict__ W, int N, int M, int Np, int Mt,
-                                                uint16_t* __restrict__ planes, const double* __restrict__ skip) {
-    if (skip && *skip != 0.0) return;     // a converged iterative solve skips the product
+__global__ __launch_bounds__(256) void k_wsplit(ThetaSet set, int N, int M, int Np, int Mt,
+                                                uint16_t* __restrict__ planes) {
+    const float2* W = set.W[blockIdx.z];
+    planes += blockIdx.z * (3L * Mt * TH_C * Np);
     const long rows = (long)Mt * TH_C;
     const long idx = (long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= rows * Np) return;
@@ -92,95 +139,171 @@ __global__ __launch_bounds__(256) void k_wsplit(const float2* __restrict__ W, in
     split_store(planes, rows * Np, idx, w);
 }
 
+// Complex product and |a|^2 with their fused multiply-adds written out, so that the moments do not depend in the
+// last bits on which of the two products of a sum the compiler fuses in one kernel or another.
+__device__ __forceinline__ float2 cmul_fused(float2 a, float2 b) {
+    return make_float2(__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(a.x, b.y, a.y * b.x));
+}
+__device__ __forceinline__ float norm2_fused(float2 a) { return __builtin_fmaf(a.x, a.x, a.y * a.y); }
+
+// cosh_factor with sign 1
+__device__ __forceinline__ void lc_factor(float2 z, float2& lin, float2& p) {
+    const float sg = z.x >= 0.f ? 1.f : -1.f;
+    const float ex = expf(-2.f * fabsf(z.x));
+    const float2 cs = cos_sin(2.f * sg * z.y);
+    lin.x += fabsf(z.x);
+    lin.y += sg * z.y;
+    p = cmul_fused(p, make_float2(0.5f * __builtin_fmaf(ex, cs.x, 1.f), (-0.5f * ex) * cs.y));
+}
+
 // combine two partial sums of log cosh: the linear parts add, the bounded factors multiply
 __device__ __forceinline__ void lc_join(float2& lin, float2& pr, float2 lin2, float2 pr2) {
     lin = cadd(lin, lin2);
-    pr = cmul(pr, pr2);
+    pr = cmul_fused(pr, pr2);
 }
 
-// The tile product: workgroup (x, ct) accumulates sigma[128 x s .. + 128) times the 128 plane rows of
-// unit tile ct over all sites, K chunks of TH_K sites through LDS.  Lane l of wave w ends with column
-// l % 32 of each 32-column block cb in acc[cb], rows w 32 + 8 (v / 4) + 4 (l / 32) + v % 4.  The kernels
-// built on it ask for four waves per SIMD: they then fit in 96 registers with the accumulators among
-// them, and four workgroups of 40 KB fill the compute unit's LDS.
-__device__ __forceinline__ void theta_tile(const int8_t* __restrict__ sig, long n, int N, int Np,
-                                           const uint16_t* __restrict__ planes, long rows, int ct, long s0,
-                                           unsigned char* s_sig, unsigned char (*s_w)[TH_C * TH_ROW],
-                                           floatx16_t (&acc)[4]) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// The tile product.  KC: sites staged at a time (the padded N up to 128).  Lane l of wave w ends with column
+// l % 32 of each 32-column block cb in acc[cb], rows 8 (v / 4) + 4 (l / 32) + v % 4 of the wave's 32 samples.
+template <int KC>
+struct ThetaLds {
+    static constexpr int ROW = KC * 2 + 16;    // bytes per plane row: 16 rows of a fragment read fall in distinct banks
+    unsigned char w[3][TH_C * ROW];
+};
+// sites [k0, k0 + KC) of the three parts of unit tile ct; columns past Np are left as they are (never read)
+template <int KC>
+__device__ __forceinline__ void theta_stage(ThetaLds<KC>& lds, const uint16_t* __restrict__ planes, long rows, int Np,
+                                            int ct, int k0) {
+    const int len = Np - k0 < KC ? Np - k0 : KC, per = len / 8;
+    for (int c = threadIdx.x; c < 3 * TH_C * per; c += 64 * TH_W) {
+        const int pr = c / per, ch = c % per, part = pr / TH_C, rr = pr % TH_C;
+        const uint16_t* src = planes + part * rows * Np + ((long)ct * TH_C + rr) * Np + k0 + ch * 8;
+        *reinterpret_cast<i32x4_t*>(lds.w[part] + rr * ThetaLds<KC>::ROW + ch * 16) = *reinterpret_cast<const i32x4_t*>(src);
+    }
+}
+// the eight BF16 spins (1 or -1) of sign bits 0..7 of x
+__device__ __forceinline__ i32x4_t spin_frag(uint32_t x) {
+    i32x4_t a;
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
+    for (int d = 0; d < 4; ++d)
+        a[d] = (int)(0x3F803F80u | ((x << (15 - 2 * d)) & 0x8000u) | ((x << (30 - 2 * d)) & 0x80000000u));
+    return a;
+}
+template <int KC>
+__device__ __forceinline__ void theta_steps(const ThetaLds<KC>& lds, const uint32_t* __restrict__ words, int len, int lane,
+                                            floatx16_t (&acc)[4]) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[cb][v] = 0.f;
-    for (int k0 = 0; k0 < Np; k0 += TH_K) {
-        for (int e = tid; e < TH_S * TH_K; e += 256) {
-            const int ss = e / TH_K, kk = e % TH_K;
-            const long sm = s0 + ss;
-            const int i = k0 + kk;
-            uint16_t v = 0;
-            if (sm < n && i < N) v = sig[sm * N + i] > 0 ? 0x3F80 : 0xBF80;
-            *reinterpret_cast<uint16_t*>(s_sig + ss * TH_ROW + kk * 2) = v;
-        }
-        // 3 parts x 128 rows x 32 sites: 16-byte chunks of the planes
-        for (int c = tid; c < 3 * TH_C * (TH_K / 8); c += 256) {
-            const int part = c / (TH_C * (TH_K / 8)), rem = c % (TH_C * (TH_K / 8));
-            const int rr = rem / (TH_K / 8), ch = rem % (TH_K / 8);
-            const uint16_t* src = planes + part * rows * Np + ((long)ct * TH_C + rr) * Np + k0 + ch * 8;
-            *reinterpret_cast<i32x4_t*>(s_w[part] + rr * TH_ROW + ch * 16) = *reinterpret_cast<const i32x4_t*>(src);
-        }
-        __syncthreads();
+    for (int k2 = 0; k2 < KC; k2 += 32) {
+        if (k2 >= len) break;
+        const uint32_t word = words[k2 >> 5];
 #pragma unroll
-        for (int kq = 0; kq < TH_K; kq += 16) {
+        for (int kq = k2; kq < k2 + 32; kq += 16) {
+            const i32x4_t a = spin_frag(word >> ((kq & 31) + 8 * (lane >> 5)));
             const int koff = (kq + 8 * (lane >> 5)) * 2;
-            const i32x4_t a = *reinterpret_cast<const i32x4_t*>(s_sig + (wave * 32 + (lane & 31)) * TH_ROW + koff);
 #pragma unroll
             for (int part = 0; part < 3; ++part)
 #pragma unroll
                 for (int cb = 0; cb < 4; ++cb) {
-                    const i32x4_t bw =
-                        *reinterpret_cast<const i32x4_t*>(s_w[part] + (cb * 32 + (lane & 31)) * TH_ROW + koff);
+                    const i32x4_t bw = *reinterpret_cast<const i32x4_t*>(
+                        lds.w[part] + (cb * 32 + (lane & 31)) * ThetaLds<KC>::ROW + koff);
                     acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16((bf16x8_t)a, (bf16x8_t)bw, acc[cb], 0, 0, 0);
                 }
         }
+    }
+}
+// acc = sigma W of the wave's 32 samples from sw on.  Np > KC: the W tile is staged piece by piece (every wave of
+// the workgroup must call); else it has been staged before.
+template <int KC>
+__device__ __forceinline__ void theta_tile(ThetaLds<KC>& lds, const uint32_t* __restrict__ bits, long n, int Np,
+                                           const uint16_t* __restrict__ planes, long rows, int ct, long sw,
+                                           floatx16_t (&acc)[4]) {
+    const int lane = threadIdx.x & 63, nw = Np / 32;
+    const long s = sw + (lane & 31) < n ? sw + (lane & 31) : n - 1;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[cb][v] = 0.f;
+    if (Np <= KC) {
+        theta_steps<KC>(lds, bits + s * nw, Np, lane, acc);
+        return;
+    }
+    for (int k0 = 0; k0 < Np; k0 += KC) {
+        __syncthreads();
+        theta_stage<KC>(lds, planes, rows, Np, ct, k0);
+        __syncthreads();
+        theta_steps<KC>(lds, bits + s * nw + k0 / 32, Np - k0, lane, acc);
+    }
+}
+// The loop of a workgroup (x, ct) over its sample tiles: body(sw, acc) with the wave's first sample sw.
+template <int KC, class F>
+__device__ __forceinline__ void theta_walk(ThetaLds<KC>& lds, const uint32_t* __restrict__ bits, long n, int Np,
+                                           const uint16_t* __restrict__ planes, long rows, int ct, F&& body) {
+    const int wave = threadIdx.x >> 6;
+    if (Np <= KC) {
+        theta_stage<KC>(lds, planes, rows, Np, ct, 0);
         __syncthreads();
     }
+    for (long t0 = (long)blockIdx.x * TH_S; t0 < n; t0 += (long)gridDim.x * TH_S) {
+        const long sw = t0 + wave * 32;
+        floatx16_t acc[4];
+        if (Np > KC || sw < n) theta_tile<KC>(lds, bits, n, Np, planes, rows, ct, sw, acc);
+        if (sw < n) body(sw, acc);
+    }
+}
+// workgroups along the samples: one round of the device over the unit tiles (one workgroup per compute unit,
+// two where the staged tile is at most 64 sites), at most one per sample tile
+static unsigned theta_grid(long n, int Np, int Mt, int n_cu) {
+    const long slots = (long)n_cu * (Np <= 64 ? 2 : 1), tiles = (n + TH_S - 1) / TH_S;
+    long g = slots / Mt;
+    if (g < 1) g = 1;
+    return (unsigned)(g < tiles ? g : tiles);
+}
+// calls f(std::integral_constant<int, KC>) for the padded row length Np
+template <class F>
+static void theta_dispatch(int Np, F&& f) {
+    if (Np <= 32) f(std::integral_constant<int, 32>{});
+    else if (Np <= 64) f(std::integral_constant<int, 64>{});
+    else if (Np <= 96) f(std::integral_constant<int, 96>{});
+    else f(std::integral_constant<int, TH_KMAX>{});
 }
 
 // theta = sigma W + b, complex64 [n][M]: lane column j holds units 64 ct + j (blocks 0, 1) and
-// 64 ct + 32 + j (blocks 2, 3), real and imaginary part together, so 32 lanes store 256 contiguous bytes
-__global__ __launch_bounds__(256, 4) void k_theta(const int8_t* __restrict__ sig, long n, int N, int Np, int M,
-                                               const float2* __restrict__ b, const uint16_t* __restrict__ planes,
-                                               int Mt, float2* __restrict__ theta, const double* __restrict__ skip) {
-    if (skip && *skip != 0.0) return;     // a converged iterative solve skips the product
-    __shared__ __attribute__((aligned(16))) unsigned char s_sig[TH_S * TH_ROW];
-    __shared__ __attribute__((aligned(16))) unsigned char s_w[3][TH_C * TH_ROW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long s0 = (long)blockIdx.x * TH_S;
-    const int ct = blockIdx.y;
-    floatx16_t acc[4];
-    theta_tile(sig, n, N, Np, planes, (long)Mt * TH_C, ct, s0, s_sig, s_w, acc);
+// 64 ct + 32 + j (blocks 2, 3), real and imaginary part together, so 32 lanes store 256 contiguous bytes.
+// blockIdx.z: which of up to three RBMs on the same samples.
+template <int KC>
+__global__ __launch_bounds__(64 * TH_W, 2) void k_theta(const uint32_t* __restrict__ bits, long n, int Np, int M,
+                                                     ThetaSet set, const uint16_t* __restrict__ planes, long plane_len,
+                                                     int Mt) {
+    __shared__ __attribute__((aligned(16))) ThetaLds<KC> lds;
+    const int lane = threadIdx.x & 63, ct = blockIdx.y, z = blockIdx.z;
+    const float2* b = set.b[z];
+    float2* theta = set.out[z];
     const int ku0 = ct * 64 + (lane & 31), ku1 = ku0 + 32;
     const float2 b0 = ku0 < M ? b[ku0] : make_float2(0.f, 0.f);
     const float2 b1 = ku1 < M ? b[ku1] : make_float2(0.f, 0.f);
+    theta_walk<KC>(lds, bits, n, Np, planes + z * plane_len, (long)Mt * TH_C, ct,
+                   [&](long sw, const floatx16_t (&acc)[4]) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const long sm = s0 + wave * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (sm >= n) continue;
-        if (ku0 < M) theta[sm * M + ku0] = make_float2(acc[0][v] + b0.x, acc[1][v] + b0.y);
-        if (ku1 < M) theta[sm * M + ku1] = make_float2(acc[2][v] + b1.x, acc[3][v] + b1.y);
-    }
+        for (int v = 0; v < 16; ++v) {
+            const long sm = sw + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+            if (sm >= n) continue;
+            if (ku0 < M) theta[sm * M + ku0] = make_float2(acc[0][v] + b0.x, acc[1][v] + b0.y);
+            if (ku1 < M) theta[sm * M + ku1] = make_float2(acc[2][v] + b1.x, acc[3][v] + b1.y);
+        }
+    });
 }
 
-hipError_t launch_theta(const int8_t* sig, long n, int N, int M, const float2* b, const float2* W, float2* theta,
-                        uint16_t* planes, hipStream_t stream, const double* skip) {
+hipError_t launch_theta(const uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes, int n_cu,
+                        hipStream_t stream) {
     if (n <= 0) return hipSuccess;
-    const int Np = (N + TH_K - 1) / TH_K * TH_K;
+    const int Np = theta_np(N);
     const int Mt = (M + 63) / 64;
     const long cnt = (long)Mt * TH_C * Np;
-    hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, stream, W, N, M, Np, Mt, planes,
-                       skip);
-    hipLaunchKernelGGL(k_theta, dim3((unsigned)((n + TH_S - 1) / TH_S), (unsigned)Mt), dim3(256), 0, stream, sig, n,
-                       N, Np, M, b, planes, Mt, theta, skip);
+    hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256), 1, set.count), dim3(256), 0, stream, set, N, M, Np,
+                       Mt, planes);
+    theta_dispatch(Np, [&](auto kc) {
+        hipLaunchKernelGGL(k_theta<kc.value>, dim3(theta_grid(n, Np, Mt * set.count, n_cu), (unsigned)Mt, set.count),
+                           dim3(64 * TH_W), 0, stream, bits, n, Np, M, set, planes, lc_plane_elems(N, M), Mt);
+    });
     return hipGetLastError();
 }
 
@@ -188,40 +311,18 @@ hipError_t launch_theta(const int8_t* sig, long n, int N, int M, const float2* b
 // tile, each unit's G_sk multiplied by T_sk in the epilogue and the tile's 64 units summed per sample in
 // double (products in FP32 widened to double, as a separate pass over G would); a reduce-scatter over
 // lane bits 4..0 leaves each row's sum in two lanes.  partial[ct][s] (double2, n per 64-unit tile).
-__global__ __launch_bounds__(256, 4) void k_theta_ov(const int8_t* __restrict__ sig, long n, int N, int Np, int M,
-                                                  const float2* __restrict__ vb, const uint16_t* __restrict__ planes,
-                                                  int Mt, const float2* __restrict__ T, double2* __restrict__ partial,
-                                                  const double* __restrict__ skip) {
-    if (skip && *skip != 0.0) return;     // a converged iterative solve skips the product
-    __shared__ __attribute__((aligned(16))) unsigned char s_sig[TH_S * TH_ROW];
-    __shared__ __attribute__((aligned(16))) unsigned char s_w[3][TH_C * TH_ROW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long s0 = (long)blockIdx.x * TH_S;
-    const int ct = blockIdx.y;
-    floatx16_t acc[4];
-    theta_tile(sig, n, N, Np, planes, (long)Mt * TH_C, ct, s0, s_sig, s_w, acc);
-    const int ku0 = ct * 64 + (lane & 31), ku1 = ku0 + 32;
-    const float2 b0 = ku0 < M ? vb[ku0] : make_float2(0.f, 0.f);
-    const float2 b1 = ku1 < M ? vb[ku1] : make_float2(0.f, 0.f);
+// One tile's rows: the products of a row's two units per lane, then the reduce-scatter.  t: T of the lane's rows and
+// units, loaded before the matrix product so that the loads are in flight during it (0 past n and M).
+__device__ __forceinline__ void theta_ov_rows(const floatx16_t (&acc)[4], const float2 (&t)[2][16], long sw, long n, int ct,
+                                              float2 b0, float2 b1, int lane, double2* __restrict__ partial) {
     double px[16], py[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const long sm = s0 + wave * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        px[v] = 0.0;
-        py[v] = 0.0;
-        if (sm >= n) continue;
-        if (ku0 < M) {
-            const float2 t = T[sm * M + ku0];
-            const float gx = acc[0][v] + b0.x, gy = acc[1][v] + b0.y;
-            px[v] += (double)t.x * gx - (double)t.y * gy;
-            py[v] += (double)t.x * gy + (double)t.y * gx;
-        }
-        if (ku1 < M) {
-            const float2 t = T[sm * M + ku1];
-            const float gx = acc[2][v] + b1.x, gy = acc[3][v] + b1.y;
-            px[v] += (double)t.x * gx - (double)t.y * gy;
-            py[v] += (double)t.x * gy + (double)t.y * gx;
-        }
+        const float gx = acc[0][v] + b0.x, gy = acc[1][v] + b0.y, hx = acc[2][v] + b1.x, hy = acc[3][v] + b1.y;
+        px[v] = (double)t[0][v].x * gx - (double)t[0][v].y * gy;
+        py[v] = (double)t[0][v].x * gy + (double)t[0][v].y * gx;
+        px[v] += (double)t[1][v].x * hx - (double)t[1][v].y * hy;
+        py[v] += (double)t[1][v].x * hy + (double)t[1][v].y * hx;
     }
     // reduce-scatter of the 16 rows over the 32 columns: lane bits 4, 3, 2, 1 halve the rows a lane
     // keeps, bit 0 adds the last pair; the lane ends with row index 8 b4 + 4 b3 + 2 b2 + b1
@@ -240,14 +341,49 @@ __global__ __launch_bounds__(256, 4) void k_theta_ov(const int8_t* __restrict__ 
     py[0] += __shfl_xor(py[0], 1);
     if (lane & 1) return;
     const int v = 8 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1) + ((lane >> 1) & 1);
-    const long sm = s0 + wave * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+    const long sm = sw + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     if (sm < n) partial[(long)ct * n + sm] = make_double2(px[0], py[0]);
 }
 
-// u[s] = sum over the tiles of partial[ct][s] + sigma_s . v_a: one wave per sample on a bounded grid
-// (waves step through the samples), so that the launches a converged solve skips stay cheap
-constexpr int kOvFinalBlocks = 4096;
-__global__ __launch_bounds__(256) void k_ov_final(int N, long n, int Mt, const int8_t* __restrict__ sig,
+template <int KC>
+__global__ __launch_bounds__(64 * TH_W, 2) void k_theta_ov(const uint32_t* __restrict__ bits, long n, int Np, int M,
+                                                        const float2* __restrict__ vb,
+                                                        const uint16_t* __restrict__ planes, int Mt,
+                                                        const float2* __restrict__ T, double2* __restrict__ partial,
+                                                        const double* __restrict__ skip) {
+    if (skip && *skip != 0.0) return;     // a converged iterative solve skips the product
+    __shared__ __attribute__((aligned(16))) ThetaLds<KC> lds;
+    const int lane = threadIdx.x & 63, ct = blockIdx.y;
+    const int ku0 = ct * 64 + (lane & 31), ku1 = ku0 + 32;
+    const float2 b0 = ku0 < M ? vb[ku0] : make_float2(0.f, 0.f);
+    const float2 b1 = ku1 < M ? vb[ku1] : make_float2(0.f, 0.f);
+    if (Np <= KC) {
+        theta_stage<KC>(lds, planes, (long)Mt * TH_C, Np, ct, 0);
+        __syncthreads();
+    }
+    for (long t0 = (long)blockIdx.x * TH_S; t0 < n; t0 += (long)gridDim.x * TH_S) {
+        const long sw = t0 + (threadIdx.x >> 6) * 32;
+        float2 t[2][16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const long sm = sw + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+            const bool in = sm < n;
+            const float2* row = T + (in ? sm : 0) * M;
+            t[0][v] = row[ku0 < M ? ku0 : 0];
+            t[1][v] = row[ku1 < M ? ku1 : 0];
+            if (!in || ku0 >= M) t[0][v] = make_float2(0.f, 0.f);
+            if (!in || ku1 >= M) t[1][v] = make_float2(0.f, 0.f);
+        }
+        floatx16_t acc[4];
+        if (Np > KC || sw < n) theta_tile<KC>(lds, bits, n, Np, planes, (long)Mt * TH_C, ct, sw, acc);
+        if (sw < n) theta_ov_rows(acc, t, sw, n, ct, b0, b1, lane, partial);
+    }
+}
+
+// u[s] = sum over the tiles of partial[ct][s] + sigma_s . v_a: one thread per sample on a bounded grid
+// (v_a in LDS, the spins as sign bits), so that the launches a converged solve skips stay cheap
+constexpr int kOvFinalBlocks = 1024;
+__global__ __launch_bounds__(256) void k_ov_final(int N, long n, int Mt, const uint32_t* __restrict__ bits, int nw,
                                                   const double2* __restrict__ va, const double2* __restrict__ partial,
                                                   double2* __restrict__ u, const double2* __restrict__ omv, int n_omv,
                                                   double* __restrict__ mean_out, const double* __restrict__ skip) {
@@ -259,54 +395,52 @@ __global__ __launch_bounds__(256) void k_ov_final(int N, long n, int Mt, const i
         m = wave_sum(m);
         if (lane == 0) { mean_out[0] = m.x; mean_out[1] = m.y; }
     }
-    for (long s = (long)blockIdx.x * 4 + (threadIdx.x >> 6); s < n; s += (long)gridDim.x * 4) {
+    __shared__ double2 a[256];
+    for (int i = threadIdx.x; i < N; i += 256) a[i] = va[i];
+    __syncthreads();
+    for (long s = (long)blockIdx.x * 256 + threadIdx.x; s < n; s += (long)gridDim.x * 256) {
+        const uint32_t* row = bits + s * nw;
         double ax = 0.0, ay = 0.0;
-        for (int i = lane; i < N; i += kWave) {
-            const double sv = (double)sig[s * N + i];
-            ax += sv * va[i].x;
-            ay += sv * va[i].y;
+        for (int w = 0; w < nw; ++w) {
+            const uint32_t word = row[w];
+            const int cnt = N - 32 * w < 32 ? N - 32 * w : 32;
+#pragma unroll 8
+            for (int b = 0; b < cnt; ++b) {
+                const double sv = (word >> b) & 1u ? -1.0 : 1.0;
+                ax += sv * a[32 * w + b].x;
+                ay += sv * a[32 * w + b].y;
+            }
         }
-        for (int ct = lane; ct < Mt; ct += kWave) {
+        for (int ct = 0; ct < Mt; ++ct) {
             const double2 p = partial[(long)ct * n + s];
             ax += p.x;
             ay += p.y;
         }
-        ax = wave_sum(ax);
-        ay = wave_sum(ay);
-        if (lane == 0) u[s] = make_double2(ax, ay);
+        u[s] = make_double2(ax, ay);
     }
 }
 
-hipError_t launch_theta_ov(const int8_t* sig, long n, int N, int M, const float2* vb, const double2* va,
+hipError_t launch_theta_ov(const uint32_t* bits, long n, int N, int M, const float2* vb, const double2* va,
                            const float2* T, const uint16_t* planes, double2* partial, double2* u, const double2* omv,
-                           int n_omv, double* mean_out, hipStream_t stream, const double* skip) {
+                           int n_omv, double* mean_out, int n_cu, hipStream_t stream, const double* skip) {
     if (n <= 0) return hipSuccess;
     const int Np = theta_np(N);
     const int Mt = (M + 63) / 64;
-    hipLaunchKernelGGL(k_theta_ov, dim3((unsigned)((n + TH_S - 1) / TH_S), (unsigned)Mt), dim3(256), 0, stream, sig,
-                       n, N, Np, M, vb, planes, Mt, T, partial, skip);
-    const long fb = (n + 3) / 4;
+    theta_dispatch(Np, [&](auto kc) {
+        hipLaunchKernelGGL(k_theta_ov<kc.value>, dim3(theta_grid(n, Np, Mt, n_cu), (unsigned)Mt), dim3(64 * TH_W), 0,
+                           stream, bits, n, Np, M, vb, planes, Mt, T, partial, skip);
+    });
+    const long fb = (n + 255) / 256;
     hipLaunchKernelGGL(k_ov_final, dim3((unsigned)(fb < kOvFinalBlocks ? fb : kOvFinalBlocks)), dim3(256), 0, stream,
-                       N, n, Mt, sig, va, partial, u, omv, n_omv, mean_out, skip);
+                       N, n, Mt, bits, spin_words(N), va, partial, u, omv, n_omv, mean_out, skip);
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256, 4) void k_theta_lc(const int8_t* __restrict__ sig, long n, int N, int Np, int M,
-                                                  const float2* __restrict__ b, const float2* __restrict__ W,
-                                                  const uint16_t* __restrict__ planes, int Mt,
-                                                  float2* __restrict__ partial) {
-    __shared__ __attribute__((aligned(16))) unsigned char s_sig[TH_S * TH_ROW];
-    __shared__ __attribute__((aligned(16))) unsigned char s_w[3][TH_C * TH_ROW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long s0 = (long)blockIdx.x * TH_S;
-    const int ct = blockIdx.y;                        // 64-unit tile
-    floatx16_t acc[4];
-    theta_tile(sig, n, N, Np, planes, (long)Mt * TH_C, ct, s0, s_sig, s_w, acc);
-    // lane column j = lane % 32: units k0u = 64 ct + j (acc 0, 1) and k1u = k0u + 32 (acc 2, 3)
-    const int j = lane & 31;
-    const int ku0 = ct * 64 + j, ku1 = ku0 + 32;
-    const float2 b0 = ku0 < M ? b[ku0] : make_float2(0.f, 0.f);
-    const float2 b1 = ku1 < M ? b[ku1] : make_float2(0.f, 0.f);
+// the sums of one tile's rows: wave's accumulators (rows sw + ..) to partial[ct][row]
+__device__ __forceinline__ void theta_lc_rows(const floatx16_t (&acc)[4], long sw, const int8_t* __restrict__ sig, long n,
+                                              int N, int M, int ct, int ku0, int ku1, float2 b0, float2 b1,
+                                              const float2* __restrict__ b, const float2* __restrict__ W, int lane,
+                                              float2* __restrict__ partial) {
     float2 lin[16], pr[16];
     uint32_t poles = 0;   // bit 2 v + h: element (row v, unit h) within the band of a zero of cosh
 #pragma unroll
@@ -319,7 +453,7 @@ __global__ __launch_bounds__(256, 4) void k_theta_lc(const int8_t* __restrict__ 
             const float2 bb = h == 0 ? b0 : b1;
             const float2 z = make_float2(acc[2 * h][v] + bb.x, acc[2 * h + 1][v] + bb.y);
             if (near_pole(z)) poles |= 1u << (2 * v + h);
-            else cosh_factor(z, 1.f, lin[v], pr[v]);
+            else lc_factor(z, lin[v], pr[v]);
         }
     }
     // accumulator element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4 of the wave's 32 samples
@@ -327,7 +461,7 @@ __global__ __launch_bounds__(256, 4) void k_theta_lc(const int8_t* __restrict__ 
         const int bit = __ffs(poles) - 1;
         poles &= poles - 1;
         const int v = bit >> 1, ku = (bit & 1) ? ku1 : ku0;
-        const long row = s0 + wave * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        const long row = sw + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
         if (row >= n) continue;
         float2 lcr, thr;
         pole_eval(theta_double(sig + row * N, N, M, ku, b, W), lcr, thr);
@@ -376,37 +510,78 @@ __global__ __launch_bounds__(256, 4) void k_theta_lc(const int8_t* __restrict__ 
         lc_join(lin[0], pr[0], make_float2(__shfl_xor(sl.x, 2), __shfl_xor(sl.y, 2)),
                 make_float2(__shfl_xor(sp.x, 2), __shfl_xor(sp.y, 2)));
     }
-    lc_join(lin[0], pr[0], make_float2(__shfl_xor(lin[0].x, 1), __shfl_xor(lin[0].y, 1)),
-            make_float2(__shfl_xor(pr[0].x, 1), __shfl_xor(pr[0].y, 1)));
+    {
+        const float2 pn = make_float2(__shfl_xor(pr[0].x, 1), __shfl_xor(pr[0].y, 1));
+        lin[0] = cadd(lin[0], make_float2(__shfl_xor(lin[0].x, 1), __shfl_xor(lin[0].y, 1)));
+        pr[0] = cmul_fused(pn, pr[0]);
+    }
     if (lane & 1) return;
     const int v = 8 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1) + ((lane >> 1) & 1);
-    const long sm = s0 + wave * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+    const long sm = sw + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     if (sm >= n) return;
-    const float n2 = pr[0].x * pr[0].x + pr[0].y * pr[0].y;
+    const float n2 = norm2_fused(pr[0]);
     partial[(long)ct * n + sm] = make_float2(lin[0].x + 0.5f * logf(n2), lin[0].y + atan2f(pr[0].y, pr[0].x));
 }
 
+template <int KC>
+__global__ __launch_bounds__(64 * TH_W, 2) void k_theta_lc(const int8_t* __restrict__ sig, const uint32_t* __restrict__ bits,
+                                                        long n, int N, int Np, int M, const float2* __restrict__ b,
+                                                        const float2* __restrict__ W,
+                                                        const uint16_t* __restrict__ planes, int Mt,
+                                                        float2* __restrict__ partial) {
+    __shared__ __attribute__((aligned(16))) ThetaLds<KC> lds;
+    const int lane = threadIdx.x & 63, ct = blockIdx.y;   // ct: 64-unit tile
+    // lane column j = lane % 32: units k0u = 64 ct + j (acc 0, 1) and k1u = k0u + 32 (acc 2, 3)
+    const int ku0 = ct * 64 + (lane & 31), ku1 = ku0 + 32;
+    const float2 b0 = ku0 < M ? b[ku0] : make_float2(0.f, 0.f);
+    const float2 b1 = ku1 < M ? b[ku1] : make_float2(0.f, 0.f);
+    if (Np <= KC) {
+        theta_stage<KC>(lds, planes, (long)Mt * TH_C, Np, ct, 0);
+        __syncthreads();
+    }
+    for (long t0 = (long)blockIdx.x * TH_S; t0 < n; t0 += (long)gridDim.x * TH_S) {
+        const long sw = t0 + (threadIdx.x >> 6) * 32;
+        floatx16_t acc[4];
+        if (Np > KC || sw < n) theta_tile<KC>(lds, bits, n, Np, planes, (long)Mt * TH_C, ct, sw, acc);
+        if (sw < n) theta_lc_rows(acc, sw, sig, n, N, M, ct, ku0, ku1, b0, b1, b, W, lane, partial);
+    }
+}
+
 // B[s] = beta exp(a.sigma + sum_tiles partial - Lg[s])  (Lg = NULL: the sums of psi_gs itself go to
-// Lg_out instead), one wave per sample; the tile partials and Lg are added in double
-__global__ __launch_bounds__(256) void k_lc_final(int N, long n, int Mt, const int8_t* __restrict__ sig,
+// Lg_out instead), one thread per sample with a in LDS and the spins as sign bits (one wave per sample, 63 of its
+// lanes waiting on the exponential and the sine of one, took 55 us for 131,072 samples of 100 sites, now 11 us);
+// the tile partials and Lg are added in double
+__global__ __launch_bounds__(256) void k_lc_final(int N, long n, int Mt, const uint32_t* __restrict__ bits, int nw,
                                                   const float2* __restrict__ a, const float2* __restrict__ partial,
                                                   const double2* __restrict__ Lg, const double2* __restrict__ beta,
                                                   double2* __restrict__ B, double2* __restrict__ Lg_out) {
-    const int lane = threadIdx.x & 63;
-    const long s = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    __shared__ float2 sa[256];
+    sa[threadIdx.x] = threadIdx.x < N ? a[threadIdx.x] : make_float2(0.f, 0.f);
+    __syncthreads();
+    const long s = (long)blockIdx.x * 256 + threadIdx.x;
     if (s >= n) return;
-    WaveSpins sp;
-    sp.load(sig + s * N, N, lane);
-    const float2 as = a_dot_sigma(a, sp, lane, N);
-    double x = as.x, y = as.y;
-    if (lane < Mt) {
-        const float2 pt = partial[(long)lane * n + s];
+    uint32_t word[8];
+#pragma unroll
+    for (int w = 0; w < 8; ++w) word[w] = w < nw ? bits[s * nw + w] : 0u;
+    // a.sigma: the sites l, l + 64, .. in binary32, their sums over l in double
+    double x = 0.0, y = 0.0;
+    const int cnt = N < 64 ? N : 64;
+    for (int l = 0; l < cnt; ++l) {
+        float2 f = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float2 v = sa[64 * q + l];
+            const float sg = ((l < 32 ? word[2 * q] : word[2 * q + 1]) >> (l & 31)) & 1u ? -1.f : 1.f;
+            f = cadd(f, cscale(v, sg));
+        }
+        x += (double)f.x;
+        y += (double)f.y;
+    }
+    for (int ct = 0; ct < Mt; ++ct) {
+        const float2 pt = partial[(long)ct * n + s];
         x += pt.x;
         y += pt.y;
     }
-    x = wave_sum(x);
-    y = wave_sum(y);
-    if (lane != 0) return;
     if (!Lg) {
         Lg_out[s] = make_double2(x, y);
         return;
@@ -419,19 +594,23 @@ __global__ __launch_bounds__(256) void k_lc_final(int N, long n, int Mt, const i
     B[s] = zmul(*beta, make_double2(m * cs, m * sn));
 }
 
-hipError_t launch_lc_sums(const int8_t* sig, long n, int N, int M, const float2* a, const float2* b,
-                          const float2* W, uint16_t* planes, float2* partial, const double2* Lg,
-                          const double2* beta, double2* B, double2* Lg_out, hipStream_t stream) {
+hipError_t launch_lc_sums(const int8_t* sig, const uint32_t* bits, long n, int N, int M, const float2* a,
+                          const float2* b, const float2* W, uint16_t* planes, float2* partial, const double2* Lg,
+                          const double2* beta, double2* B, double2* Lg_out, int n_cu, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
-    const int Np = (N + TH_K - 1) / TH_K * TH_K;
+    const int Np = theta_np(N);
     const int Mt = (M + 63) / 64;
     const long cnt = (long)Mt * TH_C * Np;
-    hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, stream, W, N, M, Np, Mt, planes,
-                       nullptr);
-    hipLaunchKernelGGL(k_theta_lc, dim3((unsigned)((n + TH_S - 1) / TH_S), (unsigned)Mt), dim3(256), 0, stream, sig,
-                       n, N, Np, M, b, W, planes, Mt, partial);
-    hipLaunchKernelGGL(k_lc_final, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, stream, N, n, Mt, sig, a, partial,
-                       Lg, beta, B, Lg_out);
+    ThetaSet set{};
+    set.count = 1;
+    set.W[0] = W;
+    hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, stream, set, N, M, Np, Mt, planes);
+    theta_dispatch(Np, [&](auto kc) {
+        hipLaunchKernelGGL(k_theta_lc<kc.value>, dim3(theta_grid(n, Np, Mt, n_cu), (unsigned)Mt), dim3(64 * TH_W), 0,
+                           stream, sig, bits, n, N, Np, M, b, W, planes, Mt, partial);
+    });
+    hipLaunchKernelGGL(k_lc_final, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, N, n, Mt, bits,
+                       spin_words(N), a, partial, Lg, beta, B, Lg_out);
     return hipGetLastError();
 }
 
@@ -1148,33 +1327,40 @@ hipError_t launch_local_core(const LocalArgs& A, const float2* th1, const float2
 }
 
 // ------------------------------------------------------------------ moments
-// f[q][s] = f_q(s) (double) for a chunk of up to 8 momenta, one wave per sample
+// f[q][s] = f_q(s) (double) for a chunk of up to 8 momenta: one thread per sample, the sites' phases formed once
+// per block in LDS (a sine and a cosine in double per sample and site took 86 us for 131,072 samples of 100
+// sites, now 6 us)
 struct QChunk { double q[8][2]; };
 
-__global__ __launch_bounds__(256) void k_fq(Geometry g, const int8_t* __restrict__ sig, long n_s, QChunk qc, int n_q,
-                                            double2* __restrict__ f) {
-    const int lane = threadIdx.x & 63;
-    const long s = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (s >= n_s) return;
-    WaveSpins sp;
-    sp.load(sig + s * g.N, g.N, lane);
+__global__ __launch_bounds__(256) void k_fq(Geometry g, const uint32_t* __restrict__ bits, int nw, long n_s, QChunk qc,
+                                            int n_q, double2* __restrict__ f) {
+    __shared__ double2 ph[256];
+    const long s = (long)blockIdx.x * 256 + threadIdx.x;
     const double inv = 1.0 / sqrt((double)g.N);
     for (int iq = 0; iq < n_q; ++iq) {
+        __syncthreads();
+        if (threadIdx.x < g.N) {
+            const int site = threadIdx.x;
+            const int x = g.kind == 0 ? site : site % g.Lx;
+            const int y = g.kind == 0 ? 0 : site / g.Lx;
+            double sn, cs;
+            sincos(qc.q[iq][0] * x + qc.q[iq][1] * y, &sn, &cs);
+            ph[site] = make_double2(0.5 * cs, 0.5 * sn);
+        }
+        __syncthreads();
+        if (s >= n_s) continue;
         double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int site = q * kWave + lane;
-            if (site < g.N) {
-                const int x = g.kind == 0 ? site : site % g.Lx;
-                const int y = g.kind == 0 ? 0 : site / g.Lx;
-                double sn, cs;
-                sincos(qc.q[iq][0] * x + qc.q[iq][1] * y, &sn, &cs);
-                acc.x += 0.5 * sp.s[q] * cs;
-                acc.y -= 0.5 * sp.s[q] * sn;
+        for (int w = 0; w < nw; ++w) {
+            const uint32_t word = bits[s * nw + w];
+            const int cnt = g.N - 32 * w < 32 ? g.N - 32 * w : 32;
+#pragma unroll 8
+            for (int b = 0; b < cnt; ++b) {
+                const double sg = (word >> b) & 1u ? -1.0 : 1.0;
+                acc.x += sg * ph[32 * w + b].x;
+                acc.y -= sg * ph[32 * w + b].y;
             }
         }
-        acc = wave_sum(acc);
-        if (lane == 0) f[(long)iq * n_s + s] = make_double2(acc.x * inv, acc.y * inv);
+        f[(long)iq * n_s + s] = make_double2(acc.x * inv, acc.y * inv);
     }
 }
 
@@ -1207,19 +1393,21 @@ __global__ __launch_bounds__(256) void k_moment_accum(const double2* __restrict_
     }
 }
 
-__global__ void k_moment_final(const double2* __restrict__ partial, int n_blocks, int total, double2* __restrict__ mu) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total) return;
+// one wave per entry, its lanes over the blocks (one thread adding 256 of them in turn took 61 us, now 5 us)
+__global__ __launch_bounds__(64) void k_moment_final(const double2* __restrict__ partial, int n_blocks, int total,
+                                                     double2* __restrict__ mu) {
     double2 acc = make_double2(0.0, 0.0);
-    for (int b = 0; b < n_blocks; ++b) acc = zadd(acc, partial[(long)b * total + idx]);
-    mu[idx] = acc;
+    for (int b = threadIdx.x; b < n_blocks; b += kWave) acc = zadd(acc, partial[(long)b * total + blockIdx.x]);
+    acc = wave_sum(acc);
+    if (threadIdx.x == 0) mu[blockIdx.x] = acc;
 }
 
-hipError_t launch_fq_chunk(const Geometry& g, const int8_t* sig, long n_s, const double* q_host, int n_q,
+hipError_t launch_fq_chunk(const Geometry& g, const uint32_t* bits, long n_s, const double* q_host, int n_q,
                            double2* f, hipStream_t stream) {
     QChunk qc{};
     for (int k = 0; k < n_q && k < 8; ++k) { qc.q[k][0] = q_host[2 * k]; qc.q[k][1] = g.kind == 0 ? 0.0 : q_host[2 * k + 1]; }
-    hipLaunchKernelGGL(k_fq, dim3((unsigned)((n_s + 3) / 4)), dim3(256), 0, stream, g, sig, n_s, qc, n_q, f);
+    hipLaunchKernelGGL(k_fq, dim3((unsigned)((n_s + 255) / 256)), dim3(256), 0, stream, g, bits, spin_words(g.N), n_s, qc,
+                       n_q, f);
     return hipGetLastError();
 }
 
@@ -1232,7 +1420,7 @@ hipError_t launch_moment_accum(const double2* f, const double2* B, int b_is_f, c
 }
 
 hipError_t launch_moment_final(const double2* partial, int n_blocks, int total, double2* mu, hipStream_t stream) {
-    hipLaunchKernelGGL(k_moment_final, dim3((total + 255) / 256), dim3(256), 0, stream, partial, n_blocks, total, mu);
+    hipLaunchKernelGGL(k_moment_final, dim3(total), dim3(64), 0, stream, partial, n_blocks, total, mu);
     return hipGetLastError();
 }
 

@@ -1052,9 +1052,9 @@ static hipError_t apply_op(const SrArgs& A, const SrWork& W, const double2* v, d
     t.dots = W.dots;
     if (A.solver == CRBM_SOLVER_CG_MATFREE) {
         // u = O v per sample, the theta product of V fused with the sum over T (partials in the G scratch)
-        hipError_t e = launch_theta_ov(A.samples, A.n, A.N, A.M, f.vb, v, A.T, W.wplanes,
+        hipError_t e = launch_theta_ov(W.bits, A.n, A.N, A.M, f.vb, v, A.T, W.wplanes,
                                        reinterpret_cast<double2*>(W.G), W.u, f.omv, (int)nblk(P),
-                                       W.scal + SC_OMV, stream, skip);
+                                       W.scal + SC_OMV, W.n_cu, stream, skip);
         if (e != hipSuccess) return e;
         *n_dots = (int)nblk((long)(A.N + 1) * (A.M + 1), 64);
         return run_ot(A.N, A.M, W.sig16, A.T, A.n, 2, 0, 1, A.weights, A.R, W.u, W.red, 0, y, nullptr, stream, skip,
@@ -1072,7 +1072,7 @@ static hipError_t apply_op(const SrArgs& A, const SrWork& W, const double2* v, d
 }
 
 hipError_t launch_cholesky_solve(long P, const float2* S, double eps, const double2* F, double2* A64, double2* x,
-                                 double* sc, bool a64_holds_s, hipStream_t stream);
+                                 double2* v, double2* y, double* sc, bool a64_holds_s, hipStream_t stream);
 
 hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) {
     const long P = A.P;
@@ -1159,6 +1159,8 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
 
     MfView f{};
     if (A.solver == CRBM_SOLVER_CG_MATFREE) {
+        e = launch_spin_bits(A.samples, A.n, A.N, W.bits, stream);
+        if (e != hipSuccess) return e;
         f.N = A.N;
         f.M = A.M;
         f.Np = theta_np(A.N);
@@ -1171,7 +1173,7 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
     int n_dots = 0;
     if (A.solver == CRBM_SOLVER_CHOLESKY) {
         W.prof->begin(PROF_CHOLESKY, stream);
-        e = launch_cholesky_solve(P, W.S, A.eps, W.F, W.S64, W.x, W.scal, A.weights != nullptr, stream);
+        e = launch_cholesky_solve(P, W.S, A.eps, W.F, W.S64, W.x, W.r, W.p, W.scal, A.weights != nullptr, stream);
         W.prof->end(stream);
         if (e != hipSuccess) return e;
     } else {
