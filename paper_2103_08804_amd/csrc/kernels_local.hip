@@ -618,12 +618,61 @@ hipError_t launch_lc_sums(const int8_t* sig, const uint32_t* bits, long n, int N
 // A wave takes kLocalSpw consecutive samples.  Per sample it evaluates log psi, tanh theta and O
 // (lanes over the hidden units) and marks the anti-aligned bonds; then it walks the bonds once:
 // a bond's table row is read once and serves every sample of the wave in which the bond is
-// anti-aligned.  Each such (sample, bond) pair leaves its per-lane share of the factor product,
-// as (log |p|, p/|p|), in a per-wave LDS ring; every 8 pairs a reduce-scatter over lane bits
-// 5, 4, 3 gives pair g of the batch to the 8 lanes of group g = lane / 8, which finish it (the
-// exponential, the phase of a and the f_q factors) lane-parallel.
+// anti-aligned.  Each such (sample, bond) pair leaves its per-lane share of the factor product in a
+// per-wave LDS buffer; every 13 to 16 pairs the buffer is read back across the lanes, four lanes per pair,
+// each multiplying 16 of its 64 shares, and these lanes finish the pair (the exponential, the phase of a and
+// the f_q factors) with all pairs side by side.
+// Bound by VALU issue.  Against a reduce-scatter of eight pairs at a time over shuffles, with the shares as
+// (log |p|, p / |p|), the read-back takes a third of the instructions per pair, and a share is scaled by its
+// binary exponent (no logarithm); the masks that steer the walk and the selection of the bond factors are wave-uniform
+// and sit in scalar registers.  65,536 samples, 10 x 10, M = 400: 3.71 to 2.64 ms; 8,192 samples, 16 x 16, M = 512: 1.28 to 0.89 ms.
 constexpr int kLocalSpw = 4;       // samples per wave
-constexpr int kRing = 16;          // ring slots per wave: at most 7 + kLocalSpw pairs wait
+constexpr int kPairs = 16;         // pair buffer slots per wave
+constexpr int kPairRow = 68;       // share of lane l of a slot: entry 68 slot + l + l / 16 (conflict-free both ways)
+
+struct PairBuf {
+    float2 p[kPairs * kPairRow];           // shares, scaled to max(|re|, |im|) in [1/2, 1)
+    __attribute__((aligned(16))) int8_t ex[kPairs * kWave];   // their binary exponents
+    int item[kPairs];                      // sample << 16 | (first site's spin negative) << 15 | bond
+};
+
+// a wave-uniform 64-bit value in scalar registers
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+    const uint32_t lo = (uint32_t)uniform((int)(uint32_t)v), hi = (uint32_t)uniform((int)(uint32_t)(v >> 32));
+    return (uint64_t)hi << 32 | lo;
+}
+
+// this lane's share p of a pair into slot (all lanes)
+__device__ __forceinline__ void pair_push(PairBuf& b, int slot, int lane, float2 p, int item) {
+    const int e = __builtin_amdgcn_frexp_expf(fmaxf(fabsf(p.x), fabsf(p.y)));
+    b.p[slot * kPairRow + lane + (lane >> 4)] = make_float2(ldexpf(p.x, -e), ldexpf(p.y, -e));
+    b.ex[slot * kWave + lane] = (int8_t)max(min(e, 127), -128);
+    if (lane == 0) b.item[slot] = item;
+}
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_int(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
+}
+// product of the 64 shares of slot lane / 4, in its four lanes, as mantissa and binary exponent
+__device__ __forceinline__ float2 pair_total(const PairBuf& b, int lane, int& ex) {
+    const int g = lane >> 2, r = lane & 3;
+    const float2* row = b.p + g * kPairRow + 17 * r;
+    float2 m = row[0];
+#pragma unroll
+    for (int t = 1; t < 16; ++t) m = cmul(m, row[t]);
+    const int4 e4 = *reinterpret_cast<const int4*>(b.ex + g * kWave + 16 * r);
+    const int w[4] = {e4.x, e4.y, e4.z, e4.w};
+    ex = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        ex += (int)(int8_t)w[k] + (int)(int8_t)(w[k] >> 8) + (int)(int8_t)(w[k] >> 16) + (w[k] >> 24);
+    m = cmul(m, make_float2(dpp_move<0xB1, 0xF>(m.x), dpp_move<0xB1, 0xF>(m.y)));
+    ex += dpp_int<0xB1>(ex);
+    m = cmul(m, make_float2(dpp_move<0x4E, 0xF>(m.x), dpp_move<0x4E, 0xF>(m.y)));
+    ex += dpp_int<0x4E>(ex);
+    return m;
+}
 
 // Reduce-scatter of 8 bond shares (log |p|, p/|p|) over the wave: across lane bit 5 keep 4 of the 8,
 // bit 4 keep 2, bit 3 keep 1, then add (multiply) within the 8 lanes, so that lanes 8 g .. 8 g + 7
@@ -677,41 +726,65 @@ __device__ __forceinline__ void share_polar(float2 prod, float n2, float& lm, fl
 // the same for every bond of the sample: qinv = prod 1/(1 + w_k) over this lane's units (each factor in
 // [0.58, 1.72] off the zeros of cosh), multiplied into the lane's share so that its logarithm stays the
 // logarithm of the lane's part of the ratio; units near a zero of cosh enter a per-sample constant
-// instead (bond_term).  neg: bit e set when s_k < 0 for this lane's unit e, flipped for s_i = +1.
+// instead (bond_term).  nm[e]: the lanes whose unit e has s_k < 0; si_neg: the first site's spin is -1.
 template <int E>
-__device__ __forceinline__ float2 bond_share(const float4 (&tq)[E], const float2 (&tw)[E], uint32_t neg,
-                                             float2 qinv) {
+__device__ __forceinline__ float2 bond_share(const float4 (&tq)[E], const float2 (&tw)[E], const uint64_t (&nm)[E],
+                                             bool si_neg, float2 qinv) {
+    const uint64_t flip = si_neg ? ~0ull : 0ull;
     float2 prod = make_float2(1.f, 0.f);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const bool sel = ((neg >> e) & 1u) == 0u;
+        // exp(s_k Delta_k) is exp 2D when s_k = -s_i
+        const bool sel = __builtin_amdgcn_inverse_ballot_w64(nm[e] ^ flip);
         const float2 X = sel ? make_float2(tq[e].x, tq[e].y) : make_float2(tq[e].z, tq[e].w);
         const float2 Y = sel ? make_float2(tq[e].z, tq[e].w) : make_float2(tq[e].x, tq[e].y);
         const float2 num = make_float2(fmaf(tw[e].x, Y.x, fmaf(-tw[e].y, Y.y, X.x)),
                                        fmaf(tw[e].x, Y.y, fmaf(tw[e].y, Y.x, X.y)));
-        prod = cmul(prod, num);
+        prod = e == 0 ? num : cmul(prod, num);
     }
     return cmul(prod, qinv);
 }
-// the sign word of bond_share for a bond whose first site has spin si
-__device__ __forceinline__ uint32_t bond_neg(uint32_t neg, float si) { return si > 0.f ? ~neg : neg; }
 
-// The bond's row of the table for this lane's hidden units (padding lanes give the factor 1).
+// The bond's row of the table for this lane's hidden units (padding lanes give the factor 1): every load is
+// issued, lanes past M re-reading the row's last entry.  E = ceil(M / 64), so only the last group holds such lanes.
 template <int E>
 __device__ __forceinline__ void bond_row(const Geometry& g, int bnd, int lane, float4 (&tq)[E]) {
     const float4* tab = g.bond_tab + (long)bnd * g.M;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int k = e * kWave + lane;
-        tq[e] = (k < g.M) ? tab[k] : make_float4(1.f, 0.f, 1.f, 0.f);
+    for (int e = 0; e < E; ++e) tq[e] = tab[e < E - 1 ? e * kWave + lane : min(e * kWave + lane, g.M - 1)];
+    if ((E - 1) * kWave + lane >= g.M) tq[E - 1] = make_float4(1.f, 0.f, 1.f, 0.f);
+}
+
+// The exchange term of bond (i, j) for the sample with spin s_i = si, given the whole factor product
+// m 2^ex: J/2 d1 psi(s^ij)/psi(s) with psi(s^ij)/psi(s) = m 2^ex exp(da), da = -2 s_i (a_i - a_j) + cq
+// (cq = -sum log(1 + w_k) over the units next to a zero of cosh, whose denominators are kept out of the
+// shares), and d1 the diagonal factor of t_0 after the swap (phases: e^{-iq.r} of the sites).
+__device__ __forceinline__ float2 bond_term(const LocalArgs& A, const RbmView& pe, int i, int j, float si, float2 m, int ex,
+                                            float2 d0, float2 cq, bool with_fq, float inv_sqrt_n, const float2* phases) {
+    const Geometry& g = A.g;
+    const float2 da = cadd(cscale(csub(pe.a[i], pe.a[j]), -2.f * si), cq);
+    float sn, cs;
+    sincosf(da.y, &sn, &cs);
+    float2 rho = cscale(cmul(m, make_float2(cs, sn)), expf(da.x));
+    rho = make_float2(ldexpf(rho.x, ex), ldexpf(rho.y, ex));
+    float2 d1 = make_float2(1.f, 0.f);
+    if (with_fq) {
+        if (A.local_op) {
+            // s_0 / 2 after the swap of sites i and j (s_j = -s_i)
+            d1 = make_float2(i == 0 ? -0.5f * si : (j == 0 ? 0.5f * si : d0.x), 0.f);
+        } else {
+            // f_q(s^{ij}) = f_q(s) - N^{-1/2} s_i (e^{-iq.r_i} - e^{-iq.r_j})
+            d1 = csub(d0, cscale(csub(phases[i], phases[j]), inv_sqrt_n * si));
+        }
     }
+    return cscale(cmul(d1, rho), 0.5f * (float)g.J);
 }
 
 // The exchange term of bond (i, j) for the sample with spin s_i = si, given the whole factor product
 // as (log |p|, phase): J/2 d1 psi(s^ij)/psi(s) with psi(s^ij)/psi(s) = exp(lm + Re da) phase
 // exp(i Im da), da = -2 s_i (a_i - a_j) + cq (cq = -sum log(1 + w_k) over the units next to a zero of
 // cosh, whose denominators are kept out of the shares), and d1 the diagonal factor of t_0 after the swap.
-__device__ __forceinline__ float2 bond_term(const LocalArgs& A, const RbmView& pe, int i, int j, float si, float lm,
+__device__ __forceinline__ float2 bond_term_polar(const LocalArgs& A, const RbmView& pe, int i, int j, float si, float lm,
                                             float2 ph, float2 d0, float2 cq, bool with_fq, float inv_sqrt_n) {
     const Geometry& g = A.g;
     const float2 da = cadd(cscale(csub(pe.a[i], pe.a[j]), -2.f * si), cq);
@@ -733,40 +806,11 @@ __device__ __forceinline__ float2 bond_term(const LocalArgs& A, const RbmView& p
     return cscale(cmul(d1, rho), 0.5f * (float)g.J);
 }
 
-template <int SPW>
-__device__ __forceinline__ void local_flush(const LocalArgs& A, const RbmView& pe, int lane, long s0, int done,
-                                            int cnt, bool with_fq, float inv_sqrt_n, const float2 (&d0)[SPW],
-                                            const float2 (&cq)[SPW], float2 (&acc)[SPW], float (*s_lm)[kWave],
-                                            float2 (*s_ph)[kWave], const int* s_item) {
-    const Geometry& g = A.g;
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float lm[8];
-    float2 ph[8];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const int slot = (done + b) & (kRing - 1);
-        lm[b] = b < cnt ? s_lm[slot][lane] : 0.f;
-        ph[b] = b < cnt ? s_ph[slot][lane] : make_float2(1.f, 0.f);
-    }
-    reduce_scatter8(lm, ph, lane);
-    const int gq = lane >> 3;
-    if (gq >= cnt) return;
-    const int item = s_item[(done + gq) & (kRing - 1)];
-    const int q = item >> 16, bnd = item & 0xFFFF;
-    const int2 ij = g.bonds[bnd];
-    const float si = (float)A.samples[(s0 + q) * g.N + ij.x];
-    float2 d0q = d0[0], cqq = cq[0];
-#pragma unroll
-    for (int qq = 1; qq < SPW; ++qq) {
-        d0q = q == qq ? d0[qq] : d0q;
-        cqq = q == qq ? cq[qq] : cqq;
-    }
-    const float2 c = bond_term(A, pe, ij.x, ij.y, si, lm[0], ph[0], d0q, cqq, with_fq, inv_sqrt_n);
-    if ((lane & 7) == 0)
-#pragma unroll
-        for (int qq = 0; qq < SPW; ++qq)
-            if (q == qq) acc[qq] = cadd(acc[qq], c);
+// the sites' phases e^{-iq.r} into LDS (all threads of the workgroup; needed for t_0 = S^z_q psi only)
+__device__ __forceinline__ void stage_phases(const LocalArgs& A, bool with_fq, float2* phases) {
+    if (with_fq && !A.local_op && threadIdx.x < A.g.N)
+        phases[threadIdx.x] = site_phase(threadIdx.x, A.g.kind, A.g.Lx, A.q0, A.q1);
+    __syncthreads();
 }
 
 // This lane's share of sum_k [log cosh theta_k - log cosh phi_k] over its hidden units, theta and phi
@@ -815,20 +859,19 @@ template <int E>
 __device__ __forceinline__ void local_sample(const LocalArgs& A, const float2* __restrict__ th1g,
                                              const float2* __restrict__ thng, int lane, long s0, int q, int nq,
                                              bool want_local, bool with_fq, int n_words, float2 (&tw)[E],
-                                             uint32_t& neg, float2& qinv, float2& cq, float2& d0, int& n_anti,
-                                             bool& node, uint64_t* mask) {
+                                             uint64_t (&nm)[E], float2& qinv, float2& cq, float2& d0, int& n_anti,
+                                             uint64_t* mask, uint64_t* sneg) {
     const Geometry& g = A.g;
     const int N = g.N, M = g.M;
     d0 = make_float2(1.f, 0.f);
     n_anti = 0;
-    neg = 0u;
+    uint32_t neg = 0u;
     qinv = make_float2(1.f, 0.f);
     cq = make_float2(0.f, 0.f);
-    node = false;
 #pragma unroll
-    for (int e = 0; e < E; ++e) tw[e] = make_float2(0.f, 0.f);
+    for (int e = 0; e < E; ++e) { tw[e] = make_float2(0.f, 0.f); nm[e] = 0ull; }
     if (q >= nq) {
-        if (lane < n_words) mask[lane] = 0ull;
+        if (lane < n_words) mask[lane] = sneg[lane] = 0ull;
         return;
     }
     const long s = s0 + q;
@@ -843,13 +886,14 @@ __device__ __forceinline__ void local_sample(const LocalArgs& A, const float2* _
     }
     // tanh theta of fit, and log psi of fit when asked for; units near a zero of cosh re-evaluated in double
     const int8_t* srow = A.samples + s * N;
+    const bool want_t = A.tanh_out || A.O_out, want_1 = want_t || A.logpsi_out;
     uint32_t poles = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int k = e * kWave + lane;
-        const bool p = k < M && near_pole(t1[e]);
+        const bool p = want_1 && k < M && near_pole(t1[e]);
         poles |= p ? 1u << e : 0u;
-        T1[e] = (k < M && !p) ? ctanhf(t1[e]) : make_float2(0.f, 0.f);
+        T1[e] = (want_t && k < M && !p) ? ctanhf(t1[e]) : make_float2(0.f, 0.f);
         if (A.logpsi_out && k < M && !p) lc1 = cadd(lc1, log2cosh(t1[e]));
     }
     while (poles) {
@@ -917,7 +961,9 @@ __device__ __forceinline__ void local_sample(const LocalArgs& A, const float2* _
             if (near_pole(z)) pw |= 1u << e;
             else q1 = cmul(q1, make_float2(1.f + tw[e].x, tw[e].y));   // |1 + w| in [0.58, 2] off the band
         }
-        node = __ballot(pw != 0u) != 0ull;
+#pragma unroll
+        for (int e = 0; e < E; ++e) nm[e] = __ballot((neg >> e) & 1u);
+        const bool node = __ballot(pw != 0u) != 0ull;
         if (lane == 0) g.node_flag[s] = node ? 1 : 0;
         while (pw) {
             const int e = __ffs(pw) - 1;
@@ -934,16 +980,17 @@ __device__ __forceinline__ void local_sample(const LocalArgs& A, const float2* _
     }
     // diagonal factor of t_0: f_q (momentum q) or, with local_op, the local S^z_0 = s_0 / 2
     if (with_fq) d0 = A.local_op ? make_float2(0.5f * (float)sp.get(0), 0.f) : fq_wave(sp, lane, g, A.q0, A.q1);
-    // anti-aligned bonds of the sample
+    // anti-aligned bonds of the sample, and the spin of their first site
     for (int c = 0; c < n_words; ++c) {
         const int bnd = c * kWave + lane;
-        bool anti = false;
+        bool anti = false, down = false;
         if (bnd < g.n_bonds) {
             const int2 ij = g.bonds[bnd];
             anti = srow[ij.x] != srow[ij.y];
+            down = srow[ij.x] < 0;
         }
-        const uint64_t m = __ballot(anti);
-        if (lane == 0) mask[c] = m;
+        const uint64_t m = __ballot(anti), d = __ballot(down);
+        if (lane == 0) { mask[c] = m; sneg[c] = d; }
         n_anti += __popcll(m);
     }
 }
@@ -951,21 +998,36 @@ __device__ __forceinline__ void local_sample(const LocalArgs& A, const float2* _
 // The exchange part of E_loc, sum over anti-aligned bonds of (J/2) d1 psi(s^ij)/psi(s), in double, for a
 // sample at which psi (the RBM whose Hamiltonian action is taken) is next to a node (a unit next to a zero
 // of cosh): there psi(s) ~ 0 while (H psi)(s) is of the size of E psi(s), so the bond terms are large and
-// cancel, which binary32 factors cannot resolve.  theta, every unit factor cosh(theta + Delta)/cosh theta,
-// a_i - a_j and f_q are taken in double.  Used by k_local_nodes only, so that the main kernels keep their
-// registers and need no stack.
+// cancel, which binary32 factors cannot resolve.  theta, w = exp(-2 s theta) (s = sign Re theta), the unit factors
+// [exp(s Delta) + w exp(-s Delta)] / (1 + w) of bond_share, a_i - a_j and f_q are taken in double, 1 + w through
+// log cosh theta so that it holds next to a zero; the numerators of a lane are multiplied and their logarithm taken
+// once per bond (a logarithm per unit took three times as long).  Every n_parts-th bond from the
+// part-th on.  Used by k_local_nodes only, so that the main kernels keep their registers.
 template <int E>
 __device__ __forceinline__ double2 exchange_double(const LocalArgs& A, const RbmView& pe, long s, int lane,
-                                                const uint64_t* mask, int n_words, bool with_fq) {
+                                                const uint64_t* mask, int n_words, bool with_fq, int part,
+                                                int n_parts) {
     const Geometry& g = A.g;
     const int N = g.N, M = g.M;
     const int8_t* srow = A.samples + s * N;
-    double2 th[E], lc[E];
+    double2 w[E];
+    double sg[E];
+    double2 lq = make_double2(0.0, 0.0);   // -sum log(1 + w), log(1 + w) = log 2 - s theta + log cosh theta
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int k = e * kWave + lane;
-        th[e] = k < M ? theta_double(srow, N, M, k, pe.b, pe.W) : make_double2(0.0, 0.0);
-        lc[e] = k < M ? log_cosh_double(th[e]) : make_double2(0.0, 0.0);
+        w[e] = make_double2(0.0, 0.0);
+        sg[e] = 1.0;
+        if (k >= M) continue;
+        const double2 th = theta_double(srow, N, M, k, pe.b, pe.W);
+        sg[e] = th.x >= 0.0 ? 1.0 : -1.0;
+        const double ex = exp(-2.0 * fabs(th.x));
+        double sn, cs;
+        sincos(2.0 * sg[e] * th.y, &sn, &cs);
+        w[e] = make_double2(ex * cs, -ex * sn);
+        const double2 lc = log_cosh_double(th);
+        lq.x -= lc.x + 0.6931471805599453 - fabs(th.x);
+        lq.y -= lc.y - sg[e] * th.y;
     }
     const double inv_sqrt_n = 1.0 / sqrt((double)N);
     auto phase = [&](int r) {
@@ -985,25 +1047,35 @@ __device__ __forceinline__ double2 exchange_double(const LocalArgs& A, const Rbm
         fq = make_double2(fq.x * inv_sqrt_n, fq.y * inv_sqrt_n);
     }
     double2 acc = make_double2(0.0, 0.0);
+    int turn = 0;
     for (int c = 0; c < n_words; ++c) {
-        uint64_t m = mask[c];
+        uint64_t m = uniform64(mask[c]);
         while (m) {
             const int bnd = c * kWave + __builtin_ctzll(m);
             m &= m - 1ull;
+            const bool mine = turn == part;
+            turn = turn + 1 == n_parts ? 0 : turn + 1;
+            if (!mine) continue;
             const int2 ij = g.bonds[bnd];
             const double si = (double)srow[ij.x];
-            double2 d = make_double2(0.0, 0.0);
+            double2 p = make_double2(1.0, 0.0);
+            double up = 0.0;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const int k = e * kWave + lane;
                 if (k >= M) continue;
                 const float2 wi = pe.W[(long)ij.x * M + k], wj = pe.W[(long)ij.y * M + k];
-                const double2 z = make_double2(th[e].x - 2.0 * si * ((double)wi.x - (double)wj.x),
-                                               th[e].y - 2.0 * si * ((double)wi.y - (double)wj.y));
-                const double2 l2 = log_cosh_double(z);
-                d.x += l2.x - lc[e].x;
-                d.y += l2.y - lc[e].y;
+                const double m2s = -2.0 * si * sg[e];                 // s Delta = m2s (W_i - W_j)
+                const double dx = m2s * ((double)wi.x - (double)wj.x), dy = m2s * ((double)wi.y - (double)wj.y);
+                const double t = exp(-2.0 * fabs(dx));                 // exp(|dx|) is taken out of both terms
+                const double ep = dx < 0.0 ? t : 1.0, em = dx < 0.0 ? 1.0 : t;
+                double sn, cs;
+                sincos(dy, &sn, &cs);
+                const double2 y = zmul(w[e], make_double2(em * cs, -em * sn));
+                p = zmul(p, make_double2(ep * cs + y.x, ep * sn + y.y));
+                up += fabs(dx);
             }
+            double2 d = make_double2(0.5 * log(p.x * p.x + p.y * p.y) + lq.x + up, atan2(p.y, p.x) + lq.y);
             d = wave_sum(d);
             const float2 ai = pe.a[ij.x], aj = pe.a[ij.y];
             d.x -= 2.0 * si * ((double)ai.x - (double)aj.x);
@@ -1028,24 +1100,15 @@ __device__ __forceinline__ double2 exchange_double(const LocalArgs& A, const Rbm
     return acc;
 }
 
-// One sample's local energy (J/4 s_i s_j over all bonds plus the exchange part in acc, already summed
-// over the lanes that hold it, or formed in double at a node of psi) and, in Chebyshev mode, R = phi / psi_{n+1}.
-template <int E, bool NODE>
+// One sample's local energy (J/4 s_i s_j over all bonds plus the exchange part exch) and, in Chebyshev mode,
+// R = phi / psi_{n+1}.
+template <int E>
 __device__ __forceinline__ void local_finish(const LocalArgs& A, const float2* __restrict__ th1g,
                                              const float2* __restrict__ thng, const float2* __restrict__ thmg,
-                                             int lane, long s, float2 acc, float2 d0, int n_anti,
-                                             const uint64_t* mask, int n_words) {
+                                             int lane, long s, float2 exch, float2 d0, int n_anti) {
     const Geometry& g = A.g;
     const int N = g.N, M = g.M;
     const float J = (float)g.J;
-    float2 exch;
-    if (NODE) {
-        const double2 x = exchange_double<E>(A, A.cheb_mode ? A.psn : A.fit, s, lane, mask, n_words,
-                                             A.cheb_mode && A.order == 0);
-        exch = make_float2((float)x.x, (float)x.y);
-    } else {
-        exch = wave_sum(acc);
-    }
     const float2 eloc = cadd(exch, cscale(d0, 0.25f * J * (float)(g.n_bonds - 2 * n_anti)));
     if (A.eloc_out && lane == 0) A.eloc_out[s] = eloc;
     if (!A.cheb_mode || !A.R_out) return;
@@ -1073,116 +1136,374 @@ __device__ __forceinline__ void local_finish(const LocalArgs& A, const float2* _
     if (lane == 0) A.R_out[s] = R;
 }
 
-// Three waves per SIMD up to 7 x 64 hidden units: E = 6 and 7 then spill 44 and 80 bytes per lane, and
-// the third wave still makes the bond walk 15% faster at E = 7; E = 8 keeps two waves (with three, its
-// 128-byte spill made it 2% slower).
+// One unit: s = sign Re z, w = exp(-2 s z) as the modulus ex and (cos, -sin) cs
+struct UnitW {
+    float s, ex;
+    float2 cs;
+    __device__ __forceinline__ float2 w() const { return make_float2(ex * cs.x, -ex * cs.y); }
+    // (1 + w) / 2, of modulus <= 1: log cosh z = s z + log of it, so that no logarithm holds a log 2 to cancel
+    __device__ __forceinline__ float2 half() const {
+        return make_float2(0.5f * __builtin_fmaf(ex, cs.x, 1.f), (-0.5f * ex) * cs.y);
+    }
+    // tanh z = s (1 - w) / (1 + w)
+    __device__ __forceinline__ float2 tanh() const {
+        const float2 t = cdiv(make_float2(__builtin_fmaf(-ex, cs.x, 1.f), ex * cs.y),
+                              make_float2(__builtin_fmaf(ex, cs.x, 1.f), -ex * cs.y));
+        return make_float2(s * t.x, s * t.y);
+    }
+};
+__device__ __forceinline__ UnitW unit_w(float2 z) {
+    UnitW u;
+    u.s = z.x >= 0.f ? 1.f : -1.f;
+    u.ex = expf(-2.f * fabsf(z.x));
+    u.cs = cos_sin(2.f * u.s * z.y);
+    return u;
+}
+__device__ __forceinline__ float log_abs2(float2 a) { return logf(a.x * a.x + a.y * a.y); }
+
+// What a wave of the wide kernel keeps of one sample: the bond-factor data of the RBM whose Hamiltonian action is
+// taken (w_k of this lane's units, the lanes whose unit has Re theta_k < 0, the lane's inverse product of the
+// denominators, the constant of those next to a zero of cosh) and, wave-uniform, the logarithms of psi_n / fit and
+// psi_{n-1} / fit and the diagonal factor of t_0.
 template <int E>
-__global__ __launch_bounds__(256, E <= 7 ? 3 : 2) void k_local(LocalArgs A, const float2* __restrict__ th1g,
-                                               const float2* __restrict__ thng, const float2* __restrict__ thmg) {
-    constexpr int SPW = kLocalSpw;
-    __shared__ uint64_t s_mask[4][SPW][kMaxBonds / 64];
-    __shared__ float s_lm[4][kRing][kWave];
-    __shared__ float2 s_ph[4][kRing][kWave];
-    __shared__ int s_item[4][kRing];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const long s0 = ((long)blockIdx.x * 4 + wv) * SPW;
-    if (s0 >= A.n_samples) return;
+struct LocalSample {
+    float2 tw[E];
+    uint64_t nm[E];
+    float2 qinv, cq, d0, dn, dm;
+    int n_anti;
+};
+// One pass over the units of the three RBMs: w_k serves tanh theta, the bond factors and the log amplitudes alike
+// (log cosh z = s z + log((1 + w)/2), the factors of a lane's units multiplied and their logarithm taken once).
+template <int E>
+__device__ __forceinline__ void local_prepare(const LocalArgs& A, const float2* __restrict__ th1g,
+                                              const float2* __restrict__ thng, const float2* __restrict__ thmg, int lane,
+                                              long s0, int q, int nq, bool want_local, bool with_fq, int n_words,
+                                              LocalSample<E>& S, uint64_t* mask, uint64_t* sneg) {
     const Geometry& g = A.g;
     const int N = g.N, M = g.M;
-    const int nq = (int)(A.n_samples - s0 < SPW ? A.n_samples - s0 : SPW);
+    S.n_anti = 0;
+    S.qinv = make_float2(1.f, 0.f);
+    S.cq = S.dn = S.dm = make_float2(0.f, 0.f);
+    S.d0 = make_float2(1.f, 0.f);
+#pragma unroll
+    for (int e = 0; e < E; ++e) { S.tw[e] = make_float2(0.f, 0.f); S.nm[e] = 0ull; }
+    if (q >= nq) {
+        if (lane < n_words) mask[lane] = sneg[lane] = 0ull;
+        return;
+    }
+    const long s = s0 + q;
+    const int8_t* srow = A.samples + s * N;
+    const bool want_t = A.tanh_out || A.O_out, want_r = A.cheb_mode && A.R_out, use_m = want_r && A.order >= 1;
+    const bool use_1 = want_t || want_r || A.logpsi_out;
+    const float2* thp = A.cheb_mode ? thng : th1g;
+    const RbmView& vp = A.cheb_mode ? A.psn : A.fit;
+    constexpr float kLn2 = 0.69314718055994531f;
+    float2 T1[E];
+    float2 lc1 = make_float2(0.f, 0.f);                                        // log psi of fit
+    float2 ln = make_float2(0.f, 0.f), lm = make_float2(0.f, 0.f);             // linear parts of log psi_n/fit, psi_{n-1}/fit
+    float2 p1 = make_float2(1.f, 0.f), pn = p1, pm = p1;                       // products of (1 + w) / 2
+    int cn = 0;                                                                // their count for pn
+    uint32_t k1 = 0, kp = 0, km = 0;                                           // units next to a zero of cosh
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int k = e * kWave + lane;
+        const bool in = e < E - 1 || k < M;
+        const int kk = in ? k : 0;
+        T1[e] = make_float2(0.f, 0.f);
+        float2 zp = make_float2(0.f, 0.f);
+        UnitW up{1.f, 0.f, zp};
+        if (want_local) {
+            zp = thp[s * M + kk];
+            up = unit_w(zp);
+            S.nm[e] = __ballot(in && up.s < 0.f);
+            if (in) {
+                S.tw[e] = up.w();
+                if (near_pole(zp)) kp |= 1u << e;
+                else {
+                    pn = cmul(pn, up.half());                 // |1 + w| in [0.58, 2] off the band
+                    ++cn;
+                    if (want_r) ln = cadd(ln, cscale(zp, up.s));
+                }
+            }
+        }
+        if (use_m) {
+            const float2 z = thmg[s * M + kk];
+            const UnitW u = unit_w(z);
+            if (in) {
+                if (near_pole(z)) km |= 1u << e;
+                else {
+                    pm = cmul(pm, u.half());
+                    lm = cadd(lm, cscale(z, u.s));
+                }
+            }
+        }
+        if (use_1) {
+            const bool same = want_local && !A.cheb_mode;
+            const float2 z = same ? zp : th1g[s * M + kk];
+            const UnitW u = same ? up : unit_w(z);
+            if (in) {
+                if (near_pole(z)) k1 |= 1u << e;
+                else {
+                    if (want_t) T1[e] = u.tanh();
+                    if (want_r) {
+                        const float2 l = cscale(z, u.s);
+                        p1 = cmul(p1, u.half());
+                        ln = csub(ln, l);
+                        lm = csub(lm, l);
+                    }
+                    if (A.logpsi_out) lc1 = cadd(lc1, log2cosh(z));
+                }
+            }
+        }
+    }
+    // units next to a zero of cosh, theta summed again in double
+    float2 cl = make_float2(0.f, 0.f);
+    const bool node = __ballot(kp != 0u) != 0ull;
+    while (k1) {
+        const int e = __ffs(k1) - 1;
+        k1 &= k1 - 1;
+        float2 lcr, thr;
+        pole_eval(theta_double(srow, N, M, e * kWave + lane, A.fit.b, A.fit.W), lcr, thr);
+        lc1 = cadd(lc1, make_float2(lcr.x + kLn2, lcr.y));
+        ln = csub(ln, lcr);
+        lm = csub(lm, lcr);
+#pragma unroll
+        for (int ee = 0; ee < E; ++ee)
+            if (ee == e) T1[ee] = thr;
+    }
+    while (kp) {
+        const int e = __ffs(kp) - 1;
+        kp &= kp - 1;
+        const double2 td = theta_double(srow, N, M, e * kWave + lane, vp.b, vp.W);
+        float2 lcr, thr;
+        pole_eval(td, lcr, thr);
+        ln = cadd(ln, lcr);
+        // -log(1 + w_k) = -(log 2 - s_k theta_k + log cosh theta_k), s_k as the bond factors have it
+        const float sg = thp[s * M + e * kWave + lane].x >= 0.f ? 1.f : -1.f;
+        cl = cadd(cl, make_float2(lcr.x + kLn2 - sg * (float)td.x, lcr.y - sg * (float)td.y));
+    }
+    while (km) {
+        const int e = __ffs(km) - 1;
+        km &= km - 1;
+        float2 lcr, thr;
+        pole_eval(theta_double(srow, N, M, e * kWave + lane, A.psm.b, A.psm.W), lcr, thr);
+        lm = cadd(lm, lcr);
+    }
+    WaveSpins sp;
+    sp.load(srow, N, lane);
+    if (A.logpsi_out) {
+        const float2 lp = wave_sum(cadd(lc1, a_dot_sigma(A.fit.a, sp, lane, N)));
+        if (lane == 0) A.logpsi_out[s] = lp;
+    }
+    if (A.tanh_out) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int k = e * kWave + lane;
+            if (k < M) A.tanh_out[s * M + k] = T1[e];
+        }
+    }
+    if (A.O_out) {
+        float2* row = A.O_out + s * (long)g.P;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int site = c * kWave + lane;
+            if (site < N) row[site] = make_float2((float)sp.s[c], 0.f);
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int k = e * kWave + lane;
+            if (k < M) row[N + k] = T1[e];
+        }
+        for (int i = 0; i < N; ++i) {
+            const float si = (float)sp.get(i);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int k = e * kWave + lane;
+                if (k < M) row[N + M + (long)i * M + k] = cscale(T1[e], si);
+            }
+        }
+    }
+    if (!want_local) return;
+    if (lane == 0) g.node_flag[s] = node ? 1 : 0;
+    if (want_r) {
+        // log(psi / fit) = a-part + linear part + log of the quotient of the products
+        const float2 as1 = a_dot_sigma(A.fit.a, sp, lane, N);
+        const float l1 = log_abs2(p1);
+        const float2 qn = cmul(pn, cconj(p1));
+        float2 d = cadd(csub(a_dot_sigma(A.psn.a, sp, lane, N), as1),
+                        make_float2(ln.x + 0.5f * (log_abs2(pn) - l1), ln.y + atan2f(qn.y, qn.x)));
+        d = wave_sum(d);
+        S.dn = make_float2(uniform(d.x), uniform(d.y));
+        if (use_m) {
+            const float2 qm = cmul(pm, cconj(p1));
+            d = cadd(csub(a_dot_sigma(A.psm.a, sp, lane, N), as1),
+                     make_float2(lm.x + 0.5f * (log_abs2(pm) - l1), lm.y + atan2f(qm.y, qm.x)));
+            d = wave_sum(d);
+            S.dm = make_float2(uniform(d.x), uniform(d.y));
+        }
+    }
+    S.qinv = cdiv(make_float2(1.f, 0.f), pn);                 // 1 / prod (1 + w): 2^-cn over the product of the halves
+    S.qinv = make_float2(ldexpf(S.qinv.x, -cn), ldexpf(S.qinv.y, -cn));
+    const float2 cq = wave_sum(make_float2(-cl.x, -cl.y));
+    S.cq = make_float2(uniform(cq.x), uniform(cq.y));   // wave-uniform: scalar registers
+    // diagonal factor of t_0: f_q (momentum q) or, with local_op, the local S^z_0 = s_0 / 2
+    if (with_fq) S.d0 = A.local_op ? make_float2(0.5f * (float)sp.get(0), 0.f) : fq_wave(sp, lane, g, A.q0, A.q1);
+    // anti-aligned bonds of the sample, and the spin of their first site
+    for (int c = 0; c < n_words; ++c) {
+        const int bnd = c * kWave + lane;
+        bool anti = false, down = false;
+        if (bnd < g.n_bonds) {
+            const int2 ij = g.bonds[bnd];
+            anti = srow[ij.x] != srow[ij.y];
+            down = srow[ij.x] < 0;
+        }
+        const uint64_t m = __ballot(anti), d = __ballot(down);
+        if (lane == 0) { mask[c] = m; sneg[c] = d; }
+        S.n_anti += __popcll(m);
+    }
+}
+
+// E_loc = the exchange terms (acc, over the lanes that hold them) plus J/4 s_i s_j over all bonds; R = phi / fit
+template <int E>
+__device__ __forceinline__ void local_close(const LocalArgs& A, int lane, long s, float2 acc, const LocalSample<E>& S) {
+    const Geometry& g = A.g;
+    const float2 eloc = cadd(wave_sum(acc), cscale(S.d0, 0.25f * (float)g.J * (float)(g.n_bonds - 2 * S.n_anti)));
+    if (A.eloc_out && lane == 0) A.eloc_out[s] = eloc;
+    if (!A.cheb_mode || !A.R_out) return;
+    const float2 ht = cscale(csub(eloc, cmul(make_float2((float)A.E_c, 0.f), S.d0)), (float)(1.0 / A.W_scale));
+    // beta enters through its logarithm, added to the log-amplitude difference before the exponential, so
+    // that neither a small beta nor a large ratio of unnormalised states leaves the binary32 range on its own
+    float2 R = cmul(ht, cexpf(cadd(S.dn, A.lbeta_n)));
+    if (A.order >= 1) {
+        float2 fm = make_float2(1.f, 0.f);
+        if (A.order == 1) {
+            WaveSpins sp;
+            sp.load(A.samples + s * g.N, g.N, lane);
+            fm = A.local_op ? make_float2(0.5f * (float)sp.get(0), 0.f) : fq_wave(sp, lane, g, A.q0, A.q1);
+        }
+        R = csub(cscale(R, 2.f), cmul(fm, cexpf(cadd(S.dm, A.lbeta_nm1))));
+    }
+    if (lane == 0) A.R_out[s] = R;
+}
+
+// finish the cnt (<= kPairs) pairs of the buffer: acc[q] += their terms
+template <int E>
+__device__ __forceinline__ void local_flush(const LocalArgs& A, const RbmView& pe, int lane, int cnt, bool with_fq,
+                                            float inv_sqrt_n, const float2* phases,
+                                            const LocalSample<E> (&S)[kLocalSpw], float2 (&acc)[kLocalSpw],
+                                            const PairBuf& buf) {
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int ex;
+    const float2 m = pair_total(buf, lane, ex);
+    const int gq = lane >> 2;
+    if (gq < cnt) {
+        const int item = buf.item[gq];
+        const int q = item >> 16, bnd = item & 0x7FFF;
+        const int2 ij = A.g.bonds[bnd];
+        const float si = (item & 0x8000) ? -1.f : 1.f;
+        float2 d0q = S[0].d0, cqq = S[0].cq;
+#pragma unroll
+        for (int qq = 1; qq < kLocalSpw; ++qq) {
+            d0q = q == qq ? S[qq].d0 : d0q;
+            cqq = q == qq ? S[qq].cq : cqq;
+        }
+        const float2 c = bond_term(A, pe, ij.x, ij.y, si, m, ex, d0q, cqq, with_fq, inv_sqrt_n, phases);
+        if ((lane & 3) == 0)
+#pragma unroll
+            for (int qq = 0; qq < kLocalSpw; ++qq)
+                if (q == qq) acc[qq] = cadd(acc[qq], c);
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// Three waves per SIMD (registers, and the pair buffers in LDS).
+template <int E>
+__global__ __launch_bounds__(256, 3) void k_local(LocalArgs A, const float2* __restrict__ th1g,
+                                               const float2* __restrict__ thng, const float2* __restrict__ thmg) {
+    constexpr int SPW = kLocalSpw;
+    __shared__ uint64_t s_mask[4][SPW][kMaxBonds / 64], s_neg[4][SPW][kMaxBonds / 64];
+    __shared__ PairBuf s_buf[4];
+    __shared__ float2 s_phase[256];
+    const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6));
+    const long s0 = ((long)blockIdx.x * 4 + wv) * SPW;
+    const Geometry& g = A.g;
     const bool want_local = A.eloc_out || A.R_out;
     const bool with_fq = A.cheb_mode && A.order == 0;
+    stage_phases(A, with_fq, s_phase);
+    if (s0 >= A.n_samples) return;
+    const int N = g.N, M = g.M;
+    const int nq = (int)(A.n_samples - s0 < SPW ? A.n_samples - s0 : SPW);
     // the RBM whose Hamiltonian action is needed
     const RbmView& pe = A.cheb_mode ? A.psn : A.fit;
     const int n_words = (g.n_bonds + 63) / 64;
 
-    float2 TW[SPW][E];
-    uint32_t NEG[SPW];
-    float2 QI[SPW], CQ[SPW];
-    bool NODE[SPW];
-    float2 d0[SPW];
-    int n_anti[SPW];
+    LocalSample<E> S[SPW];
     static_assert(SPW == 4, "the per-sample calls below are written out for 4 samples");
-    local_sample<E>(A, th1g, thng, lane, s0, 0, nq, want_local, with_fq, n_words, TW[0], NEG[0], QI[0], CQ[0], d0[0],
-                    n_anti[0], NODE[0],
-                    s_mask[wv][0]);
-    local_sample<E>(A, th1g, thng, lane, s0, 1, nq, want_local, with_fq, n_words, TW[1], NEG[1], QI[1], CQ[1], d0[1],
-                    n_anti[1], NODE[1],
-                    s_mask[wv][1]);
-    local_sample<E>(A, th1g, thng, lane, s0, 2, nq, want_local, with_fq, n_words, TW[2], NEG[2], QI[2], CQ[2], d0[2],
-                    n_anti[2], NODE[2],
-                    s_mask[wv][2]);
-    local_sample<E>(A, th1g, thng, lane, s0, 3, nq, want_local, with_fq, n_words, TW[3], NEG[3], QI[3], CQ[3], d0[3],
-                    n_anti[3], NODE[3],
-                    s_mask[wv][3]);
+#define CRBM_SAMPLE(q) local_prepare<E>(A, th1g, thng, thmg, lane, s0, q, nq, want_local, with_fq, n_words, S[q], \
+                                        s_mask[wv][q], s_neg[wv][q]);
+    CRBM_SAMPLE(0) CRBM_SAMPLE(1) CRBM_SAMPLE(2) CRBM_SAMPLE(3)
+#undef CRBM_SAMPLE
     if (!want_local) return;
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
     const float inv_sqrt_n = rsqrtf((float)N);
     float2 acc[SPW];
 #pragma unroll
     for (int q = 0; q < SPW; ++q) acc[q] = make_float2(0.f, 0.f);
-    int pushed = 0, done = 0;
+    PairBuf& buf = s_buf[wv];
+    int cnt = 0;
     for (int c = 0; c < n_words; ++c) {
-        uint64_t mk[SPW];
+        uint64_t mk[SPW], sg[SPW];
         uint64_t any = 0ull;
 #pragma unroll
         for (int q = 0; q < SPW; ++q) {
-            mk[q] = s_mask[wv][q][c];
+            mk[q] = uniform64(s_mask[wv][q][c]);
+            sg[q] = uniform64(s_neg[wv][q][c]);
             any |= mk[q];
         }
         while (any) {
             const int bit = __builtin_ctzll(any);
             any &= any - 1ull;
             const int bnd = c * kWave + bit;
-            const int i = uniform(g.bonds[bnd].x);
             float4 tq[E];
             bond_row<E>(g, bnd, lane, tq);
 #pragma unroll
             for (int q = 0; q < SPW; ++q) {
                 if (!((mk[q] >> bit) & 1ull)) continue;
-                const float2 prod =
-                    bond_share<E>(tq, TW[q], bond_neg(NEG[q], (float)A.samples[(s0 + q) * N + i]), QI[q]);
-                const int slot = pushed & (kRing - 1);
-                float lmv;
-                float2 phv;
-                share_polar(prod, prod.x * prod.x + prod.y * prod.y, lmv, phv);
-                s_lm[wv][slot][lane] = lmv;
-                s_ph[wv][slot][lane] = phv;
-                if (lane == 0) s_item[wv][slot] = (q << 16) | bnd;
-                ++pushed;
+                const bool down = (sg[q] >> bit) & 1ull;
+                const float2 prod = bond_share<E>(tq, S[q].tw, S[q].nm, down, S[q].qinv);
+                pair_push(buf, cnt, lane, prod, (q << 16) | (down ? 0x8000 : 0) | bnd);
+                ++cnt;
             }
-            if (pushed - done >= 8) {
-                local_flush<SPW>(A, pe, lane, s0, done, 8, with_fq, inv_sqrt_n, d0, CQ, acc, s_lm[wv], s_ph[wv],
-                                 s_item[wv]);
-                done += 8;
+            if (cnt > kPairs - SPW) {
+                local_flush<E>(A, pe, lane, cnt, with_fq, inv_sqrt_n, s_phase, S, acc, buf);
+                cnt = 0;
             }
         }
     }
-    while (done < pushed) {
-        const int cnt = pushed - done < 8 ? pushed - done : 8;
-        local_flush<SPW>(A, pe, lane, s0, done, cnt, with_fq, inv_sqrt_n, d0, CQ, acc, s_lm[wv], s_ph[wv],
-                         s_item[wv]);
-        done += cnt;
-    }
+    if (cnt) local_flush<E>(A, pe, lane, cnt, with_fq, inv_sqrt_n, s_phase, S, acc, buf);
 
-    local_finish<E, false>(A, th1g, thng, thmg, lane, s0, acc[0], d0[0], n_anti[0], s_mask[wv][0], n_words);
-    if (nq > 1) local_finish<E, false>(A, th1g, thng, thmg, lane, s0 + 1, acc[1], d0[1], n_anti[1], s_mask[wv][1], n_words);
-    if (nq > 2) local_finish<E, false>(A, th1g, thng, thmg, lane, s0 + 2, acc[2], d0[2], n_anti[2], s_mask[wv][2], n_words);
-    if (nq > 3) local_finish<E, false>(A, th1g, thng, thmg, lane, s0 + 3, acc[3], d0[3], n_anti[3], s_mask[wv][3], n_words);
+    local_close<E>(A, lane, s0, acc[0], S[0]);
+    if (nq > 1) local_close<E>(A, lane, s0 + 1, acc[1], S[1]);
+    if (nq > 2) local_close<E>(A, lane, s0 + 2, acc[2], S[2]);
+    if (nq > 3) local_close<E>(A, lane, s0 + 3, acc[3], S[3]);
 }
 
 // Narrow RBMs (M <= 3 x 64): one sample per wave.  With few hidden units per lane the bookkeeping of
 // the bond-major walk costs more than the table reads it saves, so each wave walks its own sample's
-// anti-aligned bonds in batches of 8 with the shares kept in registers.  Five waves per SIMD: the
-// kernel fits in 96 registers without spilling, and the walk's table reads want the extra wave.
+// anti-aligned bonds in batches of 8 with the shares kept in registers, (log |p|, p/|p|) each, and a
+// reduce-scatter that leaves a bond to 8 lanes.  The bonds come from the mask words by scalar instructions and
+// the rows of four bonds are in flight together.  147,456 images on 6 x 6, M = 72: 835 us per order (852 us with the
+// list of bonds and the spins read back from memory).
 template <int E>
-__global__ __launch_bounds__(256, 5) void k_local_one(LocalArgs A, const float2* __restrict__ th1g,
+__global__ __launch_bounds__(256, 4) void k_local_one(LocalArgs A, const float2* __restrict__ th1g,
                                                    const float2* __restrict__ thng, const float2* __restrict__ thmg) {
-    __shared__ uint64_t s_mask[4][kMaxBonds / 64];
+    __shared__ uint64_t s_mask[4][kMaxBonds / 64], s_neg[4][kMaxBonds / 64];
     __shared__ short s_anti[4][kMaxBonds];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6));
     const long s = (long)blockIdx.x * 4 + wv;
     if (s >= A.n_samples) return;
     const Geometry& g = A.g;
@@ -1191,17 +1512,16 @@ __global__ __launch_bounds__(256, 5) void k_local_one(LocalArgs A, const float2*
     const RbmView& pe = A.cheb_mode ? A.psn : A.fit;
     const int n_words = (g.n_bonds + 63) / 64;
     float2 TW[E];
-    uint32_t neg;
+    uint64_t NM[E];
     float2 qinv, cq;
     float2 d0;
     int n_anti;
-    bool node;
-    local_sample<E>(A, th1g, thng, lane, s, 0, 1, want_local, with_fq, n_words, TW, neg, qinv, cq, d0, n_anti, node,
-                    s_mask[wv]);
+    local_sample<E>(A, th1g, thng, lane, s, 0, 1, want_local, with_fq, n_words, TW, NM, qinv, cq, d0, n_anti,
+                    s_mask[wv], s_neg[wv]);
     if (!want_local) return;
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // the anti-aligned bonds in bond order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // the anti-aligned bonds in bond order, for the lanes that finish them
     short* lst = s_anti[wv];
     int base = 0;
     for (int c = 0; c < n_words; ++c) {
@@ -1210,71 +1530,106 @@ __global__ __launch_bounds__(256, 5) void k_local_one(LocalArgs A, const float2*
         base += __popcll(m);
     }
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const float inv_sqrt_n = rsqrtf((float)g.N);
     const int8_t* srow = A.samples + s * g.N;
     float2 acc = make_float2(0.f, 0.f);
+    int c = 0;
+    uint64_t m = uniform64(s_mask[wv][0]), sg = uniform64(s_neg[wv][0]);
     for (int b0 = 0; b0 < n_anti; b0 += 8) {
+        const int cnt = n_anti - b0 < 8 ? n_anti - b0 : 8;
         float lm[8];
         float2 ph[8];
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            lm[b] = 0.f;
-            ph[b] = make_float2(1.f, 0.f);
-            if (b0 + b < n_anti) {
-                const int bnd = uniform((int)lst[b0 + b]);
-                float4 tq[E];
-                bond_row<E>(g, bnd, lane, tq);
-                const float2 prod = bond_share<E>(tq, TW, bond_neg(neg, (float)srow[uniform(g.bonds[bnd].x)]), qinv);
-                share_polar(prod, prod.x * prod.x + prod.y * prod.y, lm[b], ph[b]);
+        for (int h = 0; h < 8; h += 4) {
+            float4 tq[4][E];
+            bool down[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                int bit = 0;
+                if (h + b < cnt) {
+                    while (!m) {
+                        ++c;
+                        m = uniform64(s_mask[wv][c]);
+                        sg = uniform64(s_neg[wv][c]);
+                    }
+                    bit = (int)__builtin_ctzll(m);
+                    m &= m - 1ull;
+                }
+                down[b] = (sg >> bit) & 1ull;
+                bond_row<E>(g, c * kWave + bit, lane, tq[b]);
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                lm[h + b] = 0.f;
+                ph[h + b] = make_float2(1.f, 0.f);
+                if (h + b < cnt) {
+                    const float2 prod = bond_share<E>(tq[b], TW, NM, down[b], qinv);
+                    share_polar(prod, prod.x * prod.x + prod.y * prod.y, lm[h + b], ph[h + b]);
+                }
             }
         }
         reduce_scatter8(lm, ph, lane);
         const int bb = b0 + (lane >> 3);
         if (bb < n_anti) {
             const int2 ij = g.bonds[lst[bb]];
-            const float2 c = bond_term(A, pe, ij.x, ij.y, (float)srow[ij.x], lm[0], ph[0], d0, cq, with_fq, inv_sqrt_n);
-            if ((lane & 7) == 0) acc = cadd(acc, c);
+            const float2 t = bond_term_polar(A, pe, ij.x, ij.y, (float)srow[ij.x], lm[0], ph[0], d0, cq, with_fq, inv_sqrt_n);
+            if ((lane & 7) == 0) acc = cadd(acc, t);
         }
     }
-    local_finish<E, false>(A, th1g, thng, thmg, lane, s, acc, d0, n_anti, s_mask[wv], n_words);
+    local_finish<E>(A, th1g, thng, thmg, lane, s, wave_sum(acc), d0, n_anti);
 }
 
 // Samples at which the local-energy RBM is next to a node (flagged by k_local / k_local_one): E_loc with
 // the exchange sum in double (exchange_double) and, in Chebyshev mode, R, overwriting the binary32 values
-// of the main kernel.  One wave per sample; unflagged samples return at once.
+// of the main kernel.  A workgroup takes kNodeSpan samples and gives each flagged one to all its waves, every
+// kNodeWaves-th anti-aligned bond to a wave: flagged samples are few (some tens of 65,536 at 10 x 10, M = 400), and
+// one wave per sample left the launch waiting on the longest chain of double logarithms (1.2 ms, now 0.47 ms).
+constexpr int kNodeWaves = 8, kNodeSpan = 16;
 template <int E>
-__global__ __launch_bounds__(256) void k_local_nodes(LocalArgs A, const float2* __restrict__ th1g,
-                                                     const float2* __restrict__ thng, const float2* __restrict__ thmg) {
-    __shared__ uint64_t s_mask[4][kMaxBonds / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const long s = (long)blockIdx.x * 4 + wv;
-    if (s >= A.n_samples) return;
+__global__ __launch_bounds__(64 * kNodeWaves) void k_local_nodes(LocalArgs A, const float2* __restrict__ th1g,
+                                                                 const float2* __restrict__ thng,
+                                                                 const float2* __restrict__ thmg) {
+    __shared__ uint64_t s_mask[kMaxBonds / 64];
+    __shared__ double2 s_part[kNodeWaves];
+    const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6));
     const Geometry& g = A.g;
-    if (!g.node_flag[s]) return;
-    const int8_t* srow = A.samples + s * g.N;
+    const long s0 = (long)blockIdx.x * kNodeSpan;
+    const uint64_t flagged = __ballot(lane < kNodeSpan && s0 + lane < A.n_samples && g.node_flag[s0 + lane] != 0);
     const int n_words = (g.n_bonds + 63) / 64;
-    int n_anti = 0;
-    for (int c = 0; c < n_words; ++c) {
-        const int bnd = c * kWave + lane;
-        bool anti = false;
-        if (bnd < g.n_bonds) {
-            const int2 ij = g.bonds[bnd];
-            anti = srow[ij.x] != srow[ij.y];
+    const bool with_fq = A.cheb_mode && A.order == 0;
+    for (uint64_t todo = flagged; todo; todo &= todo - 1ull) {
+        const long s = s0 + __builtin_ctzll(todo);
+        const int8_t* srow = A.samples + s * g.N;
+        int n_anti = 0;
+        __syncthreads();
+        for (int c = 0; c < n_words; ++c) {
+            const int bnd = c * kWave + lane;
+            bool anti = false;
+            if (bnd < g.n_bonds) {
+                const int2 ij = g.bonds[bnd];
+                anti = srow[ij.x] != srow[ij.y];
+            }
+            const uint64_t m = __ballot(anti);
+            if (threadIdx.x == 0) s_mask[c] = m;
+            n_anti += __popcll(m);
         }
-        const uint64_t m = __ballot(anti);
-        if (lane == 0) s_mask[wv][c] = m;
-        n_anti += __popcll(m);
+        __syncthreads();
+        const double2 x = exchange_double<E>(A, A.cheb_mode ? A.psn : A.fit, s, lane, s_mask, n_words, with_fq, wv,
+                                             kNodeWaves);
+        if (lane == 0) s_part[wv] = x;
+        __syncthreads();
+        if (wv != 0) continue;
+        double2 t = s_part[0];
+        for (int k = 1; k < kNodeWaves; ++k) t = zadd(t, s_part[k]);
+        float2 d0 = make_float2(1.f, 0.f);
+        if (with_fq) {
+            WaveSpins sp;
+            sp.load(srow, g.N, lane);
+            d0 = A.local_op ? make_float2(0.5f * (float)sp.get(0), 0.f) : fq_wave(sp, lane, g, A.q0, A.q1);
+        }
+        local_finish<E>(A, th1g, thng, thmg, lane, s, make_float2((float)t.x, (float)t.y), d0, n_anti);
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float2 d0 = make_float2(1.f, 0.f);
-    if (A.cheb_mode && A.order == 0) {
-        WaveSpins sp;
-        sp.load(srow, g.N, lane);
-        d0 = A.local_op ? make_float2(0.5f * (float)sp.get(0), 0.f) : fq_wave(sp, lane, g, A.q0, A.q1);
-    }
-    local_finish<E, true>(A, th1g, thng, thmg, lane, s, make_float2(0.f, 0.f), d0, n_anti, s_mask[wv], n_words);
 }
 
 // (exp 2D, exp -2D) per bond and hidden unit, D = W_i - W_j, from the binary32 weights in double
@@ -1305,6 +1660,7 @@ hipError_t launch_local_core(const LocalArgs& A, const float2* th1, const float2
     const dim3 block(256);
     const dim3 grid1((unsigned)((A.n_samples + 3) / 4));
     const long per_block = 4L * kLocalSpw;
+    const dim3 gridn((unsigned)((A.n_samples + kNodeSpan - 1) / kNodeSpan));
     const dim3 grid4((unsigned)((A.n_samples + per_block - 1) / per_block));
     switch (E) {
 #define CRBM_ONE(e) case e: hipLaunchKernelGGL(k_local_one<e>, grid1, block, 0, stream, A, th1, thn, thm); break;
@@ -1316,7 +1672,8 @@ hipError_t launch_local_core(const LocalArgs& A, const float2* th1, const float2
     }
     if (A.eloc_out || A.R_out) {
         switch (E) {
-#define CRBM_NODES(e) case e: hipLaunchKernelGGL(k_local_nodes<e>, grid1, block, 0, stream, A, th1, thn, thm); break;
+#define CRBM_NODES(e) \
+    case e: hipLaunchKernelGGL(k_local_nodes<e>, gridn, dim3(64 * kNodeWaves), 0, stream, A, th1, thn, thm); break;
             CRBM_NODES(1) CRBM_NODES(2) CRBM_NODES(3) CRBM_NODES(4) CRBM_NODES(5) CRBM_NODES(6) CRBM_NODES(7)
             CRBM_NODES(8)
 #undef CRBM_NODES
