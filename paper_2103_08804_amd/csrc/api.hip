@@ -110,7 +110,7 @@ struct crbm_plan_s {
     unsigned long long* bclocks = nullptr;   // [CRBM_MAX_CLOCK_WAVES][2] per-wave clocks of the batched kernel
     double2* bpartial = nullptr;
     int n_cu = 256;
-    int b_waves = 4, b_blocks = 1024, b_lanes = 64;
+    int b_waves = 8, b_blocks = 512, b_lanes = 64;
     Profiler prof;
     std::vector<void*> allocs;
     // workspace of the moment-correction path, reserved at creation (CRBM_PLAN_BASIS / CRBM_PLAN_SYM_BASIS;
@@ -403,8 +403,10 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     p->w.prof = &p->prof;
     if (rc) { delete p; return rc; }
     p->w.red_len = red_len;
-    p->b_waves = 4;
-    p->b_blocks = 4 * p->n_cu;
+    // 16 waves per compute unit either way; in blocks of 8 two copies of the ground state's W fit beside each other in LDS,
+    // in blocks of 4 they would not (8 x 8, M = 128: 12.1 ms against 22.5 ms from L2)
+    p->b_waves = 8;
+    p->b_blocks = 2 * p->n_cu;
     p->w.n_cu = p->n_cu;
     p->w.sb_kt = 128;
     e = hipMemcpy(p->bonds, bonds.data(), bonds.size() * sizeof(int2), hipMemcpyHostToDevice);

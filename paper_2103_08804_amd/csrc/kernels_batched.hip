@@ -13,13 +13,17 @@
 // each recorded sweep it adds the chain's terms in double precision.  The rows
 // of psi_gs, the same for every chain, are read from a copy in LDS when it fits
 // without lowering the occupancy: every live proposal reads two of them, and
-// from L2 those reads, with the rows of t~_i, ran at the L2 gather ceiling.  Per-chain partial sums are reduced per instance
+// from L2 those reads, with the rows of t~_i, ran at the L2 gather ceiling.  Null moves are known from the spins at
+// the sites of 64 draws and cost nothing; the next live move's rows are on their way while one is evaluated (see the
+// sweep).  Bound by VALU issue and by the chain of one move's dependent steps, four waves per SIMD.  Before, every
+// proposal was visited, the start's exchanges were drawn one after the other by one lane, and blocks of four waves
+// left no room for the copy of W at full occupancy.  256 instances, 8 x 8, M = 128, 4 + 16 sweeps: 20.7 to 12.1 ms, of
+// which the block shape (eight waves, two blocks per compute unit) is the largest part.
+// Per-chain partial sums are reduced per instance
 // in chain order by a second kernel, so the result does not depend on the
 // schedule.  All launches are stream-ordered kernels (no host work), so the
 // sequence can be captured in a graph.
 #include <hip/hip_runtime.h>
-
-#include <type_traits>
 
 #include "../../include/chebrbm.h"
 #include "device.hpp"
@@ -45,43 +49,6 @@ hipError_t launch_clear_u64(unsigned long long* p, long n, hipStream_t stream) {
     hipLaunchKernelGGL(k_clear_u64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p, n);
     return hipGetLastError();
 }
-
-// Value at site i (wave-uniform) of a per-lane array holding sites 64 q + lane; ONE: all sites in slot 0
-// (N <= 64), a single readlane.
-template <bool ONE, typename T>
-__device__ __forceinline__ T site_value(const T (&v)[4], int i) {
-    const int l = i & 63;
-    if (ONE) return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[0]), l));
-    const int q = i >> 6;
-    const int v0 = __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[0]), l);
-    const int v1 = __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[1]), l);
-    const int v2 = __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[2]), l);
-    const int v3 = __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[3]), l);
-    return __builtin_bit_cast(T, q == 0 ? v0 : q == 1 ? v1 : q == 2 ? v2 : v3);
-}
-
-// Spins of a chain of N <= 64 sites as one wave-uniform 64-bit word, bit i set for s_i = +1: reads,
-// flips and the null test of an exchange are scalar operations.
-struct SpinBits {
-    uint64_t m;
-    __device__ __forceinline__ void load(const int8_t* row, int N, int lane) {
-        m = __ballot(lane < N && row[lane] > 0);
-    }
-    __device__ __forceinline__ int get(int i) const { return ((m >> i) & 1ull) ? 1 : -1; }
-    __device__ __forceinline__ void flip(int i, int) { m ^= 1ull << i; }
-    // spin at site 64 q + lane (0 past N)
-    __device__ __forceinline__ int at(int q, int lane, int N) const {
-        return (q == 0 && lane < N) ? (((m >> lane) & 1ull) ? 1 : -1) : 0;
-    }
-};
-// The same interface over one site per lane and slot (N <= 256).
-struct SpinLanes {
-    WaveSpins w;
-    __device__ __forceinline__ void load(const int8_t* row, int N, int lane) { w.load(row, N, lane); }
-    __device__ __forceinline__ int get(int i) const { return w.get(i); }
-    __device__ __forceinline__ void flip(int i, int lane) { w.set(i, -w.get(i), lane); }
-    __device__ __forceinline__ int at(int q, int, int) const { return w.s[q]; }
-};
 
 // Rows of one whole [N][M] complex64 matrix through a single buffer descriptor: a row is a 32-bit scalar
 // offset and the lanes' columns loop-invariant vector offsets (clamped to the row), so a proposal's loads
@@ -111,17 +78,12 @@ __device__ __forceinline__ void mat_fetch(const MatRows& m, const unsigned (&lof
 // Per-chain state of one wave.  theta of t~ changes only on accepted moves;
 // its rows are fetched when a move is accepted and added at the next accepted
 // move or measurement, so their L2 round trip overlaps the following proposals.
-template <int E, bool PAIR, bool ONE>
+template <int E>
 struct BatchedChain {
-    std::conditional_t<ONE, SpinBits, SpinLanes> sp;
-    float ag[4];            // Re a of psi_gs at sites 64 q + lane
     float2 thg[E], tht[E];  // theta of psi_gs and of t~
     float Lg[E];            // Re log 2cosh theta_gs
     float2 pti[E], ptj[E];  // rows of t~'s W for the pending update of tht
     float pm;               // -2 s_i of the pending update, 0 when none
-    float lu;               // ln(u) / 2 of this lane's draw: the acceptance test in the log domain
-    float thp, thm;         // ONE: lu less the move's change of Re(a . s) of psi_gs, for s_i = +1 and -1
-    int acc;                // lane l: accept bit of proposal 64 k + l of the current 64
     double m0, mr, mi;      // sums of |f|^2 and conj(f) beta r
 };
 
@@ -151,8 +113,8 @@ __device__ __forceinline__ float2 unit_log_ratio(float2 zt, float2 zg) {
     return make_float2(fabsf(zt.x) - fabsf(zg.x) + lr, st * zt.y - sg * zg.y + atan2f(q.y, q.x));
 }
 
-template <int E, bool PAIR, bool ONE>
-__device__ __forceinline__ void apply_pending(BatchedChain<E, PAIR, ONE>& c, int lane, int M) {
+template <int E, bool PAIR>
+__device__ __forceinline__ void apply_pending(BatchedChain<E>& c, int lane, int M) {
     if (c.pm != 0.f) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
@@ -169,20 +131,21 @@ __device__ __forceinline__ void apply_pending(BatchedChain<E, PAIR, ONE>& c, int
 // grouped kernel below): per lane the slots in sequence (units 64 e + lane, sites 64 q + lane),
 // then the lanes by bits 0 .. 5.  The unit terms are log 2cosh(theta_t) - log 2cosh(theta_gs) per
 // unit (unit_log_ratio), the site terms (a_t - a_gs) s and e^{-i q.r} s / 2.
-// ph: e^{-i q.r} and da: a_t - a_gs at this lane's sites
-template <int E, bool PAIR, bool ONE>
-__device__ __forceinline__ void measure(const BatchedArgs& A, BatchedChain<E, PAIR, ONE>& c, const float2 (&ph)[4],
-                                        const float2 (&da)[4], double2 beta, int lane) {
+// ph: e^{-i q.r} at this lane's sites; da1: a_t - a_gs there, held when there is one slot (read again otherwise)
+template <int E, bool PAIR, int Q>
+__device__ __forceinline__ void measure(const BatchedArgs& A, BatchedChain<E>& c, const int8_t* row,
+                                        const float2* __restrict__ at, const float2 (&ph)[Q], float2 da1, double2 beta,
+                                        int lane) {
     const int N = A.N, M = A.M;
-    apply_pending(c, lane, M);
+    apply_pending<E, PAIR>(c, lane, M);
     float2 f = make_float2(0.f, 0.f), dA = make_float2(0.f, 0.f), dU = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq) {
+    for (int qq = 0; qq < Q; ++qq) {
         const int site = qq * kWave + lane;
         if (site < N) {
-            const float s = (float)c.sp.at(qq, lane, N);
+            const float s = (float)row[site];
             f = cadd(f, cscale(ph[qq], 0.5f * s));
-            dA = cadd(dA, cscale(da[qq], s));
+            dA = cadd(dA, cscale(Q == 1 ? da1 : csub(at[site], A.gs.a[site]), s));
         }
     }
 #pragma unroll
@@ -198,85 +161,22 @@ __device__ __forceinline__ void measure(const BatchedArgs& A, BatchedChain<E, PA
     c.mi += fx * br.y - fy * br.x;
 }
 
-// Trace words of the `count` proposals t0 .. t0 + count - 1 (t0 a multiple of 64) from their accept
-// bits, one per lane.
-template <int E, bool PAIR, bool ONE>
-__device__ __forceinline__ void flush_accepts(BatchedChain<E, PAIR, ONE>& c, uint32_t* trow, int t0, int count,
-                                              int lane) {
-    if (trow) {
-        const uint64_t bits = __ballot(c.acc != 0);
-        if (lane == 0) {
-            trow[t0 >> 5] = (uint32_t)bits;
-            if (count > 32) trow[(t0 >> 5) + 1] = (uint32_t)(bits >> 32);
-        }
+// Rows i (and j) of psi_gs: with LDSG from LDS (s_w: rows of E 64 columns that hold zeros past M).
+template <int E, bool PAIR, bool LDSG>
+__device__ __forceinline__ void gs_rows(const MatRows& Wg, const unsigned (&loff)[E], const float2* s_w, int i, int j,
+                                        int lane, float2 (&wi)[E], float2 (&wj)[E]) {
+    if (!LDSG) {
+        mat_fetch<E, PAIR>(Wg, loff, i, j, wi, wj);
+        return;
     }
-    c.acc = 0;
+    constexpr int Mp = E * kWave;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        wi[e] = s_w[i * Mp + e * kWave + lane];
+        if (PAIR) wj[e] = s_w[j * Mp + e * kWave + lane];
+    }
 }
 
-// Proposal t of chain g.  Rows of psi_gs are read only for live moves; with LDSG from LDS (s_w: rows
-// of E 64 columns that hold zeros past M).  Every 64th proposal draws the next 64 (one per lane) with
-// their thresholds ln(u)/2 (with ONE less each draw's change of Re(a . s), for both signs of s_i), and
-// writes the accept bits of the previous 64 to the trace.  The move is accepted when the wave total of
-// the log-cosh change exceeds ln(u)/2 less the change of Re(a . s), the same test in every kernel here.
-template <int E, bool PAIR, bool ONE, bool LDSG>
-__device__ __forceinline__ void batched_step(const BatchedArgs& A, const float2* s_w, uint64_t g, int lane, int t,
-                                             BatchedChain<E, PAIR, ONE>& c, const MatRows& Wg, const MatRows& Wt,
-                                             const unsigned (&loff)[E], uint32_t* trow, DrawBatch& batch) {
-    const int N = A.N, M = A.M;
-    const int l = t & 63;
-    if (l == 0) {
-        if (t > 0) flush_accepts(c, trow, t - 64, 64, lane);
-        batch = draw_batch(A.seed, (uint32_t)g, (uint64_t)t, lane, N);
-        c.lu = half_ln(batch.u);
-        if (ONE) {
-            // Re a of psi_gs at this lane's sites i, j (site k sits in lane k): the move changes
-            // Re(a . s) by -2 s_i (a_i - a_j), or by -2 s_i a_i for a flip, that is by -s_i d2 (exactly
-            // as -2 s_i a_i + 2 s_i a_j rounds)
-            const float ai = __int_as_float(__builtin_amdgcn_ds_bpermute(batch.i << 2, __float_as_int(c.ag[0])));
-            const float aj = __int_as_float(__builtin_amdgcn_ds_bpermute(batch.j << 2, __float_as_int(c.ag[0])));
-            const float d2 = PAIR ? 2.f * (ai - aj) : 2.f * ai;
-            c.thp = c.lu + d2;   // s_i = +1: the change is -d2
-            c.thm = c.lu - d2;
-        }
-    }
-    Proposal cur = proposal_at(batch, l);
-    const int si = c.sp.get(cur.i), sj = c.sp.get(cur.j);
-    if (!(PAIR && si == sj)) {
-        float2 wi[E], wj[E], tn[E];
-        float Ln[E];
-        float total, thr;
-        if (LDSG) {
-            constexpr int Mp = E * kWave;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                wi[e] = s_w[cur.i * Mp + e * kWave + lane];
-                if (PAIR) wj[e] = s_w[cur.j * Mp + e * kWave + lane];
-            }
-        } else {
-            mat_fetch<E, PAIR>(Wg, loff, cur.i, cur.j, wi, wj);
-        }
-        if (ONE) {
-            total = units_dlog<E, PAIR, !LDSG>(si, wi, wj, c.thg, c.Lg, tn, Ln, lane, M);
-            thr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si > 0 ? c.thp : c.thm), l));
-        } else {
-            const float m2si = -2.f * (float)si;
-            float da = m2si * site_value<ONE>(c.ag, cur.i);
-            if (PAIR) da -= m2si * site_value<ONE>(c.ag, cur.j);
-            total = units_dlog<E, PAIR>(si, wi, wj, c.thg, c.Lg, tn, Ln, lane, M);
-            thr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c.lu), l)) - uniform(da);
-        }
-        if (total > thr) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) { c.thg[e] = tn[e]; c.Lg[e] = Ln[e]; }
-            apply_pending(c, lane, M);
-            mat_fetch<E, PAIR>(Wt, loff, cur.i, cur.j, c.pti, c.ptj);
-            c.pm = -2.f * (float)si;
-            c.sp.flip(cur.i, lane);
-            if (PAIR) c.sp.flip(cur.j, lane);
-            if (trow) c.acc = lane == l ? 1 : c.acc;
-        }
-    }
-}
 // Four waves per SIMD (at most 128 registers) for the small chain widths, which hides more of each
 // wave's dependency stalls.  LDSG: the block first copies W of psi_gs ([N][M] complex64, rows padded
 // with zeros to E 64 columns) into LDS after its spin rows, and live proposals read their rows there.
@@ -318,60 +218,68 @@ void k_batched(BatchedArgs A) {
         const float2* Wt = tp + N + M;
         const double q0 = A.q[2 * inst], q1 = A.q[2 * inst + 1];
 
-        // Fisher-Yates start at total S^z = 0 (Philox tag 1, counter a = chain id)
-        if (lane == 0) {
-            for (int i = 0; i < N; ++i) row[i] = (i < N / 2) ? 1 : -1;
-            for (int k = N - 1; k >= 1; --k) {
-                const int m = draw_index(draw(A.seed, (uint32_t)g, (uint64_t)k, 1u).x, k + 1);
-                const int8_t t = row[k];
-                row[k] = row[m];
-                row[m] = t;
+        // Fisher-Yates start at total S^z = 0 (Philox tag 1, counter a = chain id): 64 exchange partners are drawn at
+        // once, one per lane; the exchanges themselves run on one wave-uniform word (N <= 64) or on the LDS bytes
+        uint64_t ups = (1ull << (N / 2)) - 1ull;
+        if (!ONE)
+            for (int i = lane; i < N; i += kWave) row[i] = (i < N / 2) ? 1 : -1;
+        for (int c0 = (N - 1) & ~63; c0 >= 0; c0 -= 64) {
+            const int part = draw_index(draw(A.seed, (uint32_t)g, (uint64_t)(c0 + lane), 1u).x, c0 + lane + 1);
+            for (int k = min(63, N - 1 - c0); k >= (c0 == 0 ? 1 : 0); --k) {
+                const int m = __builtin_amdgcn_readlane(part, k);
+                if (ONE) {
+                    const uint64_t x = ((ups >> k) ^ (ups >> m)) & 1ull;
+                    ups ^= (x << k) | (x << m);
+                } else {
+                    const int8_t vk = row[c0 + k], vm = row[m];
+                    if (lane == 0) { row[c0 + k] = vm; row[m] = vk; }
+                }
             }
         }
+        if (ONE && lane < N) row[lane] = ((ups >> lane) & 1ull) ? 1 : -1;
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        BatchedChain<E, PAIR, ONE> c;
-        c.sp.load(row, N, lane);
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            const int site = qq * kWave + lane;
-            c.ag[qq] = site < N ? A.gs.a[site].x : 0.f;
-        }
+        BatchedChain<E> c;
 
-        // theta of psi_gs and of t~_inst from the spins (lanes past M: theta = 0, see proposal_dlog)
+        // theta of psi_gs and of t~_inst from the spins (lanes past M: theta = 0, see units_dlog)
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int k = e * kWave + lane;
             c.thg[e] = (k < M) ? A.gs.b[k] : make_float2(0.f, 0.f);
             c.tht[e] = (k < M) ? bt[k] : make_float2(0.f, 0.f);
         }
-#pragma unroll 2
+        const MatRows Wg = mat_rows(A.gs.W, N, M), Wtr = mat_rows(Wt, N, M);
+        unsigned loff[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) loff[e] = (unsigned)min(e * kWave + lane, M - 1) * (unsigned)sizeof(float2);
+        float2 wi[E], wj[E];
+#pragma unroll 4
         for (int i = 0; i < N; ++i) {
-            const float si = (float)c.sp.get(i);
+            const float si = (float)row[i];
+            gs_rows<E, false, LDSG>(Wg, loff, s_w, i, i, lane, wi, wj);
+            float2 wt[E], none[E];
+            mat_fetch<E, false>(Wtr, loff, i, i, wt, none);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const int k = e * kWave + lane;
-                const long at_ik = (long)i * M + min(k, M - 1);
-                const float2 wg = A.gs.W[at_ik], wt = Wt[at_ik];
-                const float s = (k < M) ? si : 0.f;
-                c.thg[e].x = fmaf(s, wg.x, c.thg[e].x);
-                c.thg[e].y = fmaf(s, wg.y, c.thg[e].y);
-                c.tht[e].x = fmaf(s, wt.x, c.tht[e].x);
-                c.tht[e].y = fmaf(s, wt.y, c.tht[e].y);
+                const float s = (e * kWave + lane < M) ? si : 0.f;
+                c.thg[e].x = fmaf(s, wi[e].x, c.thg[e].x);
+                c.thg[e].y = fmaf(s, wi[e].y, c.thg[e].y);
+                c.tht[e].x = fmaf(s, wt[e].x, c.tht[e].x);
+                c.tht[e].y = fmaf(s, wt[e].y, c.tht[e].y);
             }
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) c.Lg[e] = re_log2cosh_fast(c.thg[e]);
         // phases e^{-i q.r} of this lane's sites (q.r reduced to [-pi, pi] in double, then cos_sin of
-        // the float, accurate there) and a_t - a_gs there
-        float2 ph[4], da[4];
+        // the float, accurate there)
+        constexpr int Q = ONE ? 1 : 4;             // slots of 64 sites
+        float2 ph[Q], da1 = make_float2(0.f, 0.f);
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
+        for (int qq = 0; qq < Q; ++qq) {
             const int site = qq * kWave + lane;
             ph[qq] = make_float2(0.f, 0.f);
-            da[qq] = make_float2(0.f, 0.f);
             if (site < N) {
-                da[qq] = csub(at[site], A.gs.a[site]);
+                if (ONE) da1 = csub(at[site], A.gs.a[site]);
                 const int x = A.kind == 0 ? site : site % A.Lx;
                 const int y = A.kind == 0 ? 0 : site / A.Lx;
                 const double arg = q0 * x + q1 * y;
@@ -383,22 +291,88 @@ void k_batched(BatchedArgs A) {
         }
         const double2 beta = A.betas[inst];
         c.pm = 0.f;
-        c.lu = c.thp = c.thm = 0.f;
-        c.acc = 0;
         c.m0 = c.mr = c.mi = 0.0;
         uint32_t* trow = A.trace ? A.trace + (long)g * A.trace_words : nullptr;
         const int total = (A.n_burn + A.n_sweeps) * N;   // the plan checks that it fits
-        const MatRows Wg = mat_rows(A.gs.W, N, M), Wtr = mat_rows(Wt, N, M);
-        unsigned loff[E];
+        int sw = 0, sweep_end = N;                // end of sweep sw, counted from the batch's first proposal
+        for (int t0 = 0; t0 < total; t0 += 64) {
+            // 64 proposals, one per lane, with their thresholds ln(u)/2 less the move's change of Re(a . s), for
+            // s_i = +1 (thp) and -1 (thm); up_i, up_j: the spins at the sites of each draw, wave-uniform words
+            const DrawBatch b = draw_batch(A.seed, (uint32_t)g, (uint64_t)t0, lane, N);
+            const int count = min(64, total - t0);
+            const uint64_t in_range = count == 64 ? ~0ull : (1ull << count) - 1ull;
+            uint64_t up_i = __builtin_amdgcn_ballot_w64(row[b.i] > 0);
+            uint64_t up_j = PAIR ? __builtin_amdgcn_ballot_w64(row[b.j] > 0) : 0ull;
+            const float lu = half_ln(b.u);
+            const float d2 = PAIR ? 2.f * (A.gs.a[b.i].x - A.gs.a[b.j].x) : 2.f * A.gs.a[b.i].x;
+            const float thp = lu + d2, thm = lu - d2;
+            uint64_t taken = 0, applied = 0;
+            uint64_t rest = (PAIR ? up_i ^ up_j : ~0ull) & in_range;
+            int l = rest ? __builtin_ctzll(rest) : 0;
+            int ci = __builtin_amdgcn_readlane(b.i, l), cj = __builtin_amdgcn_readlane(b.j, l);
+            gs_rows<E, PAIR, LDSG>(Wg, loff, s_w, ci, cj, lane, wi, wj);
+            for (;;) {
+                const int seg = min(count, sweep_end);
+                while (rest && l < seg) {
+                    const bool up = (up_i >> l) & 1ull;
+                    const float thr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(up ? thp : thm), l));
+                    const uint64_t after = (~0ull << l) << 1;
+                    // the differences are formed before the next rows are asked for, so that those take the same registers
+                    float2 d[E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) loff[e] = (unsigned)min(e * kWave + lane, M - 1) * (unsigned)sizeof(float2);
-        DrawBatch batch;
-        int t = 0;
-        for (int sw = 0; sw < A.n_burn + A.n_sweeps; ++sw) {
-            for (int p = 0; p < N; ++p, ++t) batched_step<E, PAIR, ONE, LDSG>(A, s_w, g, lane, t, c, Wg, Wtr, loff, trow, batch);
-            if (sw >= A.n_burn) measure(A, c, ph, da, beta, lane);
+                    for (int e = 0; e < E; ++e) {
+                        d[e] = row_delta<E, PAIR, !LDSG>(wi, wj, e, lane, M);
+                        asm volatile("" : "+v"(d[e].x), "+v"(d[e].y));
+                    }
+                    rest &= after;
+                    int next = rest ? __builtin_ctzll(rest) : l;
+                    int ni = __builtin_amdgcn_readlane(b.i, next), nj = __builtin_amdgcn_readlane(b.j, next);
+                    gs_rows<E, PAIR, LDSG>(Wg, loff, s_w, ni, nj, lane, wi, wj);
+                    const float m2si = up ? -2.f : 2.f;
+                    float Ln[E];
+                    if (units_dlog<E>(m2si, d, c.thg, c.Lg, Ln) > thr) {
+#pragma unroll
+                        for (int e = 0; e < E; ++e) { c.thg[e] = d[e]; c.Lg[e] = Ln[e]; }
+                        apply_pending<E, PAIR>(c, lane, M);
+                        mat_fetch<E, PAIR>(Wtr, loff, ci, cj, c.pti, c.ptj);
+                        c.pm = m2si;
+                        up_i ^= __builtin_amdgcn_ballot_w64(b.i == ci);
+                        if (PAIR) {
+                            up_i ^= __builtin_amdgcn_ballot_w64(b.i == cj);
+                            up_j ^= __builtin_amdgcn_ballot_w64(b.j == ci) ^ __builtin_amdgcn_ballot_w64(b.j == cj);
+                            rest = (up_i ^ up_j) & in_range & after;
+                            const int actual = rest ? __builtin_ctzll(rest) : next;
+                            if (actual != next) {
+                                next = actual;
+                                ni = __builtin_amdgcn_readlane(b.i, next);
+                                nj = __builtin_amdgcn_readlane(b.j, next);
+                                gs_rows<E, PAIR, LDSG>(Wg, loff, s_w, ni, nj, lane, wi, wj);
+                            }
+                        }
+                        taken |= 1ull << l;
+                    }
+                    l = next;
+                    ci = ni;
+                    cj = nj;
+                }
+                if (seg == sweep_end) {
+                    if (sw >= A.n_burn) {
+                        apply_moves<PAIR>(row, taken ^ applied, b, lane);
+                        applied = taken;
+                        measure<E, PAIR, Q>(A, c, row, at, ph, da1, beta, lane);
+                    }
+                    ++sw;
+                    sweep_end += N;
+                }
+                if (seg == count) break;
+            }
+            sweep_end -= 64;
+            apply_moves<PAIR>(row, taken ^ applied, b, lane);
+            if (trow && lane == 0) {
+                trow[t0 >> 5] = (uint32_t)taken;
+                if (count > 32) trow[(t0 >> 5) + 1] = (uint32_t)(taken >> 32);
+            }
         }
-        if (total > 0) flush_accepts(c, trow, (total - 1) & ~63, total - ((total - 1) & ~63), lane);
         if (lane == 0) {
             A.partial[2 * g] = make_double2(c.m0, 0.0);
             A.partial[2 * g + 1] = make_double2(c.mr, c.mi);

@@ -3,12 +3,14 @@
 // Sampling (Sec. III): configurations s are drawn from |psi_s|^2 / <psi|psi>
 // by Metropolis chains.  One wavefront owns one chain: lane l keeps the
 // hidden units k = 64 e + l (e < E) of theta in registers together with the
-// cached Re log(2 cosh theta_k), and the spins of sites 64 q + l.  A proposal
+// cached Re log(2 cosh theta_k); the spins are bytes in LDS.  A proposal
 // touches rows W_i (and W_j), recomputes Re log(2 cosh theta'_k) per element,
 // reduces the change over the wave and accepts on u < |psi'/psi|^2; only the
 // real part of the log-amplitude is needed for the acceptance, so the
 // imaginary part (and its atan2) never enters the inner loop.  theta is
 // rebuilt from the spins at the start of every call.
+#include <algorithm>
+
 #include "device.hpp"
 #include "internal.hpp"
 #include "sweep.hpp"
@@ -71,63 +73,78 @@ hipError_t launch_init_chains(int8_t* spins, int N, int n_chains, uint64_t seed,
 }
 
 // ------------------------------------------------------------------ Metropolis sweep
-// Rows are read only for live moves (an exchange of equal spins changes nothing), and all loads of a
-// move are issued together before the first use.
-struct SweepPos {
-    long tloc;   // proposal index within this call
-    int p, sw;   // position within the sweep, sweep index
-};
-
-// One proposal: a single flip, or with PAIR an exchange of sites i and j.
-template <int E, bool PAIR>
-__device__ __forceinline__ void sweep_step(const SampleArgs& A, int chain, int lane, SweepPos& pos,
-                                           WaveSpins& sp, float2 (&th)[E], float (&L)[E], uint32_t& accepted,
-                                           uint32_t& bits, DrawBatch& batch) {
-    const int M = A.M;
-    Proposal cur = next_proposal(batch, A.seed, (uint32_t)chain, A.step_offset, pos.tloc, lane, A.N);
-    const int si = sp.get(cur.i);
-    const int sj = sp.get(cur.j);
-    if (!(PAIR && si == sj)) {
-        float2 wi[E], wj[E], tn[E];
-        float Ln[E];
-        fetch_rows<E, PAIR>(A.psi, M, cur, lane, wi, wj);
-        const float dl = proposal_dlog<E, PAIR>(cur, si, wi, wj, th, L, tn, Ln, lane, M);
-        if (cur.u < __expf(2.f * dl)) {
+// Spins of a chain as stored bytes, from its LDS row; `words`: N and the address allow four sites per store.
+__device__ __forceinline__ void store_spins(const int8_t* row, int8_t* __restrict__ out, int N, int lane, bool words) {
+    if (words) {
+        if (4 * lane < N) reinterpret_cast<int*>(out)[lane] = reinterpret_cast<const int*>(row)[lane];
+        return;
+    }
 #pragma unroll
-            for (int e = 0; e < E; ++e) { th[e] = tn[e]; L[e] = Ln[e]; }
-            sp.set(cur.i, -si, lane);
-            if (PAIR) sp.set(cur.j, -sj, lane);
-            ++accepted;
-            bits |= 1u << (pos.tloc & 31);
-        }
-    }
-    if (A.trace && ((pos.tloc & 31) == 31)) {
-        if (lane == 0) A.trace[(long)chain * A.trace_words + (pos.tloc >> 5)] = bits;
-        bits = 0;
-    }
-    ++pos.tloc;
-    if (++pos.p == A.N) {
-        if (A.samples_out) sp.store(A.samples_out + ((long)pos.sw * A.n_chains + chain) * A.N, A.N, lane);
-        pos.p = 0;
-        ++pos.sw;
+    for (int q = 0; q < 4; ++q) {
+        const int site = q * kWave + lane;
+        if (site < N) out[site] = row[site];
     }
 }
 
-template <int E, bool PAIR>
-__global__ __launch_bounds__(256) void k_sample(SampleArgs A) {
-    const int lane = threadIdx.x & 63;
-    const int chain = uniform((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-    if (chain >= A.n_chains) return;
+// Rows i (and j) of W: unit groups e < E - G from L2 (whole groups, through one descriptor of W), the last G from
+// the workgroup's copy s_w ([N][G 64], zeros past M).
+template <int E, bool PAIR, int G>
+__device__ __forceinline__ void sample_rows(__amdgpu_buffer_rsrc_t W, const float2* s_w, int M, int i, int j, int lane,
+                                            float2 (&wi)[E], float2 (&wj)[E]) {
+    const int row = M * (int)sizeof(float2);
+#pragma unroll
+    for (int e = 0; e < E - G; ++e) {
+        const unsigned off = (unsigned)(e * kWave + lane) * (unsigned)sizeof(float2);
+        wi[e] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(W, off, i * row, 0));
+        if (PAIR) wj[e] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(W, off, j * row, 0));
+    }
+#pragma unroll
+    for (int e = E - G; e < E; ++e) {
+        wi[e] = s_w[i * (G * kWave) + (e - (E - G)) * kWave + lane];
+        if (PAIR) wj[e] = s_w[j * (G * kWave) + (e - (E - G)) * kWave + lane];
+    }
+}
+
+// One wave per chain, up to 16 chains to a workgroup, which keeps the last G of the E unit groups of W in LDS.
+// 64 proposals are drawn at once, one per lane, and their liveness is kept as two wave-uniform words, the spins at
+// sites i and j of each draw: an exchange of equal spins costs nothing, an accepted move toggles the bits of the draws
+// that touch its sites, and the spin bytes are brought up to date only where a sweep or a batch ends.  The rows of the
+// next live proposal are fetched while the current one is evaluated, and again only when the current one, once
+// accepted, changed which one is next.  Few chains: bound by one move's chain of row read, transcendentals and wave
+// total; a full chip: by VALU issue (15 instructions per unit and move, three of them transcendental).
+// Before, a move read its rows from L2 and waited for them, and every null move took the scalar path.
+// 1,024 chains, 256 sweeps, N = 40, M = 80: 3.89 to 1.39 ms; 4,096 chains, 128 sweeps, N = 100, M = 400: 12.64 to 8.09 ms.
+template <int E, bool PAIR, int G>
+__global__ __launch_bounds__(1024) void k_sample(SampleArgs A) {
+    extern __shared__ float2 s_w[];               // [N][G 64] of W, then a 256-byte spin row per wave, then Re a
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int N = A.N, M = A.M;
     const float2* __restrict__ W = A.psi.W;
-    const float2* __restrict__ av = A.psi.a;
-
-    WaveSpins sp;
-    sp.load(A.spins + (long)chain * N, N, lane);
+    constexpr int kCols = G * kWave, k0 = (E - G) * kWave;   // columns held here, the first of them
+    int8_t* const row = reinterpret_cast<int8_t*>(s_w + N * kCols) + wv * 256;
+    float* const s_a = reinterpret_cast<float*>(reinterpret_cast<int8_t*>(s_w + N * kCols) + n_waves * 256);
+    for (int i = wv; i < N; i += n_waves)
+#pragma unroll
+        for (int e = 0; e < G; ++e) {
+            const int k = k0 + e * kWave + lane;
+            s_w[i * kCols + e * kWave + lane] = k < M ? W[(long)i * M + k] : make_float2(0.f, 0.f);
+        }
+    for (int i = threadIdx.x; i < N; i += blockDim.x) s_a[i] = A.psi.a[i].x;
+    const int chain = uniform((int)(blockIdx.x * n_waves + wv));
+    const bool have = chain < A.n_chains;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int site = q * kWave + lane;
+        row[site] = have && site < N ? A.spins[(long)chain * N + site] : (int8_t)0;
+    }
+    __syncthreads();
+    if (!have) return;
 
     // theta = b + sigma W; lanes past M keep theta = 0, and their cached L is
     // the same function of the same value, so they add exactly zero below
-    float2 th[E];
+    const __amdgpu_buffer_rsrc_t Wr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float2*>(W), (short)0, N * M * (int)sizeof(float2), 0x00020000);
+    float2 th[E], wi[E], wj[E];
     float L[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -136,28 +153,102 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs A) {
     }
 #pragma unroll 4
     for (int i = 0; i < N; ++i) {
-        const float si = (float)sp.get(i);
-        const float2* Wi = W + (long)i * M;
+        const float si = (float)row[i];
+        sample_rows<E, false, G>(Wr, s_w, M, i, i, lane, wi, wj);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int k = e * kWave + lane;
-            const float2 w = Wi[min(k, M - 1)];
-            const float s = (k < M) ? si : 0.f;
-            th[e].x = fmaf(s, w.x, th[e].x);
-            th[e].y = fmaf(s, w.y, th[e].y);
+            th[e].x = fmaf(si, wi[e].x, th[e].x);
+            th[e].y = fmaf(si, wi[e].y, th[e].y);
         }
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) L[e] = re_log2cosh_fast(th[e]);
 
-    uint32_t accepted = 0, bits = 0;
+    uint32_t accepted = 0;
     const long total = (long)A.n_sweeps * N;
-    SweepPos pos{0, 0, 0};
-    DrawBatch batch;
-    while (pos.tloc < total) sweep_step<E, PAIR>(A, chain, lane, pos, sp, th, L, accepted, bits, batch);
-    if (A.trace && (total & 31) != 0 && lane == 0) A.trace[(long)chain * A.trace_words + (total >> 5)] = bits;
+    const bool words = ((N | (int)reinterpret_cast<uintptr_t>(A.samples_out)) & 3) == 0;
+    int8_t* out = A.samples_out ? A.samples_out + (long)chain * N : nullptr;
+    const long out_step = (long)A.n_chains * N;
+    int sweep_end = N;                            // end of the current sweep, counted from the batch's first proposal
+    for (long t0 = 0; t0 < total; t0 += 64) {
+        const DrawBatch b = draw_batch(A.seed, (uint32_t)chain, A.step_offset + (uint64_t)t0, lane, N);
+        const int count = (int)min((long)64, total - t0);
+        const uint64_t in_range = count == 64 ? ~0ull : (1ull << count) - 1ull;
+        uint64_t up_i = __ballot(row[b.i] > 0), up_j = PAIR ? __ballot(row[b.j] > 0) : 0ull;
+        // the move changes Re(a . s) by -s_i d2
+        const float d2 = PAIR ? 2.f * (s_a[b.i] - s_a[b.j]) : 2.f * s_a[b.i];
+        uint64_t taken = 0, applied = 0;
+        uint64_t rest = (PAIR ? up_i ^ up_j : ~0ull) & in_range;
+        auto sweeps_done = [&](int l) {           // sweeps that end at or before draw l of this batch
+            while (sweep_end <= l) {
+                if (out) {
+                    apply_moves<PAIR>(row, taken ^ applied, b, lane);
+                    applied = taken;
+                    store_spins(row, out, N, lane, words);
+                    out += out_step;
+                }
+                sweep_end += N;
+            }
+        };
+        if (rest) {
+            int l = __builtin_ctzll(rest);
+            int ci = __builtin_amdgcn_readlane(b.i, l), cj = __builtin_amdgcn_readlane(b.j, l);
+            sample_rows<E, PAIR, G>(Wr, s_w, M, ci, cj, lane, wi, wj);
+            do {
+                sweeps_done(l);
+                const float u = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(b.u), l));
+                const float dd = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d2), l));
+                const bool up = (up_i >> l) & 1ull;
+                const uint64_t after = (~0ull << l) << 1;
+                // the differences are formed before the next rows are asked for, so that those take the same registers
+                float2 d[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    d[e] = PAIR ? csub(wi[e], wj[e]) : wi[e];
+                    asm volatile("" : "+v"(d[e].x), "+v"(d[e].y));
+                }
+                rest &= after;
+                int next = rest ? __builtin_ctzll(rest) : l;
+                int ni = __builtin_amdgcn_readlane(b.i, next), nj = __builtin_amdgcn_readlane(b.j, next);
+                sample_rows<E, PAIR, G>(Wr, s_w, M, ni, nj, lane, wi, wj);
+                const float m2si = up ? -2.f : 2.f;
+                float Ln[E];
+                const float dl = units_dlog<E>(m2si, d, th, L, Ln) + (up ? -dd : dd);
+                if (u < __expf(2.f * dl)) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) { th[e] = d[e]; L[e] = Ln[e]; }
+                    up_i ^= __builtin_amdgcn_ballot_w64(b.i == ci);
+                    if (PAIR) {
+                        up_i ^= __builtin_amdgcn_ballot_w64(b.i == cj);
+                        up_j ^= __builtin_amdgcn_ballot_w64(b.j == ci) ^ __builtin_amdgcn_ballot_w64(b.j == cj);
+                        rest = (up_i ^ up_j) & in_range & after;
+                        const int actual = rest ? __builtin_ctzll(rest) : next;
+                        if (actual != next) {
+                            next = actual;
+                            ni = __builtin_amdgcn_readlane(b.i, next);
+                            nj = __builtin_amdgcn_readlane(b.j, next);
+                            sample_rows<E, PAIR, G>(Wr, s_w, M, ni, nj, lane, wi, wj);
+                        }
+                    }
+                    ++accepted;
+                    taken |= 1ull << l;
+                }
+                l = next;
+                ci = ni;
+                cj = nj;
+            } while (rest);
+        }
+        sweeps_done(count);
+        sweep_end -= 64;
+        apply_moves<PAIR>(row, taken ^ applied, b, lane);
+        if (A.trace && lane == 0) {
+            uint32_t* w = A.trace + (long)chain * A.trace_words + (t0 >> 5);
+            w[0] = (uint32_t)taken;
+            if (count > 32) w[1] = (uint32_t)(taken >> 32);
+        }
+    }
 
-    sp.store(A.spins + (long)chain * N, N, lane);
+    store_spins(row, A.spins + (long)chain * N, N, lane, ((N | (int)reinterpret_cast<uintptr_t>(A.spins)) & 3) == 0);
     if (A.n_accept && lane == 0) A.n_accept[chain] = accepted;
     if (A.theta_out) {
 #pragma unroll
@@ -175,28 +266,53 @@ __global__ __launch_bounds__(256) void k_sample(SampleArgs A) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int site = q * kWave + lane;
-            if (site < N) acc = cadd(acc, cscale(av[site], (float)sp.s[q]));
+            if (site < N) acc = cadd(acc, cscale(A.psi.a[site], (float)row[site]));
         }
         acc = wave_sum(acc);
         if (lane == 0) A.logpsi_out[chain] = acc;
     }
 }
 
+// LDS of one compute unit
+constexpr size_t kSampleLds = 160 * 1024;
+
+template <int E, bool PAIR, int G>
+static hipError_t sample_groups(const SampleArgs& A, int waves, hipStream_t stream) {
+    const size_t lds = (size_t)A.N * G * kWave * sizeof(float2) + 256 * (size_t)waves + sizeof(float) * (size_t)A.N;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_sample<E, PAIR, G>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSampleLds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_sample<E, PAIR, G>), dim3((unsigned)(((long)A.n_chains + waves - 1) / waves)), dim3(kWave * waves), lds, stream, A);
+    return hipGetLastError();
+}
+
+// Waves per workgroup: as many as give each of 256 compute units one workgroup, at most 16 (the largest workgroup).
+// Above 4,096 chains a compute unit takes several workgroups in turn, two at a time where registers and half the LDS
+// allow it.  As many unit groups of W go to LDS as fit, out of 1, 2, 3 and all: at N = 100, M = 400 three of seven
+// cut the L2 reads that a full chip was waiting on.  One group always fits (N <= 256: 128 KB).
+template <int E, bool PAIR>
+static hipError_t sample_width(const SampleArgs& A, hipStream_t stream) {
+    const int waves = A.n_chains >= 4096 ? 16 : (A.n_chains + 255) / 256;
+    const size_t budget = A.n_chains > 4096 ? kSampleLds / 2 : kSampleLds;
+    const size_t group = (size_t)A.N * kWave * sizeof(float2), rest = 256 * (size_t)waves + sizeof(float) * (size_t)A.N;
+    const int fit = std::max(1, (int)((budget - rest) / group));
+    if (fit >= E) return sample_groups<E, PAIR, E>(A, waves, stream);
+    if constexpr (E > 3) if (fit >= 3) return sample_groups<E, PAIR, 3>(A, waves, stream);
+    if constexpr (E > 2) if (fit >= 2) return sample_groups<E, PAIR, 2>(A, waves, stream);
+    return sample_groups<E, PAIR, 1>(A, waves, stream);
+}
+
 hipError_t launch_sample(const SampleArgs& args, hipStream_t stream) {
-    const int E = (args.M + kWave - 1) / kWave;
-    const dim3 grid((args.n_chains + 3) / 4), block(256);
     const bool pair = args.proposal == 1;
-    switch (E) {
-#define CRBM_CASE(e)                                                                                   \
-    case e:                                                                                            \
-        if (pair) hipLaunchKernelGGL((k_sample<e, true>), grid, block, 0, stream, args);               \
-        else hipLaunchKernelGGL((k_sample<e, false>), grid, block, 0, stream, args);                   \
-        break;
+    switch ((args.M + kWave - 1) / kWave) {
+#define CRBM_CASE(e) \
+    case e: return pair ? sample_width<e, true>(args, stream) : sample_width<e, false>(args, stream);
         CRBM_CASE(1) CRBM_CASE(2) CRBM_CASE(3) CRBM_CASE(4) CRBM_CASE(5) CRBM_CASE(6) CRBM_CASE(7) CRBM_CASE(8)
 #undef CRBM_CASE
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace crbm
