@@ -47,8 +47,10 @@ inline long lc_plane_elems(long N, long M) { return 3L * ((M + 63) / 64) * 128L 
 // bonds of the largest lattice (square, N <= 256 sites, 2 N bonds); the local-estimator kernel keeps
 // a per-wave list of the anti-aligned ones in LDS
 constexpr int kMaxBonds = 512;
-// row length of the packed sigma~ of the O^H c contraction: sites 0..N-1, then 1 (b), then zeros
-inline int sig16_row(int N) { return ((N + 1 + 15) / 16) * 16; }
+// row length (words) and bytes of the sign bits by site of the O^H c contraction: sites 0..N-1, the b row, padding to 32,
+// for samples rounded up to 64
+inline int ot_sites(int N) { return (N + 1 + 31) / 32 * 32; }
+inline size_t ot_bits_bytes(long n, int N) { return (size_t)((n + 63) / 64) * 2 * (size_t)ot_sites(N) * sizeof(uint32_t); }
 
 struct Geometry {
     int N, M, P;
@@ -141,7 +143,7 @@ struct SrWork {
     double2* S64;             // [P][P] dense double (Cholesky, may be null)
     float2* G;                // [n][2 ceil(M / 64)] scratch of the matrix-free product (its O v partials)
     uint32_t* bits;           // [n][spin_words(N)] sign bits of the samples
-    int8_t* sig16;            // [n][sig16_row(N)] sigma~ rows for the O^H c contraction
+    uint32_t* ot_bits;        // [2 ceil(n / 64)][ot_sites(N)] sign bits of sigma~ by site for the O^H c contraction
     float2* vstage;           // [P] float copy of a CG direction
     void* pack;               // packed operand planes of the matrix-core S contraction
     size_t pack_bytes;

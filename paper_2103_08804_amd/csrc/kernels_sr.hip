@@ -174,18 +174,22 @@ hipError_t launch_enum_weights(const float2* lp, long n, double2* part, double* 
 // out_c[i][j] = sum_s sigma~_i(s) y_c(s, j) with y_c(s, j) = c_c(s) conj(t~_j(s)), sigma~_N = 1 and
 // t~_M = 1: per coefficient a real (N+1) x n by n x (M+1) complex product (rows i < N are the a
 // parameters' O, row N the b parameters', the rest W's, up to conjugation and the sample weights).
-// On the matrix cores with v_mfma_f32_32x32x2f32, so products and sums stay FP32 as on the vector
-// units.  A workgroup (4 waves) owns 128 extended sites x 32 extended hidden units and a run of
-// sample chunks; per 32-sample tile it stages sigma~ as floats [site][sample] and y as [c][Re/Im][sample][unit]
-// in LDS, and wave w accumulates rows 32 w .. 32 w + 31 against the 32 columns for every coefficient
-// and both parts (64 accumulator registers for two coefficients), so that three workgroups share a
-// CU and one's staging overlaps another's products.  The tile after the current one is loaded into
-// registers while the products run.  Chunk sums are written in FP32 and added across chunks in FP64.
+// On the matrix cores: sigma~ is +-1 and exact in BF16, y (formed in binary32 as before) is the exact sum of three
+// BF16 parts, so with v_mfma_f32_32x32x16_bf16 every product is exact and only the FP32 sums round.
+// A wave owns 32 extended hidden units and SB blocks of 32 extended sites and walks a run of sample chunks, 16
+// samples per step: lane l loads T of its unit l % 32 at the eight samples 8 (l / 32) .. + 7 (half a wave reads 256
+// contiguous bytes), which is the B operand's own layout, so y needs no LDS; the A operand comes from sign bits stored
+// by site (k_spin_cols), one word per 32 samples.  The next step's T is loaded before the current step is used.  Up to
+// four waves share a workgroup and its coefficients.  Bound by reading T and writing the chunk planes (290 MB at the
+// first size below, 60 us).  Chunk sums are written in FP32 and added across chunks in FP64.
+// Against sigma~ as floats and y through LDS to v_mfma_f32_32x32x2f32, at 157 TFLOP/s the bound then: 65,536 samples,
+// N = 100, M = 400: 195 to 83 us; 8,192 samples, N = 256, M = 512: 93 to 34 us.  Errors against 64 bits are the same
+// (a matrix-free step at the first size: 4.0e-6 both).
 // coef kinds: 0 -> c = w; 1 -> c = w R; 2 -> c = w (u - mean) (u double2 [n], mean a double pair);
 //             3 -> c = 2 (1 - R) conj(R) / n; 4 -> c = w (R - u[0]) (u pointing at <R>: the centred
 //             ratio, whose contraction <O^* (R - <R>)> = <O^* R> - <O^*><R> carries no cancellation of
 //             the mean of O)
-constexpr int OM_R = 128, OM_C = 32, OM_S = 32;
+constexpr int OM_C = 32, OM_S = 32;   // units of a wave, multiple of samples of a chunk
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
@@ -212,167 +216,190 @@ __device__ __forceinline__ float2 coef_of(int kind, long s, const double* w, dou
     }
 }
 
-// sigma~ rows of the contraction, packed once per call: sites 0..N-1, then 1 (the b row), then zeros up
-// to a multiple of 16 sites, so that a thread reads its 16 sites with one aligned 16-byte load.
-__global__ void k_pack_sig16(const int8_t* __restrict__ sig, long n, int N, int row, int8_t* __restrict__ out) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * row) return;
-    const long s = e / row;
-    const int i = (int)(e % row);
-    out[e] = i < N ? sig[s * N + i] : (int8_t)(i == N ? 1 : 0);
-}
-
-// One sample tile's raw operands in registers: the tile after the current one is loaded while the
-// matrix cores work on the current one, so the loads' latency is hidden behind the products.  Thread t
-// holds sample t / 8 of the tile with sites 16 (t % 8) .. + 15 of the block and units 4 (t % 8) .. + 3.
-template <int NK>
-struct OtRaw {
-    float sg[16];   // sigma~
-    float2 t[4];    // conj(t~)
-    float2 cf;      // coefficient of sample t % 32 (t < NK * 32)
-};
-
-template <int NK>
-__device__ __forceinline__ void ot_load(OtRaw<NK>& r, int tid, int row, int M, int i0, int j0, long sb, long s_end,
-                                        const int8_t* __restrict__ sig16, const float2* __restrict__ T, int kind0,
-                                        int kind1, const double* __restrict__ w, double wdef,
-                                        const float2* __restrict__ R, const double2* __restrict__ u, const double* __restrict__ mean,
-                                        double two_over_n, int round_bf16, const double2* __restrict__ shift_b) {
-    const long s = sb + (tid >> 3);
-    const int g = tid & 7;
-    const bool in = s < s_end;
-    const int base = i0 + 16 * g;   // a multiple of 16, as is the packed row length
-    int4 v = make_int4(0, 0, 0, 0);
-    if (in && base < row) v = *reinterpret_cast<const int4*>(sig16 + s * row + base);
-    const int word[4] = {v.x, v.y, v.z, v.w};
+// Sign bits of sigma~ by site, once per call: word [s / 32][i] (ot_sites(N) words a row), bit s % 32 set where
+// sigma_i(s) = -1; the b row i = N, the rows past it and the samples past n are +1.  A wave takes 64 samples and 64 sites.
+template <bool WORDS>
+__global__ __launch_bounds__(256) void k_spin_cols(const int8_t* __restrict__ sig, long n, int N, int sites,
+                                                   uint32_t* __restrict__ bits) {
+    const int lane = threadIdx.x & 63;
+    const long blk = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blk * 64 >= n) return;
+    const long s = blk * 64 + lane;
+    const bool in = s < n;
+    const int8_t* row = sig + (in ? s : 0) * N;
+    const int c0 = 64 * blockIdx.y, len = min(64, N - c0);
+    uint64_t mine = 0;
+    if (WORDS) {   // rows start on 4 bytes and N is a multiple of 4
+#pragma unroll 4
+        for (int i = 0; i < len; i += 4) {
+            const uint32_t x = in ? *reinterpret_cast<const uint32_t*>(row + c0 + i) : 0u;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) r.sg[k] = (float)(int8_t)(word[k >> 2] >> (8 * (k & 3)));
-    const float2* trow = T + s * M;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int j = j0 + 4 * g + k;
-        float2 t = make_float2(0.f, 0.f);
-        if (in && j <= M) t = (j == M) ? make_float2(1.f, 0.f) : trow[j];
-        if (shift_b && in && j < M) {
-            const double2 c = shift_b[j];
-            t = make_float2(t.x - (float)c.x, t.y - (float)c.y);
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t m = __builtin_amdgcn_ballot_w64((x >> (8 * k + 7)) & 1u);
+                if (lane == i + k) mine = m;
+            }
         }
-        if (round_bf16) t = make_float2(round_to_bf16(t.x), round_to_bf16(t.y));
-        r.t[k] = cconj(t);
-    }
-    r.cf = make_float2(0.f, 0.f);
-    if (tid < NK * OM_S) {
-        const long sc = sb + tid % OM_S;
-        if (sc < s_end) r.cf = coef_of(tid / OM_S == 0 ? kind0 : kind1, sc, w, wdef, R, u, mean, two_over_n);
-    }
-}
-
-// Stage one tile from registers into LDS (two barriers), then issue the loads of the tile after it.
-template <int NK>
-__device__ __forceinline__ void ot_stage(OtRaw<NK>& raw, float (&sA)[OM_S][OM_R + 4],
-                                         float (&sY)[NK][2][OM_S][OM_C], float2 (&sC)[NK][OM_S], int tid, int row,
-                                         int M, int i0, int j0, long sb, long s_end, const int8_t* __restrict__ sig16,
-                                         const float2* __restrict__ T, int kind0, int kind1,
-                                         const double* __restrict__ w, double wdef, const float2* __restrict__ R,
-                                         const double2* __restrict__ u, const double* __restrict__ mean,
-                                         double two_over_n, int round_bf16,
-                                         const double2* __restrict__ shift_b) {
-    const int ss = tid >> 3, g = tid & 7;
-    if (tid < NK * OM_S) sC[tid / OM_S][tid % OM_S] = raw.cf;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) sA[ss][16 * g + k] = raw.sg[k];
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < NK; ++c) {
-        const float2 cf = sC[c][ss];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float2 y = cmul(raw.t[k], cf);
-            sY[c][0][ss][4 * g + k] = y.x;
-            sY[c][1][ss][4 * g + k] = y.y;
+    } else {
+#pragma unroll 4
+        for (int i = 0; i < len; ++i) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in && row[c0 + i] < 0);
+            if (lane == i) mine = m;
         }
     }
-    __syncthreads();
-    // the next tile's loads, in flight during the products
-    if (sb + OM_S < s_end)
-        ot_load<NK>(raw, tid, row, M, i0, j0, sb + OM_S, s_end, sig16, T, kind0, kind1, w, wdef, R, u, mean, two_over_n,
-                    round_bf16, shift_b);
+    if (c0 + lane < sites) {
+        bits[2 * blk * sites + c0 + lane] = (uint32_t)mine;
+        bits[(2 * blk + 1) * sites + c0 + lane] = (uint32_t)(mine >> 32);
+    }
 }
 
-// One coefficient vector: four waves per SIMD in 128 registers; two: three waves in 168 (no spills in
-// either, the matrix-core accumulators among the vector registers).
-template <int NK>
-__global__ __launch_bounds__(256, NK == 1 ? 4 : 3) void k_ot(int N, int M, int row, const int8_t* __restrict__ sig16,
+typedef __attribute__((__vector_size__(4 * sizeof(int)))) int ot_i32x4;
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 ot_bf16x8;
+
+// the eight BF16 spins (1 or -1) of sign bits 0..7 of x
+__device__ __forceinline__ ot_i32x4 ot_spins(uint32_t x) {
+    ot_i32x4 a;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+        a[d] = (int)(0x3F803F80u | ((x << (15 - 2 * d)) & 0x8000u) | ((x << (30 - 2 * d)) & 0x80000000u));
+    return a;
+}
+
+// The three BF16 parts (by truncation, an exact sum) of eight binary32 values; an infinity keeps to its first part.
+__device__ __forceinline__ void ot_split(const float (&y)[8], ot_i32x4 (&part)[3]) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        uint32_t p[3][2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float v = y[2 * d + k];
+            p[0][k] = __float_as_uint(v);
+            const float r1 = fabsf(v) == INFINITY ? 0.f : v - __uint_as_float(p[0][k] & 0xFFFF0000u);
+            p[1][k] = __float_as_uint(r1);
+            p[2][k] = __float_as_uint(r1 - __uint_as_float(p[1][k] & 0xFFFF0000u));
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) part[q][d] = (int)__builtin_amdgcn_perm(p[q][1], p[q][0], 0x07060302u);
+    }
+}
+
+// eight rows of T from byte offset off on (range-checked against the whole offset, which is in the vector register)
+__device__ __forceinline__ void ot_rows(__amdgpu_buffer_rsrc_t r, int off, int row_bytes, float2 (&t)[8]) {
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        t[m] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off + m * row_bytes, 0, 0));
+}
+
+template <int SB>
+__global__ __launch_bounds__(256, SB <= 2 ? 3 : 2) void k_ot(int N, int M, int sites, const uint32_t* __restrict__ bits,
                                             const float2* __restrict__ T,
-                                            long n, long chunk, int n_chunks, int kind0, int kind1,
+                                            long n, long chunk, int n_chunks, int nk, int kind0, int kind1,
                                             const double* __restrict__ w, const float2* __restrict__ R,
                                             const double2* __restrict__ u, const double* __restrict__ mean,
                                             float* __restrict__ partial, const double* __restrict__ skip, int round_bf16,
                                             const double2* __restrict__ shift_b) {
     if (skip && *skip != 0.0) return;
-    __shared__ __align__(16) float sA[OM_S][OM_R + 4];      // sigma~ [sample][site]
-    __shared__ __align__(16) float sY[NK][2][OM_S][OM_C];   // y [c][Re/Im][sample][unit]
-    __shared__ float2 sC[NK][OM_S];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int i0 = blockIdx.x * OM_R, j0 = blockIdx.y * OM_C;
+    __shared__ float2 sC[256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, half = lane >> 5, tile = blockDim.x;
+    const int b0 = blockIdx.x * SB, c = blockIdx.z % nk;
+    const int jw = (blockIdx.y * (blockDim.x >> 6) + wv) * OM_C, j = jw + (lane & 31);
+    const bool live = jw <= M, ones = jw + OM_C > M;     // wave-uniform: some unit; units at or past M
     const double wdef = 1.0 / (double)n;
     const double two_over_n = 2.0 / (double)n;
-    const int j = j0 + (lane & 31);
     const long plane = (long)(N + 1) * (M + 1);
-    // chunks ck = blockIdx.z, blockIdx.z + gridDim.z, ...: each summed in FP32 on its own
-    for (int ck = blockIdx.z; ck < n_chunks; ck += gridDim.z) {
+    const int row_bytes = M * (int)sizeof(float2), toff = 8 * half * row_bytes + j * (int)sizeof(float2);
+    float2 shift = make_float2(0.f, 0.f);
+    if (shift_b && j < M) shift = make_float2((float)shift_b[j].x, (float)shift_b[j].y);
+    const bool shifted = shift_b != nullptr;
+    const uint32_t* bw[SB];   // a block past the last reads the last one's spins and writes nothing
+#pragma unroll
+    for (int b = 0; b < SB; ++b) bw[b] = bits + min(32 * (b0 + b), sites - 32) + (lane & 31);
+    // chunks ck = z, z + planes of the grid, ...: each summed in FP32 on its own
+    for (int ck = blockIdx.z / nk; ck < n_chunks; ck += gridDim.z / nk) {
         const long s_begin = (long)ck * chunk;
         const long s_end = min(n, s_begin + chunk);
-        OtRaw<NK> raw;
-        ot_load<NK>(raw, tid, row, M, i0, j0, s_begin, s_end, sig16, T, kind0, kind1, w, wdef, R, u, mean, two_over_n,
-                    round_bf16, shift_b);
-        if (i0 + 32 * wv > N) {
-            // no extended site in this wave's rows: it only helps to stage the tiles
-            for (long sb = s_begin; sb < s_end; sb += OM_S) {
-                ot_stage<NK>(raw, sA, sY, sC, tid, row, M, i0, j0, sb, s_end, sig16, T, kind0, kind1, w, wdef, R, u,
-                             mean, two_over_n, round_bf16, shift_b);
-                __syncthreads();
-            }
-            continue;
-        }
-        f32x16 acc[NK][2];
+        f32x16 acc[SB][2];
 #pragma unroll
-        for (int c = 0; c < NK; ++c)
+        for (int b = 0; b < SB; ++b)
 #pragma unroll
             for (int ri = 0; ri < 2; ++ri)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[c][ri][v] = 0.f;
-        for (long sb = s_begin; sb < s_end; sb += OM_S) {
-            ot_stage<NK>(raw, sA, sY, sC, tid, row, M, i0, j0, sb, s_end, sig16, T, kind0, kind1, w, wdef, R, u,
-                         mean, two_over_n, round_bf16, shift_b);
-            // lane l supplies row l % 32 (A) and column l % 32 (B) at sample 2 ks + l / 32; rows past N are zeros
-#pragma unroll 4
-            for (int ks = 0; ks < OM_S / 2; ++ks) {
-                const int kk = 2 * ks + (lane >> 5);
-                const float a = sA[kk][32 * wv + (lane & 31)];
-#pragma unroll
-                for (int c = 0; c < NK; ++c)
-#pragma unroll
-                    for (int ri = 0; ri < 2; ++ri)
-                        acc[c][ri] =
-                            __builtin_amdgcn_mfma_f32_32x32x2f32(a, sY[c][ri][kk][lane & 31], acc[c][ri], 0, 0, 0);
-            }
+                for (int v = 0; v < 16; ++v) acc[b][ri][v] = 0.f;
+        for (long t0 = s_begin; t0 < s_end; t0 += tile) {
+            const long t_end = min(s_end, t0 + tile);
             __syncthreads();
+            sC[tid] = t0 + tid < t_end ? coef_of(c == 0 ? kind0 : kind1, t0 + tid, w, wdef, R, u, mean, two_over_n)
+                                       : make_float2(0.f, 0.f);
+            __syncthreads();
+            if (!live) continue;
+            // the tile's rows of T; rows past it read as zero (columns past M read the next row and are dropped at the end)
+            const __amdgpu_buffer_rsrc_t Tr = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<float2*>(T + t0 * M), (short)0, (int)(t_end - t0) * row_bytes, 0x00020000);
+            float2 t[8];
+            uint32_t word[SB];
+            ot_rows(Tr, toff, row_bytes, t);
+#pragma unroll
+            for (int b = 0; b < SB; ++b) word[b] = bw[b][(t0 >> 5) * sites];
+            const int len = (int)(t_end - t0);
+            for (int s0 = 0; s0 < len; s0 += 16) {
+                ot_i32x4 a[SB];
+#pragma unroll
+                for (int b = 0; b < SB; ++b) a[b] = ot_spins(word[b] >> ((s0 & 16) + 8 * half));
+                if ((s0 & 16) && s0 + 16 < len)
+#pragma unroll
+                    for (int b = 0; b < SB; ++b) word[b] = bw[b][((t0 + s0 + 16) >> 5) * sites];
+                if (ones)
+#pragma unroll
+                    for (int m = 0; m < 8; ++m)
+                        if (j >= M) t[m] = make_float2(1.f, 0.f);
+                if (shifted)
+#pragma unroll
+                    for (int m = 0; m < 8; ++m) t[m] = csub(t[m], shift);
+                if (round_bf16)
+#pragma unroll
+                    for (int m = 0; m < 8; ++m) t[m] = make_float2(round_to_bf16(t[m].x), round_to_bf16(t[m].y));
+                if ((ones || shifted) && s0 + 16 > len)   // the rows past the tile are zero again
+#pragma unroll
+                    for (int m = 0; m < 8; ++m)
+                        if (s0 + 8 * half + m >= len) t[m] = make_float2(0.f, 0.f);
+                float yx[8], yy[8];
+#pragma unroll
+                for (int m = 0; m < 8; ++m) {
+                    const float2 y = cmul(cconj(t[m]), sC[s0 + 8 * half + m]);
+                    yx[m] = y.x;
+                    yy[m] = y.y;
+                    asm volatile("" : "+v"(yx[m]), "+v"(yy[m]));   // t is free before the next rows are asked for
+                }
+                ot_rows(Tr, toff + (s0 + 16) * row_bytes, row_bytes, t);
+                __builtin_amdgcn_sched_barrier(0);   // issued here, in flight during the products
+#pragma unroll
+                for (int ri = 0; ri < 2; ++ri) {
+                    ot_i32x4 part[3];
+                    ot_split(ri == 0 ? yx : yy, part);
+#pragma unroll
+                    for (int q = 2; q >= 0; --q)
+#pragma unroll
+                        for (int b = 0; b < SB; ++b)
+                            acc[b][ri] = __builtin_amdgcn_mfma_f32_32x32x16_bf16((ot_bf16x8)a[b], (ot_bf16x8)part[q],
+                                                                               acc[b][ri], 0, 0, 0);
+                }
+            }
         }
         // accumulator element v of lane l: row 8(v/4) + 4(l/32) + v%4 of the fragment, column l % 32;
         // the chunk's FP32 sums go to planes [chunk][c][Re/Im] straight from the accumulators
+        int i0 = 32 * b0 + 4 * half;
+        asm volatile("" : "+v"(i0));   // the 16 SB row offsets are formed here, not kept through the loop over chunks
         if (j <= M) {
 #pragma unroll
-            for (int c = 0; c < NK; ++c)
+            for (int ri = 0; ri < 2; ++ri) {
+                float* out = partial + (((long)ck * nk + c) * 2 + ri) * plane + j;
 #pragma unroll
-                for (int ri = 0; ri < 2; ++ri) {
-                    float* out = partial + (((long)ck * NK + c) * 2 + ri) * plane + j;
+                for (int b = 0; b < SB; ++b)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const int i = i0 + 32 * wv + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                        if (i <= N) out[(long)i * (M + 1)] = acc[c][ri][v];
+                        const int i = i0 + 32 * b + 8 * (v >> 2) + (v & 3);
+                        if (i <= N) out[i * (M + 1)] = acc[b][ri][v];
                     }
-                }
+            }
         }
     }
 }
@@ -470,17 +497,9 @@ __global__ __launch_bounds__(256) void k_ot_reduce(int N, int M, const float* __
 // chunks); each chunk is summed in FP32 on its own, as many samples as on the vector units before.
 // The grid holds as many workgroups as the device keeps resident at once (the kernel's occupancy
 // times the CUs, so that no second, nearly empty round follows); each loops over its chunks.
-struct OtPlan { long chunk; int n_chunks; int grid_z; };
-template <int NK>
-static int ot_resident_per_cu() {
-    static int cached = 0;
-    if (!cached) {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_ot<NK>, 256, 0) != hipSuccess || nb < 1) nb = 1;
-        cached = nb;
-    }
-    return cached;
-}
+// Sites: the blocks of 32 in as few equal groups of at most 4 as hold them (SB of the kernel); units: the blocks of 32
+// in as few equal groups of at most 4 waves.
+struct OtPlan { long chunk; int n_chunks, sb, site_groups, waves, unit_groups, grid_z; };
 static void ot_chunking(long n, long& chunk, int& n_chunks) {
     chunk = (n + 255) / 256;
     chunk = ((chunk + OM_S - 1) / OM_S) * OM_S;
@@ -488,37 +507,43 @@ static void ot_chunking(long n, long& chunk, int& n_chunks) {
     n_chunks = (int)((n + chunk - 1) / chunk);
 }
 static OtPlan ot_plan(int N, int M, long n, int nk, int n_cu) {
-    long chunk;
-    int n_chunks;
-    ot_chunking(n, chunk, n_chunks);
-    const long tiles = (long)((N + 1 + OM_R - 1) / OM_R) * ((M + 1 + OM_C - 1) / OM_C);
-    const long slots = (long)n_cu * (nk == 2 ? ot_resident_per_cu<2>() : ot_resident_per_cu<1>());
-    long z = slots / tiles;
+    OtPlan p;
+    ot_chunking(n, p.chunk, p.n_chunks);
+    const int site_blocks = ot_sites(N) / 32, unit_blocks = (M + 1 + OM_C - 1) / OM_C;
+    p.site_groups = (site_blocks + 3) / 4;
+    p.sb = (site_blocks + p.site_groups - 1) / p.site_groups;
+    p.unit_groups = (unit_blocks + 3) / 4;
+    p.waves = (unit_blocks + p.unit_groups - 1) / p.unit_groups;
+    const long slots = (long)n_cu * (4 * (p.sb <= 2 ? 3 : 2) / p.waves);
+    long z = slots / ((long)p.site_groups * p.unit_groups * nk);
     if (z < 1) z = 1;
-    if (z > n_chunks) z = n_chunks;
+    if (z > p.n_chunks) z = p.n_chunks;
     // the same number of chunks for every workgroup where possible
-    z = (n_chunks + ((n_chunks + z - 1) / z) - 1) / ((n_chunks + z - 1) / z);
-    return {chunk, n_chunks, (int)z};
+    z = (p.n_chunks + ((p.n_chunks + z - 1) / z) - 1) / ((p.n_chunks + z - 1) / z);
+    p.grid_z = (int)z * nk;
+    return p;
 }
 
-// sig16: the packed sigma~ rows (k_pack_sig16) of the n samples; partial: scratch of at least
+// bits: the sign bits by site (spin_cols) of the n samples; partial: scratch of at least
 // 2 nk (N + 1)(M + 1) floats per chunk
-static hipError_t run_ot(int N, int M, const int8_t* sig16, const float2* T, long n, int kind0, int kind1, int nk,
+static hipError_t run_ot(int N, int M, const uint32_t* bits, const float2* T, long n, int kind0, int kind1, int nk,
                          const double* w, const float2* R, const double2* u, void* partial_buf, int conj0,
                          double2* out0, double2* out1, hipStream_t stream, const double* skip, Profiler* prof,
                          int n_cu, int round_bf16 = 0, const double2* shift_b = nullptr,
                          const double* mean = nullptr, const OpTail& tail = OpTail{}) {
     const OtPlan op = ot_plan(N, M, n, nk, n_cu);
-    const int row = sig16_row(N);
     float* partial = static_cast<float*>(partial_buf);
-    dim3 grid((N + 1 + OM_R - 1) / OM_R, (M + 1 + OM_C - 1) / OM_C, op.grid_z);
+    const dim3 grid(op.site_groups, op.unit_groups, op.grid_z), block(64 * op.waves);
     if (prof) prof->begin(PROF_OT, stream);
-    if (nk == 2)
-        hipLaunchKernelGGL(k_ot<2>, grid, dim3(256), 0, stream, N, M, row, sig16, T, n, op.chunk, op.n_chunks, kind0,
-                           kind1, w, R, u, mean, partial, skip, round_bf16, shift_b);
-    else
-        hipLaunchKernelGGL(k_ot<1>, grid, dim3(256), 0, stream, N, M, row, sig16, T, n, op.chunk, op.n_chunks, kind0,
-                           kind1, w, R, u, mean, partial, skip, round_bf16, shift_b);
+    switch (op.sb) {
+#define CRBM_CASE(b)                                                                                                  \
+    case b:                                                                                                           \
+        hipLaunchKernelGGL(k_ot<b>, grid, block, 0, stream, N, M, ot_sites(N), bits, T, n, op.chunk, op.n_chunks, nk, \
+                           kind0, kind1, w, R, u, mean, partial, skip, round_bf16, shift_b);                          \
+        break;
+        CRBM_CASE(1) CRBM_CASE(2) CRBM_CASE(3) CRBM_CASE(4)
+#undef CRBM_CASE
+    }
     if (prof) prof->end(stream);
     const long plane = (long)(N + 1) * (M + 1);
     hipLaunchKernelGGL(k_ot_reduce, dim3((unsigned)((plane + 63) / 64)), dim3(256), 0, stream, N, M, partial,
@@ -526,10 +551,12 @@ static hipError_t run_ot(int N, int M, const int8_t* sig16, const float2* T, lon
     return hipGetLastError();
 }
 
-static void pack_sig16(const int8_t* sig, long n, int N, int8_t* out, hipStream_t stream) {
-    const long cnt = n * (long)sig16_row(N);
-    hipLaunchKernelGGL(k_pack_sig16, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, stream, sig, n, N,
-                       sig16_row(N), out);
+static void spin_cols(const int8_t* sig, long n, int N, uint32_t* bits, hipStream_t stream) {
+    const dim3 grid((unsigned)(((n + 63) / 64 + 3) / 4), (unsigned)((ot_sites(N) + 63) / 64));
+    if (N % 4 == 0 && (reinterpret_cast<uintptr_t>(sig) & 3) == 0)
+        hipLaunchKernelGGL(k_spin_cols<true>, grid, dim3(256), 0, stream, sig, n, N, ot_sites(N), bits);
+    else
+        hipLaunchKernelGGL(k_spin_cols<false>, grid, dim3(256), 0, stream, sig, n, N, ot_sites(N), bits);
 }
 
 // sum of v over the workgroup (256 threads, four waves); thread 0 has the result
@@ -1057,7 +1084,7 @@ static hipError_t apply_op(const SrArgs& A, const SrWork& W, const double2* v, d
                                        W.scal + SC_OMV, W.n_cu, stream, skip);
         if (e != hipSuccess) return e;
         *n_dots = (int)nblk((long)(A.N + 1) * (A.M + 1), 64);
-        return run_ot(A.N, A.M, W.sig16, A.T, A.n, 2, 0, 1, A.weights, A.R, W.u, W.red, 0, y, nullptr, stream, skip,
+        return run_ot(A.N, A.M, W.ot_bits, A.T, A.n, 2, 0, 1, A.weights, A.R, W.u, W.red, 0, y, nullptr, stream, skip,
                       nullptr, W.n_cu, 0, nullptr, W.scal + SC_OMV, t);
     }
     const int nT = hemv_tiles(P);
@@ -1084,7 +1111,7 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
     double* ff = W.dots + 4 * dots_blocks(P);
     int n_ff;
     // the packed sigma~ rows serve the O^H c contraction only
-    if (!A.weights || A.solver == CRBM_SOLVER_CG_MATFREE) pack_sig16(A.samples, A.n, A.N, W.sig16, stream);
+    if (!A.weights || A.solver == CRBM_SOLVER_CG_MATFREE) spin_cols(A.samples, A.n, A.N, W.ot_bits, stream);
     // conj(<O>) and <O^* (R - <R>)>: FP32 chunk sums on the matrix cores, or in double with sample weights
     if (A.weights) {
         // runs of at least 16 samples, as many as the reduction buffer holds up to 64
@@ -1101,7 +1128,7 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
                            W.F, ff);
         e = hipGetLastError();
     } else {
-        e = run_ot(A.N, A.M, W.sig16, A.T, A.n, 0, 4, 2, A.weights, A.R,
+        e = run_ot(A.N, A.M, W.ot_bits, A.T, A.n, 0, 4, 2, A.weights, A.R,
                    reinterpret_cast<const double2*>(W.scal + SC_RM_RE), W.red, 0, W.Om, W.ORm, stream, nullptr, W.prof,
                    W.n_cu);
         n_ff = (int)nblk(P);
@@ -1119,14 +1146,14 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
                 // F from the same rounded operands: the step then solves the ridge problem of one set of
                 // vectors, min |O~ x - D|^2 + eps |x|^2.  With F from the unrounded O, the part of
                 // <O^* D> outside the span of the rounded O~ would be divided by eps.
-                e = run_ot(A.N, A.M, W.sig16, A.T, A.n, 0, 4, 2, nullptr, A.R,
+                e = run_ot(A.N, A.M, W.ot_bits, A.T, A.n, 0, 4, 2, nullptr, A.R,
                            reinterpret_cast<const double2*>(W.scal + SC_RM_RE), W.red, 1, W.Om16, W.ORm, stream,
                            nullptr, nullptr, W.n_cu, 1, W.Om + A.N);
                 if (e != hipSuccess) return e;
                 hipLaunchKernelGGL(k_make_f, dim3(n_ff), dim3(256), 0, stream, P, A.mode, 0, W.Om, W.ORm, W.scal, W.F,
                                    ff);
             } else {
-                e = run_ot(A.N, A.M, W.sig16, A.T, A.n, 0, 0, 1, nullptr, A.R, nullptr, W.red, 1, W.Om16, nullptr,
+                e = run_ot(A.N, A.M, W.ot_bits, A.T, A.n, 0, 0, 1, nullptr, A.R, nullptr, W.red, 1, W.Om16, nullptr,
                            stream, nullptr, nullptr, W.n_cu, 0, W.Om + A.N);
                 if (e != hipSuccess) return e;
             }
@@ -1213,12 +1240,12 @@ __global__ __launch_bounds__(1024) void k_loss(const float2* __restrict__ R, lon
     *loss = t / (double)n;
 }
 
-// the gradient from caller-chosen scratch: sig16 (n sig16_row(N) bytes) and the contraction's chunk planes
-static hipError_t fidelity_grad_on(const GradArgs& A, int8_t* sig16, void* partial, int n_cu, Profiler* prof,
+// the gradient from caller-chosen scratch: bits (ot_bits_bytes(n, N)) and the contraction's chunk planes
+static hipError_t fidelity_grad_on(const GradArgs& A, uint32_t* bits, void* partial, int n_cu, Profiler* prof,
                                    hipStream_t stream) {
     if (A.grad) {
-        pack_sig16(A.samples, A.n, A.N, sig16, stream);
-        hipError_t e = run_ot(A.N, A.M, sig16, A.T, A.n, 3, 0, 1, nullptr, A.R, nullptr, partial, 0, A.grad, nullptr,
+        spin_cols(A.samples, A.n, A.N, bits, stream);
+        hipError_t e = run_ot(A.N, A.M, bits, A.T, A.n, 3, 0, 1, nullptr, A.R, nullptr, partial, 0, A.grad, nullptr,
                               stream, nullptr, prof, n_cu);
         if (e != hipSuccess) return e;
     }
@@ -1227,7 +1254,7 @@ static hipError_t fidelity_grad_on(const GradArgs& A, int8_t* sig16, void* parti
 }
 
 hipError_t launch_fidelity_grad(const GradArgs& A, const SrWork& W, hipStream_t stream) {
-    return fidelity_grad_on(A, W.sig16, W.red, W.n_cu, W.prof, stream);
+    return fidelity_grad_on(A, W.ot_bits, W.red, W.n_cu, W.prof, stream);
 }
 
 // Scratch of the gradient for n samples, laid out as [sigma~ rows | 256-byte alignment | chunk planes of one
@@ -1236,14 +1263,13 @@ size_t fidelity_grad_scratch_bytes(int N, int M, long n) {
     long chunk;
     int n_chunks;
     ot_chunking(n, chunk, n_chunks);
-    const size_t rows = ((size_t)n * (size_t)sig16_row(N) + 255) / 256 * 256;
+    const size_t rows = (ot_bits_bytes(n, N) + 255) / 256 * 256;
     return rows + (size_t)n_chunks * 2 * (size_t)(N + 1) * (size_t)(M + 1) * sizeof(float);
 }
 
 hipError_t launch_fidelity_grad_scratch(const GradArgs& A, void* scratch, int n_cu, hipStream_t stream) {
-    int8_t* sig16 = static_cast<int8_t*>(scratch);
-    const size_t rows = ((size_t)A.n * (size_t)sig16_row(A.N) + 255) / 256 * 256;
-    return fidelity_grad_on(A, sig16, static_cast<unsigned char*>(scratch) + rows, n_cu, nullptr, stream);
+    const size_t rows = (ot_bits_bytes(A.n, A.N) + 255) / 256 * 256;
+    return fidelity_grad_on(A, static_cast<uint32_t*>(scratch), static_cast<unsigned char*>(scratch) + rows, n_cu, nullptr, stream);
 }
 
 }  // namespace crbm
