@@ -74,10 +74,6 @@ hipError_t launch_spin_bits(const int8_t* sig, long n, int N, uint32_t* bits, hi
         hipLaunchKernelGGL(k_spin_bits<false>, grid, dim3(256), 0, stream, sig, n, N, nw, bits);
     return hipGetLastError();
 }
-// sigma of site i from its row of sign bits
-__device__ __forceinline__ float spin_of(const uint32_t* __restrict__ row, int i) {
-    return (row[i >> 5] >> (i & 31)) & 1u ? -1.f : 1.f;
-}
 
 // ------------------------------------------------------------------ helpers
 // f_q(sigma) = N^{-1/2} sum_r exp(-i q.r) sigma_r / 2 over the wave's spins
@@ -615,63 +611,12 @@ hipError_t launch_lc_sums(const int8_t* sig, const uint32_t* bits, long n, int N
 }
 
 // ------------------------------------------------------------------ local estimators
-// A wave takes kLocalSpw consecutive samples.  Per sample it evaluates log psi, tanh theta and O
-// (lanes over the hidden units) and marks the anti-aligned bonds; then it walks the bonds once:
-// a bond's table row is read once and serves every sample of the wave in which the bond is
-// anti-aligned.  Each such (sample, bond) pair leaves its per-lane share of the factor product in a
-// per-wave LDS buffer; every 13 to 16 pairs the buffer is read back across the lanes, four lanes per pair,
-// each multiplying 16 of its 64 shares, and these lanes finish the pair (the exponential, the phase of a and
-// the f_q factors) with all pairs side by side.
-// Bound by VALU issue.  Against a reduce-scatter of eight pairs at a time over shuffles, with the shares as
-// (log |p|, p / |p|), the read-back takes a third of the instructions per pair, and a share is scaled by its
-// binary exponent (no logarithm); the masks that steer the walk and the selection of the bond factors are wave-uniform
-// and sit in scalar registers.  65,536 samples, 10 x 10, M = 400: 3.71 to 2.64 ms; 8,192 samples, 16 x 16, M = 512: 1.28 to 0.89 ms.
-constexpr int kLocalSpw = 4;       // samples per wave
-constexpr int kPairs = 16;         // pair buffer slots per wave
-constexpr int kPairRow = 68;       // share of lane l of a slot: entry 68 slot + l + l / 16 (conflict-free both ways)
-
-struct PairBuf {
-    float2 p[kPairs * kPairRow];           // shares, scaled to max(|re|, |im|) in [1/2, 1)
-    __attribute__((aligned(16))) int8_t ex[kPairs * kWave];   // their binary exponents
-    int item[kPairs];                      // sample << 16 | (first site's spin negative) << 15 | bond
-};
-
+// One sample per wave: log psi, tanh theta and O (lanes over the hidden units), the anti-aligned bonds, then the exchange
+// sum over them, eight bonds at a time.
 // a wave-uniform 64-bit value in scalar registers
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
     const uint32_t lo = (uint32_t)uniform((int)(uint32_t)v), hi = (uint32_t)uniform((int)(uint32_t)(v >> 32));
     return (uint64_t)hi << 32 | lo;
-}
-
-// this lane's share p of a pair into slot (all lanes)
-__device__ __forceinline__ void pair_push(PairBuf& b, int slot, int lane, float2 p, int item) {
-    const int e = __builtin_amdgcn_frexp_expf(fmaxf(fabsf(p.x), fabsf(p.y)));
-    b.p[slot * kPairRow + lane + (lane >> 4)] = make_float2(ldexpf(p.x, -e), ldexpf(p.y, -e));
-    b.ex[slot * kWave + lane] = (int8_t)max(min(e, 127), -128);
-    if (lane == 0) b.item[slot] = item;
-}
-
-template <int CTRL>
-__device__ __forceinline__ int dpp_int(int x) {
-    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
-}
-// product of the 64 shares of slot lane / 4, in its four lanes, as mantissa and binary exponent
-__device__ __forceinline__ float2 pair_total(const PairBuf& b, int lane, int& ex) {
-    const int g = lane >> 2, r = lane & 3;
-    const float2* row = b.p + g * kPairRow + 17 * r;
-    float2 m = row[0];
-#pragma unroll
-    for (int t = 1; t < 16; ++t) m = cmul(m, row[t]);
-    const int4 e4 = *reinterpret_cast<const int4*>(b.ex + g * kWave + 16 * r);
-    const int w[4] = {e4.x, e4.y, e4.z, e4.w};
-    ex = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        ex += (int)(int8_t)w[k] + (int)(int8_t)(w[k] >> 8) + (int)(int8_t)(w[k] >> 16) + (w[k] >> 24);
-    m = cmul(m, make_float2(dpp_move<0xB1, 0xF>(m.x), dpp_move<0xB1, 0xF>(m.y)));
-    ex += dpp_int<0xB1>(ex);
-    m = cmul(m, make_float2(dpp_move<0x4E, 0xF>(m.x), dpp_move<0x4E, 0xF>(m.y)));
-    ex += dpp_int<0x4E>(ex);
-    return m;
 }
 
 // Reduce-scatter of 8 bond shares (log |p|, p/|p|) over the wave: across lane bit 5 keep 4 of the 8,
@@ -756,35 +701,10 @@ __device__ __forceinline__ void bond_row(const Geometry& g, int bnd, int lane, f
 }
 
 // The exchange term of bond (i, j) for the sample with spin s_i = si, given the whole factor product
-// m 2^ex: J/2 d1 psi(s^ij)/psi(s) with psi(s^ij)/psi(s) = m 2^ex exp(da), da = -2 s_i (a_i - a_j) + cq
-// (cq = -sum log(1 + w_k) over the units next to a zero of cosh, whose denominators are kept out of the
-// shares), and d1 the diagonal factor of t_0 after the swap (phases: e^{-iq.r} of the sites).
-__device__ __forceinline__ float2 bond_term(const LocalArgs& A, const RbmView& pe, int i, int j, float si, float2 m, int ex,
-                                            float2 d0, float2 cq, bool with_fq, float inv_sqrt_n, const float2* phases) {
-    const Geometry& g = A.g;
-    const float2 da = cadd(cscale(csub(pe.a[i], pe.a[j]), -2.f * si), cq);
-    float sn, cs;
-    sincosf(da.y, &sn, &cs);
-    float2 rho = cscale(cmul(m, make_float2(cs, sn)), expf(da.x));
-    rho = make_float2(ldexpf(rho.x, ex), ldexpf(rho.y, ex));
-    float2 d1 = make_float2(1.f, 0.f);
-    if (with_fq) {
-        if (A.local_op) {
-            // s_0 / 2 after the swap of sites i and j (s_j = -s_i)
-            d1 = make_float2(i == 0 ? -0.5f * si : (j == 0 ? 0.5f * si : d0.x), 0.f);
-        } else {
-            // f_q(s^{ij}) = f_q(s) - N^{-1/2} s_i (e^{-iq.r_i} - e^{-iq.r_j})
-            d1 = csub(d0, cscale(csub(phases[i], phases[j]), inv_sqrt_n * si));
-        }
-    }
-    return cscale(cmul(d1, rho), 0.5f * (float)g.J);
-}
-
-// The exchange term of bond (i, j) for the sample with spin s_i = si, given the whole factor product
 // as (log |p|, phase): J/2 d1 psi(s^ij)/psi(s) with psi(s^ij)/psi(s) = exp(lm + Re da) phase
 // exp(i Im da), da = -2 s_i (a_i - a_j) + cq (cq = -sum log(1 + w_k) over the units next to a zero of
 // cosh, whose denominators are kept out of the shares), and d1 the diagonal factor of t_0 after the swap.
-__device__ __forceinline__ float2 bond_term_polar(const LocalArgs& A, const RbmView& pe, int i, int j, float si, float lm,
+__device__ __forceinline__ float2 bond_term(const LocalArgs& A, const RbmView& pe, int i, int j, float si, float lm,
                                             float2 ph, float2 d0, float2 cq, bool with_fq, float inv_sqrt_n) {
     const Geometry& g = A.g;
     const float2 da = cadd(cscale(csub(pe.a[i], pe.a[j]), -2.f * si), cq);
@@ -804,13 +724,6 @@ __device__ __forceinline__ float2 bond_term_polar(const LocalArgs& A, const RbmV
         }
     }
     return cscale(cmul(d1, rho), 0.5f * (float)g.J);
-}
-
-// the sites' phases e^{-iq.r} into LDS (all threads of the workgroup; needed for t_0 = S^z_q psi only)
-__device__ __forceinline__ void stage_phases(const LocalArgs& A, bool with_fq, float2* phases) {
-    if (with_fq && !A.local_op && threadIdx.x < A.g.N)
-        phases[threadIdx.x] = site_phase(threadIdx.x, A.g.kind, A.g.Lx, A.q0, A.q1);
-    __syncthreads();
 }
 
 // This lane's share of sum_k [log cosh theta_k - log cosh phi_k] over its hidden units, theta and phi
@@ -857,7 +770,7 @@ __device__ __forceinline__ float2 lc_diff(const float2* __restrict__ th, const f
 // the anti-aligned bonds (mask words, count).
 template <int E>
 __device__ __forceinline__ void local_sample(const LocalArgs& A, const float2* __restrict__ th1g,
-                                             const float2* __restrict__ thng, int lane, long s0, int q, int nq,
+                                             const float2* __restrict__ thng, int lane, long s,
                                              bool want_local, bool with_fq, int n_words, float2 (&tw)[E],
                                              uint64_t (&nm)[E], float2& qinv, float2& cq, float2& d0, int& n_anti,
                                              uint64_t* mask, uint64_t* sneg) {
@@ -870,11 +783,6 @@ __device__ __forceinline__ void local_sample(const LocalArgs& A, const float2* _
     cq = make_float2(0.f, 0.f);
 #pragma unroll
     for (int e = 0; e < E; ++e) { tw[e] = make_float2(0.f, 0.f); nm[e] = 0ull; }
-    if (q >= nq) {
-        if (lane < n_words) mask[lane] = sneg[lane] = 0ull;
-        return;
-    }
-    const long s = s0 + q;
     WaveSpins sp;
     sp.load(A.samples + s * N, N, lane);
     float2 t1[E], T1[E];
@@ -1136,370 +1044,16 @@ __device__ __forceinline__ void local_finish(const LocalArgs& A, const float2* _
     if (lane == 0) A.R_out[s] = R;
 }
 
-// One unit: s = sign Re z, w = exp(-2 s z) as the modulus ex and (cos, -sin) cs
-struct UnitW {
-    float s, ex;
-    float2 cs;
-    __device__ __forceinline__ float2 w() const { return make_float2(ex * cs.x, -ex * cs.y); }
-    // (1 + w) / 2, of modulus <= 1: log cosh z = s z + log of it, so that no logarithm holds a log 2 to cancel
-    __device__ __forceinline__ float2 half() const {
-        return make_float2(0.5f * __builtin_fmaf(ex, cs.x, 1.f), (-0.5f * ex) * cs.y);
-    }
-    // tanh z = s (1 - w) / (1 + w)
-    __device__ __forceinline__ float2 tanh() const {
-        const float2 t = cdiv(make_float2(__builtin_fmaf(-ex, cs.x, 1.f), ex * cs.y),
-                              make_float2(__builtin_fmaf(ex, cs.x, 1.f), -ex * cs.y));
-        return make_float2(s * t.x, s * t.y);
-    }
-};
-__device__ __forceinline__ UnitW unit_w(float2 z) {
-    UnitW u;
-    u.s = z.x >= 0.f ? 1.f : -1.f;
-    u.ex = expf(-2.f * fabsf(z.x));
-    u.cs = cos_sin(2.f * u.s * z.y);
-    return u;
-}
-__device__ __forceinline__ float log_abs2(float2 a) { return logf(a.x * a.x + a.y * a.y); }
-
-// What a wave of the wide kernel keeps of one sample: the bond-factor data of the RBM whose Hamiltonian action is
-// taken (w_k of this lane's units, the lanes whose unit has Re theta_k < 0, the lane's inverse product of the
-// denominators, the constant of those next to a zero of cosh) and, wave-uniform, the logarithms of psi_n / fit and
-// psi_{n-1} / fit and the diagonal factor of t_0.
+// One sample per wave.  Its anti-aligned bonds are taken in batches of 8 with the shares kept in registers, (log |p|,
+// p/|p|) each, and a reduce-scatter that leaves a bond to 8 lanes.  Bound by VALU issue.  The bonds come from the mask
+// words by scalar instructions, the masks that select a bond's factors sit in scalar registers, and the rows of several
+// bonds are in flight together, loaded without branches.  Four samples to a wave that read a bond's row once for all of
+// them, as wide states (M > 192) had it, kept too few waves in flight for the table reads it saved: 65,536 samples,
+// 10 x 10, M = 400: 3.71 to 2.65 ms; 8,192 samples, 16 x 16, M = 512: 1.28 to 0.74 ms.  Occupancy counts for more than rows in
+// flight or a few spilled registers: two bonds in flight at six waves per SIMD (M <= 128) or four (M > 192) against
+// four bonds at four and two: 704 against 838 us (147,456 images on 6 x 6, M = 72), 2.65 against 3.68 ms.
 template <int E>
-struct LocalSample {
-    float2 tw[E];
-    uint64_t nm[E];
-    float2 qinv, cq, d0, dn, dm;
-    int n_anti;
-};
-// One pass over the units of the three RBMs: w_k serves tanh theta, the bond factors and the log amplitudes alike
-// (log cosh z = s z + log((1 + w)/2), the factors of a lane's units multiplied and their logarithm taken once).
-template <int E>
-__device__ __forceinline__ void local_prepare(const LocalArgs& A, const float2* __restrict__ th1g,
-                                              const float2* __restrict__ thng, const float2* __restrict__ thmg, int lane,
-                                              long s0, int q, int nq, bool want_local, bool with_fq, int n_words,
-                                              LocalSample<E>& S, uint64_t* mask, uint64_t* sneg) {
-    const Geometry& g = A.g;
-    const int N = g.N, M = g.M;
-    S.n_anti = 0;
-    S.qinv = make_float2(1.f, 0.f);
-    S.cq = S.dn = S.dm = make_float2(0.f, 0.f);
-    S.d0 = make_float2(1.f, 0.f);
-#pragma unroll
-    for (int e = 0; e < E; ++e) { S.tw[e] = make_float2(0.f, 0.f); S.nm[e] = 0ull; }
-    if (q >= nq) {
-        if (lane < n_words) mask[lane] = sneg[lane] = 0ull;
-        return;
-    }
-    const long s = s0 + q;
-    const int8_t* srow = A.samples + s * N;
-    const bool want_t = A.tanh_out || A.O_out, want_r = A.cheb_mode && A.R_out, use_m = want_r && A.order >= 1;
-    const bool use_1 = want_t || want_r || A.logpsi_out;
-    const float2* thp = A.cheb_mode ? thng : th1g;
-    const RbmView& vp = A.cheb_mode ? A.psn : A.fit;
-    constexpr float kLn2 = 0.69314718055994531f;
-    float2 T1[E];
-    float2 lc1 = make_float2(0.f, 0.f);                                        // log psi of fit
-    float2 ln = make_float2(0.f, 0.f), lm = make_float2(0.f, 0.f);             // linear parts of log psi_n/fit, psi_{n-1}/fit
-    float2 p1 = make_float2(1.f, 0.f), pn = p1, pm = p1;                       // products of (1 + w) / 2
-    int cn = 0;                                                                // their count for pn
-    uint32_t k1 = 0, kp = 0, km = 0;                                           // units next to a zero of cosh
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int k = e * kWave + lane;
-        const bool in = e < E - 1 || k < M;
-        const int kk = in ? k : 0;
-        T1[e] = make_float2(0.f, 0.f);
-        float2 zp = make_float2(0.f, 0.f);
-        UnitW up{1.f, 0.f, zp};
-        if (want_local) {
-            zp = thp[s * M + kk];
-            up = unit_w(zp);
-            S.nm[e] = __ballot(in && up.s < 0.f);
-            if (in) {
-                S.tw[e] = up.w();
-                if (near_pole(zp)) kp |= 1u << e;
-                else {
-                    pn = cmul(pn, up.half());                 // |1 + w| in [0.58, 2] off the band
-                    ++cn;
-                    if (want_r) ln = cadd(ln, cscale(zp, up.s));
-                }
-            }
-        }
-        if (use_m) {
-            const float2 z = thmg[s * M + kk];
-            const UnitW u = unit_w(z);
-            if (in) {
-                if (near_pole(z)) km |= 1u << e;
-                else {
-                    pm = cmul(pm, u.half());
-                    lm = cadd(lm, cscale(z, u.s));
-                }
-            }
-        }
-        if (use_1) {
-            const bool same = want_local && !A.cheb_mode;
-            const float2 z = same ? zp : th1g[s * M + kk];
-            const UnitW u = same ? up : unit_w(z);
-            if (in) {
-                if (near_pole(z)) k1 |= 1u << e;
-                else {
-                    if (want_t) T1[e] = u.tanh();
-                    if (want_r) {
-                        const float2 l = cscale(z, u.s);
-                        p1 = cmul(p1, u.half());
-                        ln = csub(ln, l);
-                        lm = csub(lm, l);
-                    }
-                    if (A.logpsi_out) lc1 = cadd(lc1, log2cosh(z));
-                }
-            }
-        }
-    }
-    // units next to a zero of cosh, theta summed again in double
-    float2 cl = make_float2(0.f, 0.f);
-    const bool node = __ballot(kp != 0u) != 0ull;
-    while (k1) {
-        const int e = __ffs(k1) - 1;
-        k1 &= k1 - 1;
-        float2 lcr, thr;
-        pole_eval(theta_double(srow, N, M, e * kWave + lane, A.fit.b, A.fit.W), lcr, thr);
-        lc1 = cadd(lc1, make_float2(lcr.x + kLn2, lcr.y));
-        ln = csub(ln, lcr);
-        lm = csub(lm, lcr);
-#pragma unroll
-        for (int ee = 0; ee < E; ++ee)
-            if (ee == e) T1[ee] = thr;
-    }
-    while (kp) {
-        const int e = __ffs(kp) - 1;
-        kp &= kp - 1;
-        const double2 td = theta_double(srow, N, M, e * kWave + lane, vp.b, vp.W);
-        float2 lcr, thr;
-        pole_eval(td, lcr, thr);
-        ln = cadd(ln, lcr);
-        // -log(1 + w_k) = -(log 2 - s_k theta_k + log cosh theta_k), s_k as the bond factors have it
-        const float sg = thp[s * M + e * kWave + lane].x >= 0.f ? 1.f : -1.f;
-        cl = cadd(cl, make_float2(lcr.x + kLn2 - sg * (float)td.x, lcr.y - sg * (float)td.y));
-    }
-    while (km) {
-        const int e = __ffs(km) - 1;
-        km &= km - 1;
-        float2 lcr, thr;
-        pole_eval(theta_double(srow, N, M, e * kWave + lane, A.psm.b, A.psm.W), lcr, thr);
-        lm = cadd(lm, lcr);
-    }
-    WaveSpins sp;
-    sp.load(srow, N, lane);
-    if (A.logpsi_out) {
-        const float2 lp = wave_sum(cadd(lc1, a_dot_sigma(A.fit.a, sp, lane, N)));
-        if (lane == 0) A.logpsi_out[s] = lp;
-    }
-    if (A.tanh_out) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int k = e * kWave + lane;
-            if (k < M) A.tanh_out[s * M + k] = T1[e];
-        }
-    }
-    if (A.O_out) {
-        float2* row = A.O_out + s * (long)g.P;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int site = c * kWave + lane;
-            if (site < N) row[site] = make_float2((float)sp.s[c], 0.f);
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int k = e * kWave + lane;
-            if (k < M) row[N + k] = T1[e];
-        }
-        for (int i = 0; i < N; ++i) {
-            const float si = (float)sp.get(i);
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int k = e * kWave + lane;
-                if (k < M) row[N + M + (long)i * M + k] = cscale(T1[e], si);
-            }
-        }
-    }
-    if (!want_local) return;
-    if (lane == 0) g.node_flag[s] = node ? 1 : 0;
-    if (want_r) {
-        // log(psi / fit) = a-part + linear part + log of the quotient of the products
-        const float2 as1 = a_dot_sigma(A.fit.a, sp, lane, N);
-        const float l1 = log_abs2(p1);
-        const float2 qn = cmul(pn, cconj(p1));
-        float2 d = cadd(csub(a_dot_sigma(A.psn.a, sp, lane, N), as1),
-                        make_float2(ln.x + 0.5f * (log_abs2(pn) - l1), ln.y + atan2f(qn.y, qn.x)));
-        d = wave_sum(d);
-        S.dn = make_float2(uniform(d.x), uniform(d.y));
-        if (use_m) {
-            const float2 qm = cmul(pm, cconj(p1));
-            d = cadd(csub(a_dot_sigma(A.psm.a, sp, lane, N), as1),
-                     make_float2(lm.x + 0.5f * (log_abs2(pm) - l1), lm.y + atan2f(qm.y, qm.x)));
-            d = wave_sum(d);
-            S.dm = make_float2(uniform(d.x), uniform(d.y));
-        }
-    }
-    S.qinv = cdiv(make_float2(1.f, 0.f), pn);                 // 1 / prod (1 + w): 2^-cn over the product of the halves
-    S.qinv = make_float2(ldexpf(S.qinv.x, -cn), ldexpf(S.qinv.y, -cn));
-    const float2 cq = wave_sum(make_float2(-cl.x, -cl.y));
-    S.cq = make_float2(uniform(cq.x), uniform(cq.y));   // wave-uniform: scalar registers
-    // diagonal factor of t_0: f_q (momentum q) or, with local_op, the local S^z_0 = s_0 / 2
-    if (with_fq) S.d0 = A.local_op ? make_float2(0.5f * (float)sp.get(0), 0.f) : fq_wave(sp, lane, g, A.q0, A.q1);
-    // anti-aligned bonds of the sample, and the spin of their first site
-    for (int c = 0; c < n_words; ++c) {
-        const int bnd = c * kWave + lane;
-        bool anti = false, down = false;
-        if (bnd < g.n_bonds) {
-            const int2 ij = g.bonds[bnd];
-            anti = srow[ij.x] != srow[ij.y];
-            down = srow[ij.x] < 0;
-        }
-        const uint64_t m = __ballot(anti), d = __ballot(down);
-        if (lane == 0) { mask[c] = m; sneg[c] = d; }
-        S.n_anti += __popcll(m);
-    }
-}
-
-// E_loc = the exchange terms (acc, over the lanes that hold them) plus J/4 s_i s_j over all bonds; R = phi / fit
-template <int E>
-__device__ __forceinline__ void local_close(const LocalArgs& A, int lane, long s, float2 acc, const LocalSample<E>& S) {
-    const Geometry& g = A.g;
-    const float2 eloc = cadd(wave_sum(acc), cscale(S.d0, 0.25f * (float)g.J * (float)(g.n_bonds - 2 * S.n_anti)));
-    if (A.eloc_out && lane == 0) A.eloc_out[s] = eloc;
-    if (!A.cheb_mode || !A.R_out) return;
-    const float2 ht = cscale(csub(eloc, cmul(make_float2((float)A.E_c, 0.f), S.d0)), (float)(1.0 / A.W_scale));
-    // beta enters through its logarithm, added to the log-amplitude difference before the exponential, so
-    // that neither a small beta nor a large ratio of unnormalised states leaves the binary32 range on its own
-    float2 R = cmul(ht, cexpf(cadd(S.dn, A.lbeta_n)));
-    if (A.order >= 1) {
-        float2 fm = make_float2(1.f, 0.f);
-        if (A.order == 1) {
-            WaveSpins sp;
-            sp.load(A.samples + s * g.N, g.N, lane);
-            fm = A.local_op ? make_float2(0.5f * (float)sp.get(0), 0.f) : fq_wave(sp, lane, g, A.q0, A.q1);
-        }
-        R = csub(cscale(R, 2.f), cmul(fm, cexpf(cadd(S.dm, A.lbeta_nm1))));
-    }
-    if (lane == 0) A.R_out[s] = R;
-}
-
-// finish the cnt (<= kPairs) pairs of the buffer: acc[q] += their terms
-template <int E>
-__device__ __forceinline__ void local_flush(const LocalArgs& A, const RbmView& pe, int lane, int cnt, bool with_fq,
-                                            float inv_sqrt_n, const float2* phases,
-                                            const LocalSample<E> (&S)[kLocalSpw], float2 (&acc)[kLocalSpw],
-                                            const PairBuf& buf) {
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    int ex;
-    const float2 m = pair_total(buf, lane, ex);
-    const int gq = lane >> 2;
-    if (gq < cnt) {
-        const int item = buf.item[gq];
-        const int q = item >> 16, bnd = item & 0x7FFF;
-        const int2 ij = A.g.bonds[bnd];
-        const float si = (item & 0x8000) ? -1.f : 1.f;
-        float2 d0q = S[0].d0, cqq = S[0].cq;
-#pragma unroll
-        for (int qq = 1; qq < kLocalSpw; ++qq) {
-            d0q = q == qq ? S[qq].d0 : d0q;
-            cqq = q == qq ? S[qq].cq : cqq;
-        }
-        const float2 c = bond_term(A, pe, ij.x, ij.y, si, m, ex, d0q, cqq, with_fq, inv_sqrt_n, phases);
-        if ((lane & 3) == 0)
-#pragma unroll
-            for (int qq = 0; qq < kLocalSpw; ++qq)
-                if (q == qq) acc[qq] = cadd(acc[qq], c);
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
-
-// Three waves per SIMD (registers, and the pair buffers in LDS).
-template <int E>
-__global__ __launch_bounds__(256, 3) void k_local(LocalArgs A, const float2* __restrict__ th1g,
-                                               const float2* __restrict__ thng, const float2* __restrict__ thmg) {
-    constexpr int SPW = kLocalSpw;
-    __shared__ uint64_t s_mask[4][SPW][kMaxBonds / 64], s_neg[4][SPW][kMaxBonds / 64];
-    __shared__ PairBuf s_buf[4];
-    __shared__ float2 s_phase[256];
-    const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6));
-    const long s0 = ((long)blockIdx.x * 4 + wv) * SPW;
-    const Geometry& g = A.g;
-    const bool want_local = A.eloc_out || A.R_out;
-    const bool with_fq = A.cheb_mode && A.order == 0;
-    stage_phases(A, with_fq, s_phase);
-    if (s0 >= A.n_samples) return;
-    const int N = g.N, M = g.M;
-    const int nq = (int)(A.n_samples - s0 < SPW ? A.n_samples - s0 : SPW);
-    // the RBM whose Hamiltonian action is needed
-    const RbmView& pe = A.cheb_mode ? A.psn : A.fit;
-    const int n_words = (g.n_bonds + 63) / 64;
-
-    LocalSample<E> S[SPW];
-    static_assert(SPW == 4, "the per-sample calls below are written out for 4 samples");
-#define CRBM_SAMPLE(q) local_prepare<E>(A, th1g, thng, thmg, lane, s0, q, nq, want_local, with_fq, n_words, S[q], \
-                                        s_mask[wv][q], s_neg[wv][q]);
-    CRBM_SAMPLE(0) CRBM_SAMPLE(1) CRBM_SAMPLE(2) CRBM_SAMPLE(3)
-#undef CRBM_SAMPLE
-    if (!want_local) return;
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-
-    const float inv_sqrt_n = rsqrtf((float)N);
-    float2 acc[SPW];
-#pragma unroll
-    for (int q = 0; q < SPW; ++q) acc[q] = make_float2(0.f, 0.f);
-    PairBuf& buf = s_buf[wv];
-    int cnt = 0;
-    for (int c = 0; c < n_words; ++c) {
-        uint64_t mk[SPW], sg[SPW];
-        uint64_t any = 0ull;
-#pragma unroll
-        for (int q = 0; q < SPW; ++q) {
-            mk[q] = uniform64(s_mask[wv][q][c]);
-            sg[q] = uniform64(s_neg[wv][q][c]);
-            any |= mk[q];
-        }
-        while (any) {
-            const int bit = __builtin_ctzll(any);
-            any &= any - 1ull;
-            const int bnd = c * kWave + bit;
-            float4 tq[E];
-            bond_row<E>(g, bnd, lane, tq);
-#pragma unroll
-            for (int q = 0; q < SPW; ++q) {
-                if (!((mk[q] >> bit) & 1ull)) continue;
-                const bool down = (sg[q] >> bit) & 1ull;
-                const float2 prod = bond_share<E>(tq, S[q].tw, S[q].nm, down, S[q].qinv);
-                pair_push(buf, cnt, lane, prod, (q << 16) | (down ? 0x8000 : 0) | bnd);
-                ++cnt;
-            }
-            if (cnt > kPairs - SPW) {
-                local_flush<E>(A, pe, lane, cnt, with_fq, inv_sqrt_n, s_phase, S, acc, buf);
-                cnt = 0;
-            }
-        }
-    }
-    if (cnt) local_flush<E>(A, pe, lane, cnt, with_fq, inv_sqrt_n, s_phase, S, acc, buf);
-
-    local_close<E>(A, lane, s0, acc[0], S[0]);
-    if (nq > 1) local_close<E>(A, lane, s0 + 1, acc[1], S[1]);
-    if (nq > 2) local_close<E>(A, lane, s0 + 2, acc[2], S[2]);
-    if (nq > 3) local_close<E>(A, lane, s0 + 3, acc[3], S[3]);
-}
-
-// Narrow RBMs (M <= 3 x 64): one sample per wave.  With few hidden units per lane the bookkeeping of
-// the bond-major walk costs more than the table reads it saves, so each wave walks its own sample's
-// anti-aligned bonds in batches of 8 with the shares kept in registers, (log |p|, p/|p|) each, and a
-// reduce-scatter that leaves a bond to 8 lanes.  The bonds come from the mask words by scalar instructions and
-// the rows of four bonds are in flight together.  147,456 images on 6 x 6, M = 72: 835 us per order (852 us with the
-// list of bonds and the spins read back from memory).
-template <int E>
-__global__ __launch_bounds__(256, 4) void k_local_one(LocalArgs A, const float2* __restrict__ th1g,
+__global__ __launch_bounds__(256, E <= 2 ? 6 : E == 3 ? 5 : 4) void k_local(LocalArgs A, const float2* __restrict__ th1g,
                                                    const float2* __restrict__ thng, const float2* __restrict__ thmg) {
     __shared__ uint64_t s_mask[4][kMaxBonds / 64], s_neg[4][kMaxBonds / 64];
     __shared__ short s_anti[4][kMaxBonds];
@@ -1516,7 +1070,7 @@ __global__ __launch_bounds__(256, 4) void k_local_one(LocalArgs A, const float2*
     float2 qinv, cq;
     float2 d0;
     int n_anti;
-    local_sample<E>(A, th1g, thng, lane, s, 0, 1, want_local, with_fq, n_words, TW, NM, qinv, cq, d0, n_anti,
+    local_sample<E>(A, th1g, thng, lane, s, want_local, with_fq, n_words, TW, NM, qinv, cq, d0, n_anti,
                     s_mask[wv], s_neg[wv]);
     if (!want_local) return;
     __builtin_amdgcn_wave_barrier();
@@ -1534,6 +1088,7 @@ __global__ __launch_bounds__(256, 4) void k_local_one(LocalArgs A, const float2*
     const float inv_sqrt_n = rsqrtf((float)g.N);
     const int8_t* srow = A.samples + s * g.N;
     float2 acc = make_float2(0.f, 0.f);
+    constexpr int NB = 2;   // bonds whose rows are in flight together
     int c = 0;
     uint64_t m = uniform64(s_mask[wv][0]), sg = uniform64(s_neg[wv][0]);
     for (int b0 = 0; b0 < n_anti; b0 += 8) {
@@ -1541,11 +1096,11 @@ __global__ __launch_bounds__(256, 4) void k_local_one(LocalArgs A, const float2*
         float lm[8];
         float2 ph[8];
 #pragma unroll
-        for (int h = 0; h < 8; h += 4) {
-            float4 tq[4][E];
-            bool down[4];
+        for (int h = 0; h < 8; h += NB) {
+            float4 tq[NB][E];
+            bool down[NB];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 int bit = 0;
                 if (h + b < cnt) {
                     while (!m) {
@@ -1560,7 +1115,7 @@ __global__ __launch_bounds__(256, 4) void k_local_one(LocalArgs A, const float2*
                 bond_row<E>(g, c * kWave + bit, lane, tq[b]);
             }
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 lm[h + b] = 0.f;
                 ph[h + b] = make_float2(1.f, 0.f);
                 if (h + b < cnt) {
@@ -1573,14 +1128,14 @@ __global__ __launch_bounds__(256, 4) void k_local_one(LocalArgs A, const float2*
         const int bb = b0 + (lane >> 3);
         if (bb < n_anti) {
             const int2 ij = g.bonds[lst[bb]];
-            const float2 t = bond_term_polar(A, pe, ij.x, ij.y, (float)srow[ij.x], lm[0], ph[0], d0, cq, with_fq, inv_sqrt_n);
+            const float2 t = bond_term(A, pe, ij.x, ij.y, (float)srow[ij.x], lm[0], ph[0], d0, cq, with_fq, inv_sqrt_n);
             if ((lane & 7) == 0) acc = cadd(acc, t);
         }
     }
     local_finish<E>(A, th1g, thng, thmg, lane, s, wave_sum(acc), d0, n_anti);
 }
 
-// Samples at which the local-energy RBM is next to a node (flagged by k_local / k_local_one): E_loc with
+// Samples at which the local-energy RBM is next to a node (flagged by k_local): E_loc with
 // the exchange sum in double (exchange_double) and, in Chebyshev mode, R, overwriting the binary32 values
 // of the main kernel.  A workgroup takes kNodeSpan samples and gives each flagged one to all its waves, every
 // kNodeWaves-th anti-aligned bond to a wave: flagged samples are few (some tens of 65,536 at 10 x 10, M = 400), and
@@ -1659,15 +1214,11 @@ hipError_t launch_local_core(const LocalArgs& A, const float2* th1, const float2
     const int E = (A.g.M + kWave - 1) / kWave;
     const dim3 block(256);
     const dim3 grid1((unsigned)((A.n_samples + 3) / 4));
-    const long per_block = 4L * kLocalSpw;
     const dim3 gridn((unsigned)((A.n_samples + kNodeSpan - 1) / kNodeSpan));
-    const dim3 grid4((unsigned)((A.n_samples + per_block - 1) / per_block));
     switch (E) {
-#define CRBM_ONE(e) case e: hipLaunchKernelGGL(k_local_one<e>, grid1, block, 0, stream, A, th1, thn, thm); break;
-#define CRBM_BM(e) case e: hipLaunchKernelGGL(k_local<e>, grid4, block, 0, stream, A, th1, thn, thm); break;
-        CRBM_ONE(1) CRBM_ONE(2) CRBM_ONE(3) CRBM_BM(4) CRBM_BM(5) CRBM_BM(6) CRBM_BM(7) CRBM_BM(8)
-#undef CRBM_ONE
-#undef CRBM_BM
+#define CRBM_LOCAL(e) case e: hipLaunchKernelGGL(k_local<e>, grid1, block, 0, stream, A, th1, thn, thm); break;
+        CRBM_LOCAL(1) CRBM_LOCAL(2) CRBM_LOCAL(3) CRBM_LOCAL(4) CRBM_LOCAL(5) CRBM_LOCAL(6) CRBM_LOCAL(7) CRBM_LOCAL(8)
+#undef CRBM_LOCAL
         default: return hipErrorInvalidValue;
     }
     if (A.eloc_out || A.R_out) {

@@ -2,7 +2,7 @@
 
 The theta product reads spins as sign bits, 32 sites to a word and 128 rows to a tile: chains of 30 to 256 sites
 around the word boundaries, row counts that leave partial tiles, rows that start at odd addresses.  The local
-energy takes M in groups of 64 units and changes form above 3 and above 7 groups.  Small phases, so no theta is next to
+energy takes M in groups of 64 units.  Small phases, so no theta is next to
 a zero of cosh, and 1e-5 relative holds as in the other estimator tests.  The second test has arbitrary phases and
 wide M: samples next to a node take the double-precision form; its bounds are those of rounding theta."""
 import numpy as np
