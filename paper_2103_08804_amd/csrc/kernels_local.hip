@@ -296,11 +296,45 @@ hipError_t launch_theta(const uint32_t* bits, long n, int N, int M, const ThetaS
     const long cnt = (long)Mt * TH_C * Np;
     hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256), 1, set.count), dim3(256), 0, stream, set, N, M, Np,
                        Mt, planes);
-    theta_dispatch(Np, [&](auto kc) {
-        hipLaunchKernelGGL(k_theta<kc.value>, dim3(theta_grid(n, Np, Mt * set.count, n_cu), (unsigned)Mt, set.count),
+    // W of more than 128 sites is staged in pieces anyway: pieces of 64 leave room for two workgroups per compute unit
+    // (8,192 samples, N = 256, M = 512: 68 us against 98 us in pieces of 128); up to 128 sites it is staged once
+    theta_dispatch(Np > TH_KMAX ? 64 : Np, [&](auto kc) {
+        hipLaunchKernelGGL(k_theta<kc.value>, dim3(theta_grid(n, kc.value, Mt * set.count, n_cu), (unsigned)Mt, set.count),
                            dim3(64 * TH_W), 0, stream, bits, n, Np, M, set, planes, lc_plane_elems(N, M), Mt);
     });
     return hipGetLastError();
+}
+
+// a double moved between lanes by a DPP control
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// a of this lane and of lane ^ 16 added where lane bit 4 is clear, b of the two where it is set
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) + __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+// the same swap on binary32 values: x the value of the lane with bit 4 clear, y that of its partner
+__device__ __forceinline__ float2 swap16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// rows t and t + W, t < W: a lane keeps the second where hi and adds the other lane's (CTRL) sent row
+template <int W, int CTRL>
+__device__ __forceinline__ void scatter_step(double (&px)[16], double (&py)[16], bool hi) {
+#pragma unroll
+    for (int t = 0; t < W; ++t) {
+        const double kx = hi ? px[t + W] : px[t], ky = hi ? py[t + W] : py[t];
+        const double sx = hi ? px[t] : px[t + W], sy = hi ? py[t] : py[t + W];
+        px[t] = kx + dpp_double<CTRL>(sx);
+        py[t] = ky + dpp_double<CTRL>(sy);
+    }
 }
 
 // O v of the matrix-free S product without writing G = sigma V_W + v_b: the theta product of V tile by
@@ -321,20 +355,26 @@ __device__ __forceinline__ void theta_ov_rows(const floatx16_t (&acc)[4], const 
         py[v] += (double)t[1][v].x * hy + (double)t[1][v].y * hx;
     }
     // reduce-scatter of the 16 rows over the 32 columns: lane bits 4, 3, 2, 1 halve the rows a lane
-    // keeps, bit 0 adds the last pair; the lane ends with row index 8 b4 + 4 b3 + 2 b2 + b1
+    // keeps, bit 0 adds the last pair; the lane ends with row index 8 b4 + 4 b3 + 2 b2 + b1.  Bit 4 by row swaps, which
+    // leave both addends of a kept row in its lane, the others by lane moves within a row of 16: over LDS permutes, this
+    // and the products took 40 of the kernel's 108 us (65,536 samples, N = 100, M = 400; now 71)
 #pragma unroll
-    for (int w = 8, bit = 16; w >= 1; w >>= 1, bit >>= 1) {
-        const bool hi = (lane & bit) != 0;
-#pragma unroll
-        for (int t = 0; t < w; ++t) {
-            const double kx = hi ? px[t + w] : px[t], ky = hi ? py[t + w] : py[t];
-            const double sx = hi ? px[t] : px[t + w], sy = hi ? py[t] : py[t + w];
-            px[t] = kx + __shfl_xor(sx, bit);
-            py[t] = ky + __shfl_xor(sy, bit);
-        }
+    for (int t = 0; t < 8; ++t) {
+        px[t] = swap_add(px[t], px[t + 8]);
+        py[t] = swap_add(py[t], py[t + 8]);
     }
-    px[0] += __shfl_xor(px[0], 1);
-    py[0] += __shfl_xor(py[0], 1);
+    scatter_step<4, 0x128>(px, py, (lane & 8) != 0);    // row_ror:8
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const bool hi = (lane & 4) != 0;
+        const double kx = hi ? px[t + 2] : px[t], ky = hi ? py[t + 2] : py[t];
+        const double sx = hi ? px[t] : px[t + 2], sy = hi ? py[t] : py[t + 2];
+        px[t] = kx + __shfl_xor(sx, 4);
+        py[t] = ky + __shfl_xor(sy, 4);
+    }
+    scatter_step<1, 0x4E>(px, py, (lane & 2) != 0);     // quad_perm [2, 3, 0, 1]
+    px[0] += dpp_double<0xB1>(px[0]);                   // quad_perm [1, 0, 3, 2]
+    py[0] += dpp_double<0xB1>(py[0]);
     if (lane & 1) return;
     const int v = 8 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1) + ((lane >> 1) & 1);
     const long sm = sw + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
@@ -468,14 +508,13 @@ __device__ __forceinline__ void theta_lc_rows(const floatx16_t (&acc)[4], long s
     // reduce-scatter of the 16 rows over the 32 columns (lane bits 4..1), then the last pair (bit 0):
     // lane ends with row 8 b4 + 4 b3 + 2 b2 + b1 of its half
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        const bool hi = (lane & 16) != 0;
-        const float2 kl = hi ? lin[t + 8] : lin[t], kp = hi ? pr[t + 8] : pr[t];
-        const float2 sl = hi ? lin[t] : lin[t + 8], sp = hi ? pr[t] : pr[t + 8];
-        lin[t] = kl;
-        pr[t] = kp;
-        lc_join(lin[t], pr[t], make_float2(__shfl_xor(sl.x, 16), __shfl_xor(sl.y, 16)),
-                make_float2(__shfl_xor(sp.x, 16), __shfl_xor(sp.y, 16)));
+    for (int t = 0; t < 8; ++t) {   // bit 4: the swap leaves both addends of a kept row in its lane
+        const float2 lx = swap16(lin[t].x, lin[t + 8].x), ly = swap16(lin[t].y, lin[t + 8].y);
+        const float2 px = swap16(pr[t].x, pr[t + 8].x), py = swap16(pr[t].y, pr[t + 8].y);
+        const bool hi = (lane & 16) != 0;   // there the lane's own factor is the second
+        lin[t] = make_float2(lx.x + lx.y, ly.x + ly.y);
+        pr[t] = cmul_fused(hi ? make_float2(px.y, py.y) : make_float2(px.x, py.x),
+                           hi ? make_float2(px.x, py.x) : make_float2(px.y, py.y));
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -484,8 +523,8 @@ __device__ __forceinline__ void theta_lc_rows(const floatx16_t (&acc)[4], long s
         const float2 sl = hi ? lin[t] : lin[t + 4], sp = hi ? pr[t] : pr[t + 4];
         lin[t] = kl;
         pr[t] = kp;
-        lc_join(lin[t], pr[t], make_float2(__shfl_xor(sl.x, 8), __shfl_xor(sl.y, 8)),
-                make_float2(__shfl_xor(sp.x, 8), __shfl_xor(sp.y, 8)));
+        lc_join(lin[t], pr[t], make_float2(dpp_move<0x128, 0xF>(sl.x), dpp_move<0x128, 0xF>(sl.y)),
+                make_float2(dpp_move<0x128, 0xF>(sp.x), dpp_move<0x128, 0xF>(sp.y)));
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -503,12 +542,12 @@ __device__ __forceinline__ void theta_lc_rows(const floatx16_t (&acc)[4], long s
         const float2 sl = hi ? lin[0] : lin[1], sp = hi ? pr[0] : pr[1];
         lin[0] = kl;
         pr[0] = kp;
-        lc_join(lin[0], pr[0], make_float2(__shfl_xor(sl.x, 2), __shfl_xor(sl.y, 2)),
-                make_float2(__shfl_xor(sp.x, 2), __shfl_xor(sp.y, 2)));
+        lc_join(lin[0], pr[0], make_float2(dpp_move<0x4E, 0xF>(sl.x), dpp_move<0x4E, 0xF>(sl.y)),
+                make_float2(dpp_move<0x4E, 0xF>(sp.x), dpp_move<0x4E, 0xF>(sp.y)));
     }
     {
-        const float2 pn = make_float2(__shfl_xor(pr[0].x, 1), __shfl_xor(pr[0].y, 1));
-        lin[0] = cadd(lin[0], make_float2(__shfl_xor(lin[0].x, 1), __shfl_xor(lin[0].y, 1)));
+        const float2 pn = make_float2(dpp_move<0xB1, 0xF>(pr[0].x), dpp_move<0xB1, 0xF>(pr[0].y));
+        lin[0] = cadd(lin[0], make_float2(dpp_move<0xB1, 0xF>(lin[0].x), dpp_move<0xB1, 0xF>(lin[0].y)));
         pr[0] = cmul_fused(pn, pr[0]);
     }
     if (lane & 1) return;
