@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void k_chol_load(long P, const float2* __restr
 //    the first wave alone, lane = row with the group's entries of the row in registers: the pivot and the
 //    multipliers reach all lanes through scalar registers, so the serial chain of a column (square root,
 //    reciprocal, scaling) holds no LDS round trip and no barrier.  Then all 16 waves subtract the group from the
-//    columns right of it through LDS.  bound by that chain: 36 us per block (55 us with a barrier and an LDS
+//    columns right of it through LDS.  Bound by that chain: 36 us per block (55 us with a barrier and an LDS
 //    round trip per column).
 constexpr int CH_PW = 16;
 __global__ __launch_bounds__(1024) void k_chol_diagblock(long P, long k0, int nb, double2* __restrict__ A,

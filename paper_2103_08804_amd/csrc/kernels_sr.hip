@@ -1257,18 +1257,24 @@ hipError_t launch_fidelity_grad(const GradArgs& A, const SrWork& W, hipStream_t 
     return fidelity_grad_on(A, W.ot_bits, W.red, W.n_cu, W.prof, stream);
 }
 
-// Scratch of the gradient for n samples, laid out as [sigma~ rows | 256-byte alignment | chunk planes of one
+// Bytes before the chunk planes: the sign bits, and at least a byte per extended site (16 at a time) and sample, which
+// the spins took before they were bits: the sizes that callers are told, and what the static scratch accepts, stay.
+static size_t grad_bits_bytes(long n, int N) {
+    const size_t b = std::max(ot_bits_bytes(n, N), (size_t)n * (size_t)((N + 1 + 15) / 16 * 16));
+    return (b + 255) / 256 * 256;
+}
+
+// Scratch of the gradient for n samples, laid out as [sign bits | 256-byte alignment | chunk planes of one
 // coefficient, 2 (N + 1)(M + 1) floats per sample chunk]; the chunk count depends on n only.
 size_t fidelity_grad_scratch_bytes(int N, int M, long n) {
     long chunk;
     int n_chunks;
     ot_chunking(n, chunk, n_chunks);
-    const size_t rows = (ot_bits_bytes(n, N) + 255) / 256 * 256;
-    return rows + (size_t)n_chunks * 2 * (size_t)(N + 1) * (size_t)(M + 1) * sizeof(float);
+    return grad_bits_bytes(n, N) + (size_t)n_chunks * 2 * (size_t)(N + 1) * (size_t)(M + 1) * sizeof(float);
 }
 
 hipError_t launch_fidelity_grad_scratch(const GradArgs& A, void* scratch, int n_cu, hipStream_t stream) {
-    const size_t rows = (ot_bits_bytes(A.n, A.N) + 255) / 256 * 256;
+    const size_t rows = grad_bits_bytes(A.n, A.N);
     return fidelity_grad_on(A, static_cast<uint32_t*>(scratch), static_cast<unsigned char*>(scratch) + rows, n_cu, nullptr, stream);
 }
 
