@@ -258,13 +258,17 @@ def main():
         roof["frac_of_measured"] = roof["achieved"] / ceil
     # the Metropolis sweep against its own ceilings (it has no datasheet roofline): half of the pair
     # exchanges are null moves at S^z = 0 in expectation; every other proposal evaluates M Re log 2cosh
-    # and reads the rows W_i and W_j (2 M complex64) from L2
+    # and reads the rows W_i and W_j (2 M complex64), from L2 but for the unit groups that the sweep keeps in LDS
+    # (of E = ceil(M / 64) groups all, or the last 3, 2 or 1, as many as fit beside 16 spin rows and Re a)
     sampler = None
     if "sample" in prof:
         c, t = prof["sample"]
         rate = C * sweeps * N / (t / c / 1e3)
         lc = 0.5 * rate * M
-        gb = 0.5 * rate * 2 * M * 8 / 1e9
+        groups = (M + 63) // 64
+        in_lds = max(1, (160 * 1024 - 16 * 256 - 4 * N) // (512 * N))
+        cols = 0 if in_lds >= groups else 64 * (groups - min(in_lds, 3))
+        gb = 0.5 * rate * 2 * cols * 8 / 1e9
         lc_ceil = crbm.probe_logcosh()
         g_ceil = crbm.probe_gather(N, M)
         sampler = {"proposals_per_s": rate, "logcosh_per_s": lc, "logcosh_ceiling": lc_ceil,
@@ -739,9 +743,9 @@ def cg_overhead(crbm, plan, fit, flat, T, R, wl, args, s_prec):
             out["cg_ms"] = t / c
         else:
             out["cg_ms_cap_at_iterations"] = t / c
-    out.update({"iterations": its, "cap": args.cg_maxit, "early_exit_launches": 5 * (args.cg_maxit - int(its)),
+    out.update({"iterations": its, "cap": args.cg_maxit, "early_exit_launches": 3 * (args.cg_maxit - int(its)),
                 "overhead_ms": out["cg_ms"] - out["cg_ms_cap_at_iterations"],
-                "note": ("every iteration up to the cap is enqueued (5 launches) so that the host never waits on "
+                "note": ("every iteration up to the cap is enqueued (3 launches) so that the host never waits on "
                          "a device flag; the ones after convergence return at once")})
     return out
 
