@@ -43,3 +43,28 @@ def test_sweep_edges(orc, N, M, C, sweeps, proposal, std, shift):
     assert np.array_equal(np_of(nacc).view(np.uint32), nacc_ref)
     assert rel_err(np_of(theta), psi.b[None, :] + s_ref.astype(np.float64) @ psi.W) < 1e-5
     plan.close()
+
+
+def test_sweep_in_a_graph(orc):
+    """A sweep whose copy of W takes more than 64 KB of LDS, captured on its first call and replayed."""
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    N, M, C = 100, 400, 64
+    psi = to_device_rbm(orc.RBM(*synth.random_rbm_arrays(3, N, M, 0.03, std_im=0.02)))
+    plan = crbm.Plan(crbm.CHAIN, N, 1, M, 1)
+    start = torch.zeros(C, N, dtype=torch.int8, device="cuda")
+    crbm.init_chains(plan, start, 5, True)
+    spins, out = start.clone(), torch.zeros(2, C, N, dtype=torch.int8, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        crbm.sample(plan, psi, spins, 2, crbm.EXCHANGE, 11, 0, samples_out=out)
+    want, ref = start.clone(), torch.zeros_like(out)
+    crbm.sample(plan, psi, want, 2, crbm.EXCHANGE, 11, 0, samples_out=ref)
+    for _ in range(3):
+        spins.copy_(start)
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and torch.equal(spins, want)
+    plan.close()
