@@ -87,12 +87,18 @@ struct BatchedChain {
     double m0, mr, mi;      // sums of |f|^2 and conj(f) beta r
 };
 
-// ln(u) / 2 from the hardware base-2 logarithm.  A move is accepted when u < |psi(s')/psi(s)|^2, that
-// is when the change of Re log psi exceeds ln(u) / 2: the test compares that change with this
-// threshold less the change of Re(a . s), so no exponential is taken per move (u = 0 gives -inf: accept).
-__device__ __forceinline__ float half_ln(float u) {
+// A move is accepted when u < |psi(s')/psi(s)|^2, that is when the change of its log cosh sum exceeds
+// ln(u) / 2 less the change -d of Re(a . s): the threshold ln(u) / 2 + d, with log2 u from the hardware base-2
+// logarithm, so no exponential is taken per move (u = 0 gives -inf: accept).  The last bit of a threshold decides
+// moves, and with them the rest of a chain, so its rounding is written out and not left to the compiler, which may
+// fuse in one kernel and not in another: fused, the product and the sum round once together; otherwise each by itself.
+__device__ __forceinline__ float move_threshold(float u, float d, bool fused) {
+#pragma clang fp contract(off)
     constexpr float kHalfLn2 = 0.34657359027997264f;  // ln(u)/2 = (ln 2 / 2) log2 u
-    return kHalfLn2 * __builtin_amdgcn_logf(u);
+    const float l = __builtin_amdgcn_logf(u);
+    if (fused) return __builtin_fmaf(kHalfLn2, l, d);
+    const float h = kHalfLn2 * l;
+    return h + d;
 }
 
 // log 2cosh(zt) - log 2cosh(zg) of one unit (modulo 2 pi i): with s = sign Re z and w = exp(-2 s z),
@@ -303,9 +309,8 @@ void k_batched(BatchedArgs A) {
             const uint64_t in_range = count == 64 ? ~0ull : (1ull << count) - 1ull;
             uint64_t up_i = __builtin_amdgcn_ballot_w64(row[b.i] > 0);
             uint64_t up_j = PAIR ? __builtin_amdgcn_ballot_w64(row[b.j] > 0) : 0ull;
-            const float lu = half_ln(b.u);
             const float d2 = PAIR ? 2.f * (A.gs.a[b.i].x - A.gs.a[b.j].x) : 2.f * A.gs.a[b.i].x;
-            const float thp = lu + d2, thm = lu - d2;
+            const float thp = move_threshold(b.u, d2, ONE), thm = move_threshold(b.u, -d2, ONE);
             uint64_t taken = 0, applied = 0;
             uint64_t rest = (PAIR ? up_i ^ up_j : ~0ull) & in_range;
             int l = rest ? __builtin_ctzll(rest) : 0;
@@ -565,7 +570,7 @@ __global__ __launch_bounds__(512) void k_batched_grp(BatchedArgs A) {
                     }
                     float da = m2si * ai;
                     if (PAIR) da -= m2si * aj;
-                    acc = live && (group_total<L>(ds) > half_ln(cu) - da);
+                    acc = live && (group_total<L>(ds) > move_threshold(cu, -da, true));
                     if (acc) {
 #pragma unroll
                         for (int k = 0; k < EL; ++k) { thg[k] = tn[k]; Lg[k] = Ln[k]; }
