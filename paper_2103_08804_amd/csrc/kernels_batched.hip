@@ -91,7 +91,8 @@ struct BatchedChain {
 // ln(u) / 2 less the change -d of Re(a . s): the threshold ln(u) / 2 + d, with log2 u from the hardware base-2
 // logarithm, so no exponential is taken per move (u = 0 gives -inf: accept).  The last bit of a threshold decides
 // moves, and with them the rest of a chain, so its rounding is written out and not left to the compiler, which may
-// fuse in one kernel and not in another: fused, the product and the sum round once together; otherwise each by itself.
+// fuse in one kernel and not in another: up to 64 sites (fused) the product and the sum round once together, past
+// them each by itself, the same on 64, 32 and 16 lanes, so that a chain's moves do not depend on the launch shape.
 __device__ __forceinline__ float move_threshold(float u, float d, bool fused) {
 #pragma clang fp contract(off)
     constexpr float kHalfLn2 = 0.34657359027997264f;  // ln(u)/2 = (ln 2 / 2) log2 u
@@ -570,7 +571,7 @@ __global__ __launch_bounds__(512) void k_batched_grp(BatchedArgs A) {
                     }
                     float da = m2si * ai;
                     if (PAIR) da -= m2si * aj;
-                    acc = live && (group_total<L>(ds) > move_threshold(cu, -da, true));
+                    acc = live && (group_total<L>(ds) > move_threshold(cu, -da, N <= kWave));
                     if (acc) {
 #pragma unroll
                         for (int k = 0; k < EL; ++k) { thg[k] = tn[k]; Lg[k] = Ln[k]; }
