@@ -21,10 +21,12 @@ namespace crbm {
 
 
 // device scalar slots (SC_DONE0 and SC_DONE1: whether the solve had ended before an even and an odd CG
-// iteration; SC_WSUM the sum of the sample weights; SC_OMV <O>.p of the matrix-free product, two slots)
+// iteration; SC_LATE0 and SC_LATE1: whether the iteration before left the stopping test to it, SC_LATE: whether the last
+// one left it to the end; SC_WSUM the sum of the sample weights; SC_OMV <O>.p of the matrix-free product, two slots)
 enum {
     SC_RM_RE = 0, SC_RM_IM, SC_R2, SC_GAMMA, SC_GCOT, SC_COEF,
     SC_DONE0 = 8, SC_DONE1, SC_WSUM = 11, SC_FF, SC_ITERS = 14, SC_FLAGS, SC_OMV = 18,
+    SC_LATE0 = 20, SC_LATE1, SC_LATE,
     SC_COUNT = 32
 };
 
@@ -972,14 +974,21 @@ __global__ __launch_bounds__(256) void k_cg_init(long P, const double2* __restri
 // alpha^2 |Ap|^2 (r^H r is formed from r itself in every iteration, so nothing accumulates), the convergence test
 // and p = r + beta p.  Every block adds the partials in the same order and takes the same decision; block 0
 // records it in the other of the two done slots than the one this iteration reads.
+// The new |r|^2 cancels: its terms round to within kCgSlack of r^H r + alpha^2 |Ap|^2 (up to 30 roundings in a row in
+// each dot product, and 2 alpha |r| |Ap| is at most the sum of the other two).  Where the tolerance lies within
+// that bound the test is left to the next iteration, which has the norm of r itself before it changes anything (after
+// the last one, to k_finish), and where the value does not exceed it p starts again from r: an iteration that takes
+// nearly all of the residual away (a shift far above S) would otherwise be judged by rounding noise.
 // Launches that a finished solve skips cost about 2 us each, so an iteration has 3 (dense) or 5 (matrix-free) of
 // them; with the vector updates, dot products and operand packing apart it had 5 and 12.
+constexpr double kCgSlack = 0x1p-47;
 __global__ __launch_bounds__(256) void k_cg_step(long P, double2* __restrict__ x, double2* __restrict__ r,
                                                  double2* __restrict__ p, const double2* __restrict__ Ap,
                                                  const double* __restrict__ dots, int n_dots, double* __restrict__ sc,
                                                  double tol, int maxit, int it, MfView f) {
     __shared__ double s0[4], s1[4], s2[4], s3[4];
     const int now = SC_DONE0 + (it & 1), next = SC_DONE0 + ((it + 1) & 1);
+    const int late = SC_LATE0 + (it & 1), late_next = SC_LATE0 + ((it + 1) & 1);
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     if (sc[now] != 0.0) {
         if (lead) sc[next] = 1.0;
@@ -991,11 +1000,16 @@ __global__ __launch_bounds__(256) void k_cg_step(long P, double2* __restrict__ x
         d0 += u.x; d1 += u.y; d2 += v.x; d3 += v.y;
     }
     const double rr = block_total(d0, s0), pap = block_total(d1, s1), rap = block_total(d2, s2), aa = block_total(d3, s3);
-    const double alpha = rr / pap;
-    double rn = rr - 2.0 * alpha * rap + alpha * alpha * aa;
+    const double limit = tol * sqrt(sc[SC_FF]);
+    if (sc[late] != 0.0 && sqrt(rr) <= limit) {      // converged in the iteration before
+        if (lead) sc[next] = 1.0;
+        return;
+    }
+    const double alpha = rr / pap, step2 = alpha * alpha * aa;
+    const double rn = rr - 2.0 * alpha * rap + step2, slack = kCgSlack * (rr + step2);
     const bool bad = !isfinite(rn) || !(pap > 0.0);
-    rn = fmax(rn, 0.0);
-    const bool conv = !bad && sqrt(rn) <= tol * sqrt(sc[SC_FF]);
+    const bool conv = !bad && sqrt(fmax(rn + slack, 0.0)) <= limit;
+    const bool decided = bad || conv || sqrt(fmax(rn - slack, 0.0)) > limit;
     const bool stop = bad || conv || it + 1 >= maxit;
     const long k = (long)blockIdx.x * 256 + threadIdx.x;
     double2 pk = make_double2(0.0, 0.0);
@@ -1006,7 +1020,7 @@ __global__ __launch_bounds__(256) void k_cg_step(long P, double2* __restrict__ x
         const double2 rk = make_double2(r[k].x - alpha * ak.x, r[k].y - alpha * ak.y);
         r[k] = rk;
         if (!stop) {
-            const double beta = rn / rr;
+            const double beta = rn > slack ? rn / rr : 0.0;
             pk = make_double2(rk.x + beta * pk.x, rk.y + beta * pk.y);
             p[k] = pk;
         }
@@ -1016,21 +1030,26 @@ __global__ __launch_bounds__(256) void k_cg_step(long P, double2* __restrict__ x
         mf_publish(f, k, k < P, pk, shx, shy);
     }
     if (lead) {
-        if (bad || (stop && !conv))
+        if (bad || (stop && !conv && decided))
             sc[SC_FLAGS] = (double)((int)sc[SC_FLAGS] | (bad ? CRBM_FLAG_NONFINITE : CRBM_FLAG_NOT_CONVERGED));
         sc[SC_ITERS] = (double)(it + 1);
         sc[next] = stop ? 1.0 : 0.0;
+        sc[late_next] = decided ? 0.0 : 1.0;
+        if (stop) sc[SC_LATE] = decided ? 0.0 : 1.0;
     }
 }
 
 // a, b, W += dalpha  (skipped when the step was flagged non-finite); the first block adds the residual's, the
-// solution's and F's partials and writes the statistics
+// solution's and F's partials, takes the stopping test that a last CG iteration left open, from the norm of its
+// residual r, and writes the statistics
 __global__ __launch_bounds__(256) void k_finish(int N, int M, float2* __restrict__ a, float2* __restrict__ b,
                                                 float2* __restrict__ W, const double2* __restrict__ x,
                                                 const double* __restrict__ dots, int n_dots,
                                                 const double* __restrict__ ff, int n_ff,
+                                                const double2* __restrict__ r, double tol,
                                                 const double* __restrict__ sc, double* __restrict__ out) {
-    __shared__ double s0[4], s1[4], s2[4];
+    __shared__ double s0[4], s1[4], s2[4], s3[4];
+    const long P = (long)N + M + (long)N * M;
     if (out && blockIdx.x == 0) {
         double d0 = 0.0, d1 = 0.0, d2 = 0.0;
         for (int k = threadIdx.x; k < n_dots; k += 256) {
@@ -1039,6 +1058,13 @@ __global__ __launch_bounds__(256) void k_finish(int N, int M, float2* __restrict
         }
         for (int k = threadIdx.x; k < n_ff; k += 256) d2 += ff[k];
         const double res = block_total(d0, s0), xx = block_total(d1, s1), f2 = block_total(d2, s2);
+        int flags = (int)sc[SC_FLAGS];
+        if (sc[SC_LATE] != 0.0) {
+            double d3 = 0.0;
+            for (long k = threadIdx.x; k < P; k += 256) d3 += r[k].x * r[k].x + r[k].y * r[k].y;
+            const double rr = block_total(d3, s3);
+            if (!(sqrt(rr) <= tol * sqrt(sc[SC_FF]))) flags |= CRBM_FLAG_NOT_CONVERGED;
+        }
         if (threadIdx.x == 0) {
             out[0] = sc[SC_GAMMA];
             out[1] = sc[SC_RM_RE];
@@ -1046,12 +1072,11 @@ __global__ __launch_bounds__(256) void k_finish(int N, int M, float2* __restrict
             out[3] = sqrt(f2);
             out[4] = f2 > 0.0 ? sqrt(res / f2) : 0.0;
             out[5] = sc[SC_ITERS];
-            out[6] = sc[SC_FLAGS];
+            out[6] = (double)flags;
             out[7] = sqrt(xx);
         }
     }
     if (((int)sc[SC_FLAGS] & (CRBM_FLAG_NONFINITE | CRBM_FLAG_CHOLESKY_FAIL)) != 0) return;
-    const long P = (long)N + M + (long)N * M;
     const long k = (long)blockIdx.x * 256 + threadIdx.x;
     if (k >= P) return;
     float2* dst = (k < N) ? &a[k] : (k < N + M) ? &b[k - N] : &W[k - N - M];
@@ -1219,7 +1244,7 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
     e = apply_op(A, W, W.x, W.Ap, W.F, nullptr, &n_dots, f, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_finish, dim3(nblk(P)), dim3(256), 0, stream, A.N, A.M, A.a, A.b, A.W, W.x, W.dots, n_dots, ff,
-                       n_ff, W.scal, A.stats);
+                       n_ff, W.r, A.cg_tol, W.scal, A.stats);
     return hipGetLastError();
 }
 
