@@ -1273,7 +1273,7 @@ int crbm_sbuild_autotune(crbm_plan p, const int8_t* samples, const void* tanh_th
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return fail(CRBM_EHIP, "hipEventCreate");
     const int nsplit = p->w.spart ? sbuild_splits((int)p->N, (int)p->M, n, p->w.n_cu, p->w.nsplit_max,
-                                                   p->w.sb_fold) : 1;
+                                                   p->w.sb_fold, true) : 1;
     const int nsb = sbuild_border_splits((int)p->N, (int)p->M, n, p->w.n_cu, p->w.nsb_max);
     Profiler off;
     double best = 1e300;

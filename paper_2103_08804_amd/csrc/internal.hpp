@@ -215,7 +215,7 @@ hipError_t launch_sbuild_mfma(int N, int M, long P, const int8_t* sig, const flo
                               size_t pack_bytes, const int2* order, long n_order, float2* split_buf, int nsplit,
                               float2* bx, float2* bx_part, int nsb, bool fold, Profiler* prof,
                               hipStream_t stream);
-int sbuild_splits(int N, int M, long n, int n_cu, int max_splits, bool fold);
+int sbuild_splits(int N, int M, long n, int n_cu, int max_splits, bool fold, bool bf16);
 bool sbuild_fold(int N, int M, int n_cu, int max_splits);
 int sbuild_border_splits(int N, int M, long n, int n_cu, int max_splits);
 

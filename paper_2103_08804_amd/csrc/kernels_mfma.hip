@@ -978,8 +978,15 @@ static double sbuild_rounds(int N, int M, bool fold, double w_rag, long s, long 
 
 // Number of sample splits for a contraction of n samples when the tile pairs alone cannot fill the
 // device: the split count s (at most max_splits, which the plan's slice buffer holds, and at least 4
-// K tiles per split) of the shortest modelled launch (sbuild_rounds).
-int sbuild_splits(int N, int M, long n, int n_cu, int max_splits, bool fold) {
+// K tiles per split) of the shortest modelled time, the launch (sbuild_rounds) and, in BF16, the slices: s splits write
+// and read 2 s P^2 entries that one does not, at about 3.9 TB/s, while a full pair takes 43 ns per sample on a full
+// device, so that few samples are not worth them (N = 100, M = 40, 4,000 samples: 831 us in 7 slices, 380 us in one;
+// N = 100, M = 72, 1,000 samples: 1,034 us in 2, 482 us in one).  FP32 products take ten times as long, so there the
+// slices never decide, and their sums in double keep the shorter FP32 chains.
+int sbuild_splits(int N, int M, long n, int n_cu, int max_splits, bool fold, bool bf16) {
+    constexpr double kPairPerSample = 43e-9, kSliceRate = 3.9e12;
+    const double P = (double)N + M + (double)N * M;
+    const double slice = bf16 ? 2.0 * P * P * sizeof(float2) / kSliceRate / (kPairPerSample * (double)n) : 0.0;
     const long n_kt = ((n + MK_KT - 1) / MK_KT * MK_KT) / 64;    // the finest K tile of any variant is 64
     long smax = max_splits < n_kt / 4 ? max_splits : n_kt / 4;
     if (smax < 1) smax = 1;
@@ -988,7 +995,7 @@ int sbuild_splits(int N, int M, long n, int n_cu, int max_splits, bool fold) {
     double best = 1e300;
     long bs = 1;
     for (long sp = 1; sp <= smax; ++sp) {
-        const double t = sbuild_rounds(N, M, fold, w_rag, sp, slots);
+        const double t = sbuild_rounds(N, M, fold, w_rag, sp, slots) + (sp > 1 ? slice * (double)sp : 0.0);
         if (t < best * (1.0 - 1e-9)) { best = t; bs = sp; }
     }
     return (int)bs;

@@ -1182,7 +1182,8 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
                            stream, nullptr, nullptr, W.n_cu, 0, W.Om + A.N);
                 if (e != hipSuccess) return e;
             }
-            const int nsplit = W.spart ? sbuild_splits(A.N, A.M, A.n, W.n_cu, W.nsplit_max, W.sb_fold) : 1;
+            const int nsplit = W.spart ? sbuild_splits(A.N, A.M, A.n, W.n_cu, W.nsplit_max, W.sb_fold,
+                                                       A.prec == CRBM_PREC_BF16) : 1;
             const int nsb = sbuild_border_splits(A.N, A.M, A.n, W.n_cu, W.nsb_max);
             e = launch_sbuild_mfma(A.N, A.M, P, A.samples, A.T, A.n, W.Om, W.Om16, W.S, A.prec, W.sb_kt, W.pack,
                                    W.pack_bytes, W.sb_order, W.sb_order_len,
