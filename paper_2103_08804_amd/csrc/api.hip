@@ -171,7 +171,8 @@ struct crbm_plan_s {
 
 namespace {
 // Upper bound on the sample chunks of the O^H c contraction for any n <= max_samples:
-// chunks of at least 256 samples and at least n/256 samples, so at most min(ceil(n/256), 257).
+// chunks of at least 256 samples and at least n/256 samples, so at most min(ceil(n/256), 257).  The plan's
+// buffer holds twice as many of two coefficients, for the few samples that go in chunks of 128.
 long ot_chunks_bound(long max_samples) {
     const long c = (max_samples + 255) / 256;
     return c < 257 ? c : 257;
