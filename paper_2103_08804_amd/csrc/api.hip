@@ -18,7 +18,8 @@
 namespace crbm {
 hipError_t launch_local_core(const LocalArgs& A, const float2* th1, const float2* thn, const float2* thm,
                              hipStream_t stream);
-hipError_t launch_lc_sums(const int8_t* sig, const uint32_t* bits, long n, int N, int M, const float2* a,
+// new_samples: the sign bits are written first from sig
+hipError_t launch_lc_sums(const int8_t* sig, uint32_t* bits, bool new_samples, long n, int N, int M, const float2* a,
                           const float2* b, const float2* W, uint16_t* planes, float2* partial, const double2* Lg,
                           const double2* beta, double2* B, double2* Lg_out, int n_cu, hipStream_t stream);
 hipError_t launch_fq_chunk(const Geometry& g, const uint32_t* bits, long n_s, const double* q_host, int n_q,
@@ -583,12 +584,9 @@ int crbm_local_estimators(crbm_plan p, const crbm_rbm* fit, const crbm_rbm* psi_
         set.W[k] = views[k]->W;
         set.out[k] = p->theta[k];
     }
-    hipError_t e = launch_spin_bits(samples, n, p->N, p->w.bits, stream);
-    if (e == hipSuccess) {
-        p->prof.begin(PROF_THETA, stream);
-        e = launch_theta(p->w.bits, n, p->N, p->M, set, p->wplanes, p->n_cu, stream);
-        p->prof.end(stream);
-    }
+    p->prof.begin(PROF_THETA, stream);
+    hipError_t e = launch_theta(samples, p->w.bits, n, p->N, p->M, set, p->wplanes, p->n_cu, stream);
+    p->prof.end(stream);
     if (e == hipSuccess) {
         p->prof.begin(PROF_LOCAL, stream);
         e = launch_local_core(A, p->theta[0], p->theta[1], p->theta[2], stream);
@@ -695,12 +693,10 @@ int crbm_chebyshev_moment(crbm_plan p, const crbm_rbm* gs, const void* t_params,
     const int nn = n_max + 1;
     const long P = p->P;
     const float2* tp = static_cast<const float2*>(t_params);
-    hipError_t e = launch_spin_bits(samples, n, p->N, p->w.bits, stream);
-    if (e != hipSuccess) return hip_fail(e, "chebyshev_moment launch");
     // per-sample sum log cosh theta + a.sigma of psi_gs, once; the tile partials go to theta[2]
     p->prof.begin(PROF_MOMENT, stream);
-    e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2], nullptr,
-                                  nullptr, nullptr, p->lcLg, p->n_cu, stream);
+    hipError_t e = launch_lc_sums(samples, p->w.bits, true, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2],
+                                  nullptr, nullptr, nullptr, p->lcLg, p->n_cu, stream);
     p->prof.end(stream);
     for (int q0 = 0; q0 < n_q && e == hipSuccess; q0 += kQChunk) {
         const int nq = (n_q - q0) < kQChunk ? (n_q - q0) : kQChunk;
@@ -712,7 +708,7 @@ int crbm_chebyshev_moment(crbm_plan p, const crbm_rbm* gs, const void* t_params,
             const float2* at = tp + (long)(t - 1) * P;
             // B_t = beta_t t~_t / psi_gs from the fused product and log-cosh sums
             p->prof.begin(PROF_MOMENT, stream);
-            e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, at, at + p->N, at + p->N + p->M, p->wplanes, p->theta[2],
+            e = launch_lc_sums(samples, p->w.bits, false, n, p->N, p->M, at, at + p->N, at + p->N + p->M, p->wplanes, p->theta[2],
                                p->lcLg, reinterpret_cast<const double2*>(betas) + (t - 1), p->momB, nullptr, p->n_cu, stream);
             p->prof.end(stream);
             if (e == hipSuccess)
@@ -841,19 +837,18 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
     const float2* tp = static_cast<const float2*>(t_params);
 
     // order 0: B_0 = f_q, HB_0 = (H S^z_q psi_gs)/psi_gs
-    auto theta = [&](const RbmView& v, float2* out) {
+    auto theta = [&](const int8_t* sig, const RbmView& v, float2* out) {   // sig: new samples
         ThetaSet set{};
         set.count = 1;
         set.b[0] = v.b;
         set.W[0] = v.W;
         set.out[0] = out;
         p->prof.begin(PROF_THETA, stream);
-        hipError_t r = launch_theta(p->w.bits, n, p->N, p->M, set, p->wplanes, p->n_cu, stream);
+        hipError_t r = launch_theta(sig, p->w.bits, n, p->N, p->M, set, p->wplanes, p->n_cu, stream);
         p->prof.end(stream);
         return r;
     };
-    hipError_t e = launch_spin_bits(samples, n, p->N, p->w.bits, stream);
-    if (e == hipSuccess) e = theta(vg, p->theta[0]);
+    hipError_t e = theta(samples, vg, p->theta[0]);
     if (e == hipSuccess) e = launch_fq_chunk(g, p->w.bits, n, q, 1, p->momF, stream);
     LocalArgs A{};
     A.g = g;
@@ -875,7 +870,7 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
     if (e == hipSuccess) e = launch_basis_pack(n, p->momF, loc, 0, Bm, HBm, stream);
     if (e == hipSuccess && n_max > 0) {
         p->prof.begin(PROF_MOMENT, stream);
-        e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2], nullptr, nullptr,
+        e = launch_lc_sums(samples, p->w.bits, false, n, p->N, p->M, vg.a, vg.b, vg.W, p->wplanes, p->theta[2], nullptr, nullptr,
                            nullptr, p->lcLg, p->n_cu, stream);
         p->prof.end(stream);
     }
@@ -886,7 +881,7 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
         vt.a = at;
         vt.b = at + p->N;
         vt.W = at + p->N + p->M;
-        e = theta(vt, p->theta[1]);
+        e = theta(nullptr, vt, p->theta[1]);
         LocalArgs At{};
         At.g = g;
         At.samples = samples;
@@ -900,7 +895,7 @@ int crbm_moment_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, 
         }
         if (e == hipSuccess) {
             p->prof.begin(PROF_MOMENT, stream);
-            e = launch_lc_sums(samples, p->w.bits, n, p->N, p->M, at, vt.b, vt.W, p->wplanes, p->theta[2], p->lcLg,
+            e = launch_lc_sums(samples, p->w.bits, false, n, p->N, p->M, at, vt.b, vt.W, p->wplanes, p->theta[2], p->lcLg,
                                reinterpret_cast<const double2*>(betas) + (t - 1), p->momB, nullptr, p->n_cu, stream);
             p->prof.end(stream);
         }
@@ -966,14 +961,14 @@ int crbm_sym_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, con
     const float2* tp = static_cast<const float2*>(t_params);
     const int Ly = p->lat.kind == CRBM_LATTICE_CHAIN ? 1 : p->lat.Ly;
     hipError_t e = hipSuccess;
-    auto theta = [&](long rows, const RbmView& v, float2* out) {
+    auto theta = [&](const int8_t* sig, long rows, const RbmView& v, float2* out) {   // sig: new samples
         ThetaSet set{};
         set.count = 1;
         set.b[0] = v.b;
         set.W[0] = v.W;
         set.out[0] = out;
         p->prof.begin(PROF_THETA, stream);
-        hipError_t r = launch_theta(p->w.bits, rows, N, M, set, p->wplanes, p->n_cu, stream);
+        hipError_t r = launch_theta(sig, p->w.bits, rows, N, M, set, p->wplanes, p->n_cu, stream);
         p->prof.end(stream);
         return r;
     };
@@ -988,16 +983,14 @@ int crbm_sym_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, con
         const long rows = c * ng;
         const int8_t* sig = samples + s0 * N;
         // log psi_gs of the chunk's samples
-        e = launch_spin_bits(sig, c, N, p->w.bits, stream);
-        if (e == hipSuccess) e = theta(c, vg, p->theta[2]);
+        e = theta(sig, c, vg, p->theta[2]);
         LocalArgs A0{};
         A0.g = geo; A0.fit = vg; A0.samples = sig; A0.n_samples = c; A0.logpsi_out = lg;
         if (e == hipSuccess) e = local(A0, p->theta[2]);
         // the images of every sample under the group
         if (e == hipSuccess) e = launch_sym_images(sig, c, N, p->lat.kind, p->lat.Lx, Ly, nrot, img, stream);
-        if (e == hipSuccess) e = launch_spin_bits(img, rows, N, p->w.bits, stream);
         // order 0: t_000 = S^z_0 psi_gs on the images
-        if (e == hipSuccess) e = theta(rows, vg, p->theta[0]);
+        if (e == hipSuccess) e = theta(img, rows, vg, p->theta[0]);
         LocalArgs A1{};
         A1.g = geo; A1.fit = vg; A1.psn = vg; A1.cheb_mode = 1; A1.local_op = 1; A1.order = 0; A1.W_scale = 1.0;
         A1.samples = img; A1.n_samples = rows; A1.logpsi_out = lt; A1.eloc_out = el;
@@ -1007,7 +1000,7 @@ int crbm_sym_matrices(crbm_plan p, const crbm_rbm* gs, const void* t_params, con
             const float2* at = tp + (long)(t - 1) * P;
             RbmView vt;
             vt.a = at; vt.b = at + N; vt.W = at + N + M;
-            e = theta(rows, vt, p->theta[1]);
+            e = theta(nullptr, rows, vt, p->theta[1]);
             LocalArgs At{};
             At.g = geo; At.fit = vt; At.samples = img; At.n_samples = rows; At.logpsi_out = lt; At.eloc_out = el;
             if (e == hipSuccess) e = local(At, p->theta[1]);

@@ -26,10 +26,10 @@ struct ThetaSet {
     float2* out[3];
     int count;
 };
-// theta = sigma W + b (complex64 [n][M]) on the matrix cores; planes: count x lc_plane_elems(N, M) scratch for
-// the split W
-hipError_t launch_theta(const uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes, int n_cu,
-                        hipStream_t stream);
+// theta = sigma W + b (complex64 [n][M]) on the matrix cores; bits: sign bits of the samples, written first from the spins
+// sig where that is not null; planes: count x lc_plane_elems(N, M) scratch for the split W
+hipError_t launch_theta(const int8_t* sig, uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes,
+                        int n_cu, hipStream_t stream);
 // O v of the matrix-free S product, u[s] = sum_k T_sk (sigma_s V_W + v_b)_k + sigma_s . v_a, without
 // writing the n x M product; planes: V_W split as the theta product's W; partial: n * ceil(M / 64) double2
 // scratch; mean_out <- the sum of the n_omv partials omv (a double pair)

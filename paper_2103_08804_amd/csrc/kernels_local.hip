@@ -41,11 +41,10 @@ constexpr int TH_C = 128, TH_K = 32;           // plane rows of a unit tile; sit
 constexpr int TH_W = 8, TH_S = 32 * TH_W;      // waves and samples of a workgroup's tile
 constexpr int TH_KMAX = 128;                   // sites of W staged at a time
 
-// bits[s][w]: bit b of word w set where sigma of site 32 w + b is negative; nw = ceil(N / 32) words a row
+// Word e of bits[s][w]: bit b of word w set where sigma of site 32 w + b is negative; nw = ceil(N / 32) words a row
 template <bool WORDS>
-__global__ __launch_bounds__(256) void k_spin_bits(const int8_t* __restrict__ sig, long n, int N, int nw,
-                                                   uint32_t* __restrict__ bits) {
-    const long e = (long)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void spin_word(const int8_t* __restrict__ sig, long n, int N, int nw,
+                                          uint32_t* __restrict__ bits, long e) {
     if (e >= n * nw) return;
     const long s = e / nw;
     const int i0 = 32 * (int)(e % nw), cnt = N - i0 < 32 ? N - i0 : 32;
@@ -63,12 +62,20 @@ __global__ __launch_bounds__(256) void k_spin_bits(const int8_t* __restrict__ si
     }
     bits[e] = m;
 }
+template <bool WORDS>
+__global__ __launch_bounds__(256) void k_spin_bits(const int8_t* __restrict__ sig, long n, int N, int nw,
+                                                   uint32_t* __restrict__ bits) {
+    spin_word<WORDS>(sig, n, N, nw, bits, (long)blockIdx.x * 256 + threadIdx.x);
+}
+
+// whether four sign bits may be taken from each word of four spins
+static bool spin_rows_aligned(const int8_t* sig, int N) { return N % 4 == 0 && (reinterpret_cast<uintptr_t>(sig) & 3) == 0; }
 
 hipError_t launch_spin_bits(const int8_t* sig, long n, int N, uint32_t* bits, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     const int nw = spin_words(N);
     const dim3 grid((unsigned)((n * nw + 255) / 256));
-    if (N % 4 == 0 && (reinterpret_cast<uintptr_t>(sig) & 3) == 0)
+    if (spin_rows_aligned(sig, N))
         hipLaunchKernelGGL(k_spin_bits<true>, grid, dim3(256), 0, stream, sig, n, N, nw, bits);
     else
         hipLaunchKernelGGL(k_spin_bits<false>, grid, dim3(256), 0, stream, sig, n, N, nw, bits);
@@ -116,9 +123,16 @@ __device__ __forceinline__ float2 a_dot_sigma(const float2* a, const WaveSpins& 
 // by a reduce-scatter over the lane bits and takes one complex log per sample row.
 //
 // The planes of W are [3][Mt 128][Np], Np = N rounded up to TH_K, zero padded; the product's
-// workgroups only copy tiles of them.
-__global__ __launch_bounds__(256) void k_wsplit(ThetaSet set, int N, int M, int Np, int Mt,
-                                                uint16_t* __restrict__ planes) {
+// workgroups only copy tiles of them.  With spins given (sig), the blocks past the planes' w_blocks write their sign
+// bits, so that a call on new samples has no launch of its own for them.
+template <bool WORDS>
+__global__ __launch_bounds__(256) void k_wsplit(ThetaSet set, int N, int M, int Np, int Mt, uint16_t* __restrict__ planes,
+                                                unsigned w_blocks, const int8_t* __restrict__ sig, long n, int nw,
+                                                uint32_t* __restrict__ bits) {
+    if (blockIdx.x >= w_blocks) {
+        if (blockIdx.z == 0) spin_word<WORDS>(sig, n, N, nw, bits, (long)(blockIdx.x - w_blocks) * 256 + threadIdx.x);
+        return;
+    }
     const float2* W = set.W[blockIdx.z];
     planes += blockIdx.z * (3L * Mt * TH_C * Np);
     const long rows = (long)Mt * TH_C;
@@ -133,6 +147,20 @@ __global__ __launch_bounds__(256) void k_wsplit(ThetaSet set, int N, int M, int 
         w = (cb & 1) ? v.y : v.x;
     }
     split_store(planes, rows * Np, idx, w);
+}
+// W of the set into planes; the sign bits of the n samples sig into bits (sig null: they are there already)
+static void launch_wsplit(const ThetaSet& set, int N, int M, uint16_t* planes, const int8_t* sig, long n, uint32_t* bits,
+                          hipStream_t stream) {
+    const int Np = theta_np(N), nw = spin_words(N);
+    const unsigned w_blocks = (unsigned)((theta_rows(M) * Np + 255) / 256);
+    const unsigned s_blocks = sig ? (unsigned)((n * nw + 255) / 256) : 0u;
+    const dim3 grid(w_blocks + s_blocks, 1, set.count);
+    if (spin_rows_aligned(sig, N))
+        hipLaunchKernelGGL(k_wsplit<true>, grid, dim3(256), 0, stream, set, N, M, Np, (M + 63) / 64, planes, w_blocks, sig, n,
+                           nw, bits);
+    else
+        hipLaunchKernelGGL(k_wsplit<false>, grid, dim3(256), 0, stream, set, N, M, Np, (M + 63) / 64, planes, w_blocks, sig, n,
+                           nw, bits);
 }
 
 // Complex product and |a|^2 with their fused multiply-adds written out, so that the moments do not depend in the
@@ -288,14 +316,12 @@ __global__ __launch_bounds__(64 * TH_W, 2) void k_theta(const uint32_t* __restri
     });
 }
 
-hipError_t launch_theta(const uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes, int n_cu,
-                        hipStream_t stream) {
+hipError_t launch_theta(const int8_t* sig, uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes,
+                        int n_cu, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     const int Np = theta_np(N);
     const int Mt = (M + 63) / 64;
-    const long cnt = (long)Mt * TH_C * Np;
-    hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256), 1, set.count), dim3(256), 0, stream, set, N, M, Np,
-                       Mt, planes);
+    launch_wsplit(set, N, M, planes, sig, n, bits, stream);
     // W of more than 128 sites is staged in pieces anyway: pieces of 64 leave room for two workgroups per compute unit
     // (8,192 samples, N = 256, M = 512: 68 us against 98 us in pieces of 128); up to 128 sites it is staged once
     theta_dispatch(Np > TH_KMAX ? 64 : Np, [&](auto kc) {
@@ -629,17 +655,16 @@ __global__ __launch_bounds__(256) void k_lc_final(int N, long n, int Mt, const u
     B[s] = zmul(*beta, make_double2(m * cs, m * sn));
 }
 
-hipError_t launch_lc_sums(const int8_t* sig, const uint32_t* bits, long n, int N, int M, const float2* a,
+hipError_t launch_lc_sums(const int8_t* sig, uint32_t* bits, bool new_samples, long n, int N, int M, const float2* a,
                           const float2* b, const float2* W, uint16_t* planes, float2* partial, const double2* Lg,
                           const double2* beta, double2* B, double2* Lg_out, int n_cu, hipStream_t stream) {
     if (n <= 0) return hipSuccess;
     const int Np = theta_np(N);
     const int Mt = (M + 63) / 64;
-    const long cnt = (long)Mt * TH_C * Np;
     ThetaSet set{};
     set.count = 1;
     set.W[0] = W;
-    hipLaunchKernelGGL(k_wsplit, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, stream, set, N, M, Np, Mt, planes);
+    launch_wsplit(set, N, M, planes, new_samples ? sig : nullptr, n, bits, stream);
     theta_dispatch(Np, [&](auto kc) {
         hipLaunchKernelGGL(k_theta_lc<kc.value>, dim3(theta_grid(n, Np, Mt, n_cu), (unsigned)Mt), dim3(64 * TH_W), 0,
                            stream, sig, bits, n, N, Np, M, b, W, planes, Mt, partial);
