@@ -117,18 +117,34 @@ __device__ __forceinline__ void sample_rows(__amdgpu_buffer_rsrc_t W, const floa
 template <int E, bool PAIR, int G>
 __global__ __launch_bounds__(1024) void k_sample(SampleArgs A) {
     extern __shared__ float2 s_w[];               // [N][G 64] of W, then a 256-byte spin row per wave, then Re a
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6)), n_waves = blockDim.x >> 6;
     const int N = A.N, M = A.M;
     const float2* __restrict__ W = A.psi.W;
     constexpr int kCols = G * kWave, k0 = (E - G) * kWave;   // columns held here, the first of them
     int8_t* const row = reinterpret_cast<int8_t*>(s_w + N * kCols) + wv * 256;
     float* const s_a = reinterpret_cast<float*>(reinterpret_cast<int8_t*>(s_w + N * kCols) + n_waves * 256);
-    for (int i = wv; i < N; i += n_waves)
+    // Each wave copies its rows in blocks of U whose loads are in flight together: a lone wave of few chains would wait
+    // for one row after the other, longer than a sweep takes (1 chain, N = 40, M = 400, one sweep: 45 us, now 21).
+    // U is small enough for the sweep's own registers, and lanes past M and rows past N read what is then dropped.
+    const __amdgpu_buffer_rsrc_t Wr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float2*>(W), (short)0, N * M * (int)sizeof(float2), 0x00020000);
+    constexpr int U = G <= 2 ? 8 : 24 / G;
+    for (int i0 = wv; i0 < N; i0 += U * n_waves) {
+        float2 v[U][G];
 #pragma unroll
-        for (int e = 0; e < G; ++e) {
-            const int k = k0 + e * kWave + lane;
-            s_w[i * kCols + e * kWave + lane] = k < M ? W[(long)i * M + k] : make_float2(0.f, 0.f);
-        }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < G; ++e)
+                v[u][e] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(
+                    Wr, (unsigned)(k0 + e * kWave + lane) * (unsigned)sizeof(float2),
+                    min(i0 + u * n_waves, N - 1) * M * (int)sizeof(float2), 0));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < G; ++e)
+                if (i0 + u * n_waves < N)
+                    s_w[(i0 + u * n_waves) * kCols + e * kWave + lane] = k0 + e * kWave + lane < M ? v[u][e] : make_float2(0.f, 0.f);
+    }
     for (int i = threadIdx.x; i < N; i += blockDim.x) s_a[i] = A.psi.a[i].x;
     const int chain = uniform((int)(blockIdx.x * n_waves + wv));
     const bool have = chain < A.n_chains;
@@ -142,8 +158,6 @@ __global__ __launch_bounds__(1024) void k_sample(SampleArgs A) {
 
     // theta = b + sigma W; lanes past M keep theta = 0, and their cached L is
     // the same function of the same value, so they add exactly zero below
-    const __amdgpu_buffer_rsrc_t Wr = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float2*>(W), (short)0, N * M * (int)sizeof(float2), 0x00020000);
     float2 th[E], wi[E], wj[E];
     float L[E];
 #pragma unroll
