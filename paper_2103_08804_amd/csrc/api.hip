@@ -412,9 +412,9 @@ int crbm_plan_create_ex(crbm_plan* out, const crbm_lattice* lat, int n_hidden, l
     p->w.n_cu = p->n_cu;
     p->w.sb_kt = 128;
     e = hipMemcpy(p->bonds, bonds.data(), bonds.size() * sizeof(int2), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(p->w.scal, 0, 32 * sizeof(double));
-    // the padding of the split-W planes stays zero: every writer fills the places of real sites and units, or all
-    if (e == hipSuccess) e = hipMemset(p->wplanes, 0, 3 * lc_plane_elems(N, M) * sizeof(uint16_t));
+    // no buffer is filled here: a fill may still be running when hipMemset returns, and the plan's first call may come on
+    // a stream that does not wait for the null stream.  Every call writes what it reads (k_r_final the scalars, the
+    // split of W and the matrix-free step's first launch the planes with their padding)
     if (e == hipSuccess && !order.empty())
         e = hipMemcpy(const_cast<int2*>(p->w.sb_order), order.data(), order.size() * sizeof(int2),
                       hipMemcpyHostToDevice);

@@ -17,7 +17,6 @@ struct RbmView {            // device pointers, complex64 interleaved
 
 // rows of sign bits: ceil(N / 32) words per sample, bit set where sigma = -1
 inline int spin_words(int N) { return (N + 31) / 32; }
-hipError_t launch_spin_bits(const int8_t* sig, long n, int N, uint32_t* bits, hipStream_t stream);
 
 // up to three RBMs whose theta is taken on the same samples
 struct ThetaSet {
@@ -30,6 +29,10 @@ struct ThetaSet {
 // sig where that is not null; planes: count x lc_plane_elems(N, M) scratch for the split W
 hipError_t launch_theta(const int8_t* sig, uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes,
                         int n_cu, hipStream_t stream);
+// before the matrix-free product: the sign bits of the samples, and in the planes zeros in the padding (W of any RBM
+// in the places of sites and units, which whoever forms v overwrites)
+hipError_t launch_matfree_start(const int8_t* sig, uint32_t* bits, long n, int N, int M, const float2* W, uint16_t* planes,
+                                hipStream_t stream);
 // O v of the matrix-free S product, u[s] = sum_k T_sk (sigma_s V_W + v_b)_k + sigma_s . v_a, without
 // writing the n x M product; planes: V_W split as the theta product's W; partial: n * ceil(M / 64) double2
 // scratch; mean_out <- the sum of the n_omv partials omv (a double pair)

@@ -27,12 +27,13 @@ namespace crbm {
 // parts of W ordered [Re 0..31 | Im 0..31 | Re 32..63 | Im 32..63], so that both parts of a
 // unit end in one lane; W is split into its parts in that order once per RBM (k_wsplit).
 //
-// sigma comes as one sign bit per site (k_spin_bits, once per sample set): a lane builds its A operand, the
-// eight sites of its sample that a matrix-core step reads, from one byte in registers, so the spins pass
+// sigma comes as one sign bit per site (written once per sample set, in the launch that splits W): a lane builds its A
+// operand, the eight sites of its sample that a matrix-core step reads, from one byte in registers, so the spins pass
 // through no LDS.  The W tile (three parts x 128 rows x up to 128 sites, 104 KB) is staged in LDS once per
-// workgroup, which then walks its samples in tiles of 16 waves x 32 with no barrier; beyond 128 sites the
-// tile is staged in pieces of 128 sites per sample tile.  65,536 samples, 10 x 10, M = 400: 64 us per product,
-// bound by the writes of theta (122 us with both operands staged per 128-sample tile, the spins a byte a load).
+// workgroup, which then walks its samples in tiles of 8 waves x 32 with no barrier; beyond 128 sites the tile is
+// staged in pieces per sample tile, of 64 sites for theta and of 128 for the products that are fused with a sum.
+// 65,536 samples, 10 x 10, M = 400: 64 us per product, bound by the writes of theta (122 us with both operands staged
+// per 128-sample tile, the spins a byte a load).
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
@@ -62,25 +63,8 @@ __device__ __forceinline__ void spin_word(const int8_t* __restrict__ sig, long n
     }
     bits[e] = m;
 }
-template <bool WORDS>
-__global__ __launch_bounds__(256) void k_spin_bits(const int8_t* __restrict__ sig, long n, int N, int nw,
-                                                   uint32_t* __restrict__ bits) {
-    spin_word<WORDS>(sig, n, N, nw, bits, (long)blockIdx.x * 256 + threadIdx.x);
-}
-
 // whether four sign bits may be taken from each word of four spins
 static bool spin_rows_aligned(const int8_t* sig, int N) { return N % 4 == 0 && (reinterpret_cast<uintptr_t>(sig) & 3) == 0; }
-
-hipError_t launch_spin_bits(const int8_t* sig, long n, int N, uint32_t* bits, hipStream_t stream) {
-    if (n <= 0) return hipSuccess;
-    const int nw = spin_words(N);
-    const dim3 grid((unsigned)((n * nw + 255) / 256));
-    if (spin_rows_aligned(sig, N))
-        hipLaunchKernelGGL(k_spin_bits<true>, grid, dim3(256), 0, stream, sig, n, N, nw, bits);
-    else
-        hipLaunchKernelGGL(k_spin_bits<false>, grid, dim3(256), 0, stream, sig, n, N, nw, bits);
-    return hipGetLastError();
-}
 
 // ------------------------------------------------------------------ helpers
 // f_q(sigma) = N^{-1/2} sum_r exp(-i q.r) sigma_r / 2 over the wave's spins
@@ -314,6 +298,15 @@ __global__ __launch_bounds__(64 * TH_W, 2) void k_theta(const uint32_t* __restri
             if (ku1 < M) theta[sm * M + ku1] = make_float2(acc[2][v] + b1.x, acc[3][v] + b1.y);
         }
     });
+}
+
+hipError_t launch_matfree_start(const int8_t* sig, uint32_t* bits, long n, int N, int M, const float2* W, uint16_t* planes,
+                                hipStream_t stream) {
+    ThetaSet set{};
+    set.count = 1;
+    set.W[0] = W;
+    launch_wsplit(set, N, M, planes, sig, n, bits, stream);
+    return hipGetLastError();
 }
 
 hipError_t launch_theta(const int8_t* sig, uint32_t* bits, long n, int N, int M, const ThetaSet& set, uint16_t* planes,

@@ -1225,7 +1225,7 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
 
     MfView f{};
     if (A.solver == CRBM_SOLVER_CG_MATFREE) {
-        e = launch_spin_bits(A.samples, A.n, A.N, W.bits, stream);
+        e = launch_matfree_start(A.samples, W.bits, A.n, A.N, A.M, A.W, W.wplanes, stream);
         if (e != hipSuccess) return e;
         f.N = A.N;
         f.M = A.M;
