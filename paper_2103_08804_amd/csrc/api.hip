@@ -524,7 +524,7 @@ int crbm_sample(crbm_plan p, const crbm_rbm* psi, int8_t* spins, void* theta_out
     A.trace = accept_trace;
     A.trace_words = (int)(((long)n_sweeps * p->N + 31) / 32);
     p->prof.begin(PROF_SAMPLE, stream);
-    hipError_t e = launch_sample(A, stream);
+    hipError_t e = launch_sample(A, p->n_cu, stream);
     p->prof.end(stream);
     return e == hipSuccess ? CRBM_OK : hip_fail(e, "sample launch");
 }

@@ -84,7 +84,7 @@ struct SampleArgs {
     uint32_t* trace;
     int trace_words;
 };
-hipError_t launch_sample(const SampleArgs& args, hipStream_t stream);
+hipError_t launch_sample(const SampleArgs& args, int n_cu, hipStream_t stream);
 
 // ---------------------------------------------------------------- local estimators
 struct LocalArgs {

@@ -302,14 +302,15 @@ static hipError_t sample_groups(const SampleArgs& A, int waves, hipStream_t stre
     return hipGetLastError();
 }
 
-// Waves per workgroup: as many as give each of 256 compute units one workgroup, at most 16 (the largest workgroup).
-// Above 4,096 chains a compute unit takes several workgroups in turn, two at a time where registers and half the LDS
+// Waves per workgroup: as many as give each compute unit one workgroup, at most 16 (the largest workgroup).
+// Above that many chains (4,096 on 256 units) a compute unit takes several workgroups in turn, two at a time where registers and half the LDS
 // allow it.  As many unit groups of W go to LDS as fit, out of 1, 2, 3 and all: at N = 100, M = 400 three of seven
 // cut the L2 reads that a full chip was waiting on.  One group always fits (N <= 256: 128 KB).
 template <int E, bool PAIR>
-static hipError_t sample_width(const SampleArgs& A, hipStream_t stream) {
-    const int waves = A.n_chains >= 4096 ? 16 : (A.n_chains + 255) / 256;
-    const size_t budget = A.n_chains > 4096 ? kSampleLds / 2 : kSampleLds;
+static hipError_t sample_width(const SampleArgs& A, int n_cu, hipStream_t stream) {
+    const int full = 16 * n_cu;
+    const int waves = A.n_chains >= full ? 16 : (A.n_chains + n_cu - 1) / n_cu;
+    const size_t budget = A.n_chains > full ? kSampleLds / 2 : kSampleLds;
     const size_t group = (size_t)A.N * kWave * sizeof(float2), rest = 256 * (size_t)waves + sizeof(float) * (size_t)A.N;
     const int fit = std::max(1, (int)((budget - rest) / group));
     if (fit >= E) return sample_groups<E, PAIR, E>(A, waves, stream);
@@ -318,11 +319,11 @@ static hipError_t sample_width(const SampleArgs& A, hipStream_t stream) {
     return sample_groups<E, PAIR, 1>(A, waves, stream);
 }
 
-hipError_t launch_sample(const SampleArgs& args, hipStream_t stream) {
+hipError_t launch_sample(const SampleArgs& args, int n_cu, hipStream_t stream) {
     const bool pair = args.proposal == 1;
     switch ((args.M + kWave - 1) / kWave) {
 #define CRBM_CASE(e) \
-    case e: return pair ? sample_width<e, true>(args, stream) : sample_width<e, false>(args, stream);
+    case e: return pair ? sample_width<e, true>(args, n_cu, stream) : sample_width<e, false>(args, n_cu, stream);
         CRBM_CASE(1) CRBM_CASE(2) CRBM_CASE(3) CRBM_CASE(4) CRBM_CASE(5) CRBM_CASE(6) CRBM_CASE(7) CRBM_CASE(8)
 #undef CRBM_CASE
         default: return hipErrorInvalidValue;

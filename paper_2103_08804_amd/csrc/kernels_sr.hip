@@ -1148,7 +1148,7 @@ hipError_t launch_sr_step(const SrArgs& A, const SrWork& W, hipStream_t stream) 
     hipLaunchKernelGGL(k_r_final, dim3(1), dim3(64), 0, stream, W.red, nb_r, A.dgamma, A.mode, W.scal);
     double* ff = W.dots + 4 * dots_blocks(P);
     int n_ff;
-    // the packed sigma~ rows serve the O^H c contraction only
+    // the sign bits by site serve the O^H c contraction only
     if (!A.weights || A.solver == CRBM_SOLVER_CG_MATFREE) spin_cols(A.samples, A.n, A.N, W.ot_bits, stream);
     // conj(<O>) and <O^* (R - <R>)>: FP32 chunk sums on the matrix cores, or in double with sample weights
     if (A.weights) {
