@@ -502,8 +502,8 @@ __global__ __launch_bounds__(256) void k_ot_reduce(int N, int M, const float* __
 // The grid holds as many workgroups as the device keeps resident at once (the kernel's occupancy
 // times the CUs, so that no second, nearly empty round follows); each loops over its chunks.
 // Sites: the blocks of 32 in as few equal groups of at most 4 as hold them (SB of the kernel), in more and smaller
-// ones as long as these make no more than 3/2 workgroups per compute unit: a wave with fewer blocks forms fewer products
-// per step.  Units: the blocks of 32 in as few equal groups of at most 4 waves.
+// whole ones as long as these make no more than 3/2 workgroups per compute unit: a wave with fewer blocks forms fewer
+// products per step (three blocks as two and one were slower).  Units: the blocks of 32 in as few equal groups of at most 4 waves.
 // Gradient of N = 100, M = 400 (its four launches): 300 samples 17 us, 33 in chunks of 256 with four blocks a wave;
 // 4,096 samples 28 against 36; N = 256, M = 512, 2,000 samples 33 against 36.
 struct OtPlan { long chunk; int n_chunks, sb, site_groups, waves, unit_groups, grid_z; };
@@ -525,7 +525,7 @@ static OtPlan ot_plan(int N, int M, long n, int nk, int n_cu) {
     p.waves = (unit_blocks + p.unit_groups - 1) / p.unit_groups;
     for (int sb = 1; sb < p.sb; ++sb) {
         const long groups = (site_blocks + sb - 1) / sb;
-        if (groups * p.unit_groups * nk * p.n_chunks > 3L * n_cu / 2) continue;
+        if (groups * sb != site_blocks || groups * p.unit_groups * nk * p.n_chunks > 3L * n_cu / 2) continue;
         p.sb = sb;
         p.site_groups = (int)groups;
     }
