@@ -108,7 +108,7 @@ __device__ __forceinline__ float2 a_dot_sigma(const float2* a, const WaveSpins& 
 //
 // The planes of W are [3][Mt 128][Np], Np = N rounded up to TH_K, zero padded; the product's
 // workgroups only copy tiles of them.  With spins given (sig), the blocks past the planes' w_blocks write their sign
-// bits, so that a call on new samples has no launch of its own for them.
+// bits, so that a call on new samples has no launch of its own for them (but see launch_wsplit).
 template <bool WORDS>
 __global__ __launch_bounds__(256) void k_wsplit(ThetaSet set, int N, int M, int Np, int Mt, uint16_t* __restrict__ planes,
                                                 unsigned w_blocks, const int8_t* __restrict__ sig, long n, int nw,
@@ -132,19 +132,33 @@ __global__ __launch_bounds__(256) void k_wsplit(ThetaSet set, int N, int M, int 
     }
     split_store(planes, rows * Np, idx, w);
 }
-// W of the set into planes; the sign bits of the n samples sig into bits (sig null: they are there already)
+// W of the set into planes; the sign bits of the n samples sig into bits (sig null: they are there already).  Past 128
+// sites and 1.5 MB of bits they have a launch of their own, as the first product after them was slower with the bits
+// written by the launch before it (256 sites, M = 128, 131,072 samples: 212 us against 148 us, whole moments 876 us
+// against 815 us; 200 sites, M = 512, 65,536 samples: 1,011 us against 998 us); up to there the launch less is what
+// shows (256 sites, M = 512, 32,768 samples: 793 us against 800 us), and up to 128 sites there is no difference at
+// 4 MB either (100 sites, M = 400, 262,144 samples: 1,788 us both ways).
+constexpr long kSpinWords = 3L << 17;
 static void launch_wsplit(const ThetaSet& set, int N, int M, uint16_t* planes, const int8_t* sig, long n, uint32_t* bits,
                           hipStream_t stream) {
     const int Np = theta_np(N), nw = spin_words(N);
     const unsigned w_blocks = (unsigned)((theta_rows(M) * Np + 255) / 256);
     const unsigned s_blocks = sig ? (unsigned)((n * nw + 255) / 256) : 0u;
-    const dim3 grid(w_blocks + s_blocks, 1, set.count);
-    if (spin_rows_aligned(sig, N))
-        hipLaunchKernelGGL(k_wsplit<true>, grid, dim3(256), 0, stream, set, N, M, Np, (M + 63) / 64, planes, w_blocks, sig, n,
-                           nw, bits);
-    else
-        hipLaunchKernelGGL(k_wsplit<false>, grid, dim3(256), 0, stream, set, N, M, Np, (M + 63) / 64, planes, w_blocks, sig, n,
-                           nw, bits);
+    auto blocks = [&](unsigned w, unsigned spins, int count) {
+        const dim3 grid(w + spins, 1, count);
+        if (spin_rows_aligned(sig, N))
+            hipLaunchKernelGGL(k_wsplit<true>, grid, dim3(256), 0, stream, set, N, M, Np, (M + 63) / 64, planes, w, sig, n, nw,
+                               bits);
+        else
+            hipLaunchKernelGGL(k_wsplit<false>, grid, dim3(256), 0, stream, set, N, M, Np, (M + 63) / 64, planes, w, sig, n,
+                               nw, bits);
+    };
+    if (N > TH_KMAX && sig && n * nw > kSpinWords) {
+        blocks(0, s_blocks, 1);
+        blocks(w_blocks, 0, set.count);
+    } else {
+        blocks(w_blocks, s_blocks, set.count);
+    }
 }
 
 // Complex product and |a|^2 with their fused multiply-adds written out, so that the moments do not depend in the
@@ -257,8 +271,9 @@ __device__ __forceinline__ void theta_walk(ThetaLds<KC>& lds, const uint32_t* __
         if (sw < n) body(sw, acc);
     }
 }
-// workgroups along the samples: one round of the device over the unit tiles (one workgroup per compute unit,
-// two where the staged tile is at most 64 sites), at most one per sample tile
+// workgroups along the samples: one a compute unit over the unit tiles, two where the staged tile is at most 64 sites
+// (theta then has both resident; the products that are fused with a sum hold one at a time for their registers, and
+// take two rounds), at most one per sample tile
 static unsigned theta_grid(long n, int Np, int Mt, int n_cu) {
     const long slots = (long)n_cu * (Np <= 64 ? 2 : 1), tiles = (n + TH_S - 1) / TH_S;
     long g = slots / Mt;
